@@ -11,13 +11,18 @@
 // a workgroup owns a BN x BM output tile (up to 256 x 256), stages BN x 64 and
 // BM x 64 operand tiles in LDS (double buffered, XOR-swizzled 16-byte pieces so
 // that both the staging writes and the MFMA operand reads are bank-conflict
-// free) and runs v_mfma_f32_32x32x16_f16 on wave tiles of up to 64 x 128.
+// free) and runs v_mfma_f32_16x16x32_f16 on wave tiles of up to 64 x 128.
+//
+// Why 16x16x32 and not 32x32x16 (the same flops per cycle, the same operand bytes from LDS for a wave tile):
+// the chip runs these kernels at its power limit, and the 32x32 form moves four times the accumulator bytes
+// per instruction for twice the flops.  A loop of nothing but MFMAs on random operands sustains 1893 TFLOP/s
+// with 16x16x32 against 1643 with 32x32x16.
 //
 // Operand roles: the weight tile is the MFMA "A" operand (rows = output
 // features n), the activation tile the "B" operand (columns = tokens m), so a
-// lane ends up with 4 consecutive n of one token per register quad -- an 8-byte
+// lane ends up with 4 consecutive n of one token per fragment -- an 8-byte
 // store -- and, for SwiGLU, with g and u of the same (token, j) in registers of
-// the same lane (a tile interleaves 8 gate rows with the 8 matching up rows).
+// the same lane (a tile interleaves 16 gate rows with the 16 matching up rows).
 //
 // Scheduling: a fixed number of workgroups (one or two per CU).  Tiles that fill whole rounds of the
 // grid are computed and finished in one piece; the ragged remainder (everything, when there are fewer
@@ -44,15 +49,15 @@ namespace {
 // A staged tile row holds GK halfs = GK/8 16-byte pieces.  Piece p of tile row `row` lives at 16-byte
 // unit row*P + (p ^ f(row)), with f chosen so that 16 consecutive rows reading the same logical piece
 // (an MFMA operand read) and the linear staging writes both spread over all LDS banks:
-//   P = 8 (128-byte rows): f is a bijection on every aligned group of 8 rows and on the even and the odd
-//                          rows of every aligned group of 16;
-//   P = 4 (64-byte rows):  f is a bijection on {r, r+4, r+8, r+12} and on {r, r+2, r+4, r+6}.
+//   P = 16 (256-byte rows): 16 consecutive rows, 16 different pieces;
+//   P = 8  (128-byte rows): f is a bijection on every aligned group of 8 rows and on the even and the odd
+//                           rows of every aligned group of 16.
 template <int P>
 __device__ __forceinline__ int swz_f(int row)
 {
-    if (P == 16) return row & 15;     // 256-byte rows: 16 consecutive rows, 16 different pieces
-    if (P == 8) return ((row >> 1) & 7) ^ ((row & 1) << 2);
-    return (((row >> 1) ^ (row >> 3)) & 1) | (((row >> 2) & 1) << 1);
+    static_assert(P == 8 || P == 16, "staged rows of 64 or 128 k");
+    if (P == 16) return row & 15;
+    return ((row >> 1) & 7) ^ ((row & 1) << 2);
 }
 template <int P>
 __device__ __forceinline__ int swz(int row, int piece) { return row * P + (piece ^ swz_f<P>(row)); }
@@ -64,17 +69,10 @@ __device__ __forceinline__ uint16_t to_half_bits(float v)
 }
 
 // One 16-byte piece per lane straight from global memory into LDS (no VGPR staging): lane L of the
-// wave lands at lds_base + 16*L.  lds_base must be wave-uniform.
-__device__ __forceinline__ void dma16(const uint16_t* src, uintx4* lds_base)
-{
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)lds_base, 16, 0, 0);
-}
-
-// The same load with the address split into a wave-uniform base (scalar registers) and a 32-bit
-// per-lane byte offset: no vector ALU work per load.  Written in assembly because the builtin always
-// takes the 64-bit per-lane form.  The kernels that use it use M0 for nothing else and wait for these
-// loads explicitly (s_waitcnt vmcnt) before the barrier that publishes the stage.
+// wave lands at lds_base + 16*L (wave-uniform).  The address is split into a wave-uniform base (scalar
+// registers) and a 32-bit per-lane byte offset: no vector ALU work per load.  Written in assembly because
+// the builtin always takes 64-bit per-lane addresses.  The kernels that use it use M0 for nothing else and
+// wait for these loads explicitly (s_waitcnt vmcnt) before the barrier that publishes the stage.
 __device__ __forceinline__ void dma16_sbase(const void* base_uniform, unsigned lane_byte_offset, uintx4* lds_base)
 {
     const unsigned lds_addr = (unsigned)(size_t)(__attribute__((address_space(3))) void*)lds_base;
@@ -114,156 +112,125 @@ struct Deal {
     }
 };
 
-// Epilogue for one 32x32 accumulator fragment: lane (lr = token within the fragment, lg = which
-// half of the rows) holds, per register quad aa, four consecutive n of one token.
+// Epilogue for the two 16x16 accumulator fragments (2 tp, tm) and (2 tp + 1, tm) of a wave: a lane holds four
+// consecutive n of one token of each.  For SwiGLU the first holds gate rows and the second the matching up rows.
 template <int BN, int BM, int WN, int WM, int EPI>
-__device__ __forceinline__ void store_fragment(const GemmArgs& a, int tile_n, int tile_m, int wn, int wm, int tn,
-                                               int tm, int lr, int lg, const floatx16& f,
-                                               int aa_begin = 0, int aa_end = 4)
+__device__ __forceinline__ void store_pair(const GemmArgs& a, int tile_n, int tile_m, int wn, int wm, int tp,
+                                           int tm, int lr, int hi, const floatx4& f0, const floatx4& f1)
 {
-    constexpr int JPT = is_swiglu(EPI) ? BN / 2 : BN;
-    const int m = tile_m * BM + wm * (BM / WM) + tm * 32 + lr;
+    const int m = tile_m * BM + wm * (BM / WM) + tm * 16 + lr;
     if (m >= a.M) return;
+    const int row = wn * (BN / WN) + tp * 32;            // first tile row of the pair
     if (is_swiglu(EPI)) {
+        const int j = tile_n * (BN / 2) + (row >> 1) + 4 * hi;
+        half4 hv;
 #pragma unroll
-        for (int aa = 0; aa < 4; aa += 2) {
-            if (aa < aa_begin || aa >= aa_end) continue;
-            const int v = wn * (BN / WN) + tn * 32 + 8 * aa;
-            const int j = tile_n * JPT + (v >> 4) * 8 + 4 * lg;
-            half4 hv;
+        for (int c = 0; c < 4; ++c) hv[c] = (_Float16)(f0[c] / (1.0f + __expf(-f0[c])) * f1[c]);
+        if (j + 3 < a.N && (a.ldo & 3) == 0) {
+            *reinterpret_cast<half4*>(a.out + (size_t)m * a.ldo + j) = hv;
+        } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const float g = f[4 * aa + c], uu = f[4 * (aa + 1) + c];
-                hv[c] = (_Float16)(g / (1.0f + __expf(-g)) * uu);
-            }
-            if (j + 3 < a.N && (a.ldo & 3) == 0) {
-                *reinterpret_cast<half4*>(a.out + (size_t)m * a.ldo + j) = hv;
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (j + c < a.N) a.out[(size_t)m * a.ldo + j + c] = __builtin_bit_cast(uint16_t, hv[c]);
-            }
+            for (int c = 0; c < 4; ++c)
+                if (j + c < a.N) a.out[(size_t)m * a.ldo + j + c] = __builtin_bit_cast(uint16_t, hv[c]);
         }
-    } else {
+        return;
+    }
 #pragma unroll
-        for (int aa = 0; aa < 4; ++aa) {
-            if (aa < aa_begin || aa >= aa_end) continue;
-            const int n = tile_n * BN + wn * (BN / WN) + tn * 32 + 8 * aa + 4 * lg;
-            float v[4];
+    for (int q = 0; q < 2; ++q) {
+        const int n = tile_n * BN + row + 16 * q + 4 * hi;
+        float v[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = f[4 * aa + c];
-            if (has_rope(EPI)) {                         // the quad holds two complete pairs of one token
-                if (EPI == EPI_ROPE) {                   // cos / sin from the table the RMSNorm pass left
-                    rope_pair_table(a.rope, m, n, v[0], v[1]);
-                    rope_pair_table(a.rope, m, n + 2, v[2], v[3]);
-                } else {
-                    const int mp = a.rope.pos[m];
-                    rope_pair(a.rope, mp, n, v[0], v[1]);
-                    rope_pair(a.rope, mp, n + 2, v[2], v[3]);
-                }
+        for (int c = 0; c < 4; ++c) v[c] = q ? f1[c] : f0[c];
+        if (has_rope(EPI)) {                         // two complete pairs of one token; cos / sin from the table the RMSNorm pass left
+            rope_pair_table(a.rope, m, n, v[0], v[1]);
+            rope_pair_table(a.rope, m, n + 2, v[2], v[3]);
+        }
+        if (n + 3 < a.N && (a.ldo & 3) == 0) {
+            half4 hv;
+            if (a.residual) {
+                const half4 rv = *reinterpret_cast<const half4*>(a.residual + (size_t)m * a.ldo + n);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] += (float)rv[c];
             }
-            if (n + 3 < a.N && (a.ldo & 3) == 0) {
-                half4 hv;
-                if (a.residual) {
-                    const half4 rv = *reinterpret_cast<const half4*>(a.residual + (size_t)m * a.ldo + n);
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] += (float)rv[c];
+            for (int c = 0; c < 4; ++c) hv[c] = (_Float16)v[c];
+            *reinterpret_cast<half4*>(a.out + (size_t)m * a.ldo + n) = hv;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (n + c < a.N) {
+                    if (a.residual) v[c] += half_bits_to_float(a.residual[(size_t)m * a.ldo + n + c]);
+                    a.out[(size_t)m * a.ldo + n + c] = to_half_bits(v[c]);
                 }
-#pragma unroll
-                for (int c = 0; c < 4; ++c) hv[c] = (_Float16)v[c];
-                *reinterpret_cast<half4*>(a.out + (size_t)m * a.ldo + n) = hv;
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (n + c < a.N) {
-                        if (a.residual) v[c] += half_bits_to_float(a.residual[(size_t)m * a.ldo + n + c]);
-                        a.out[(size_t)m * a.ldo + n + c] = to_half_bits(v[c]);
-                    }
-            }
         }
     }
 }
 
-// Second pass for tiles that were cut along K: one workgroup per (shared tile, accumulator fragment, half of the
-// fragment's register quads) adds the partial fragments of the tile's contributors in workgroup order
-// and applies the epilogue.  The thread <-> element mapping is the main kernel's, so the partials are
-// read back as they were written.  (Halves, not quads: SwiGLU pairs quad 2i with quad 2i+1.)
+// Second pass for tiles that were cut along K: one workgroup per (shared tile, pair of accumulator fragments)
+// adds the partial fragments of the tile's contributors in workgroup order and applies the epilogue.  The
+// thread <-> element mapping is the main kernel's, so the partials are read back as they were written.
 template <int BN, int BM, int WN, int WM, int EPI>
 __global__ __launch_bounds__(64 * WN * WM) void gemm_fixup(GemmArgs a, int tiles_m, int ktiles, int sk_tiles, int G, int parts)
 {
     constexpr int THREADS = 64 * WN * WM;
-    constexpr int TN = BN / WN / 32, TM = BM / WM / 32;
+    constexpr int TP = BN / WN / 32, TM = BM / WM / 16;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid / 64;
-    const int wn = wv % WN, wm = wv / WN, lr = lane & 31, lg = lane >> 5;
-    const int half = blockIdx.x & 1, tf = blockIdx.x >> 1;
-    const int t = tf / (TN * TM), frag = tf % (TN * TM);
-    const int tn = frag / TM, tm = frag % TM;
+    const int wn = wv % WN, wm = wv / WN, lr = lane & 15, hi = lane >> 4;
+    const int t = blockIdx.x / (TP * TM), frag = blockIdx.x % (TP * TM);
+    const int tp = frag / TM, tm = frag % TM;
     const Deal deal(sk_tiles, ktiles, G, parts);
     const int w_first = deal.first(t), w_last = deal.last(t);
-    floatx4 g0 = {0.f, 0.f, 0.f, 0.f}, g1 = {0.f, 0.f, 0.f, 0.f};      // this half's two register quads
+    floatx4 g0 = {0.f, 0.f, 0.f, 0.f}, g1 = {0.f, 0.f, 0.f, 0.f};      // the pair's two fragments
     // a contributor's partial of this tile: slot 0 if the tile is the first of its share, else slot 1
     auto part = [&](int wc) -> const floatx4* {
         const int cslot = (deal.begin(wc) / ktiles == t) ? 0 : 1;
         return reinterpret_cast<const floatx4*>(a.partials + ((size_t)wc * 2 + cslot) * (BN * BM)) +
-               (frag * 4 + 2 * half) * THREADS + tid;
+               (size_t)(2 * tp * TM + tm) * THREADS + tid;
     };
+    constexpr int NEXT = TM * THREADS;          // from fragment (2 tp, tm) to (2 tp + 1, tm)
     auto add = [&](const floatx4& v0, const floatx4& v1) { g0 += v0; g1 += v1; };
     int wc = w_first;
     for (; wc + 3 <= w_last; wc += 4) {      // four contributors' loads in flight, added in order
         const floatx4 *p0 = part(wc), *p1 = part(wc + 1), *p2 = part(wc + 2), *p3 = part(wc + 3);
-        const floatx4 a0 = p0[0], a1 = p0[THREADS], b0 = p1[0], b1 = p1[THREADS];
-        const floatx4 c0 = p2[0], c1 = p2[THREADS], d0 = p3[0], d1 = p3[THREADS];
+        const floatx4 a0 = p0[0], a1 = p0[NEXT], b0 = p1[0], b1 = p1[NEXT];
+        const floatx4 c0 = p2[0], c1 = p2[NEXT], d0 = p3[0], d1 = p3[NEXT];
         add(a0, a1); add(b0, b1); add(c0, c1); add(d0, d1);
     }
     for (; wc <= w_last; ++wc) {
         const floatx4* p = part(wc);
-        const floatx4 v0 = p[0], v1 = p[THREADS];
+        const floatx4 v0 = p[0], v1 = p[NEXT];
         add(v0, v1);
     }
-    floatx16 f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) f[e] = 0.f;
-    if (half == 0) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) { f[c] = g0[c]; f[4 + c] = g1[c]; }
-    } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) { f[8 + c] = g0[c]; f[12 + c] = g1[c]; }
-    }
-    store_fragment<BN, BM, WN, WM, EPI>(a, t / tiles_m, t % tiles_m, wn, wm, tn, tm, lr, lg, f, 2 * half, 2 * half + 2);
+    store_pair<BN, BM, WN, WM, EPI>(a, t / tiles_m, t % tiles_m, wn, wm, tp, tm, lr, hi, g0, g1);
 }
 
-// BN x BM output tile, WN x WM waves; wave tile (BN/WN) x (BM/WM) built from 32x32 MFMA tiles.
+// BN x BM output tile, WN x WM waves; wave tile (BN/WN) x (BM/WM) built from 16x16 MFMA tiles.
 // KTAIL: K is not a multiple of 64 (pieces past K are zero-filled; operands then go through VGPRs).
-// FD: how many k-steps ahead of the MFMAs the operand fragments are read from LDS (1: two fragment buffers;
-// 2: three, the 256x256 configuration).  The two waves of a SIMD do not share the matrix pipe evenly -- the
-// older one is served first, finishes its k-tile early and waits at the barrier, and the other then runs
-// alone, with MFMA blocks of 256 cycles per k-step instead of 512 to hide its LDS reads behind (cycle counters
-// in the loop, 2048 x 8192 x 28672: the waves 0..3 waited ~1100 cycles per k-tile at the barrier, the waves 4..7
-// ~170; the wait for the direct loads was 40..80 cycles).  One more k-step of distance gives the wave that runs
-// alone more slack: 2757 -> 2625 cycles per k-tile (2048 would be the matrix pipe's own time), +2.2 % in
-// throughput -- the clock gives back half of what the cycles gain.
-template <int BN, int BM, int WN, int WM, int GK, int NS, int EPI, bool KTAIL, int FD = 1>
+// Operand fragments are read from LDS one k-step of 32 ahead of their MFMAs (two fragment buffers).  The k-tile's
+// one barrier sits in front of its last k-step: every read of the stage has been issued by then, the next
+// k-tile must have landed, and its first fragments are read behind the barrier while the last k-step is multiplied.
+// Against 32x32x16 MFMAs with the same tiles (one box, alternating): gate/up 2048 x 57344 x 8192 1553 -> 1482 us,
+// 2048 x 8192 x 8192 244 -> 214, 2048 x 8192 x 28672 802 -> 721, 512 x 27648 x 5120 146 -> 138, same bits.
+// Eight waves everywhere but in the 64-token configuration: with four (one per SIMD) nothing covers a wave's wait for
+// its fragments, and the 256x128 and 128x128 tiles lost 8-10 %.
+template <int BN, int BM, int WN, int WM, int GK, int NS, int EPI, bool KTAIL>
 __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int tiles_m, int ktiles, int sk_tiles, int parts)
 {
     constexpr int NWAVES = WN * WM;
     constexpr int THREADS = 64 * NWAVES;
     constexpr int GPIECES = GK / 8;             // 16-byte pieces per tile row
-    constexpr int KSTEPS = GK / 16;             // MFMA k-steps per staged tile (even)
+    constexpr int KSTEPS = GK / 32;             // MFMA k-steps per staged tile (even)
     constexpr int ROWS_PER_DMA = 64 / GPIECES;  // tile rows covered by one wave-wide direct load
     constexpr int ROWS_PER_PASS = THREADS / GPIECES;
     constexpr int WPASS = BN / ROWS_PER_PASS;   // per-thread pieces of the weight tile
     constexpr int XPASS = BM / ROWS_PER_PASS;
-    constexpr int TN = BN / WN / 32;            // MFMA tiles per wave along n
-    constexpr int TM = BM / WM / 32;
+    constexpr int TN = BN / WN / 16;            // MFMA tiles per wave along n (even)
+    constexpr int TM = BM / WM / 16;
     constexpr int JPT = is_swiglu(EPI) ? BN / 2 : BN;   // physical weight rows per tile
     constexpr bool W_DMA = !KTAIL;                           // weight tile: global -> LDS directly
     constexpr bool X_DMA = !KTAIL;                           // activation tile: the same
     constexpr int STAGE = (BN + BM) * GPIECES;   // 16-byte units per stage: weight tile, then activation tile
-    // A direct weight load takes a wave-uniform base; with SwiGLU and 16 tile rows per load (GK = 32) one
-    // load spans a gate block and an up block, so that variant keeps per-lane 64-bit addresses.
-    constexpr bool W_SBASE = !(is_swiglu(EPI) && ROWS_PER_DMA != 8);
-    static_assert(NS >= 2 && NS <= 8 && (KSTEPS % 2) == 0, "pipeline shape");
+    static_assert(NS >= 2 && NS <= 8 && (KSTEPS % 2) == 0 && (TN % 2) == 0, "pipeline shape");
     static_assert(WPASS >= 1 && XPASS >= 1, "tile too small for the thread count");
 
     extern __shared__ uintx4 smem[];
@@ -271,7 +238,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid / 64);     // wave index, known uniform to the compiler
     const int wn = wv % WN, wm = wv / WN;
-    const int lr = lane & 31, lg = lane >> 5;
+    const int lr = lane & 15, hi = lane >> 4;       // operand row (column) and 8-element k group; token and quad of rows
     const int K = a.K;
 
     // XCD-aware worker numbering: consecutive workers (neighbouring tiles) share an XCD
@@ -326,14 +293,13 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             const int piece = W_DMA ? slot ^ swz_f<GPIECES>(v) : vp;
             if (is_swiglu(EPI)) {
                 const int j0 = tile_n * JPT;                         // first row of the tile: always valid
-                int j = j0 + (v >> 4) * 8 + (v & 7);
+                int j = j0 + (v >> 5) * 16 + (v & 15);
                 j = j < a.N ? j : a.N - 1;
-                if (W_DMA && W_SBASE) {
-                    // ROWS_PER_DMA = 8: a wave instruction covers 8 gate rows or the 8 matching up rows
-                    wsrc[i] = ((blk & 1) ? a.w1 : a.w0) + (size_t)j0 * K;
+                if (W_DMA) {                                         // a wave instruction covers gate rows or up rows only
+                    wsrc[i] = (((blk * ROWS_PER_DMA) >> 4) & 1 ? a.w1 : a.w0) + (size_t)j0 * K;
                     woff[i] = (unsigned)((j - j0) * K + piece * 8) * 2u;
                 } else {
-                    wsrc[i] = (((v >> 3) & 1) ? a.w1 : a.w0) + (size_t)j * K + piece * 8;
+                    wsrc[i] = (((v >> 4) & 1) ? a.w1 : a.w0) + (size_t)j * K + piece * 8;
                     woff[i] = 0;
                 }
             } else {
@@ -372,10 +338,8 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
         auto load_w = [&](int kt, int buf) {      // DMA: lands in stage buf; else: into wreg
 #pragma unroll
             for (int i = 0; i < WPASS; ++i) {
-                if (W_DMA && W_SBASE) {
+                if (W_DMA) {
                     dma16_sbase(wsrc[i] + kt * GK, woff[i], smem + buf * STAGE + (wv * WPASS + i) * 64);
-                } else if (W_DMA) {
-                    dma16(wsrc[i] + kt * GK, smem + buf * STAGE + (wv * WPASS + i) * 64);
                 } else {
                     const bool kok = kt * GK + vp * 8 < K;
                     uintx4 v = *reinterpret_cast<const uintx4*>(wsrc[i] + (kok ? kt * GK : -vp * 8));
@@ -410,38 +374,39 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             }
         };
 
-        floatx16 acc[TN][TM];
+        floatx4 acc[TN][TM];
 #pragma unroll
         for (int i = 0; i < TN; ++i)
 #pragma unroll
-            for (int j = 0; j < TM; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int j = 0; j < TM; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
         half8 wa[2][TN], xb[2][TM];
         auto frags = [&](int buf, int kk, int fs) {
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
-                wa[fs][tn] = __builtin_bit_cast(half8, smem[buf * STAGE + swz<GPIECES>(wn * (BN / WN) + tn * 32 + lr, 2 * kk + lg)]);
+                wa[fs][tn] = __builtin_bit_cast(half8, smem[buf * STAGE + swz<GPIECES>(wn * (BN / WN) + tn * 16 + lr, 4 * kk + hi)]);
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm)
-                xb[fs][tm] = __builtin_bit_cast(half8, smem[buf * STAGE + BN * GPIECES + swz<GPIECES>(wm * (BM / WM) + tm * 32 + lr, 2 * kk + lg)]);
+                xb[fs][tm] = __builtin_bit_cast(half8, smem[buf * STAGE + BN * GPIECES + swz<GPIECES>(wm * (BM / WM) + tm * 16 + lr, 4 * kk + hi)]);
         };
         auto mfmas = [&](int fs) {
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm)
-                    acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[fs][tn], xb[fs][tm], acc[tn][tm], 0, 0, 0);
+                    acc[tn][tm] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[fs][tn], xb[fs][tm], acc[tn][tm], 0, 0, 0);
         };
-        // pair each LDS read of the next k-step with one MFMA of the current one
-        auto interleave = [&]() {
+        // spread the LDS reads of the next k-step over the MFMAs of the current one, `per` MFMAs between two reads
+        using One = std::integral_constant<int, 1>;
+        using PerRead = std::integral_constant<int, TN * TM / (TN + TM)>;
+        auto interleave = [&](auto per) {
+            constexpr int PER = decltype(per)::value;
 #pragma unroll
             for (int i = 0; i < TN + TM; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
                 __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, TN * TM - (TN + TM), 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, TN * TM - PER * (TN + TM), 0);
         };
 
         // ---- prologue: the first NS k-tiles into the NS stages; VGPR-path operands run one tile further
@@ -461,48 +426,6 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
         __syncthreads();
 
         constexpr int LPT = (W_DMA ? WPASS : 0) + (X_DMA ? XPASS : 0);   // direct loads per k-tile per wave
-        if constexpr (FD == 2) {
-            static_assert(NS == 2 && KSTEPS == 4 && W_DMA && X_DMA, "three fragment buffers: two stages of four k-steps, direct loads");
-            half8 wa3[3][TN], xb3[3][TM];
-            auto frags3 = [&](int buf, int kk, int fs) {
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn)
-                    wa3[fs][tn] = __builtin_bit_cast(half8, smem[buf * STAGE + swz<GPIECES>(wn * (BN / WN) + tn * 32 + lr, 2 * kk + lg)]);
-#pragma unroll
-                for (int tm = 0; tm < TM; ++tm)
-                    xb3[fs][tm] = __builtin_bit_cast(half8, smem[buf * STAGE + BN * GPIECES + swz<GPIECES>(wm * (BM / WM) + tm * 32 + lr, 2 * kk + lg)]);
-            };
-            auto mfmas3 = [&](int fs) {
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-                    for (int tm = 0; tm < TM; ++tm)
-                        acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa3[fs][tn], xb3[fs][tm], acc[tn][tm], 0, 0, 0);
-            };
-            frags3(0, 0, 0);
-            frags3(0, 1, 1);
-            // k-step s of k-tile `it` is global step 4 it + s and lives in fragment buffer (it + s) mod 3; while it is
-            // multiplied, step + 2 is read.  The barrier sits in the middle of the k-tile: all four k-steps of
-            // stage st have been read by then, k-tile it+1 must have landed, and its first fragments are read
-            // right behind it.  (A k-tile that does not exist is "read" from the current stage and never used.)
-            auto tile = [&](auto ph, int it) __attribute__((always_inline)) {
-                constexpr int P = decltype(ph)::value;
-                const int st = it % NS;
-                const int nx = (it + 1 < nk) ? (it + 1) % NS : st;
-                frags3(st, 2, (P + 2) % 3); mfmas3(P % 3); interleave();
-                frags3(st, 3, (P + 3) % 3); mfmas3((P + 1) % 3); interleave();
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
-                if (it + NS < nk) { load_w(kb + it + NS, st); load_x(kb + it + NS, st); }
-                frags3(nx, 0, (P + 4) % 3); mfmas3((P + 2) % 3); interleave();
-                frags3(nx, 1, (P + 5) % 3); mfmas3((P + 3) % 3); interleave();
-            };
-            for (int it = 0; it < nk; it += 3) {
-                tile(std::integral_constant<int, 0>{}, it);
-                if (it + 1 < nk) tile(std::integral_constant<int, 1>{}, it + 1);
-                if (it + 2 < nk) tile(std::integral_constant<int, 2>{}, it + 2);
-            }
-        } else {
         frags(0, 0, 0);
         for (int it = 0; it < nk; ++it) {
             const int st = it % NS;
@@ -510,8 +433,10 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             for (int kk = 0; kk < KSTEPS - 1; ++kk) {
                 frags(st, kk + 1, (kk + 1) & 1);
                 mfmas(kk & 1);
-                interleave();
+                if (kk < KSTEPS - 2) interleave(PerRead{});
+                else interleave(One{});          // in front of the barrier: the reads first, their latency behind MFMAs
             }
+            __builtin_amdgcn_sched_barrier(0);
             // Every read of stage st has been issued.  Before the barrier, k-tile it+1 must have landed:
             // direct loads complete in order, so it is enough that at most the loads of the k-tiles
             // behind it (up to NS-2 of them) are still in flight.  The compiler does not carry these
@@ -537,9 +462,9 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
                     if (!X_DMA) load_x(kb + it + NS + 1, st);
                 }
             }
-            if (it + 1 < nk) frags((it + 1) % NS, 0, 0);
+            frags(it + 1 < nk ? (it + 1) % NS : st, 0, 0);      // (behind the last k-tile: read and never used)
             mfmas((KSTEPS - 1) & 1);
-        }
+            interleave(PerRead{});
         }
 
         // ---- whole tile: finished below; shared tile: leave the fp32 partial for the fix-up kernel ---
@@ -550,11 +475,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        ps[((tn * TM + tm) * 4 + q) * THREADS + tid] =
-                            floatx4{acc[tn][tm][4 * q], acc[tn][tm][4 * q + 1], acc[tn][tm][4 * q + 2], acc[tn][tm][4 * q + 3]};
+                for (int tm = 0; tm < TM; ++tm) ps[(tn * TM + tm) * THREADS + tid] = acc[tn][tm];
         }
 
         // ---- epilogue ------------------------------------------------------------------------
@@ -562,8 +483,8 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-                for (int tn = 0; tn < TN; ++tn)
-                    store_fragment<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tn, tm, lr, lg, acc[tn][tm]);
+                for (int tp = 0; tp < TN / 2; ++tp)
+                    store_pair<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tp, tm, lr, hi, acc[2 * tp][tm], acc[2 * tp + 1][tm]);
         }
         // the next run rewrites the LDS stages only after this barrier
         __syncthreads();
@@ -590,7 +511,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
 // projections of the 7B..70B shapes at M = 256..2048 (weight copies rotated so that they come from HBM;
 // clocks settled under each shape's load for 40 ms first -- after a lighter kernel the first launches run
 // up to 15 % slower): 256x256 tiles 4.7 TFLOP/s + 6 us per tile, 128x128 tiles two per CU 1.8 TFLOP/s + 6
-// us, 128x128 with three stages one per CU 3.4 TFLOP/s + 4 us; the second pass 5 us + its bytes at ~8
+// us, 128x128 with four stages one per CU 3.4 TFLOP/s + 4 us; the second pass 5 us + its bytes at ~8
 // TB/s (they are still in the caches).  On those 64 shapes the pick is on average 0.5 % slower than the
 // best of the six (configuration, cut) pairs, 8 % at worst.
 struct Schedule {
@@ -629,12 +550,12 @@ Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, 
 // the three multi-token-tile configurations
 constexpr double BIG_TFLOPS = 4.7, BIG_FIXED_US = 6.0;        // 256x256, one workgroup per CU
 constexpr double SMALL_TFLOPS = 1.8, SMALL_FIXED_US = 6.0;    // 128x128, two per CU
-constexpr double DEEP_TFLOPS = 3.4, DEEP_FIXED_US = 4.0;      // 128x128, three stages, one per CU
+constexpr double DEEP_TFLOPS = 3.4, DEEP_FIXED_US = 4.0;      // 128x128, four stages, one per CU
 constexpr double FEW_TFLOPS = 900.0 / 256;                    // one token tile: bound by the weight stream anyway
 
 // ALL = also build the variant for a ragged K (operands staged through VGPRs); the direct-to-LDS
 // configurations leave it to the 128x128 one.
-template <int BN, int BM, int WN, int WM, int GK, int NS, bool ALL, int FD = 1>
+template <int BN, int BM, int WN, int WM, int GK, int NS, bool ALL>
 hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream, double wg_tflops, double tile_fixed_us)
 {
     const int per_tile = is_swiglu(epilogue) ? BN / 2 : BN;
@@ -651,7 +572,7 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream
     dim3 g((unsigned)grid), b(64 * WN * WM);
 #define THI_LAUNCH_K(E, KT)                                                                                  \
     do {                                                                                                     \
-        auto kern = gemm_streamk<BN, BM, WN, WM, GK, NS, E, KT, FD>;                                                  \
+        auto kern = gemm_streamk<BN, BM, WN, WM, GK, NS, E, KT>;                                                      \
         static std::once_flag attr_once;      /* one opt-in per kernel variant, safe from several threads */  \
         std::call_once(attr_once, [&] {                                                                      \
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                   \
@@ -659,7 +580,7 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream
         });                                                                                                  \
         hipLaunchKernelGGL(kern, g, b, lds, stream, a, tiles_m, ktiles, sk_tiles, parts);                    \
         if (sk_tiles > 0)                                                                                    \
-            hipLaunchKernelGGL((gemm_fixup<BN, BM, WN, WM, E>), dim3(2 * sk_tiles * (BN / WN / 32) * (BM / WM / 32)), \
+            hipLaunchKernelGGL((gemm_fixup<BN, BM, WN, WM, E>), dim3(sk_tiles * (BN / WN / 32) * (BM / WM / 16)), \
                                b, 0, stream, a, tiles_m, ktiles, sk_tiles, (int)grid, parts);                \
     } while (0)
 #define THI_LAUNCH(E)                                                                                        \
@@ -757,7 +678,7 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     if (direct && a.M <= 128) {
         // Few tokens: one token tile, the weights are read once and the kernel is bound by how many
         // bytes a CU keeps in flight: three stages of 128 rows x 128 k against 64 tokens (K a multiple of
-        // 128), else of 128 rows x 64 k against 128 tokens.  Every tile is cut along K here (far fewer
+        // 128), else four of 128 rows x 64 k against 128 tokens.  Every tile is cut along K here (far fewer
         // tiles than workgroups) and the second pass costs by the partial tiles' bytes, (workgroups +
         // tiles) x tile size: 128-row tiles halve them against 256-row tiles (7B-shaped O projection at
         // M = 128: 24.8 -> 18.5 us, gate/up 61 -> 53; second pass alone 8.5-9.7 us with 256 rows).  With
@@ -766,8 +687,8 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
         if (a.M <= 64 && a.K % 128 == 0) return launch_cfg<128, 64, 4, 1, 128, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
         const int per_tile = is_swiglu(epilogue) ? 64 : 128;
         if ((a.N + per_tile - 1) / per_tile <= num_cus + num_cus / 8)
-            return launch_cfg<128, 128, 2, 2, 64, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
-        return launch_cfg<256, 128, 4, 1, 64, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
+            return launch_cfg<128, 128, 2, 4, 64, 4, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
+        return launch_cfg<256, 128, 4, 2, 64, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
     }
     // 129..256 tokens and about as many 128-row tiles as workgroups (0.65..1.2 x: the gate/up shapes):
     // one token tile of 256 against 128 rows, so that the weights are read once and few tiles are cut
@@ -780,7 +701,7 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
         if (t128 * 20 >= (long)num_cus * 13 && t128 * 5 <= (long)num_cus * 6)
             return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
     }
-    // Several token tiles: the configuration with the smallest modelled time.  The three-stage 128x128
+    // Several token tiles: the configuration with the smallest modelled time.  The four-stage 128x128
     // configuration runs one workgroup per CU, which only pays where the two-per-CU one would not have a
     // second workgroup for most CUs anyway (at most one 128x128 tile per CU).
     const double c_small = config_cost(a, epilogue, 128, 128, g_small, SMALL_TFLOPS, SMALL_FIXED_US);
@@ -791,11 +712,11 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
         if (t128 <= num_cus) {
             const double c_deep = config_cost(a, epilogue, 128, 128, num_cus, DEEP_TFLOPS, DEEP_FIXED_US);
             if (c_deep < c_big && c_deep < c_small)
-                return launch_cfg<128, 128, 2, 2, 64, 3, false>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
+                return launch_cfg<128, 128, 2, 4, 64, 4, false>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
         }
-        if (c_big <= c_small) return launch_cfg<256, 256, 4, 2, 64, 2, false, 2>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
+        if (c_big <= c_small) return launch_cfg<256, 256, 4, 2, 64, 2, false>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
     }
-    return launch_cfg<128, 128, 2, 2, 64, 2, true>(a, epilogue, g_small, stream, SMALL_TFLOPS, SMALL_FIXED_US);
+    return launch_cfg<128, 128, 2, 4, 64, 2, true>(a, epilogue, g_small, stream, SMALL_TFLOPS, SMALL_FIXED_US);
 }
 
 }  // namespace thi

@@ -10,7 +10,7 @@
 // Layout: q[B,Hq,D], k/v[B,Hkv,S_max,D] (one head's positions contiguous), out[B,Hq,D], all fp16;
 // seq_lens[B] int32 on the device.  Query head h reads cache head h / (Hq/Hkv).
 //
-// Work split: a workgroup (4 waves) takes one chunk of positions of one (request, cache head) and up
+// Work split: a workgroup (4 waves) takes one chunk of positions of one (request, cache head) -- find_item -- and up
 // to GT query heads of that cache head's group.  16 (D = 128) or 8 (D = 64) lanes cover one row with
 // 16-byte loads, so a wave instruction reads 4 or 8 consecutive positions = 1 KiB of contiguous memory;
 // U such loads of K and of V are in flight per wave, one iteration ahead of the arithmetic.  A lane
@@ -19,6 +19,8 @@
 // each keep their own (maximum, sum, output) triple; triples are merged in a fixed order (row groups
 // by shuffle, waves through LDS, chunks by a second small kernel), so results are reproducible.
 #include "thi_internal.h"
+
+#include <mutex>
 
 namespace thi {
 
@@ -33,6 +35,123 @@ template <int GT> struct Unroll { static constexpr int U = (GT >= 4) ? 2 : 4; };
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The number of live chunks of a (request, query head) is left behind its last partial result, as this word in the
+// place of the next chunk's maximum (a NaN that no conversion from fp16 can produce).
+constexpr int AT_END_MARK = 0x7fc0dead;
+
+// What a workgroup works on: positions [c0, c1) of request b, chunk s of n (n = 0: nothing).
+//
+// With at least a workgroup per compute unit from the (request, cache head) pairs alone (a.nsplit == 1) a request is
+// never cut.  Otherwise the requests are cut into chunks of one common size C, the smallest with which all chunks of a
+// cache head fit a.workgroups -- chosen here, from the lengths themselves, because the host does not know
+// them: cutting S_max instead leaves every request that is shorter than its cache with fewer workgroups and the
+// longest one deciding (24 requests of 750..2940 positions in a cache of 3000, 8 cache heads: 55.9 us, with chunks of
+// the live lengths 37.9).  C depends on the lengths as a set only, so a request's result does not
+// depend on its place in the batch.  A request's chunks are then made equal.  Every wave computes this by
+// itself (lengths one per lane); at most AT_MAX_SPLIT chunks per request, of at least a.chunk positions (a multiple of 64).
+struct Item {
+    int b, c0, c1, s, n;
+};
+
+// Inclusive scan over the wave's 64 lanes (lanes shifted in from outside a row count as 0) by data-parallel
+// primitives: a few cycles a step where a lane permutation through LDS takes some hundred.
+template <typename Op>
+__device__ __forceinline__ int wave_scan(int v, Op op)
+{
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));      // row_shr:1
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));      // row_shr:2
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));      // row_shr:4
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));      // row_shr:8
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));      // row_bcast:15 into rows 1 and 3
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+__device__ __forceinline__ Item find_item(const AttnArgs& a)
+{
+    if (a.nsplit == 1) {
+        const int b = blockIdx.z, L = a.seq_lens[b];
+        return Item{b, 0, L, 0, 1};
+    }
+    auto round64 = [](int v) { return (v + 63) & ~63; };
+    if (a.B == 1) {                                      // one request: nothing to add up
+        const int L = a.seq_lens[0];
+        int size = round64((int)((unsigned)(L + a.workgroups - 1) / (unsigned)a.workgroups));
+        size = size > a.chunk ? size : a.chunk;
+        const int n = L <= size ? 1 : (int)((unsigned)(L + size - 1) / (unsigned)size), s = blockIdx.x;
+        if (s >= n) return Item{0, 0, 0, 0, 0};
+        return Item{0, s * size, (s + 1) * size < L ? (s + 1) * size : L, s, n};
+    }
+    const int lane = threadIdx.x & 63, want = a.workgroups;
+    auto add = [](int p, int q) { return p + q; };
+    auto max2 = [](int p, int q) { return p > q ? p : q; };
+    auto length = [&](int b) { return b < a.B ? a.seq_lens[b] : 0; };
+    const int L0 = length(lane);                         // (one group of 64 requests is the rule: no second load for it)
+    int total = 0, longest = 0;
+    for (int b0 = 0; b0 < a.B; b0 += 64) {
+        const int L = b0 == 0 ? L0 : length(b0 + lane);
+        total += __builtin_amdgcn_readlane(wave_scan(L, add), 63);
+        longest = max2(longest, __builtin_amdgcn_readlane(wave_scan(L, max2), 63));
+    }
+    int C = round64((int)((unsigned)(total + want - 1) / (unsigned)want));
+    C = max2(C, round64((longest + AT_MAX_SPLIT - 1) / AT_MAX_SPLIT));
+    C = max2(C, a.chunk);
+    // chunks of request b (an empty one has a chunk too, to write its zeros)
+    auto chunks = [&](int b, int L) { return b >= a.B ? 0 : L <= C ? 1 : (int)((unsigned)(L + C - 1) / (unsigned)C); };
+    while (C < longest) {
+        int n = 0;
+        for (int b0 = 0; b0 < a.B; b0 += 64)
+            n += __builtin_amdgcn_readlane(wave_scan(chunks(b0 + lane, b0 == 0 ? L0 : length(b0 + lane)), add), 63);
+        if (n <= want) break;
+        C += round64(C / 16);
+    }
+    int before = 0;
+    const int x = blockIdx.x;
+    for (int b0 = 0; b0 < a.B; b0 += 64) {
+        const int L = b0 == 0 ? L0 : length(b0 + lane);
+        const int n = chunks(b0 + lane, L), upto = before + wave_scan(n, add);
+        const unsigned long long hit = __builtin_amdgcn_ballot_w64(x >= upto - n && x < upto);
+        if (hit != 0ull) {
+            const int who = __builtin_ctzll(hit);
+            const int Lb = __builtin_amdgcn_readlane(L, who), nb = __builtin_amdgcn_readlane(n, who);
+            const int s = x - (__builtin_amdgcn_readlane(upto, who) - nb);
+            const int size = round64((int)((unsigned)(Lb + nb - 1) / (unsigned)nb));      // <= C: the chunks of a request are equal
+            const int c0 = s * size < Lb ? s * size : Lb;
+            return Item{b0 + who, c0, c0 + size < Lb ? c0 + size : Lb, s, nb};
+        }
+        before = __builtin_amdgcn_readlane(upto, 63);
+    }
+    return Item{0, 0, 0, 0, 0};
+}
+
+// A workgroup's result for one query head (threads of a head together hold its D sums): the output itself if the
+// request is one chunk, else the chunk's (sum, maximum, weight) triple; behind the last one the end mark.
+template <int D>
+__device__ __forceinline__ void put_result(const AttnArgs& a, const Item& it, int h, int d, float of, float lf, float mn)
+{
+    const size_t bh = (size_t)it.b * a.Hq + h;
+    if (it.n == 1) {
+        a.out[bh * D + d] = to_half_bits(of / lf);       // lf > 0: the chunk holds at least one live position
+    } else {
+        float* po = a.part + (bh * AT_MAX_SPLIT + it.s) * (D + 2);
+        po[d] = of;
+        if (d == 0) { po[D] = mn; po[D + 1] = lf; }
+    }
+    if (a.nsplit > 1 && it.s == it.n - 1 && it.n < AT_MAX_SPLIT && d == 0)
+        a.part[(bh * AT_MAX_SPLIT + it.n) * (D + 2) + D] = __builtin_bit_cast(float, AT_END_MARK);
+}
+// an empty request: its output is zero, and there is nothing to merge
+template <int D>
+__device__ __forceinline__ void put_empty(const AttnArgs& a, const Item& it, int h0, int heads)
+{
+    for (int idx = threadIdx.x; idx < heads * D; idx += AT_THREADS) {
+        const size_t bh = (size_t)it.b * a.Hq + h0 + idx / D;
+        a.out[bh * D + idx % D] = 0;
+        if (a.nsplit > 1 && idx % D == 0)
+            a.part[(bh * AT_MAX_SPLIT + 1) * (D + 2) + D] = __builtin_bit_cast(float, AT_END_MARK);
+    }
+}
+
 template <int D, int GT>
 __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
 {
@@ -46,18 +165,15 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int split = blockIdx.x, b = blockIdx.z;
     const int passes = (a.group + GT - 1) / GT;
     const int g = blockIdx.y / passes, pass = blockIdx.y % passes;
-    const int L = a.seq_lens[b];
-    const int c0 = split * a.chunk;
-    const int c1 = (c0 + a.chunk < L) ? c0 + a.chunk : L;
     const int h0 = g * a.group + pass * GT;    // first query head of this workgroup
     const int heads = (a.group - pass * GT < GT) ? a.group - pass * GT : GT;
-    if (c0 >= c1) {                            // nothing of this request in this chunk (uniform: no barrier yet)
-        if (L == 0 && split == 0)              // an empty request: its output is zero
-            for (int idx = tid; idx < heads * D; idx += AT_THREADS)
-                a.out[((size_t)b * a.Hq + h0 + idx / D) * D + idx % D] = 0;
+    const Item item = find_item(a);
+    const int b = item.b, c0 = item.c0, c1 = item.c1;
+    if (item.n == 0) return;
+    if (c0 >= c1) {                            // an empty request (uniform: no barrier yet)
+        put_empty<D>(a, item, h0, heads);
         return;
     }
     const int r = lane / LPR, piece = lane % LPR;
@@ -208,110 +324,141 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
             lf += s_l[w][j] * cw;
             of += s_o[w][j][d] * cw;
         }
-        const size_t bh = (size_t)b * a.Hq + h0 + j;
-        if (a.nsplit == 1) {
-            a.out[bh * D + d] = to_half_bits(of / lf);       // lf > 0: the chunk holds at least one live position
-        } else {
-            float* po = a.part + (bh * a.nsplit + split) * (D + 2);
-            po[d] = of;
-            if (d == 0) { po[D] = mn; po[D + 1] = lf; }
-        }
+        put_result<D>(a, item, h0 + j, d, of, lf, mn);
     }
 }
 
-// Grouped-query variant (D = 128, 4 or 8 query heads per cache head and pass): with several heads per
-// key row the lane-shuffle dot products of attn_decode make the vector ALU the bottleneck, so the scores
-// of 16 positions x up to 16 heads come from four v_mfma_f32_16x16x32_f16 (keys loaded straight into the
-// A-operand layout: lane = (position, 8-element k group); queries resident as the B operand).  A lane
-// then owns the scores of one head at four positions; the running maximum is shared by the four lanes of
-// a head after every block, so all accumulators of a wave refer to the same maximum and merge by plain
-// addition.  The weights reach the lanes that accumulate V (lane = (row group, 16-byte piece), positions
-// 4 * row group + u) as fp16 pairs through one lane permutation per head and pair of positions; V stays on
-// the vector ALU (packed fp16 dot products into fp32), two positions per instruction.
-template <int GT>
+// Grouped-query variant (D = 128, four or more query heads per cache head; up to 16 per pass): both products on the
+// matrix cores, all of K and V through wave-private LDS stages brought straight from memory.
+//
+// A wave takes 16 positions at a time.  Scores: K rows as the A operand (position lane % 16, 8-element k group
+// lane / 16), the queries of up to 16 heads resident as the B operand: four v_mfma_f32_16x16x32_f16.  A lane then holds
+// four consecutive positions of one head, which is exactly the B operand (k = position) of v_mfma_f32_16x16x16_f16 for
+// O^T = V^T P^T; V^T comes as the A operand from LDS by ds_read_b64_tr_b16 (a 16-lane group reads four rows x 16
+// columns, lane j of it receives column j of the four rows).  So neither product needs a lane permutation, a lane's
+// accumulators belong to one head, and rescaling them is a plain multiply (done only when some head's maximum moved).
+// The weights enter the matrix core as fp16 (in [0,1]: 2^-11 relative rounding), sums and their weights are fp32.
+// The first version kept V on the vector ALU (one lane permutation and eight packed dot products per head and pair of
+// positions): ~2 us of ALU work per 64 positions of a workgroup.  8 cache heads x 8 query heads: 6 requests of
+// 2048..8029 positions 50.8 -> 27.2 us (with the chunks of the live lengths), 32 of 512..2007 (not cut) 37.3 -> 31.6,
+// 64 of 75..294 15.5 -> 12.0.
+//
+// Stages: 16 rows x 256 bytes of K, then of V, AT_NS per wave; a row's 16-byte piece p lies at piece p ^ (row % 16), which
+// spreads the K operand reads and the transposing V reads over the banks.  The loads are written in assembly
+// and counted by hand (s_waitcnt vmcnt); nothing else in the loop touches vector memory.  Two stages and 80 KiB, so that
+// two workgroups fit a CU: four stages and one workgroup were 4 % slower on long chunks and 20 % on many short requests.
+constexpr int AT_NS = 2, AT_POS = 16, AT_GQA_HEADS = 16;
+constexpr int AT_STAGE = 2 * AT_POS * 16;                   // 16-byte units: K rows, V rows
+constexpr int AT_Q_UNITS = AT_GQA_HEADS * 16;
+constexpr int AT_WAVE_UNITS = AT_Q_UNITS + AT_NS * AT_STAGE;
+constexpr int AT_GQA_LDS = AT_WAVES * AT_WAVE_UNITS * 16;
+
+typedef short short4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void at_dma(const void* base_uniform, unsigned lane_byte_offset, unsigned lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+                 : : "v"(lane_byte_offset), "s"(base_uniform), "s"(lds_addr) : "memory");
+}
+
 __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
 {
-    constexpr int D = 128;
-    constexpr int WPOS = 16, GPOS = AT_WAVES * WPOS;
-    __shared__ float s_o[AT_WAVES][GT][D];
-    __shared__ float s_m[AT_WAVES][GT], s_l[AT_WAVES][GT];
-    __shared__ uintx4 s_q[4][64];
+    constexpr int D = 128, GT = AT_GQA_HEADS, DT = D / 16;
+    extern __shared__ uintx4 at_smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int split = blockIdx.x, b = blockIdx.z;
     const int passes = (a.group + GT - 1) / GT;
     const int g = blockIdx.y / passes, pass = blockIdx.y % passes;
-    const int L = a.seq_lens[b];
-    const int c0 = split * a.chunk;
-    const int c1 = (c0 + a.chunk < L) ? c0 + a.chunk : L;
     const int h0 = g * a.group + pass * GT;
     const int heads = (a.group - pass * GT < GT) ? a.group - pass * GT : GT;
+    const Item item = find_item(a);
+    const int b = item.b, c0 = item.c0, c1 = item.c1;
+    if (item.n == 0) return;
     if (c0 >= c1) {
-        if (L == 0 && split == 0)
-            for (int idx = tid; idx < heads * D; idx += AT_THREADS)
-                a.out[((size_t)b * a.Hq + h0 + idx / D) * D + idx % D] = 0;
+        put_empty<D>(a, item, h0, heads);
         return;
     }
-    const int lo = lane & 15, hi = lane >> 4;      // scores: (head column, position quad); V: (piece, row group)
+    const int lo = lane & 15, hi = lane >> 4;
 
-    // B operand (head lo, k group hi, per 32-wide k step), kept in LDS: every wave reads the same
-    if (wv == 0) {
+    const uint16_t* const kbase = a.k + ((size_t)(b * a.Hkv + g) * a.S_max) * D;
+    const uint16_t* const vbase = a.v + ((size_t)(b * a.Hkv + g) * a.S_max) * D;
+    uintx4* const my = at_smem + wv * AT_WAVE_UNITS;       // the queries (16 rows like K's), then the stages
+    const unsigned my_addr = (unsigned)(size_t)(__attribute__((address_space(3))) void*)my;
+    const int blocks = (c1 - c0 + AT_POS - 1) / AT_POS;
+    const int nb = (blocks - wv + AT_WAVES - 1) / AT_WAVES;   // this wave's blocks: wv, wv + 4, ...
+
+    // load i of a block: rows 4 i + hi, physical piece lo; rows past the chunk's end come from its last row
+    auto issue = [&](int blk, int st) __attribute__((always_inline)) {
+        const int base = c0 + (blk * AT_WAVES + wv) * AT_POS;
+        const int limit = c1 - 1 - base;
+        const uint16_t* const kb = kbase + (size_t)base * D;
+        const uint16_t* const vb = vbase + (size_t)base * D;
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-            uintx4 raw = {0u, 0u, 0u, 0u};
-            if (lo < heads) raw = *reinterpret_cast<const uintx4*>(a.q + ((size_t)(b * a.Hq + h0 + lo)) * D + s4 * 32 + hi * 8);
-            s_q[s4][lane] = raw;
+        for (int i = 0; i < 4; ++i) {
+            const int row = 4 * i + hi, from = row < limit ? row : limit;
+            const unsigned off = (unsigned)(from * (D * 2) + ((lo ^ row) << 4));
+            at_dma(kb, off, my_addr + (unsigned)(AT_Q_UNITS + st * AT_STAGE + i * 64) * 16u);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 4 * i + hi, from = row < limit ? row : limit;
+            const unsigned off = (unsigned)(from * (D * 2) + ((lo ^ row) << 4));
+            at_dma(vb, off, my_addr + (unsigned)(AT_Q_UNITS + st * AT_STAGE + AT_POS * 16 + i * 64) * 16u);
+        }
+    };
+
+    float m = -__builtin_inff(), l = 0.f;           // of head lo (l: this lane's positions only)
+    floatx4 o[DT];                                  // O^T: rows d = 16 t + 4 hi + i of head lo
+#pragma unroll
+    for (int t = 0; t < DT; ++t) o[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    // the queries, once per wave: a row per head (columns past the group's end repeat its last head and are not used)
+    if (nb > 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 4 * i + hi, from = row < heads ? row : heads - 1;
+            at_dma(a.q + ((size_t)b * a.Hq + h0) * D, (unsigned)(from * (D * 2) + ((lo ^ row) << 4)), my_addr + (unsigned)(i * 64) * 16u);
         }
     }
-    __syncthreads();
-    const uint16_t* kbase = a.k + ((size_t)(b * a.Hkv + g) * a.S_max) * D;
-    const uint16_t* vbase = a.v + ((size_t)(b * a.Hkv + g) * a.S_max) * D + lo * 8;
-
-    float m = -__builtin_inff(), l = 0.f;           // of head lo (l: this lane's four positions only)
-    float o[GT][8];
 #pragma unroll
-    for (int j = 0; j < GT; ++j)
+    for (int st = 0; st < AT_NS; ++st)
+        if (st < nb) issue(st, st);
+    half8 qf[4];                                    // B operand of the scores: head lo, k group hi, per 32-wide k step
+    for (int it = 0; it < nb; ++it) {
+        const int st = it % AT_NS;
+        // the block behind this one may still be in flight (AT_NS = 2: eight loads)
+        if (it + 1 < nb) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (it == 0) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[j][e] = 0.f;
-
-    auto issue_k = [&](int it, uintx4 (&kr)[4]) {
-        const int base = c0 + (it * AT_WAVES + wv) * WPOS;
-        int kp = base + lo;                          // A operand: row lo of the block
-        kp = kp < c1 ? kp : c1 - 1;
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) kr[s4] = ld_stream(kbase + (size_t)kp * D + s4 * 32 + hi * 8);
-    };
-    auto issue_v = [&](int it, uintx4 (&vr)[4]) {
-        const int base = c0 + (it * AT_WAVES + wv) * WPOS;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            int vp = base + 4 * hi + u;
-            vp = vp < c1 ? vp : c1 - 1;
-            vr[u] = ld_stream(vbase + (size_t)vp * D);
+            for (int s4 = 0; s4 < 4; ++s4) qf[s4] = __builtin_bit_cast(half8, my[lo * 16 + ((4 * s4 + hi) ^ lo)]);
         }
-    };
-
-    const int n_it = (c1 - c0 + GPOS - 1) / GPOS;
-    // Register budget (three waves per SIMD need <= 168): the keys of the next block are requested only
-    // after this block's score MFMAs have consumed the current ones (same registers), the values are
-    // one block ahead, and the queries are re-read from LDS as the B operand.
-    uintx4 kreg[4], vn[4];
-    issue_k(0, kreg);
-    issue_v(0, vn);
-    for (int it = 0; it < n_it; ++it) {
-        uintx4 vc[4];
+        const uintx4* const ks = my + AT_Q_UNITS + st * AT_STAGE;
+        uintx4* const vs = my + AT_Q_UNITS + st * AT_STAGE + AT_POS * 16;
+        const int base = c0 + (it * AT_WAVES + wv) * AT_POS;
+        const bool tail = base + AT_POS > c1;
+        if (tail) {                                 // dead rows of V are zeroed: 0 * whatever stands there must stay 0
 #pragma unroll
-        for (int u = 0; u < 4; ++u) vc[u] = vn[u];
-        issue_v(it + 1, vn);
-        const int base = c0 + (it * AT_WAVES + wv) * WPOS;
-
+            for (int i = 0; i < 4; ++i)
+                if (base + 4 * i + hi >= c1) vs[i * 64 + lane] = uintx4{0u, 0u, 0u, 0u};
+            __builtin_amdgcn_wave_barrier();
+        }
+        half8 kf[4];
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) kf[s4] = __builtin_bit_cast(half8, ks[lo * 16 + ((4 * s4 + hi) ^ lo)]);
+        half4 vf[DT];
+        {
+            const int row = 4 * hi + (lo >> 2);
+            const char* const vrow = reinterpret_cast<const char*>(vs + row * 16) + (lo & 1) * 8;
+#pragma unroll
+            for (int t = 0; t < DT; ++t)
+                vf[t] = __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) short4_t*)(vrow + (((2 * t + ((lo >> 1) & 1)) ^ row) << 4))));
+        }
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, kreg[s4]),
-                                                         __builtin_bit_cast(half8, s_q[s4][lane]), acc, 0, 0, 0);
-        issue_k(it + 1, kreg);
+        for (int s4 = 0; s4 < 4; ++s4) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[s4], qf[s4], acc, 0, 0, 0);
         float t[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) t[i] = (base + 4 * hi + i < c1) ? acc[i] * a.scale2 : -__builtin_inff();
@@ -326,103 +473,77 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
         for (int i = 0; i < 4; ++i) p[i] = exp2_fast(t[i] - ms);
         l = l * corr + ((p[0] + p[1]) + (p[2] + p[3]));
         m = mn;
-        // the accumulators are rescaled only when some head's maximum moved (rare after the first blocks)
         if (__builtin_amdgcn_ballot_w64(corr != 1.0f) != 0ull) {
 #pragma unroll
-            for (int j = 0; j < GT; ++j) {
-                const float cj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, corr), j));
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[j][e] *= cj;
-            }
+            for (int q = 0; q < DT; ++q) o[q] *= corr;
         }
-        // weights times V, two positions per instruction: v_dot2_f32_f16 on (V[u][d], V[u+1][d]) and the
-        // fp16 pair of their weights (weights are in [0,1]: 2^-11 relative rounding), fp32 accumulation
-        half2_t ppair[2];
-        ppair[0] = half2_t{(_Float16)p[0], (_Float16)p[1]};
-        ppair[1] = half2_t{(_Float16)p[2], (_Float16)p[3]};
+        const half4 pf = {(_Float16)p[0], (_Float16)p[1], (_Float16)p[2], (_Float16)p[3]};
 #pragma unroll
-        for (int up = 0; up < 2; ++up) {
-            const bool live0 = base + 4 * hi + 2 * up < c1, live1 = base + 4 * hi + 2 * up + 1 < c1;
-            half2_t vpk[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const unsigned w0 = live0 ? vc[2 * up][e] : 0u, w1 = live1 ? vc[2 * up + 1][e] : 0u;
-                vpk[2 * e] = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(w1, w0, 0x05040100u));
-                vpk[2 * e + 1] = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(w1, w0, 0x07060302u));
-            }
-#pragma unroll
-            for (int j = 0; j < GT; ++j) {
-                // head j's weights of positions 4*hi + 2*up and + 1 (held by lane j of this row group)
-                const int bits = __shfl(__builtin_bit_cast(int, ppair[up]), j + 16 * hi);
-                const half2_t pj = __builtin_bit_cast(half2_t, bits);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[j][e] = __builtin_amdgcn_fdot2(vpk[e], pj, o[j][e], false);
-            }
-        }
+        for (int q = 0; q < DT; ++q) o[q] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf[q], pf, o[q], 0, 0, 0);
+        // every read of this stage has returned before it is filled again
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (it + AT_NS < nb) issue(it + AT_NS, st);
     }
 
-    // the wave's four row groups: same maximum, so sums simply add
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
+    // the waves meet in LDS: [wave][head][d], then [wave][head] maximum and weight
+    float* const s_o = reinterpret_cast<float*>(at_smem);
+    float* const s_m = s_o + AT_WAVES * GT * D;
+    float* const s_l = s_m + AT_WAVES * GT;
+    __syncthreads();                                // every wave has read its last stage
 #pragma unroll
-    for (int j = 0; j < GT; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            o[j][e] += __shfl_xor(o[j][e], 16);
-            o[j][e] += __shfl_xor(o[j][e], 32);
-        }
-    if (hi == 0) {
-#pragma unroll
-        for (int j = 0; j < GT; ++j)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s_o[wv][j][lo * 8 + e] = o[j][e];
-        if (lo < GT) { s_m[wv][lo] = m; s_l[wv][lo] = l; }
-    }
+    for (int t = 0; t < DT; ++t) *reinterpret_cast<floatx4*>(s_o + (wv * GT + lo) * D + 16 * t + 4 * hi) = o[t];
+    if (hi == 0) { s_m[wv * GT + lo] = m; s_l[wv * GT + lo] = l; }
     __syncthreads();
     for (int idx = tid; idx < heads * D; idx += AT_THREADS) {
         const int j = idx / D, d = idx % D;
-        float mn = s_m[0][j];
+        float mn = s_m[j];
 #pragma unroll
-        for (int w = 1; w < AT_WAVES; ++w) mn = __builtin_fmaxf(mn, s_m[w][j]);
+        for (int w = 1; w < AT_WAVES; ++w) mn = __builtin_fmaxf(mn, s_m[w * GT + j]);
         const float ms = (mn == -__builtin_inff()) ? 0.f : mn;
         float lf = 0.f, of = 0.f;
 #pragma unroll
         for (int w = 0; w < AT_WAVES; ++w) {        // fixed order: waves 0..3
-            const float cw = exp2_fast(s_m[w][j] - ms);
-            lf += s_l[w][j] * cw;
-            of += s_o[w][j][d] * cw;
+            const float cw = exp2_fast(s_m[w * GT + j] - ms);
+            lf += s_l[w * GT + j] * cw;
+            of += s_o[(w * GT + j) * D + d] * cw;
         }
-        const size_t bh = (size_t)b * a.Hq + h0 + j;
-        if (a.nsplit == 1) {
-            a.out[bh * D + d] = to_half_bits(of / lf);
-        } else {
-            float* po = a.part + (bh * a.nsplit + split) * (D + 2);
-            po[d] = of;
-            if (d == 0) { po[D] = mn; po[D + 1] = lf; }
-        }
+        put_result<D>(a, item, h0 + j, d, of, lf, mn);
     }
 }
 
-// Second pass when the positions were cut into chunks: one workgroup per (request, query head) merges
-// the chunks' triples in chunk order and normalises.
+// Second pass when requests may have been cut into chunks: one workgroup per (request, query head) merges the
+// chunks' triples in chunk order and normalises.  How many there are the end mark says; maxima and weights are
+// fetched one chunk per lane, the sums eight chunks at a time, so that the memory round trips overlap.
 template <int D>
 __global__ __launch_bounds__(D) void attn_combine(AttnArgs a)
 {
-    const int bh = blockIdx.x, d = threadIdx.x;
-    const int b = bh / a.Hq;
-    const int L = a.seq_lens[b];
-    const int live = (L + a.chunk - 1) / a.chunk;       // chunks that hold positions of this request
-    float m = -__builtin_inff(), l = 0.f, o = 0.f;
-    for (int s = 0; s < live; ++s) {
-        const float* po = a.part + ((size_t)bh * a.nsplit + s) * (D + 2);
-        const float m2 = po[D], l2 = po[D + 1], o2 = po[d];
-        const float mn = __builtin_fmaxf(m, m2);
-        const float ca = exp2_fast(m - mn), cb = exp2_fast(m2 - mn);      // m2 is finite: the chunk was live
-        l = l * ca + l2 * cb;
-        o = o * ca + o2 * cb;
-        m = mn;
+    const int bh = blockIdx.x, d = threadIdx.x, lane = threadIdx.x & 63;
+    const float* const first = a.part + (size_t)bh * AT_MAX_SPLIT * (D + 2);
+    const float mine = first[(size_t)(lane < AT_MAX_SPLIT ? lane : 0) * (D + 2) + D];
+    const float mine_l = first[(size_t)(lane < AT_MAX_SPLIT ? lane : 0) * (D + 2) + D + 1];
+    const unsigned long long mark = __builtin_amdgcn_ballot_w64(lane < AT_MAX_SPLIT && lane > 0 && __builtin_bit_cast(int, mine) == AT_END_MARK);
+    const int live = mark != 0ull ? __builtin_ctzll(mark) : AT_MAX_SPLIT;
+    if (live == 1) return;                              // the first pass has written this output
+    float m = lane < live ? mine : -__builtin_inff();
+#pragma unroll
+    for (int sh = 32; sh >= 1; sh >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, sh));
+    const float w = lane < live ? exp2_fast(mine - m) : 0.f;
+    float l = 0.f, o = 0.f;
+    for (int s0 = 0; s0 < live; s0 += 8) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = first[(size_t)(s0 + i < live ? s0 + i : live - 1) * (D + 2) + d];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (s0 + i < live) {
+                const float c = __shfl(w, s0 + i);
+                l += __shfl(mine_l, s0 + i) * c;
+                o += v[i] * c;
+            }
     }
-    if (live > 0) a.out[(size_t)bh * D + d] = to_half_bits(o / l);      // (an empty request was zeroed by the first pass)
+    a.out[(size_t)bh * D + d] = to_half_bits(o / l);
 }
 
 template <int D, int GT>
@@ -435,18 +556,21 @@ template <int D>
 hipError_t launch_d(const AttnArgs& a, int gt, hipStream_t stream)
 {
     const int passes = (a.group + gt - 1) / gt;
-    dim3 grid((unsigned)a.nsplit, (unsigned)(a.Hkv * passes), (unsigned)a.B);
+    // uncut: one workgroup per request, cache head and pass; else a.workgroups for the chunks of a cache head
+    dim3 grid((unsigned)(a.nsplit == 1 ? 1 : a.workgroups), (unsigned)(a.Hkv * passes), (unsigned)(a.nsplit == 1 ? a.B : 1));
     switch (gt) {
     case 1: launch_decode<D, 1>(a, grid, stream); break;
     case 2: launch_decode<D, 2>(a, grid, stream); break;
-    case 4:
-        if (D == 128) hipLaunchKernelGGL((attn_decode_gqa<4>), grid, dim3(AT_THREADS), 0, stream, a);
-        else launch_decode<D, 4>(a, grid, stream);
+    case 4: if constexpr (D == 64) launch_decode<D, 4>(a, grid, stream); break;
+    case 8: if constexpr (D == 64) launch_decode<D, 8>(a, grid, stream); break;
+    default: {                  // D = 128 only
+        static std::once_flag attr_once;
+        std::call_once(attr_once, [] {
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(attn_decode_gqa), hipFuncAttributeMaxDynamicSharedMemorySize, AT_GQA_LDS);
+        });
+        hipLaunchKernelGGL(attn_decode_gqa, grid, dim3(AT_THREADS), AT_GQA_LDS, stream, a);
         break;
-    default:
-        if (D == 128) hipLaunchKernelGGL((attn_decode_gqa<8>), grid, dim3(AT_THREADS), 0, stream, a);
-        else launch_decode<D, 8>(a, grid, stream);
-        break;
+    }
     }
     if (a.nsplit > 1)
         hipLaunchKernelGGL((attn_combine<D>), dim3((unsigned)(a.B * a.Hq)), dim3(D), 0, stream, a);
@@ -457,7 +581,7 @@ hipError_t launch_d(const AttnArgs& a, int gt, hipStream_t stream)
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream)
 {
-    const int gt = attention_heads_per_workgroup(a.group);
+    const int gt = attention_heads_per_workgroup(a.D, a.group);
     if (a.D == 128) return launch_d<128>(a, gt, stream);
     if (a.D == 64) return launch_d<64>(a, gt, stream);
     return hipErrorInvalidValue;

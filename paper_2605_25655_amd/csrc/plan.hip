@@ -57,13 +57,22 @@ bool mlp_fused_ok(int M, int H, int I, int epilogue_up, int num_cus, int ksplit_
 size_t gemm_partial_bytes() { return (size_t)GEMM_MAX_GRID * 2 * 128 * 128 * sizeof(float); }
 
 // ---- decode attention ------------------------------------------------------------------------------
-int attention_heads_per_workgroup(int group) { return group >= 8 ? 8 : group >= 4 ? 4 : group >= 2 ? 2 : 1; }
-
-// chunks are whole multiples of this (a multiple of every kernel's positions per workgroup iteration)
-int attention_chunk_quantum(int D, int gt)
+// query heads that share a pass over their cache head: 16 on the matrix cores (D = 128, groups of four and more)
+int attention_heads_per_workgroup(int D, int group)
 {
-    (void)D; (void)gt;
-    return 128;
+    if (group >= 4 && D == 128) return 16;
+    return group >= 8 ? 8 : group >= 4 ? 4 : group >= 2 ? 2 : 1;
+}
+
+// Workgroups per cache head (and pass) for the chunks of all requests; 1 = requests are not cut: enough of them, or
+// caches of at most one chunk.  One workgroup per compute unit; two where one would leave a request fewer than two chunks.
+int attention_workgroups_per_head(int B, int heads, int S_max, int num_cus)
+{
+    if ((long)B * heads >= num_cus || S_max <= AT_MIN_CHUNK) return 1;
+    int want = num_cus / heads;
+    if (want < 2 * B) want = (2 * num_cus + heads - 1) / heads;
+    if (want > B * AT_MAX_SPLIT) want = B * AT_MAX_SPLIT;
+    return want < 2 ? 2 : want;
 }
 
 }  // namespace thi

@@ -134,15 +134,18 @@ struct AttnArgs {
     const uint16_t* v;       // [B,Hkv,S_max,D]
     const int* seq_lens;     // [B] live positions per request (device memory)
     uint16_t* out;           // [B,Hq,D]
-    float* part;             // [B*Hq][nsplit][D + 2]: a chunk's unnormalised output, running maximum, running sum
+    float* part;             // [B*Hq][AT_MAX_SPLIT][D + 2]: a chunk's unnormalised output, running maximum, running sum
     int B, Hq, Hkv, D, S_max;
     int group;               // Hq / Hkv query heads per cache head
-    int chunk, nsplit;       // positions per chunk (a multiple of the kernel's quantum), chunks per request
+    int nsplit;              // chunks per request, at most (1: requests are not cut)
+    int chunk;               // positions per chunk, at least
+    int workgroups;          // per cache head (and pass), for the chunks of all requests
     float scale2;            // softmax scale times log2(e)
 };
-constexpr int AT_MAX_SPLIT = 32;
-int attention_heads_per_workgroup(int group);
-int attention_chunk_quantum(int D, int gt);
+constexpr int AT_MAX_SPLIT = 32;      // chunks per request, at most
+constexpr int AT_MIN_CHUNK = 128;     // positions per chunk, at least
+int attention_heads_per_workgroup(int D, int group);
+int attention_workgroups_per_head(int B, int heads, int S_max, int num_cus);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream);
 
 // Rotate one interleaved pair (a, b) = (y[c], y[c+1]), c even: Algorithm 1's  y*cos + mix*sin  with

@@ -152,3 +152,38 @@ def test_attention_argument_errors(thi):
     assert thi.thi_decode_attention(z(1, 2, 96), z(1, 2, 8, 96), z(1, 2, 8, 96), lens, 1.0, z(1, 2, 96), ws, check=False) == 2
     assert thi.thi_decode_attention(z(1, 2, 128), z(1, 2, 8, 128), z(1, 2, 8, 128), None, 1.0, z(1, 2, 128), ws, check=False) == 1
     assert thi.thi_attention_workspace_bytes(1, 3, 2, 128, 8) == 0
+
+
+# Chunks are chosen on the device from the live lengths, and groups of four and more heads of 128 take up to 16 heads a
+# pass: sizes around the 16-position blocks, the 64-position chunk grid, the 128-position minimum, the 32 chunks a
+# request may have, passes of 16 heads and a rest, more than 64 requests, and one long request among short ones.
+CHUNKS = [
+    (6, 8, 1, 128, 4100, [4100, 1, 0, 129, 128, 64]),
+    (1, 5, 1, 128, 8192, [8192]),                     # 32 chunks: no end mark
+    (1, 1, 1, 64, 8191, [8191]),
+    (3, 17, 1, 128, 300, [15, 16, 17]),               # a pass of 16 heads and a pass of one
+    (2, 40, 2, 128, 700, [700, 193]),                 # groups of 20
+    (100, 4, 1, 128, 150, None),                      # more requests than lanes, cut
+    (70, 2, 1, 64, 400, None),
+    (4, 64, 8, 128, 1025, [1025, 1024, 1023, 2]),
+    (2, 52, 52, 128, 900, [900, 31]),
+    (33, 32, 8, 128, 161, None),                      # not cut
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,S_max,lens", CHUNKS)
+def test_chunks_of_live_lengths(thi, oracle_mod, B, Hq, Hkv, D, S_max, lens):
+    """Against the oracle, and: a request's result does not depend on its place in the batch, bit for bit."""
+    say(f"[case] attention chunks B={B} Hq={Hq} Hkv={Hkv} D={D} S_max={S_max}")
+    if lens is None:
+        lens = (np.arange(B) * 41 % (S_max + 1)).tolist()
+    lens = np.asarray(lens, dtype=np.int32)
+    q, k, v = make_case(9500 + B + Hq + D + S_max, B, Hq, Hkv, D, S_max, lens)
+    scale = float(np.float32(1.0 / np.sqrt(D)))
+    got = run(thi, q, k, v, lens, scale)
+    kc, vc = np.nan_to_num(k, posinf=0.0), np.nan_to_num(v, posinf=0.0)
+    y, s = oracle_mod.decode_attention(q, kc, vc, lens, scale)
+    check(got.reshape(B * Hq, D), y.reshape(B * Hq, D), s.reshape(B * Hq, D) + 1e-30, "attention chunks", argmax=False)
+    perm = np.random.default_rng(B).permutation(B)
+    again = run(thi, q[perm], k[perm], v[perm], lens[perm], scale)
+    assert np.array_equal(got[perm].view(np.uint16), again.view(np.uint16))

@@ -205,7 +205,10 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_fixup(GemmArgs a, int tiles
 }
 
 // BN x BM output tile, WN x WM waves; wave tile (BN/WN) x (BM/WM) built from 16x16 MFMA tiles.
-// KTAIL: K is not a multiple of 64 (pieces past K are zero-filled; operands then go through VGPRs).
+// KTAIL: K is not a multiple of GK.  The last k-tile's pieces past K are loaded from the k-tile's first piece (valid
+// memory) and overwritten with zeros once they have landed; K is a multiple of 8, so a 16-byte piece is entirely inside
+// or outside.  (Until the direct loads took the ragged K as well it went through VGPRs in the two-per-CU 128x128
+// configuration alone: 333 x 5001 x 1384 27.5 us, now 23.6.)
 // Operand fragments are read from LDS one k-step of 32 ahead of their MFMAs (two fragment buffers).  The k-tile's
 // one barrier sits in front of its last k-step: every read of the stage has been issued by then, the next
 // k-tile must have landed, and its first fragments are read behind the barrier while the last k-step is multiplied.
@@ -221,16 +224,13 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     constexpr int GPIECES = GK / 8;             // 16-byte pieces per tile row
     constexpr int KSTEPS = GK / 32;             // MFMA k-steps per staged tile (even)
     constexpr int ROWS_PER_DMA = 64 / GPIECES;  // tile rows covered by one wave-wide direct load
-    constexpr int ROWS_PER_PASS = THREADS / GPIECES;
-    constexpr int WPASS = BN / ROWS_PER_PASS;   // per-thread pieces of the weight tile
-    constexpr int XPASS = BM / ROWS_PER_PASS;
+    constexpr int WPASS = BN * GPIECES / THREADS;   // direct loads of the weight tile per k-tile and wave
+    constexpr int XPASS = BM * GPIECES / THREADS;
     constexpr int TN = BN / WN / 16;            // MFMA tiles per wave along n (even)
     constexpr int TM = BM / WM / 16;
     constexpr int JPT = is_swiglu(EPI) ? BN / 2 : BN;   // physical weight rows per tile
-    constexpr bool W_DMA = !KTAIL;                           // weight tile: global -> LDS directly
-    constexpr bool X_DMA = !KTAIL;                           // activation tile: the same
     constexpr int STAGE = (BN + BM) * GPIECES;   // 16-byte units per stage: weight tile, then activation tile
-    static_assert(NS >= 2 && NS <= 8 && (KSTEPS % 2) == 0 && (TN % 2) == 0, "pipeline shape");
+    static_assert(NS >= 2 && NS <= 4 && (KSTEPS % 2) == 0 && (TN % 2) == 0, "pipeline shape");
     static_assert(WPASS >= 1 && XPASS >= 1, "tile too small for the thread count");
 
     extern __shared__ uintx4 smem[];
@@ -255,13 +255,9 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     const int first_tile = u_begin / ktiles;
     int t_whole = sk_tiles + worker;
 
-    // DMA staging role.  A wave instruction covers ROWS_PER_DMA tile rows = 64 consecutive LDS units;
-    // lane L owns unit L of it: row (ROWS_PER_DMA*block + L/P), physical slot L%P, logical piece
-    // slot ^ f(row).  VGPR staging role (operands that are zero-padded: ragged K): logical piece
-    // tid%P of rows tid/P + ROWS_PER_PASS*i.
+    // A wave-wide load covers ROWS_PER_DMA tile rows = 64 consecutive LDS units; lane L owns unit L of it:
+    // row (ROWS_PER_DMA*block + L/P), physical slot L%P, logical piece slot ^ f(row).
     const int slot = lane % GPIECES;
-    const int vp = tid % GPIECES, vr0 = tid / GPIECES;
-    const uintx4 zero4 = {0u, 0u, 0u, 0u};
 
     for (int u = u_begin;;) {
         int t, kb, ke;
@@ -280,98 +276,67 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
         }
         const int tile_m = t % tiles_m, tile_n = t / tiles_m;
 
-        // Operand sources.  Direct loads: a wave-uniform base pointer per wave instruction (scalar
-        // registers, advanced by scalar adds) plus a 32-bit per-lane byte offset that never changes,
-        // so that issuing a k-tile's loads costs no vector ALU work.  Staged loads: per-thread pointers.
+        // Operand sources: a wave-uniform base pointer per wave instruction (scalar registers, advanced by
+        // scalar adds) plus a 32-bit per-lane byte offset that never changes, so that issuing a k-tile's
+        // loads costs no vector ALU work.
         const uint16_t* wsrc[WPASS];
         const uint16_t* xsrc[XPASS];
         unsigned woff[WPASS], xoff[XPASS];
 #pragma unroll
         for (int i = 0; i < WPASS; ++i) {
             const int blk = wv * WPASS + i;                          // (uniform) block of ROWS_PER_DMA rows
-            const int v = W_DMA ? blk * ROWS_PER_DMA + lane / GPIECES : vr0 + ROWS_PER_PASS * i;
-            const int piece = W_DMA ? slot ^ swz_f<GPIECES>(v) : vp;
-            if (is_swiglu(EPI)) {
+            const int v = blk * ROWS_PER_DMA + lane / GPIECES;
+            const int piece = slot ^ swz_f<GPIECES>(v);
+            if (is_swiglu(EPI)) {                                    // a wave instruction covers gate rows or up rows only
                 const int j0 = tile_n * JPT;                         // first row of the tile: always valid
                 int j = j0 + (v >> 5) * 16 + (v & 15);
                 j = j < a.N ? j : a.N - 1;
-                if (W_DMA) {                                         // a wave instruction covers gate rows or up rows only
-                    wsrc[i] = (((blk * ROWS_PER_DMA) >> 4) & 1 ? a.w1 : a.w0) + (size_t)j0 * K;
-                    woff[i] = (unsigned)((j - j0) * K + piece * 8) * 2u;
-                } else {
-                    wsrc[i] = (((v >> 4) & 1) ? a.w1 : a.w0) + (size_t)j * K + piece * 8;
-                    woff[i] = 0;
-                }
+                wsrc[i] = (((blk * ROWS_PER_DMA) >> 4) & 1 ? a.w1 : a.w0) + (size_t)j0 * K;
+                woff[i] = (unsigned)((j - j0) * K + piece * 8) * 2u;
             } else {
                 const int n0 = tile_n * BN;
                 int n = n0 + v;
                 n = n < a.N ? n : a.N - 1;
-                if (W_DMA) {
-                    wsrc[i] = a.w0 + (size_t)n0 * K;
-                    woff[i] = (unsigned)((n - n0) * K + piece * 8) * 2u;
-                } else {
-                    wsrc[i] = a.w0 + (size_t)n * K + piece * 8;
-                    woff[i] = 0;
-                }
+                wsrc[i] = a.w0 + (size_t)n0 * K;
+                woff[i] = (unsigned)((n - n0) * K + piece * 8) * 2u;
             }
         }
 #pragma unroll
         for (int i = 0; i < XPASS; ++i) {
-            const int v = X_DMA ? (wv * XPASS + i) * ROWS_PER_DMA + lane / GPIECES : vr0 + ROWS_PER_PASS * i;
-            const int piece = X_DMA ? slot ^ swz_f<GPIECES>(v) : vp;
+            const int v = (wv * XPASS + i) * ROWS_PER_DMA + lane / GPIECES;
+            const int piece = slot ^ swz_f<GPIECES>(v);
             const int m0 = tile_m * BM;
             int m = m0 + v;
             m = m < a.M ? m : a.M - 1;       // rows past M are loaded from a valid row and never stored
-            if (X_DMA) {
-                xsrc[i] = a.x + (size_t)m0 * K;
-                xoff[i] = (unsigned)((m - m0) * K + piece * 8) * 2u;
-            } else {
-                xsrc[i] = a.x + (size_t)m * K + piece * 8;
-                xoff[i] = 0;
-            }
+            xsrc[i] = a.x + (size_t)m0 * K;
+            xoff[i] = (unsigned)((m - m0) * K + piece * 8) * 2u;
         }
 
-        uintx4 wreg[W_DMA ? 1 : WPASS], xreg[X_DMA ? 1 : XPASS];
-
-        // K is a multiple of 8, so a 16-byte piece is entirely inside or outside [0,K); with KTAIL the
-        // pieces past K are read from the row start (valid memory) and replaced by zeros.
-        auto load_w = [&](int kt, int buf) {      // DMA: lands in stage buf; else: into wreg
-#pragma unroll
-            for (int i = 0; i < WPASS; ++i) {
-                if (W_DMA) {
-                    dma16_sbase(wsrc[i] + kt * GK, woff[i], smem + buf * STAGE + (wv * WPASS + i) * 64);
-                } else {
-                    const bool kok = kt * GK + vp * 8 < K;
-                    uintx4 v = *reinterpret_cast<const uintx4*>(wsrc[i] + (kok ? kt * GK : -vp * 8));
-                    wreg[i] = kok ? v : zero4;
-                }
-            }
+        // KTAIL: the logical piece (of this lane's unit of load `blk`) if it lies past K in k-tile kt, else 0
+        auto past_k = [&](int blk, int kt) {
+            const int piece = slot ^ swz_f<GPIECES>(blk * ROWS_PER_DMA + lane / GPIECES);
+            return kt * GK + piece * 8 >= K ? piece : 0;
         };
-        auto load_x = [&](int kt, int buf) {
+        auto load_tile = [&](int kt, int buf) {
+            const bool tail = KTAIL && kt == ktiles - 1;
 #pragma unroll
-            for (int i = 0; i < XPASS; ++i) {
-                if (X_DMA) {
-                    dma16_sbase(xsrc[i] + kt * GK, xoff[i], smem + buf * STAGE + BN * GPIECES + (wv * XPASS + i) * 64);
-                } else {
-                    const bool kok = !KTAIL || kt * GK + vp * 8 < K;
-                    uintx4 v = *reinterpret_cast<const uintx4*>(xsrc[i] + (kok ? kt * GK : -vp * 8));
-                    xreg[i] = kok ? v : zero4;
-                }
-            }
+            for (int i = 0; i < WPASS; ++i)
+                dma16_sbase(wsrc[i] + kt * GK, tail ? woff[i] - 16u * past_k(wv * WPASS + i, kt) : woff[i],
+                            smem + buf * STAGE + (wv * WPASS + i) * 64);
+#pragma unroll
+            for (int i = 0; i < XPASS; ++i)
+                dma16_sbase(xsrc[i] + kt * GK, tail ? xoff[i] - 16u * past_k(wv * XPASS + i, kt) : xoff[i],
+                            smem + buf * STAGE + BN * GPIECES + (wv * XPASS + i) * 64);
         };
-        auto store_w = [&](int buf) {             // VGPR path only
-            if (!W_DMA) {
+        // zeros where this wave's loads of k-tile kt (landed, in stage buf) lay past K
+        auto zero_tail = [&](int kt, int buf) {
+            if (!KTAIL || kt != ktiles - 1) return;
 #pragma unroll
-                for (int i = 0; i < WPASS; ++i) smem[buf * STAGE + swz<GPIECES>(vr0 + ROWS_PER_PASS * i, vp)] = wreg[i];
-            }
-        };
-        auto store_x = [&](int buf) {
-            if (!X_DMA) {
+            for (int i = 0; i < WPASS; ++i)
+                if (past_k(wv * WPASS + i, kt)) smem[buf * STAGE + (wv * WPASS + i) * 64 + lane] = uintx4{0u, 0u, 0u, 0u};
 #pragma unroll
-                for (int i = 0; i < XPASS; ++i) {
-                    smem[buf * STAGE + BN * GPIECES + swz<GPIECES>(vr0 + ROWS_PER_PASS * i, vp)] = xreg[i];
-                }
-            }
+            for (int i = 0; i < XPASS; ++i)
+                if (past_k(wv * XPASS + i, kt)) smem[buf * STAGE + BN * GPIECES + (wv * XPASS + i) * 64 + lane] = uintx4{0u, 0u, 0u, 0u};
         };
 
         floatx4 acc[TN][TM];
@@ -409,23 +374,16 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             __builtin_amdgcn_sched_group_barrier(0x008, TN * TM - PER * (TN + TM), 0);
         };
 
-        // ---- prologue: the first NS k-tiles into the NS stages; VGPR-path operands run one tile further
+        // ---- prologue: the first NS k-tiles into the NS stages
+        constexpr int LPT = WPASS + XPASS;           // direct loads per k-tile per wave
         const int nk = ke - kb;
 #pragma unroll
-        for (int st = 0; st < NS; ++st) {
-            if (st < nk) {
-                load_w(kb + st, st); load_x(kb + st, st);
-                store_w(st); store_x(st);
-            }
-        }
-        if (nk > NS) {
-            if (!W_DMA) load_w(kb + NS, 0);
-            if (!X_DMA) load_x(kb + NS, 0);
-        }
-        if (W_DMA || X_DMA) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        for (int st = 0; st < NS; ++st)
+            if (st < nk) load_tile(kb + st, st);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (KTAIL && nk <= NS) zero_tail(ke - 1, nk - 1);
         __syncthreads();
 
-        constexpr int LPT = (W_DMA ? WPASS : 0) + (X_DMA ? XPASS : 0);   // direct loads per k-tile per wave
         frags(0, 0, 0);
         for (int it = 0; it < nk; ++it) {
             const int st = it % NS;
@@ -441,27 +399,15 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             // direct loads complete in order, so it is enough that at most the loads of the k-tiles
             // behind it (up to NS-2 of them) are still in flight.  The compiler does not carry these
             // loads across the loop edge, hence the explicit wait.
-            if (LPT > 0) {
-                int behind = nk - 2 - it;            // k-tiles after it+1 that have been requested
-                behind = behind < NS - 2 ? behind : NS - 2;
-                static_assert((NS - 2) * LPT < 64, "wait count out of range");
-                if (behind <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
-                else if (behind == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NS > 3 ? 2 * LPT : 0) : "memory");
-                else if (behind == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NS > 4 ? 3 * LPT : 0) : "memory");
-                else if (behind == 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NS > 5 ? 4 * LPT : 0) : "memory");
-                else if (behind == 5) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NS > 6 ? 5 * LPT : 0) : "memory");
-                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NS > 7 ? 6 * LPT : 0) : "memory");
-            }
+            int behind = nk - 2 - it;            // k-tiles after it+1 that have been requested
+            behind = behind < NS - 2 ? behind : NS - 2;
+            static_assert(NS <= 4 && 2 * LPT < 64, "wait count out of range");
+            if (behind <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
+            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPT) : "memory");
+            if (KTAIL && it + 1 < nk) zero_tail(kb + it + 1, (it + 1) % NS);
             __syncthreads();
-            if (it + NS < nk) {
-                if (W_DMA) load_w(kb + it + NS, st); else store_w(st);
-                if (X_DMA) load_x(kb + it + NS, st); else store_x(st);
-                if (it + NS + 1 < nk) {
-                    if (!W_DMA) load_w(kb + it + NS + 1, st);
-                    if (!X_DMA) load_x(kb + it + NS + 1, st);
-                }
-            }
+            if (it + NS < nk) load_tile(kb + it + NS, st);
             frags(it + 1 < nk ? (it + 1) % NS : st, 0, 0);      // (behind the last k-tile: read and never used)
             mfmas((KSTEPS - 1) & 1);
             interleave(PerRead{});
@@ -553,8 +499,7 @@ constexpr double SMALL_TFLOPS = 1.8, SMALL_FIXED_US = 6.0;    // 128x128, two pe
 constexpr double DEEP_TFLOPS = 3.4, DEEP_FIXED_US = 4.0;      // 128x128, four stages, one per CU
 constexpr double FEW_TFLOPS = 900.0 / 256;                    // one token tile: bound by the weight stream anyway
 
-// ALL = also build the variant for a ragged K (operands staged through VGPRs); the direct-to-LDS
-// configurations leave it to the 128x128 one.
+// ALL = also build the variant for a ragged K (KTAIL).
 template <int BN, int BM, int WN, int WM, int GK, int NS, bool ALL>
 hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream, double wg_tflops, double tile_fixed_us)
 {
@@ -673,9 +618,9 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     int g_big = num_cus, g_small = 2 * num_cus;        // workgroups that fit: one resp. two per CU
     if (g_big * 4 > GEMM_MAX_GRID) g_big = GEMM_MAX_GRID / 4;
     if (g_small > GEMM_MAX_GRID) g_small = GEMM_MAX_GRID;
-    // the direct-to-LDS configurations: plain / SwiGLU epilogues, K a multiple of the staged k-tile
-    const bool direct = !is_rms(epilogue) && (a.K % 64 == 0);
-    if (direct && a.M <= 128) {
+    if (is_rms(epilogue)) return hipErrorInvalidValue;
+    const bool even_k = a.K % 64 == 0;                 // else: the configurations that are built with KTAIL
+    if (a.M <= 128) {
         // Few tokens: one token tile, the weights are read once and the kernel is bound by how many
         // bytes a CU keeps in flight: three stages of 128 rows x 128 k against 64 tokens (K a multiple of
         // 128), else four of 128 rows x 64 k against 128 tokens.  Every tile is cut along K here (far fewer
@@ -686,8 +631,8 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
         // activation staging wins instead (188 against 230 us).
         if (a.M <= 64 && a.K % 128 == 0) return launch_cfg<128, 64, 4, 1, 128, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
         const int per_tile = is_swiglu(epilogue) ? 64 : 128;
-        if ((a.N + per_tile - 1) / per_tile <= num_cus + num_cus / 8)
-            return launch_cfg<128, 128, 2, 4, 64, 4, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
+        if (!even_k || (a.N + per_tile - 1) / per_tile <= num_cus + num_cus / 8)
+            return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
         return launch_cfg<256, 128, 4, 2, 64, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
     }
     // 129..256 tokens and about as many 128-row tiles as workgroups (0.65..1.2 x: the gate/up shapes):
@@ -695,7 +640,7 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     // (7B-shaped gate/up at M = 192: 74.9 -> 67.4 us, 13B 98.9 -> 94.2, 30B 161 -> 152).  With fewer tiles
     // the 128 KiB partial tiles of the workgroups that share one cost more than reading the weights twice
     // (7B-shaped O projection 22.5 -> 31 us), with more the 256-row tile wins: both stay with the rule below.
-    if (direct && a.M <= 256) {
+    if (even_k && a.M <= 256) {
         const int per_tile = is_swiglu(epilogue) ? 64 : 128;
         const long t128 = (a.N + per_tile - 1) / per_tile;
         if (t128 * 20 >= (long)num_cus * 13 && t128 * 5 <= (long)num_cus * 6)
@@ -705,17 +650,15 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     // configuration runs one workgroup per CU, which only pays where the two-per-CU one would not have a
     // second workgroup for most CUs anyway (at most one 128x128 tile per CU).
     const double c_small = config_cost(a, epilogue, 128, 128, g_small, SMALL_TFLOPS, SMALL_FIXED_US);
-    if (direct) {
-        const double c_big = config_cost(a, epilogue, 256, 256, g_big, BIG_TFLOPS, BIG_FIXED_US);
-        const int per_tile = is_swiglu(epilogue) ? 64 : 128;
-        const long t128 = (long)((a.N + per_tile - 1) / per_tile) * ((a.M + 127) / 128);
-        if (t128 <= num_cus) {
-            const double c_deep = config_cost(a, epilogue, 128, 128, num_cus, DEEP_TFLOPS, DEEP_FIXED_US);
-            if (c_deep < c_big && c_deep < c_small)
-                return launch_cfg<128, 128, 2, 4, 64, 4, false>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
-        }
-        if (c_big <= c_small) return launch_cfg<256, 256, 4, 2, 64, 2, false>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
+    const double c_big = config_cost(a, epilogue, 256, 256, g_big, BIG_TFLOPS, BIG_FIXED_US);
+    const int per_tile = is_swiglu(epilogue) ? 64 : 128;
+    const long t128 = (long)((a.N + per_tile - 1) / per_tile) * ((a.M + 127) / 128);
+    if (t128 <= num_cus) {
+        const double c_deep = config_cost(a, epilogue, 128, 128, num_cus, DEEP_TFLOPS, DEEP_FIXED_US);
+        if (c_deep < c_big && c_deep < c_small)
+            return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
     }
+    if (c_big <= c_small) return launch_cfg<256, 256, 4, 2, 64, 2, true>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
     return launch_cfg<128, 128, 2, 4, 64, 2, true>(a, epilogue, g_small, stream, SMALL_TFLOPS, SMALL_FIXED_US);
 }
 

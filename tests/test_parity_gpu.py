@@ -249,6 +249,30 @@ def test_prefill_schedules(thi, oracle_mod, M, N, K, why):
     assert np.isfinite(a1.astype(np.float32)).all() and np.isfinite(b1.astype(np.float32)).all()
 
 
+# A K that is no multiple of the staged k-tile: the last k-tile holds one piece, all but one, or half of its 16-byte
+# pieces, alone in its share or as the last of many, in each configuration that takes it.
+@pytest.mark.parametrize("M,N,K", [(1, 40, 8), (40, 300, 72), (100, 272, 120), (130, 200, 64 * 5 + 8), (300, 640, 64 * 9 + 56),
+                                   (700, 1100, 456), (2048, 2304, 1032), (1500, 4096, 2048 + 24), (333, 5001, 1384)])
+def test_ragged_k_in_the_gemm(thi, oracle_mod, M, N, K):
+    say(f"[case] GEMM, ragged K M={M} N={N} K={K}")
+    x, w, g = synth.random_problem(9700 + M + N + K, M, N, K)
+    rows = synth.sample_rows(4343, M, 16)
+    r = Runner(M, K, K, N)
+    xd, wd = to_dev(x), to_dev(w)
+    I = N // 2 // 8 * 8
+    prev = thi.thi_set_kernel_family(2)
+    try:
+        a = to_host(r.linear(xd, wd))
+        h = to_host(r.swiglu_gate_up(xd, wd[:I], wd[I:2 * I]))
+    finally:
+        thi.thi_set_kernel_family(prev)
+    y, s = oracle_mod.linear(x[rows], w)
+    check(a[rows], y, s, f"linear {M}x{N}x{K}")
+    hh, sh = oracle_mod.swiglu_gate_up(x[rows], np.ascontiguousarray(w[:I]), np.ascontiguousarray(w[I:2 * I]))
+    check(h[rows], hh, sh, "swiglu_gate_up", argmax=False)
+    assert np.isfinite(a.astype(np.float32)).all() and np.isfinite(h.astype(np.float32)).all()
+
+
 @pytest.mark.parametrize("M,H,I", [(512, 1024, 2816), (768, 512, 1376), (2048, 1024, 1536),
                                    (200, 1024, 11008),      # 129..256 tokens, 172 gate/up tiles: the 128 x 256 configuration
                                    (256, 512, 13824 + 8)])

@@ -453,18 +453,20 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
 // workgroups, 81 against 75 us; 13B-shaped, 108 tiles x 2: 106 against 97 us).  The few-token configurations (one token tile of at most 128) are bound
 // by their weight traffic, every weight panel is read exactly once whatever the cut, and equal contiguous
 // shares (parts = 0) keep every workgroup busy.
-// A workgroup's speed by configuration, fitted to measurements of every configuration and cut on the four
-// projections of the 7B..70B shapes at M = 256..2048 (weight copies rotated so that they come from HBM;
-// clocks settled under each shape's load for 40 ms first -- after a lighter kernel the first launches run
-// up to 15 % slower): 256x256 tiles 4.7 TFLOP/s + 6 us per tile, 128x128 tiles two per CU 1.8 TFLOP/s + 6
-// us, 128x128 with four stages one per CU 3.4 TFLOP/s + 4 us; the second pass 5 us + its bytes at ~8
-// TB/s (they are still in the caches).  On those 64 shapes the pick is on average 0.5 % slower than the
-// best of the six (configuration, cut) pairs, 8 % at worst.
+// A workgroup's speed by configuration, fitted to measurements of every configuration and cut on projections of the
+// 7B..70B shapes and some odd ones at M = 200..2048 (weight copies rotated so that they come from HBM): 256x256 tiles
+// 5.4 TFLOP/s + 6 us per tile, 128 rows x 256 tokens 4.6 TFLOP/s + 5 us, 128x128 tiles two per CU 1.95 TFLOP/s + 6 us,
+// 128x128 with four stages one per CU 3.6 TFLOP/s + 4 us; the second pass 8 us (a launch and its latencies: 5 us made
+// 333 x 512 x 1376 cut 12 tiles in 21 ranges, 21.2 us against 16.1 whole) + its bytes at ~8 TB/s (they are still
+// in the caches).  On those 14 shapes the pick is the best of the eight (configuration, cut) pairs or within 2 % of
+// it, but for one within 5 %.
 struct Schedule {
     int sk_tiles;      // tiles cut along K (0: whole tiles only)
     int parts;         // equal k ranges per shared tile; 0 = equal contiguous shares across tile boundaries
     double us;
 };
+
+constexpr double SECOND_PASS_US = 8.0;
 
 Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, double wg_tflops, double tile_fixed_us)
 {
@@ -484,19 +486,20 @@ Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, 
     // One token tile: equal contiguous shares for the few-token configurations, and for a 256-token tile
     // when equal ranges would leave more than a tenth of the workgroups idle.
     if (tiles_m == 1 && (BM <= 128 || (long)rem * parts * 10 < (long)grid * 9)) {
-        const double shared = ((double)full + (double)rem / grid) * tile_us + 5.0 + (double)(grid + rem) * tile_bytes * 2.0 / 4.0e6;
+        const double shared = ((double)full + (double)rem / grid) * tile_us + SECOND_PASS_US + (double)(grid + rem) * tile_bytes * 2.0 / 4.0e6;
         return shared < whole ? Schedule{rem, 0, shared} : Schedule{0, 0, whole};
     }
     if (parts < 2) return Schedule{0, 1, whole};
-    const double shared = (double)full * tile_us + tile_fixed_us + work_us / parts + 5.0 +
+    const double shared = (double)full * tile_us + tile_fixed_us + work_us / parts + SECOND_PASS_US +
                           (double)rem * parts * tile_bytes * 2.0 / 8.0e6;
     return shared < whole ? Schedule{rem, parts, shared} : Schedule{0, 1, whole};
 }
 
-// the three multi-token-tile configurations
-constexpr double BIG_TFLOPS = 4.7, BIG_FIXED_US = 6.0;        // 256x256, one workgroup per CU
-constexpr double SMALL_TFLOPS = 1.8, SMALL_FIXED_US = 6.0;    // 128x128, two per CU
-constexpr double DEEP_TFLOPS = 3.4, DEEP_FIXED_US = 4.0;      // 128x128, four stages, one per CU
+// the multi-token-tile configurations
+constexpr double BIG_TFLOPS = 5.4, BIG_FIXED_US = 6.0;        // 256x256, one workgroup per CU
+constexpr double TALL_TFLOPS = 4.6, TALL_FIXED_US = 5.0;      // 128 rows x 256 tokens, one per CU
+constexpr double SMALL_TFLOPS = 1.95, SMALL_FIXED_US = 6.0;   // 128x128, two per CU
+constexpr double DEEP_TFLOPS = 3.6, DEEP_FIXED_US = 4.0;      // 128x128, four stages, one per CU
 constexpr double FEW_TFLOPS = 900.0 / 256;                    // one token tile: bound by the weight stream anyway
 
 // ALL = also build the variant for a ragged K (KTAIL).
@@ -646,19 +649,20 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
         if (t128 * 20 >= (long)num_cus * 13 && t128 * 5 <= (long)num_cus * 6)
             return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
     }
-    // Several token tiles: the configuration with the smallest modelled time.  The four-stage 128x128
-    // configuration runs one workgroup per CU, which only pays where the two-per-CU one would not have a
-    // second workgroup for most CUs anyway (at most one 128x128 tile per CU).
-    const double c_small = config_cost(a, epilogue, 128, 128, g_small, SMALL_TFLOPS, SMALL_FIXED_US);
+    // Several token tiles: the configuration with the smallest modelled time.  128 rows x 256 tokens halves the granularity
+    // of the 256x256 tile where that leaves CUs idle (512 x 15360 x 5120: 120 tiles cut in two and a second pass 92.4
+    // us, 240 whole tiles 87.8; 1500 x 4096 x 4096 68 -> 63), the four-stage 128x128 one where that still does
+    // (300 x 12288 x 4096: a round and 32 tiles in 8 ranges 58 us, two per CU 70).
     const double c_big = config_cost(a, epilogue, 256, 256, g_big, BIG_TFLOPS, BIG_FIXED_US);
-    const int per_tile = is_swiglu(epilogue) ? 64 : 128;
-    const long t128 = (long)((a.N + per_tile - 1) / per_tile) * ((a.M + 127) / 128);
-    if (t128 <= num_cus) {
-        const double c_deep = config_cost(a, epilogue, 128, 128, num_cus, DEEP_TFLOPS, DEEP_FIXED_US);
-        if (c_deep < c_big && c_deep < c_small)
-            return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
-    }
-    if (c_big <= c_small) return launch_cfg<256, 256, 4, 2, 64, 2, true>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
+    const double c_tall = even_k ? config_cost(a, epilogue, 128, 256, g_big, TALL_TFLOPS, TALL_FIXED_US) : c_big + 1.0;
+    const double c_deep = config_cost(a, epilogue, 128, 128, num_cus, DEEP_TFLOPS, DEEP_FIXED_US);
+    const double c_small = config_cost(a, epilogue, 128, 128, g_small, SMALL_TFLOPS, SMALL_FIXED_US);
+    if (c_big <= c_tall && c_big <= c_deep && c_big <= c_small)
+        return launch_cfg<256, 256, 4, 2, 64, 2, true>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
+    if (even_k && c_tall <= c_deep && c_tall <= c_small)
+        return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, g_big, stream, TALL_TFLOPS, TALL_FIXED_US);
+    if (c_deep <= c_small)
+        return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
     return launch_cfg<128, 128, 2, 4, 64, 2, true>(a, epilogue, g_small, stream, SMALL_TFLOPS, SMALL_FIXED_US);
 }
 

@@ -257,7 +257,7 @@ def test_ragged_k_in_the_gemm(thi, oracle_mod, M, N, K):
     say(f"[case] GEMM, ragged K M={M} N={N} K={K}")
     x, w, g = synth.random_problem(9700 + M + N + K, M, N, K)
     rows = synth.sample_rows(4343, M, 16)
-    r = Runner(M, K, K, N)
+    r = Runner(M, K, max(K, N // 2), N)      # (the workspace holds h for N // 2 gate/up pairs)
     xd, wd = to_dev(x), to_dev(w)
     I = N // 2 // 8 * 8
     prev = thi.thi_set_kernel_family(2)

@@ -126,8 +126,8 @@ __device__ __forceinline__ void store_pair(const GemmArgs& a, int tile_n, int ti
         half4 hv;
 #pragma unroll
         for (int c = 0; c < 4; ++c) hv[c] = (_Float16)(f0[c] / (1.0f + __expf(-f0[c])) * f1[c]);
-        if (j + 3 < a.N && (a.ldo & 3) == 0) {
-            *reinterpret_cast<half4*>(a.out + (size_t)m * a.ldo + j) = hv;
+        if (j + 3 < a.N) {
+            *reinterpret_cast<half4_any*>(a.out + (size_t)m * a.ldo + j) = hv;
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
@@ -145,16 +145,16 @@ __device__ __forceinline__ void store_pair(const GemmArgs& a, int tile_n, int ti
             rope_pair_table(a.rope, m, n, v[0], v[1]);
             rope_pair_table(a.rope, m, n + 2, v[2], v[3]);
         }
-        if (n + 3 < a.N && (a.ldo & 3) == 0) {
+        if (n + 3 < a.N) {
             half4 hv;
             if (a.residual) {
-                const half4 rv = *reinterpret_cast<const half4*>(a.residual + (size_t)m * a.ldo + n);
+                const half4 rv = *reinterpret_cast<const half4_any*>(a.residual + (size_t)m * a.ldo + n);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) v[c] += (float)rv[c];
             }
 #pragma unroll
             for (int c = 0; c < 4; ++c) hv[c] = (_Float16)v[c];
-            *reinterpret_cast<half4*>(a.out + (size_t)m * a.ldo + n) = hv;
+            *reinterpret_cast<half4_any*>(a.out + (size_t)m * a.ldo + n) = hv;
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c)

@@ -31,7 +31,12 @@ typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 // cheaper way: loaded in operand layout, every lane asks for its own 16 bytes of a different row, which
 // costs the vector cache several times the cycles per byte.  With very few tokens most lanes of an
 // operand-layout load share an address and the direct load wins.
-template <int MT, int EPI, bool XT>
+//
+// SMALLK (K < 1024, fewer than eight groups of 128 k): one group per wave, as many waves as there are groups.  Without it
+// such a K ran on the stream-K kernel, whose tiles of 128 rows leave most CUs idle on the small matrices that go
+// with it and whose k chunks of a tile meet through memory (32 tokens, back-to-back calls: 12288 x 1016 13.6 -> 9.8 us,
+// 4096 x 776 9.9 -> 7.3, which is what the calls cost the host).
+template <int MT, int EPI, bool XT, bool SMALLK = false>
 __global__ __launch_bounds__(SK_THREADS) void skinny_rowslab(const uint16_t* x_, const uint16_t* w0_, const uint16_t* w1_,
                                                              const uint16_t* gamma_, int M_, int N_, int K_, int tiles_,
                                                              SkinnyArgs a)
@@ -54,10 +59,13 @@ __global__ __launch_bounds__(SK_THREADS) void skinny_rowslab(const uint16_t* x_,
     // this wave's k range: whole groups of 128 k, so that every range starts on a 256-byte boundary of
     // its rows (K >= 1024: every wave has at least one group)
     const int S4 = (K + 127) >> 7;
-    const int k_begin = ((wv * S4) >> 3) * 128;
-    const int k_stop = (((wv + 1) * S4) >> 3) * 128;
+    // (SMALLK: a wave beyond the groups, launched for the epilogue's sake, has the empty range [0, 0))
+    constexpr int PH = SMALLK ? 1 : 2;                               // phases of 128 k per unit
+    const int waves = SMALLK ? S4 : SK_WAVES;                        // waves with a k range
+    const int k_begin = SMALLK ? (wv < S4 ? wv : 0) * 128 : ((wv * S4) >> 3) * 128;
+    const int k_stop = SMALLK ? (wv < S4 ? wv + 1 : 0) * 128 : (((wv + 1) * S4) >> 3) * 128;
     const int k_end = k_stop < K ? k_stop : K;
-    const int nU = (k_end - k_begin + SK_KC - 1) / SK_KC;            // units of 256 k per slab
+    const int nU = SMALLK ? 1 : (k_end - k_begin + SK_KC - 1) / SK_KC;            // units per slab
     const int n_slabs = (a.tiles - (int)blockIdx.x + G - 1) / G;     // slabs of this workgroup
     const int total = n_slabs * nU;
 
@@ -93,7 +101,7 @@ __global__ __launch_bounds__(SK_THREADS) void skinny_rowslab(const uint16_t* x_,
         for (int jj = 0; jj < 4; ++jj) {
             const uint16_t* base = row_base(slab, jj);
 #pragma unroll
-            for (int ph = 0; ph < 2; ++ph) {
+            for (int ph = 0; ph < PH; ++ph) {
                 const int k = k0 + ph * 128 + ld_p * 8;
                 w[ph * 4 + jj] = ld_stream(valid ? base + (k < k_lim ? k : k0) : a.x);
             }
@@ -140,14 +148,14 @@ __global__ __launch_bounds__(SK_THREADS) void skinny_rowslab(const uint16_t* x_,
                     const int m = mt * 16 + 4 * jj + ld_i;
                     const uint16_t* row = a.x + (size_t)(m < a.M ? m : a.M - 1) * K;
 #pragma unroll
-                    for (int ph = 0; ph < 2; ++ph) {
+                    for (int ph = 0; ph < PH; ++ph) {
                         const int k = k0 + ph * 128 + ld_p * 8;
                         xl[mt][ph * 4 + jj] = ld_cached(row + (k < k_end ? k : k0));
                     }
                 }
         } else {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
+            for (int s = 0; s < 4 * PH; ++s) {
                 const int kx = k0 + s * 32 + kg * 8;
                 const int kxc = kx < k_end ? kx : k0;
 #pragma unroll
@@ -164,7 +172,7 @@ __global__ __launch_bounds__(SK_THREADS) void skinny_rowslab(const uint16_t* x_,
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int ph = 0; ph < 2; ++ph) {
+                for (int ph = 0; ph < PH; ++ph) {
                     __builtin_amdgcn_wave_barrier();
 #pragma unroll
                     for (int jj = 0; jj < 4; ++jj) wt[wv][(4 * jj + ld_i) * WT_STRIDE + ld_p] = xl[mt][ph * 4 + jj];
@@ -177,14 +185,14 @@ __global__ __launch_bounds__(SK_THREADS) void skinny_rowslab(const uint16_t* x_,
         // zero what came from a redirected address
         if (k0 + SK_KC > k_end) {
 #pragma unroll
-            for (int ph = 0; ph < 2; ++ph)
+            for (int ph = 0; ph < PH; ++ph)
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj)
                     if (k0 + ph * 128 + ld_p * 8 >= k_end) cur[ph * 4 + jj] = zero4;
         }
 
 #pragma unroll
-        for (int ph = 0; ph < 2; ++ph) {
+        for (int ph = 0; ph < PH; ++ph) {
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) wt[wv][(4 * jj + ld_i) * WT_STRIDE + ld_p] = cur[ph * 4 + jj];
@@ -240,14 +248,16 @@ __global__ __launch_bounds__(SK_THREADS) void skinny_rowslab(const uint16_t* x_,
         if (tid < MT * 64) {
             floatx4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int w = 0; w < SK_WAVES; ++w) v += s_part[w][tid];
+            for (int w = 0; w < SK_WAVES; ++w)
+                if (!SMALLK || w < waves) v += s_part[w][tid];
             const int l = tid & 63, quad = l >> 4, m = (tid >> 6) * 16 + (l & 15);
             float scale = 1.0f;
             if (is_rms(EPI)) {
                 float q = 0.f;
                 if (first_slab) {         // kept in s_ssq for the later slabs
 #pragma unroll
-                    for (int w = 0; w < SK_WAVES; ++w) q += s_red[w][m];
+                    for (int w = 0; w < SK_WAVES; ++w)
+                        if (!SMALLK || w < waves) q += s_red[w][m];
                     if (quad == 0) s_ssq[m] = q;
                 } else {
                     q = s_ssq[m];
@@ -340,7 +350,34 @@ hipError_t launch_mt(const SkinnyArgs& a, int epilogue, int grid, hipStream_t st
     return hipGetLastError();
 }
 
+template <int MT, bool XT>
+hipError_t launch_small(const SkinnyArgs& a, int epilogue, int grid, hipStream_t stream)
+{
+    const int groups = (a.K + 127) >> 7, waves = groups > MT ? groups : MT;      // the epilogue takes MT waves
+    dim3 g(grid), b(64 * waves);
+    const size_t gamma_lds = (size_t)SK_WAVES * rowslab_gamma_pieces(a.K) * sizeof(uintx4);      // 2 KiB
+    switch (epilogue) {
+    case EPI_PLAIN: hipLaunchKernelGGL((skinny_rowslab<MT, EPI_PLAIN, XT, true>), g, b, 0, stream, a.x, a.w0, a.w1, a.gamma, a.M, a.N, a.K, a.tiles, a); break;
+    case EPI_RMSNORM: hipLaunchKernelGGL((skinny_rowslab<MT, EPI_RMSNORM, XT, true>), g, b, gamma_lds, stream, a.x, a.w0, a.w1, a.gamma, a.M, a.N, a.K, a.tiles, a); break;
+    case EPI_RMSNORM_ROPE: hipLaunchKernelGGL((skinny_rowslab<MT, EPI_RMSNORM_ROPE, XT, true>), g, b, gamma_lds, stream, a.x, a.w0, a.w1, a.gamma, a.M, a.N, a.K, a.tiles, a); break;
+    case EPI_RMSNORM_SWIGLU: hipLaunchKernelGGL((skinny_rowslab<MT, EPI_RMSNORM_SWIGLU, XT, true>), g, b, gamma_lds, stream, a.x, a.w0, a.w1, a.gamma, a.M, a.N, a.K, a.tiles, a); break;
+    default: hipLaunchKernelGGL((skinny_rowslab<MT, EPI_SWIGLU, XT, true>), g, b, 0, stream, a.x, a.w0, a.w1, a.gamma, a.M, a.N, a.K, a.tiles, a); break;
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_rowslab_small(const SkinnyArgs& args, int epilogue, int num_cus, hipStream_t stream)
+{
+    SkinnyArgs a = args;
+    if (a.K >= 1024 || a.M > 32) return hipErrorInvalidValue;
+    a.tiles = (a.N + (is_swiglu(epilogue) ? 7 : 15)) / (is_swiglu(epilogue) ? 8 : 16);      // slabs
+    const int grid = num_cus < a.tiles ? num_cus : a.tiles;
+    if (a.M <= 4) return launch_small<1, false>(a, epilogue, grid, stream);
+    if (a.M <= 16) return launch_small<1, true>(a, epilogue, grid, stream);
+    return launch_small<2, true>(a, epilogue, grid, stream);
+}
 
 hipError_t launch_rowslab(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t stream)
 {

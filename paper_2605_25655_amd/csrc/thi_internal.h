@@ -85,6 +85,8 @@ hipError_t launch_skinny(const SkinnyArgs& a, int epilogue, int num_cus, hipStre
 // wave's slice of gamma must fit its share of LDS); uses no workspace.
 constexpr int ROWSLAB_MAX_K = 32768;
 hipError_t launch_rowslab(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t stream);
+// The same kernel for K < 1024, up to 32 tokens (what launch_skinny runs there; sets a.tiles itself).
+hipError_t launch_rowslab_small(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t stream);
 // Row-block decode kernel: the outputs dealt to the workgroups in equal contiguous blocks, T slabs of a
 // block in flight at a time (same limits on K; a.tiles is not used; no workspace unless ksplit > 1).
 struct RowBlockPlan {

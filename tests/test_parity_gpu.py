@@ -390,6 +390,16 @@ def test_rowslab_kernel_all_epilogues(thi, oracle_mod, M, N, K):
     check(h, hh, sh, "swiglu_gate_up", argmax=False)
 
 
+# K < 1024: one group of 128 k per wave and slabs of 16 rows up to five slabs per CU, the stream-K kernel beyond
+SMALL_K = [(1, 16, 8), (1, 1536, 512), (4, 100, 120), (5, 300, 128), (16, 272, 136), (17, 640, 1016), (32, 4099, 896),
+           (32, 24, 8), (20, 20480, 264), (2, 20496, 136)]
+
+
+@pytest.mark.parametrize("M,N,K", SMALL_K)
+def test_small_k_all_epilogues(thi, oracle_mod, M, N, K):
+    test_rowslab_kernel_all_epilogues(thi, oracle_mod, M, N, K)
+
+
 # the row-block decode kernel: each workgroup owns N / #CUs outputs = several 16-row tiles (the last one
 # partly masked), 2, 4 or 6 of them in flight; more than six take several passes over K
 ROWBLOCK = [

@@ -15,7 +15,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libthi.so")
 PROBE_LIB = os.path.join(PKG, "libthi_probe.so")      # measurement probes: not part of the product library
-SOURCES = ["api.hip", "plan.hip", "skinny.hip", "rowslab.hip", "rowblock.hip", "attention.hip", "gemm.hip"]
+SOURCES = ["api.hip", "plan.hip", "skinny.hip", "rowslab.hip", "rowblock.hip", "attention.hip", "gemm.hip", "midgemm.hip"]
 PROBE_SOURCES = ["probes.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -216,7 +216,11 @@ DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus)
     if (M > 16 * SK_MAX_MT) return DecodePlan{0, 0};
     const double t_w = (is_swiglu(epilogue) ? 2.0 : 1.0) * (double)N * (double)K * 2.0 / 7.0e6;
     const double t_sk = 5.5 + 1.06 * t_w + (M <= 48 ? 8.0 : 13.0);
-    const double t_gemm = (is_rms(epilogue) ? 13.0 : 8.0) + 1.5 * (t_w < 30.0 ? t_w : 30.0) + 1.25 * (t_w > 30.0 ? t_w - 30.0 : 0.0);
+    double t_gemm = (is_rms(epilogue) ? 13.0 : 8.0) + 1.5 * (t_w < 30.0 ? t_w : 30.0) + 1.25 * (t_w > 30.0 ? t_w - 30.0 : 0.0);
+    if (!is_rms(epilogue)) {      // no pass in front: the few-token GEMM kernel, where it serves the shape, is priced by itself
+        const MidPlan mp = plan_mid(M, N, K, epilogue, cus);
+        if (mp.BN) t_gemm = mp.us;
+    }
     if (t_sk < t_gemm) return DecodePlan{DK_STREAMK, 16 * SK_MAX_MT};
     return DecodePlan{0, 0};
 }
@@ -291,6 +295,7 @@ int run_projection(const uint16_t* x, const uint16_t* gamma, float eps, const ui
     g.out = out;
     g.residual = residual;
     g.partials = ws.partials;
+    g.counters = ws.counters;
     g.tiles = 0;
     g.M = M;
     g.N = N;

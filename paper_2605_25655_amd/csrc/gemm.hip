@@ -661,6 +661,13 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     if (g_small > GEMM_MAX_GRID) g_small = GEMM_MAX_GRID;
     if (is_rms(epilogue)) return hipErrorInvalidValue;
     const bool even_k = a.K % 64 == 0;                 // else: the configurations that are built with KTAIL
+    if (a.M <= 128 && a.counters) {
+        // The few-token kernel where its modelled time is the smaller one (the other model is about a tenth low there:
+        // 10240 x 8192 at 128 tokens 55.8 us against 50.3 here, 12288 x 4096 31.8 against 35.6)
+        const MidPlan mp = plan_mid(a.M, a.N, a.K, epilogue, num_cus);
+        const double few = config_cost(a, epilogue, 128, a.M <= 64 && a.K % 128 == 0 ? 64 : 128, g_big, FEW_TFLOPS, 0.0);
+        if (mp.BN && mp.us < 1.1 * few) return launch_mid(a, epilogue, mp, stream);
+    }
     if (a.M <= 128) {
         // Few tokens: one token tile, the weights are read once and the kernel is bound by how many
         // bytes a CU keeps in flight: three stages of 128 rows x 128 k against 64 tokens (K a multiple of

@@ -56,6 +56,33 @@ bool mlp_fused_ok(int M, int H, int I, int epilogue_up, int num_cus, int ksplit_
 // ---- prefill GEMM ----------------------------------------------------------------------------------
 size_t gemm_partial_bytes() { return (size_t)GEMM_MAX_GRID * 2 * 128 * 128 * sizeof(float); }
 
+// The few-token kernel: BN rows per tile and S k ranges per tile with the smallest modelled time, at most one workgroup per
+// compute unit (a second round starts with an empty pipeline: 13B gate/up at 72 tokens as 432 tiles 68.8 us, the GEMM
+// 63.8), not above K = 24576 (the 70B down projection measured 2-4 % behind the kernels it would replace).  The
+// constants, in microseconds and KB per workgroup, are fitted to ~400 measured (shape, M, BN, S) points, 17 shapes x
+// M = 40..128: 4.2 us fixed, 24 ns a KB of weights, 13 ns a KB of activations, 93 ns a stage; sharing a tile 1 us, 32 ns a
+// KB of its partial tiles and 3 us more with 96 rows.  The pick is 1 % slower than the best measured one on average, 16 %
+// at worst (on problems of 5 us).
+MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
+{
+    MidPlan best{0, 0, 0, 0.0};
+    if (M > 128 || K > 24576) return best;
+    const int V = is_swiglu(epilogue) ? 2 * N : N;
+    const int ktiles = (K + 127) / 128;
+    for (int BN : {32, 48, 64, 96}) {
+        if (M > 96 && BN == 96) continue;                       // (registers)
+        const int tiles = (V + BN - 1) / BN;
+        for (int S = 1; S <= 16 && tiles * S <= num_cus && (S == 1 || S * 4 <= ktiles); ++S) {
+            const int per = (ktiles + S - 1) / S;
+            const double w = BN * per * 0.256, x = M * per * 0.256;
+            const double us = 4.2 + 0.024 * w + 0.013 * x + 0.093 * per +
+                              (S > 1 ? 1.0 + 0.032 * S * BN * M * 0.004 + (BN == 96 ? 3.0 : 0.0) : 0.0);
+            if (best.BN == 0 || us < best.us) best = MidPlan{BN, tiles, S, us};
+        }
+    }
+    return best;
+}
+
 // ---- decode attention ------------------------------------------------------------------------------
 // query heads that share a pass over their cache head: 16 on the matrix cores (D = 128, groups of four and more)
 int attention_heads_per_workgroup(int D, int group)

@@ -39,8 +39,8 @@ constexpr int ROPE_TABLE_MAX_HEAD_DIM = 256;     // what the workspace reserves 
 
 // ---- workspace layout (bytes from the workspace base) ----------------------
 // [0, 64 KiB)             : status words (uint32), zero between calls: the stream-K decode kernel's
-//                           hand-over flags (one per workgroup), the shared row blocks' arrival counters
-//                           (one per block); last word: time-out marker
+//                           hand-over flags (one per workgroup), the arrival counters of shared row blocks
+//                           and of the few-token GEMM's shared tiles (one each); last word: time-out marker
 // [.., + hand-over bytes) : decode kernels: one hand-over slot per workgroup
 // [.., + partial bytes)   : prefill GEMM: per-workgroup partial accumulator tiles (fp32)
 // [.., + M*I*2)           : h = silu(gate)*up of the MLP (fp16)
@@ -124,10 +124,21 @@ struct GemmArgs {
     int M, N, K, ldo;        // N = physical rows of w0
     int tiles;               // filled in by the launcher
     RopeArgs rope;
+    unsigned* counters;      // status words, zero between calls: arrival counters of the few-token kernel's shared tiles
 };
 constexpr int GEMM_MAX_GRID = 2048;   // in units of 128x128 partial tiles (a 256x256 tile takes four)
 size_t gemm_partial_bytes();
 hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t stream);
+// The few-token kernel (33..128 tokens; launch_gemm takes it where it is the faster one): how the tile rows and K are
+// dealt to the compute units.
+struct MidPlan {
+    int BN;          // virtual weight rows per tile (0: the kernel does not serve the shape)
+    int tiles;
+    int S;           // workgroups per tile, each with 1/S of K
+    double us;       // modelled time
+};
+MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
+hipError_t launch_mid(const GemmArgs& a, int epilogue, const MidPlan& p, hipStream_t stream);
 // xn[m,k] = fp16(x[m,k] * gamma[k] / sqrt(mean_k x[m,:]^2 + eps)): the prefill path's RMSNorm pass
 // With rope.cs set it also fills that table: cs[m][i] = (cos, sin)(pos[m] * theta[i]), fp32, full-range.
 hipError_t launch_rmsnorm_rows(const uint16_t* x, const uint16_t* gamma, float eps, uint16_t* xn, int M, int K,

@@ -249,6 +249,48 @@ def test_prefill_schedules(thi, oracle_mod, M, N, K, why):
     assert np.isfinite(a1.astype(np.float32)).all() and np.isfinite(b1.astype(np.float32)).all()
 
 
+# The few-token kernel (33..128 tokens): each token tile (64, 96, 128) at its edges, tiles of 32..96 rows whose last one is
+# partly empty, a K below, at and past whole stages of 128, one and several workgroups per tile.
+FEW_KERNEL = [(33, 24, 8), (64, 272, 136), (65, 1000, 1096), (96, 4096, 2112), (97, 5001, 1384), (128, 640, 11008),
+              (72, 12288, 1024), (40, 2000, 4096), (128, 8200, 1024), (1, 300, 2048), (66, 7000, 6656)]
+
+
+@pytest.mark.parametrize("M,N,K", FEW_KERNEL)
+def test_few_token_kernel_all_epilogues(thi, oracle_mod, M, N, K):
+    say(f"[case] few-token kernel M={M} N={N} K={K}")
+    x, w, g = synth.random_problem(9800 + M + N + K, M, N, K)
+    rng = np.random.Generator(np.random.Philox(key=9801 + M + N + K))
+    res = f16(rng.standard_normal((M, N)))
+    rows = synth.sample_rows(4444, M, 12)
+    hd = 8
+    n_rot = N // 2 // hd * hd
+    pos = rng.integers(0, 4096, size=M).astype(np.int32)
+    th = _theta(hd)
+    I = N // 2 // 8 * 8
+    r = Runner(M, K, max(K, I), N)
+    xd, wd, gd = to_dev(x), to_dev(w), to_dev(g)
+    prev = thi.thi_set_kernel_family(2)
+    try:
+        a = [to_host(r.linear(xd, wd)) for _ in range(3)]
+        ar = to_host(r.linear_residual(xd, wd, to_dev(res)))
+        c = to_host(r.rmsnorm_qkv_rope(xd, gd, 1e-6, wd, _dev_i32(pos), _dev_f32(th), n_rot, hd))
+        h = to_host(r.swiglu_gate_up(xd, wd[:I], wd[I:2 * I]))
+    finally:
+        thi.thi_set_kernel_family(prev)
+    assert all(np.array_equal(v.view(np.uint16), a[0].view(np.uint16)) for v in a), "not reproducible"
+    assert not _status_words(r.ws).any()
+    y, s = oracle_mod.linear(x[rows], w)
+    check(a[0][rows], y, s, "linear")
+    y, s = oracle_mod.linear_residual(x[rows], w, res[rows])
+    check(ar[rows], y, s, "linear_residual", argmax=False)
+    y, s = oracle_mod.rmsnorm_qkv_rope(x[rows], g, 1e-6, w, pos[rows], th, n_rot, hd)
+    check(c[rows], y, s, "rmsnorm_qkv_rope", argmax=False)
+    hh, sh = oracle_mod.swiglu_gate_up(x[rows], np.ascontiguousarray(w[:I]), np.ascontiguousarray(w[I:2 * I]))
+    check(h[rows], hh, sh, "swiglu_gate_up", argmax=False)
+    for v in (a[0], ar, c, h):
+        assert np.isfinite(v.astype(np.float32)).all()
+
+
 # A K that is no multiple of the staged k-tile: the last k-tile holds one piece, all but one, or half of its 16-byte
 # pieces, alone in its share or as the last of many, in each configuration that takes it.
 @pytest.mark.parametrize("M,N,K", [(1, 40, 8), (40, 300, 72), (100, 272, 120), (130, 200, 64 * 5 + 8), (300, 640, 64 * 9 + 56),

@@ -6,7 +6,7 @@
 // in flight, the loads return in order, so the activations wait behind the weights' HBM latency).  So
 //   - every CU takes part, and a weight row is read by one workgroup only (the token tile holds all tokens);
 //   - a workgroup reads BN * K / S weights and M * K / S activations: BN rows per tile, S k ranges per tile, tiles * S
-//     just below the number of CUs; tokens past M are not loaded;
+//     just below the number of CUs (tiles of 32..144 rows, so that most shapes come close); tokens past M are not loaded;
 //   - the token tile is no larger than it must be (64, 96 or 128): what it does not take deepens the pipeline
 //     (72 x 12288 x 4096: 29.1 us with a tile of 128 and three stages, 25.3 with 96 and four);
 //   - a stage is 128 k (256 bytes of a row, half the barriers of 64 k), the eight waves are two token groups x the four
@@ -22,7 +22,8 @@
 // Against the GEMM's few-token configurations and their second pass, or the stream-K decode kernel where that ran (same
 // box, rotated weights), N x K: 40 tokens 4096 x 4096 16.3 -> 12.6 us, 4096 x 11008 26.6 -> 21.8, 15360 x 5120 38 -> 31;
 // 72 tokens 4096 x 4096 18.3 -> 15.6, 4096 x 11008 32.2 -> 25.2, 12288 x 4096 33.6 -> 25.6, 19968 x 6656 71 -> 54,
-// gate/up 2 x 11008 x 4096 49.5 -> 40; 128 tokens 4096 x 11008 35.6 -> 30.8, 12288 x 4096 35.6 -> 32.
+// gate/up 2 x 11008 x 4096 49.5 -> 40, 2 x 13824 x 5120 62.7 -> 55; 128 tokens 6656 x 17920 70.7 -> 59, 4096 x 11008
+// 35.6 -> 30.8, 12288 x 4096 35.6 -> 32.
 #include "thi_internal.h"
 
 #include <mutex>
@@ -74,12 +75,20 @@ constexpr int mid_stages()
     return n > 5 ? 5 : n;
 }
 
+// the k groups' partial fragments meet in LDS: all at once where they fit, else in two rounds of a multiple of four
+template <int BN, int BM>
+constexpr int mid_round()
+{
+    constexpr int F = (BN / 16) * (BM / (16 * MID_TG));
+    return MID_WAVES * F * 1024 <= MID_LDS ? F : (F / 2 + 3) / 4 * 4;
+}
+
 template <int BN, int BM>
 constexpr int mid_lds()
 {
-    constexpr int F = (BN / 16) * (BM / (16 * MID_TG));
-    constexpr int stages = mid_stages<BN, BM>() * (BN + BM) * MID_GK * 2, parts = MID_WAVES * F * 1024;
-    static_assert(parts <= MID_LDS, "the k groups' partial fragments");
+    constexpr int F = (BN / 16) * (BM / (16 * MID_TG)), R = mid_round<BN, BM>();
+    constexpr int stages = mid_stages<BN, BM>() * (BN + BM) * MID_GK * 2, parts = MID_WAVES * R * 1024;
+    static_assert(parts <= MID_LDS && F <= 2 * R, "the k groups' partial fragments");
     return stages > parts ? stages : parts;
 }
 
@@ -226,24 +235,28 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
     else last(std::integral_constant<int, 1>{});
 
     // ---- the four k groups meet in LDS: group g finishes the fragments f % 4 == g of its token group ----------------
-    floatx4* const part = reinterpret_cast<floatx4*>(smem);      // [token group][source k group][fragment][lane]
-    __syncthreads();
-#pragma unroll
-    for (int f = 0; f < F; ++f)
-        if (f % MID_KG != kg) part[((tg * MID_KG + kg) * F + f) * 64 + lane] = acc[f / TM][f % TM];
-    __syncthreads();
+    constexpr int R = mid_round<BN, BM>();                       // fragments per round
+    floatx4* const part = reinterpret_cast<floatx4*>(smem);      // [token group][source k group][fragment of the round][lane]
     floatx4 mine[OWN];
 #pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-        mine[o] = floatx4{0.f, 0.f, 0.f, 0.f};
-        if (MID_KG * o + kg >= F) continue;
-        floatx4 own = acc[(4 * o) / TM][(4 * o) % TM];
+    for (int f0 = 0; f0 < F; f0 += R) {
+        __syncthreads();
 #pragma unroll
-        for (int g = 1; g < MID_KG; ++g)
-            if (4 * o + g < F && kg == g) own = acc[(4 * o + g < F ? 4 * o + g : 0) / TM][(4 * o + g < F ? 4 * o + g : 0) % TM];
+        for (int f = f0; f < F && f < f0 + R; ++f)
+            if (f % MID_KG != kg) part[((tg * MID_KG + kg) * R + f - f0) * 64 + lane] = acc[f / TM][f % TM];
+        __syncthreads();
 #pragma unroll
-        for (int g = 0; g < MID_KG; ++g)                     // in k order
-            mine[o] += g == kg ? own : part[((tg * MID_KG + g) * F + 4 * o + kg) * 64 + lane];
+        for (int o = f0 / MID_KG; o < OWN && MID_KG * o < f0 + R; ++o) {
+            mine[o] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (MID_KG * o + kg >= F) continue;
+            floatx4 own = acc[(4 * o) / TM][(4 * o) % TM];
+#pragma unroll
+            for (int g = 1; g < MID_KG; ++g)
+                if (4 * o + g < F && kg == g) own = acc[(4 * o + g < F ? 4 * o + g : 0) / TM][(4 * o + g < F ? 4 * o + g : 0) % TM];
+#pragma unroll
+            for (int g = 0; g < MID_KG; ++g)                     // in k order
+                mine[o] += g == kg ? own : part[((tg * MID_KG + g) * R + 4 * o + kg - f0) * 64 + lane];
+        }
     }
 
     const int m_wave = tg * (BM / MID_TG);
@@ -381,9 +394,13 @@ hipError_t launch_mid_bm(const GemmArgs& a, int epilogue, const MidPlan& p, hipS
     case 32: return launch_mid_cfg<32, BM>(a, epilogue, p, stream);
     case 48: return launch_mid_cfg<48, BM>(a, epilogue, p, stream);
     case 64: return launch_mid_cfg<64, BM>(a, epilogue, p, stream);
-    case 96: if constexpr (BM <= 96) return launch_mid_cfg<96, BM>(a, epilogue, p, stream); else return hipErrorInvalidValue;
-    default: return hipErrorInvalidValue;
+    case 80: return launch_mid_cfg<80, BM>(a, epilogue, p, stream);
+    case 96: if constexpr (BM <= 96) return launch_mid_cfg<96, BM>(a, epilogue, p, stream); else break;
+    case 112: if constexpr (BM <= 96) return launch_mid_cfg<112, BM>(a, epilogue, p, stream); else break;
+    case 144: if constexpr (BM <= 64) return launch_mid_cfg<144, BM>(a, epilogue, p, stream); else break;
+    default: break;
     }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -61,22 +61,27 @@ size_t gemm_partial_bytes() { return (size_t)GEMM_MAX_GRID * 2 * 128 * 128 * siz
 // 63.8), not above K = 24576 (the 70B down projection measured 2-4 % behind the kernels it would replace).  The
 // constants, in microseconds and KB per workgroup, are fitted to ~400 measured (shape, M, BN, S) points, 17 shapes x
 // M = 40..128: 4.2 us fixed, 24 ns a KB of weights, 13 ns a KB of activations, 93 ns a stage; sharing a tile 1 us, 32 ns a
-// KB of its partial tiles and 3 us more with 96 rows.  The pick is 1 % slower than the best measured one on average, 16 %
-// at worst (on problems of 5 us).
+// KB of its partial tiles and 2 / 3 us more with 80 / 96 rows.  The pick is 1 % slower than the best measured one on
+// average, 16 % at worst (on problems of 5 us); on 20 further points with the wide tiles it was the best one each time.
+// Tiles of 80..144 rows are for shapes that smaller ones cut into more tiles than there are compute units, or into few
+// enough that one more share would not fit (against the kernels that served them): 19968 x 6656 at 128 tokens 75.3 -> 62
+// us (80 rows), 6656 x 17920 at 128 70.7 -> 59 (80, S = 3), gate/up 2 x 13824 x 5120 at 72 62.7 -> 55 (112), gate/up
+// 2 x 17920 x 6656 at 64 107.7 -> 79 (144).  With more rows shared tiles only lose (15360 x 5120 at 72 tokens: 52 us with
+// two shares of 144 rows, 35.5 with 64).
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
 {
     MidPlan best{0, 0, 0, 0.0};
     if (M > 128 || K > 24576) return best;
     const int V = is_swiglu(epilogue) ? 2 * N : N;
     const int ktiles = (K + 127) / 128;
-    for (int BN : {32, 48, 64, 96}) {
-        if (M > 96 && BN == 96) continue;                       // (registers)
+    for (int BN : {32, 48, 64, 80, 96, 112, 144}) {
+        if (BN > (M > 96 ? 80 : M > 64 ? 112 : 144)) continue;  // (more spill registers)
         const int tiles = (V + BN - 1) / BN;
-        for (int S = 1; S <= 16 && tiles * S <= num_cus && (S == 1 || S * 4 <= ktiles); ++S) {
+        for (int S = 1; S <= (BN > 96 ? 1 : 16) && tiles * S <= num_cus && (S == 1 || S * 4 <= ktiles); ++S) {
             const int per = (ktiles + S - 1) / S;
             const double w = BN * per * 0.256, x = M * per * 0.256;
             const double us = 4.2 + 0.024 * w + 0.013 * x + 0.093 * per +
-                              (S > 1 ? 1.0 + 0.032 * S * BN * M * 0.004 + (BN == 96 ? 3.0 : 0.0) : 0.0);
+                              (S > 1 ? 1.0 + 0.032 * S * BN * M * 0.004 + (BN == 96 ? 3.0 : BN == 80 ? 2.0 : 0.0) : 0.0);
             if (best.BN == 0 || us < best.us) best = MidPlan{BN, tiles, S, us};
         }
     }

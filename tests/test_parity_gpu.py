@@ -253,6 +253,11 @@ def test_prefill_schedules(thi, oracle_mod, M, N, K, why):
 # partly empty, a K below, at and past whole stages of 128, one and several workgroups per tile.
 FEW_KERNEL = [(33, 24, 8), (64, 272, 136), (65, 1000, 1096), (96, 4096, 2112), (97, 5001, 1384), (128, 640, 11008),
               (72, 12288, 1024), (40, 2000, 4096), (128, 8200, 1024), (1, 300, 2048), (66, 7000, 6656)]
+# ... and tiles of 80, 112 and 144 rows: 80 shared and alone, the last two where smaller tiles do not fit one round (two
+# rounds of partial fragments in LDS with 112 rows x 96 tokens)
+FEW_KERNEL += [(40, 6650, 4104), (96, 19976, 1032), (120, 6650, 5128), (128, 20001, 776), (72, 24601, 4104), (33, 25000, 2056),
+               (96, 28664, 3080), (64, 33100, 1032), (40, 36856, 904),
+               (66, 22001, 2056), (50, 22001, 2056), (128, 16000, 2056), (64, 16000, 2056)]     # 96 and 64 rows alone
 
 
 @pytest.mark.parametrize("M,N,K", FEW_KERNEL)

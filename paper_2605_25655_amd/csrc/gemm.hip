@@ -112,6 +112,52 @@ struct Deal {
     }
 };
 
+// Four consecutive outputs n .. n + 3 of token m (below M): rotation, residual, one rounding, store.
+template <int EPI>
+__device__ __forceinline__ void store_quad(const GemmArgs& a, int m, int n, const floatx4& f)
+{
+    float v[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = f[c];
+    if (has_rope(EPI)) {                         // two complete pairs of one token; cos / sin from the table the RMSNorm pass left
+        rope_pair_table(a.rope, m, n, v[0], v[1]);
+        rope_pair_table(a.rope, m, n + 2, v[2], v[3]);
+    }
+    if (n + 3 < a.N) {
+        half4 hv;
+        if (a.residual) {
+            const half4 rv = *reinterpret_cast<const half4_any*>(a.residual + (size_t)m * a.ldo + n);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] += (float)rv[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) hv[c] = (_Float16)v[c];
+        *reinterpret_cast<half4_any*>(a.out + (size_t)m * a.ldo + n) = hv;
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (n + c < a.N) {
+                if (a.residual) v[c] += half_bits_to_float(a.residual[(size_t)m * a.ldo + n + c]);
+                a.out[(size_t)m * a.ldo + n + c] = to_half_bits(v[c]);
+            }
+    }
+}
+
+// Four consecutive h = silu(g) * u of token m (below M).
+__device__ __forceinline__ void store_quad_swiglu(const GemmArgs& a, int m, int j, const floatx4& g, const floatx4& u)
+{
+    half4 hv;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) hv[c] = (_Float16)(g[c] / (1.0f + __expf(-g[c])) * u[c]);
+    if (j + 3 < a.N) {
+        *reinterpret_cast<half4_any*>(a.out + (size_t)m * a.ldo + j) = hv;
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (j + c < a.N) a.out[(size_t)m * a.ldo + j + c] = __builtin_bit_cast(uint16_t, hv[c]);
+    }
+}
+
 // Epilogue for the two 16x16 accumulator fragments (2 tp, tm) and (2 tp + 1, tm) of a wave: a lane holds four
 // consecutive n of one token of each.  For SwiGLU the first holds gate rows and the second the matching up rows.
 template <int BN, int BM, int WN, int WM, int EPI>
@@ -122,47 +168,28 @@ __device__ __forceinline__ void store_pair(const GemmArgs& a, int tile_n, int ti
     if (m >= a.M) return;
     const int row = wn * (BN / WN) + tp * 32;            // first tile row of the pair
     if (is_swiglu(EPI)) {
-        const int j = tile_n * (BN / 2) + (row >> 1) + 4 * hi;
-        half4 hv;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) hv[c] = (_Float16)(f0[c] / (1.0f + __expf(-f0[c])) * f1[c]);
-        if (j + 3 < a.N) {
-            *reinterpret_cast<half4_any*>(a.out + (size_t)m * a.ldo + j) = hv;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (j + c < a.N) a.out[(size_t)m * a.ldo + j + c] = __builtin_bit_cast(uint16_t, hv[c]);
-        }
+        store_quad_swiglu(a, m, tile_n * (BN / 2) + (row >> 1) + 4 * hi, f0, f1);
         return;
     }
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int n = tile_n * BN + row + 16 * q + 4 * hi;
-        float v[4];
+    for (int q = 0; q < 2; ++q) store_quad<EPI>(a, m, tile_n * BN + row + 16 * q + 4 * hi, q ? f1 : f0);
+}
+
+// The same for one fragment (waves with an odd number of them): for SwiGLU its first eight rows are gate rows and the
+// others the matching up rows, exchanged between the wave's halves.
+template <int BN, int BM, int WN, int WM, int EPI>
+__device__ __forceinline__ void store_one(const GemmArgs& a, int tile_n, int tile_m, int wn, int wm, int tn,
+                                          int tm, int lr, int hi, const floatx4& f)
+{
+    const int m = tile_m * BM + wm * (BM / WM) + tm * 16 + lr;
+    const int row = wn * (BN / WN) + tn * 16;
+    if (is_swiglu(EPI)) {
+        floatx4 u;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = q ? f1[c] : f0[c];
-        if (has_rope(EPI)) {                         // two complete pairs of one token; cos / sin from the table the RMSNorm pass left
-            rope_pair_table(a.rope, m, n, v[0], v[1]);
-            rope_pair_table(a.rope, m, n + 2, v[2], v[3]);
-        }
-        if (n + 3 < a.N) {
-            half4 hv;
-            if (a.residual) {
-                const half4 rv = *reinterpret_cast<const half4_any*>(a.residual + (size_t)m * a.ldo + n);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] += (float)rv[c];
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) hv[c] = (_Float16)v[c];
-            *reinterpret_cast<half4_any*>(a.out + (size_t)m * a.ldo + n) = hv;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (n + c < a.N) {
-                    if (a.residual) v[c] += half_bits_to_float(a.residual[(size_t)m * a.ldo + n + c]);
-                    a.out[(size_t)m * a.ldo + n + c] = to_half_bits(v[c]);
-                }
-        }
+        for (int c = 0; c < 4; ++c) u[c] = __shfl_xor(f[c], 32);
+        if (hi < 2 && m < a.M) store_quad_swiglu(a, m, tile_n * (BN / 2) + (row >> 1) + 4 * hi, f, u);
+    } else if (m < a.M) {
+        store_quad<EPI>(a, m, tile_n * BN + row + 4 * hi, f);
     }
 }
 
@@ -224,14 +251,18 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     constexpr int GPIECES = GK / 8;             // 16-byte pieces per tile row
     constexpr int KSTEPS = GK / 32;             // MFMA k-steps per staged tile (even)
     constexpr int ROWS_PER_DMA = 64 / GPIECES;  // tile rows covered by one wave-wide direct load
-    constexpr int WPASS = BN * GPIECES / THREADS;   // direct loads of the weight tile per k-tile and wave
+    constexpr int WBLKS = BN * GPIECES / 64;        // direct loads of the weight tile per k-tile,
+    constexpr int WPASS = (WBLKS + NWAVES - 1) / NWAVES;    // ... per wave (at most),
+    constexpr bool EVEN = WBLKS % NWAVES == 0;              // ... and whether every wave has as many
     constexpr int XPASS = BM * GPIECES / THREADS;
-    constexpr int TN = BN / WN / 16;            // MFMA tiles per wave along n (even)
+    constexpr int TN = BN / WN / 16;            // MFMA tiles per wave along n
     constexpr int TM = BM / WM / 16;
+    constexpr bool PAIRS = TN % 2 == 0;          // gate and up rows alternate by fragments of 16 rows, else by 8 rows
     constexpr int JPT = is_swiglu(EPI) ? BN / 2 : BN;   // physical weight rows per tile
     constexpr int STAGE = (BN + BM) * GPIECES;   // 16-byte units per stage: weight tile, then activation tile
-    static_assert(NS >= 2 && NS <= 4 && (KSTEPS % 2) == 0 && (TN % 2) == 0, "pipeline shape");
-    static_assert(WPASS >= 1 && XPASS >= 1, "tile too small for the thread count");
+    static_assert(NS >= 2 && NS <= 4 && (KSTEPS % 2) == 0 && (PAIRS || ROWS_PER_DMA <= 8), "pipeline shape");
+    static_assert(WBLKS >= NWAVES && XPASS >= 1 && BM * GPIECES % THREADS == 0, "tile too small for the thread count");
+    static_assert(EVEN || (NS == 2 && !KTAIL), "only a wait for all loads may leave open how many there were");
 
     extern __shared__ uintx4 smem[];
 
@@ -284,14 +315,14 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
         unsigned woff[WPASS], xoff[XPASS];
 #pragma unroll
         for (int i = 0; i < WPASS; ++i) {
-            const int blk = wv * WPASS + i;                          // (uniform) block of ROWS_PER_DMA rows
+            const int blk = EVEN ? wv * WPASS + i : wv + NWAVES * i; // (uniform) block of ROWS_PER_DMA rows
             const int v = blk * ROWS_PER_DMA + lane / GPIECES;
             const int piece = slot ^ swz_f<GPIECES>(v);
             if (is_swiglu(EPI)) {                                    // a wave instruction covers gate rows or up rows only
                 const int j0 = tile_n * JPT;                         // first row of the tile: always valid
-                int j = j0 + (v >> 5) * 16 + (v & 15);
+                int j = j0 + (PAIRS ? (v >> 5) * 16 + (v & 15) : (v >> 4) * 8 + (v & 7));
                 j = j < a.N ? j : a.N - 1;
-                wsrc[i] = (((blk * ROWS_PER_DMA) >> 4) & 1 ? a.w1 : a.w0) + (size_t)j0 * K;
+                wsrc[i] = (((blk * ROWS_PER_DMA) >> (PAIRS ? 4 : 3)) & 1 ? a.w1 : a.w0) + (size_t)j0 * K;
                 woff[i] = (unsigned)((j - j0) * K + piece * 8) * 2u;
             } else {
                 const int n0 = tile_n * BN;
@@ -320,9 +351,11 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
         auto load_tile = [&](int kt, int buf) {
             const bool tail = KTAIL && kt == ktiles - 1;
 #pragma unroll
-            for (int i = 0; i < WPASS; ++i)
-                dma16_sbase(wsrc[i] + kt * GK, tail ? woff[i] - 16u * past_k(wv * WPASS + i, kt) : woff[i],
-                            smem + buf * STAGE + (wv * WPASS + i) * 64);
+            for (int i = 0; i < WPASS; ++i) {
+                const int blk = EVEN ? wv * WPASS + i : wv + NWAVES * i;
+                if (EVEN || blk < WBLKS)
+                    dma16_sbase(wsrc[i] + kt * GK, tail ? woff[i] - 16u * past_k(blk, kt) : woff[i], smem + buf * STAGE + blk * 64);
+            }
 #pragma unroll
             for (int i = 0; i < XPASS; ++i)
                 dma16_sbase(xsrc[i] + kt * GK, tail ? xoff[i] - 16u * past_k(wv * XPASS + i, kt) : xoff[i],
@@ -415,7 +448,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
 
         // ---- whole tile: finished below; shared tile: leave the fp32 partial for the fix-up kernel ---
         const bool whole = (kb == 0 && ke == ktiles);
-        if (!whole) {
+        if (PAIRS && !whole) {                       // (an odd number of fragments: never cut)
             const int pslot = (t == first_tile) ? 0 : 1;
             floatx4* ps = reinterpret_cast<floatx4*>(a.partials + ((size_t)worker * 2 + pslot) * (BN * BM));
 #pragma unroll
@@ -427,10 +460,17 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
         // ---- epilogue ------------------------------------------------------------------------
         if (whole) {
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
+            for (int tm = 0; tm < TM; ++tm) {
+                if constexpr (PAIRS) {
 #pragma unroll
-                for (int tp = 0; tp < TN / 2; ++tp)
-                    store_pair<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tp, tm, lr, hi, acc[2 * tp][tm], acc[2 * tp + 1][tm]);
+                    for (int tp = 0; tp < TN / 2; ++tp)
+                        store_pair<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tp, tm, lr, hi, acc[2 * tp][tm], acc[2 * tp + 1][tm]);
+                } else {
+#pragma unroll
+                    for (int tn = 0; tn < TN; ++tn)
+                        store_one<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tn, tm, lr, hi, acc[tn][tm]);
+                }
+            }
         }
         // the next run rewrites the LDS stages only after this barrier
         __syncthreads();
@@ -455,11 +495,12 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
 // shares (parts = 0) keep every workgroup busy.
 // A workgroup's speed by configuration, fitted to measurements of every configuration and cut on projections of the
 // 7B..70B shapes and some odd ones at M = 200..2048 (weight copies rotated so that they come from HBM): 256x256 tiles
-// 5.4 TFLOP/s + 6 us per tile, 128 rows x 256 tokens 4.6 TFLOP/s + 5 us, 128x128 tiles two per CU 1.95 TFLOP/s + 6 us,
+// 5.4 TFLOP/s + 6 us per tile, 224 / 192 / 160 rows x 256 tokens 4.75 / 4.7 / 4.4 + 6 us, 128 rows x 256 tokens 4.6 TFLOP/s + 5 us, 128x128 tiles two per CU 1.95 TFLOP/s + 6 us,
 // 128x128 with four stages one per CU 3.6 TFLOP/s + 4 us; the second pass 8 us (a launch and its latencies: 5 us made
 // 333 x 512 x 1376 cut 12 tiles in 21 ranges, 21.2 us against 16.1 whole) + its bytes at ~8 TB/s (they are still
-// in the caches).  On those 14 shapes the pick is the best of the eight (configuration, cut) pairs or within 2 % of
-// it, but for one within 5 %.
+// in the caches).  On those 14 shapes the pick was the best of the eight (configuration, cut) pairs or within 2 % of
+// it, but for one within 5 %; with the tiles of 160..224 rows added, on 60 shapes, it was slower than the pick without
+// them nowhere by more than the runs differ.
 struct Schedule {
     int sk_tiles;      // tiles cut along K (0: whole tiles only)
     int parts;         // equal k ranges per shared tile; 0 = equal contiguous shares across tile boundaries
@@ -468,7 +509,7 @@ struct Schedule {
 
 constexpr double SECOND_PASS_US = 8.0;
 
-Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, double wg_tflops, double tile_fixed_us)
+Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, double wg_tflops, double tile_fixed_us, bool cut = true)
 {
     double work_us = 2.0 * BN * BM * (double)K / (wg_tflops * 1e6);
     if (tiles_m == 1) {      // every weight panel is read by one workgroup only: its traffic is a second bound
@@ -479,7 +520,7 @@ Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, 
     const int rem = tiles % grid, full = tiles / grid;
     const double tile_bytes = (double)BN * BM * 4.0;
     const double whole = (double)((tiles + grid - 1) / grid) * tile_us;
-    if (rem == 0) return Schedule{0, tiles_m == 1 ? 0 : 1, whole};
+    if (rem == 0 || !cut) return Schedule{0, tiles_m == 1 ? 0 : 1, whole};
     const int ktiles = (K + 63) / 64;
     int parts = grid / rem;
     if (parts > ktiles) parts = ktiles;
@@ -497,6 +538,9 @@ Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, 
 
 // the multi-token-tile configurations
 constexpr double BIG_TFLOPS = 5.4, BIG_FIXED_US = 6.0;        // 256x256, one workgroup per CU
+constexpr double R224_TFLOPS = 4.75, R224_FIXED_US = 6.0;     // 224, 192 and 160 rows x 256 tokens, one per CU
+constexpr double R192_TFLOPS = 4.7, R192_FIXED_US = 6.0;
+constexpr double R160_TFLOPS = 4.4, R160_FIXED_US = 6.0;
 constexpr double TALL_TFLOPS = 4.6, TALL_FIXED_US = 5.0;      // 128 rows x 256 tokens, one per CU
 constexpr double SMALL_TFLOPS = 1.95, SMALL_FIXED_US = 6.0;   // 128x128, two per CU
 constexpr double DEEP_TFLOPS = 3.6, DEEP_FIXED_US = 4.0;      // 128x128, four stages, one per CU
@@ -514,7 +558,8 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream
     const long U = (long)a.tiles * ktiles;
     long grid = grid_cap;
     if (grid > U) grid = U;
-    const Schedule plan = plan_schedule(a.tiles, tiles_m, (int)grid, BN, BM, a.K, wg_tflops, tile_fixed_us);
+    constexpr bool CUT = BN / WN / 16 % 2 == 0;
+    const Schedule plan = plan_schedule(a.tiles, tiles_m, (int)grid, BN, BM, a.K, wg_tflops, tile_fixed_us, CUT);
     const int sk_tiles = plan.sk_tiles, parts = plan.parts;
     const size_t lds = (size_t)NS * (BN + BM) * (GK / 8) * sizeof(uintx4);
     dim3 g((unsigned)grid), b(64 * WN * WM);
@@ -527,9 +572,11 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                 \
         });                                                                                                  \
         hipLaunchKernelGGL(kern, g, b, lds, stream, a, tiles_m, ktiles, sk_tiles, parts);                    \
-        if (sk_tiles > 0)                                                                                    \
-            hipLaunchKernelGGL((gemm_fixup<BN, BM, WN, WM, E>), dim3(sk_tiles * (BN / WN / 32) * (BM / WM / 16)), \
-                               b, 0, stream, a, tiles_m, ktiles, sk_tiles, (int)grid, parts);                \
+        if constexpr (CUT) {                                                                                 \
+            if (sk_tiles > 0)                                                                                \
+                hipLaunchKernelGGL((gemm_fixup<BN, BM, WN, WM, E>), dim3(sk_tiles * (BN / WN / 32) * (BM / WM / 16)), \
+                                   b, 0, stream, a, tiles_m, ktiles, sk_tiles, (int)grid, parts);            \
+        }                                                                                                    \
     } while (0)
 #define THI_LAUNCH(E)                                                                                        \
     do {                                                                                                     \
@@ -554,14 +601,15 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream
     return hipGetLastError();
 }
 
-double config_cost(const GemmArgs& a, int epilogue, int BN, int BM, int grid, double wg_tflops, double tile_fixed_us)
+double config_cost(const GemmArgs& a, int epilogue, int BN, int BM, int grid, double wg_tflops, double tile_fixed_us,
+                   bool cut = true)
 {
     const int per_tile = is_swiglu(epilogue) ? BN / 2 : BN;
     const int tiles_m = (a.M + BM - 1) / BM;
     const long tiles = (long)((a.N + per_tile - 1) / per_tile) * tiles_m;
     const long units = tiles * ((a.K + 63) / 64);
     const int g = (int)(units < grid ? units : grid);
-    return plan_schedule((int)tiles, tiles_m, g, BN, BM, a.K, wg_tflops, tile_fixed_us).us;
+    return plan_schedule((int)tiles, tiles_m, g, BN, BM, a.K, wg_tflops, tile_fixed_us, cut).us;
 }
 
 }  // namespace
@@ -697,18 +745,36 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     // Several token tiles: the configuration with the smallest modelled time.  128 rows x 256 tokens halves the granularity
     // of the 256x256 tile where that leaves CUs idle (512 x 15360 x 5120: 120 tiles cut in two and a second pass 92.4
     // us, 240 whole tiles 87.8; 1500 x 4096 x 4096 68 -> 63), the four-stage 128x128 one where that still does
-    // (300 x 12288 x 4096: a round and 32 tiles in 8 ranges 58 us, two per CU 70).
-    const double c_big = config_cost(a, epilogue, 256, 256, g_big, BIG_TFLOPS, BIG_FIXED_US);
-    const double c_tall = even_k ? config_cost(a, epilogue, 128, 256, g_big, TALL_TFLOPS, TALL_FIXED_US) : c_big + 1.0;
-    const double c_deep = config_cost(a, epilogue, 128, 128, num_cus, DEEP_TFLOPS, DEEP_FIXED_US);
-    const double c_small = config_cost(a, epilogue, 128, 128, g_small, SMALL_TFLOPS, SMALL_FIXED_US);
-    if (c_big <= c_tall && c_big <= c_deep && c_big <= c_small)
-        return launch_cfg<256, 256, 4, 2, 64, 2, true>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
-    if (even_k && c_tall <= c_deep && c_tall <= c_small)
-        return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, g_big, stream, TALL_TFLOPS, TALL_FIXED_US);
-    if (c_deep <= c_small)
-        return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
-    return launch_cfg<128, 128, 2, 4, 64, 2, true>(a, epilogue, g_small, stream, SMALL_TFLOPS, SMALL_FIXED_US);
+    // (300 x 12288 x 4096: a round and 32 tiles in 8 ranges 58 us, two per CU 70).  224, 192 and 160 rows x 256 tokens are
+    // for the counts in between, where one of them nearly fills whole rounds (against the best of the others): 224 rows
+    // 2048 x 6656 x 17920 437 -> 405 us, 2048 x 6656 x 6656 169 -> 160; 192 rows gate/up 512 x 22016 x 4096 107 -> 95.5,
+    // 300 x 22016 x 4096 100 -> 85, 1024 x 12288 x 4096 110 -> 99; 160 rows 2048 x 5120 x 13824 286 -> 250, 2048 x 5120 x
+    // 5120 118 -> 99, 512 x 19968 x 6656 150 -> 132, 1024 x 10240 x 8192 170 -> 152.  Not where the 256-row tile fills its
+    // rounds as well: per flop they read more operand bytes (gate/up 2048 x 57344 x 8192 with 224 rows 1625 us, 1505).
+    enum { BIG, R224, R192, R160, TALL, DEEP, SMALL, CONFIGS };
+    double cost[CONFIGS];
+    cost[BIG] = config_cost(a, epilogue, 256, 256, g_big, BIG_TFLOPS, BIG_FIXED_US);
+    cost[DEEP] = config_cost(a, epilogue, 128, 128, num_cus, DEEP_TFLOPS, DEEP_FIXED_US);
+    cost[SMALL] = config_cost(a, epilogue, 128, 128, g_small, SMALL_TFLOPS, SMALL_FIXED_US);
+    cost[R224] = cost[R192] = cost[R160] = cost[TALL] = cost[BIG] + 1.0;      // not built for a ragged K
+    if (even_k) {
+        cost[R224] = config_cost(a, epilogue, 224, 256, g_big, R224_TFLOPS, R224_FIXED_US, false);
+        cost[R192] = config_cost(a, epilogue, 192, 256, g_big, R192_TFLOPS, R192_FIXED_US);
+        cost[R160] = config_cost(a, epilogue, 160, 256, g_big, R160_TFLOPS, R160_FIXED_US, false);
+        cost[TALL] = config_cost(a, epilogue, 128, 256, g_big, TALL_TFLOPS, TALL_FIXED_US);
+    }
+    int best = BIG;
+    for (int c = BIG + 1; c < CONFIGS; ++c)
+        if (cost[c] < cost[best]) best = c;
+    switch (best) {
+    case BIG: return launch_cfg<256, 256, 4, 2, 64, 2, true>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
+    case R224: return launch_cfg<224, 256, 2, 4, 64, 2, false>(a, epilogue, g_big, stream, R224_TFLOPS, R224_FIXED_US);
+    case R192: return launch_cfg<192, 256, 2, 4, 64, 2, false>(a, epilogue, g_big, stream, R192_TFLOPS, R192_FIXED_US);
+    case R160: return launch_cfg<160, 256, 2, 4, 64, 2, false>(a, epilogue, g_big, stream, R160_TFLOPS, R160_FIXED_US);
+    case TALL: return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, g_big, stream, TALL_TFLOPS, TALL_FIXED_US);
+    case DEEP: return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
+    default: return launch_cfg<128, 128, 2, 4, 64, 2, true>(a, epilogue, g_small, stream, SMALL_TFLOPS, SMALL_FIXED_US);
+    }
 }
 
 }  // namespace thi

@@ -320,6 +320,36 @@ def test_ragged_k_in_the_gemm(thi, oracle_mod, M, N, K):
     assert np.isfinite(a.astype(np.float32)).all() and np.isfinite(h.astype(np.float32)).all()
 
 
+# Tiles of 224, 192 and 160 rows x 256 tokens (the first and last with an odd number of fragments per wave and fewer loads
+# in some waves than in others): one k-tile, a few and many, last tiles partly empty along both sides.
+@pytest.mark.parametrize("M,N,K", [(1800, 6259, 64), (1955, 6710, 704), (1858, 5397, 64), (1676, 6518, 1920),
+                                   (2045, 4262, 64), (1591, 11032, 1024), (2010, 4402, 128)])
+def test_row_tiles_between_128_and_256(thi, oracle_mod, M, N, K):
+    say(f"[case] 160..224-row tiles M={M} N={N} K={K}")
+    x, w, g = synth.random_problem(9900 + M + N + K, M, N, K)
+    rng = np.random.Generator(np.random.Philox(key=9901 + M + N + K))
+    res = f16(rng.standard_normal((M, N)))
+    rows = synth.sample_rows(4545, M, 16)
+    hd = 8
+    n_rot = N // 2 // hd * hd
+    pos = rng.integers(0, 4096, size=M).astype(np.int32)
+    th = _theta(hd)
+    I = N // 2 // 8 * 8
+    r = Runner(M, K, max(K, I), N)
+    xd, wd, gd = to_dev(x), to_dev(w), to_dev(g)
+    a = to_host(r.linear_residual(xd, wd, to_dev(res)))
+    c = to_host(r.rmsnorm_qkv_rope(xd, gd, 1e-6, wd, _dev_i32(pos), _dev_f32(th), n_rot, hd))
+    h = to_host(r.swiglu_gate_up(xd, wd[:I], wd[I:2 * I]))
+    y, s = oracle_mod.linear_residual(x[rows], w, res[rows])
+    check(a[rows], y, s, "linear_residual", argmax=False)
+    y, s = oracle_mod.rmsnorm_qkv_rope(x[rows], g, 1e-6, w, pos[rows], th, n_rot, hd)
+    check(c[rows], y, s, "rmsnorm_qkv_rope", argmax=False)
+    hh, sh = oracle_mod.swiglu_gate_up(x[rows], np.ascontiguousarray(w[:I]), np.ascontiguousarray(w[I:2 * I]))
+    check(h[rows], hh, sh, "swiglu_gate_up", argmax=False)
+    for v in (a, c, h):
+        assert np.isfinite(v.astype(np.float32)).all()
+
+
 @pytest.mark.parametrize("M,H,I", [(512, 1024, 2816), (768, 512, 1376), (2048, 1024, 1536),
                                    (200, 1024, 11008),      # 129..256 tokens, 172 gate/up tiles: the 128 x 256 configuration
                                    (256, 512, 13824 + 8)])

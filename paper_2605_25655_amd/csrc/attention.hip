@@ -126,33 +126,36 @@ __device__ __forceinline__ Item find_item(const AttnArgs& a)
 
 // A workgroup's result for one query head (threads of a head together hold its D sums): the output itself if the
 // request is one chunk, else the chunk's (sum, maximum, weight) triple; behind the last one the end mark.
-template <int D>
+// CUT = false: the caller knows that no request is cut.
+template <int D, bool CUT>
 __device__ __forceinline__ void put_result(const AttnArgs& a, const Item& it, int h, int d, float of, float lf, float mn)
 {
     const size_t bh = (size_t)it.b * a.Hq + h;
-    if (it.n == 1) {
+    if (!CUT || it.n == 1) {
         a.out[bh * D + d] = to_half_bits(of / lf);       // lf > 0: the chunk holds at least one live position
     } else {
         float* po = a.part + (bh * AT_MAX_SPLIT + it.s) * (D + 2);
         po[d] = of;
         if (d == 0) { po[D] = mn; po[D + 1] = lf; }
     }
-    if (a.nsplit > 1 && it.s == it.n - 1 && it.n < AT_MAX_SPLIT && d == 0)
+    if (CUT && a.nsplit > 1 && it.s == it.n - 1 && it.n < AT_MAX_SPLIT && d == 0)
         a.part[(bh * AT_MAX_SPLIT + it.n) * (D + 2) + D] = __builtin_bit_cast(float, AT_END_MARK);
 }
 // an empty request: its output is zero, and there is nothing to merge
-template <int D>
+template <int D, bool CUT>
 __device__ __forceinline__ void put_empty(const AttnArgs& a, const Item& it, int h0, int heads)
 {
     for (int idx = threadIdx.x; idx < heads * D; idx += AT_THREADS) {
         const size_t bh = (size_t)it.b * a.Hq + h0 + idx / D;
         a.out[bh * D + idx % D] = 0;
-        if (a.nsplit > 1 && idx % D == 0)
+        if (CUT && a.nsplit > 1 && idx % D == 0)
             a.part[(bh * AT_MAX_SPLIT + 1) * (D + 2) + D] = __builtin_bit_cast(float, AT_END_MARK);
     }
 }
 
-template <int D, int GT>
+// CUT = false where requests are not cut: such calls have hundreds of short workgroups, and the search for a chunk in front
+// of each, though skipped, cost 0.1-0.2 us a call (32 requests of 512 positions, 32 heads: 28.6 us with it, 28.4 without).
+template <int D, int GT, bool CUT>
 __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
 {
     constexpr int LPR = D / 8;                 // lanes per row
@@ -169,11 +172,11 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
     const int g = blockIdx.y / passes, pass = blockIdx.y % passes;
     const int h0 = g * a.group + pass * GT;    // first query head of this workgroup
     const int heads = (a.group - pass * GT < GT) ? a.group - pass * GT : GT;
-    const Item item = find_item(a);
+    const Item item = CUT ? find_item(a) : Item{(int)blockIdx.z, 0, a.seq_lens[blockIdx.z], 0, 1};
     const int b = item.b, c0 = item.c0, c1 = item.c1;
-    if (item.n == 0) return;
+    if (CUT && item.n == 0) return;
     if (c0 >= c1) {                            // an empty request (uniform: no barrier yet)
-        put_empty<D>(a, item, h0, heads);
+        put_empty<D, CUT>(a, item, h0, heads);
         return;
     }
     const int r = lane / LPR, piece = lane % LPR;
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
             lf += s_l[w][j] * cw;
             of += s_o[w][j][d] * cw;
         }
-        put_result<D>(a, item, h0 + j, d, of, lf, mn);
+        put_result<D, CUT>(a, item, h0 + j, d, of, lf, mn);
     }
 }
 
@@ -376,7 +379,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
     const int b = item.b, c0 = item.c0, c1 = item.c1;
     if (item.n == 0) return;
     if (c0 >= c1) {
-        put_empty<D>(a, item, h0, heads);
+        put_empty<D, true>(a, item, h0, heads);
         return;
     }
     const int lo = lane & 15, hi = lane >> 4;
@@ -509,7 +512,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
             lf += s_l[w * GT + j] * cw;
             of += s_o[(w * GT + j) * D + d] * cw;
         }
-        put_result<D>(a, item, h0 + j, d, of, lf, mn);
+        put_result<D, true>(a, item, h0 + j, d, of, lf, mn);
     }
 }
 
@@ -549,7 +552,8 @@ __global__ __launch_bounds__(D) void attn_combine(AttnArgs a)
 template <int D, int GT>
 void launch_decode(const AttnArgs& a, dim3 grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((attn_decode<D, GT>), grid, dim3(AT_THREADS), 0, stream, a);
+    if (a.nsplit == 1) hipLaunchKernelGGL((attn_decode<D, GT, false>), grid, dim3(AT_THREADS), 0, stream, a);
+    else hipLaunchKernelGGL((attn_decode<D, GT, true>), grid, dim3(AT_THREADS), 0, stream, a);
 }
 
 template <int D>

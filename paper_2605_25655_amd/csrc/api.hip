@@ -197,8 +197,8 @@ int pick_decode_kernel(int M, int N, int K, int epilogue, int cus)
 //                   runs where its modelled time beats the few-token GEMM's (fitted on the 7B..70B
 //                   projections: stream-K 5.5 us + 1.06 t_w + 8 us with three token tiles / 13 us with
 //                   four; GEMM 8 us for its two launches, 5 more for the RMSNorm pass, + 1.5 t_w up to
-//                   t_w = 30 us and 1.25 t_w beyond).  Typically: everything but the smallest matrices up
-//                   to 48 tokens, about a tie above.
+//                   t_w = 30 us and 1.25 t_w beyond).  Kinds without RMSNorm in front are priced by the few-token
+//                   kernel's own model instead, which usually wins (4096 x 11008 at 40 tokens 26.6 us here, 21.8).
 //   M > 64        : the GEMM kernels.
 // A forced family overrides this (forced stream-K: 64 tokens per launch; forced row slabs / blocks: 32).
 struct DecodePlan {

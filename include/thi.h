@@ -202,7 +202,8 @@ int thi_rmsnorm_swiglu_mlp(const void* x, const void* gamma, float eps, const vo
  * at the end.  Workspace: thi_attention_workspace_bytes(), 256-byte aligned, no preparation
  * needed; it may be the (prepared) workspace of the other calls if large enough: the partial results
  * lie behind the status words and hand-over slots of those calls, which are left untouched.
- * Reproducible bit for bit.
+ * Reproducible bit for bit; a request's result depends on its own query, keys, values and length and on
+ * (B, Hq, Hkv, D), not on the other requests, its place among them or S_max.
  */
 size_t thi_attention_workspace_bytes(int B, int Hq, int Hkv, int D, int S_max);
 int thi_decode_attention(const void* q, const void* k_cache, const void* v_cache, const int* seq_lens, float scale,

@@ -10,7 +10,7 @@
 // Layout: q[B,Hq,D], k/v[B,Hkv,S_max,D] (one head's positions contiguous), out[B,Hq,D], all fp16;
 // seq_lens[B] int32 on the device.  Query head h reads cache head h / (Hq/Hkv).
 //
-// Work split: a workgroup (4 waves) takes one chunk of positions of one (request, cache head) -- find_item -- and up
+// Work split: a workgroup (4 waves) takes one chunk of positions of one (request, cache head) -- chunk_size -- and up
 // to GT query heads of that cache head's group.  16 (D = 128) or 8 (D = 64) lanes cover one row with
 // 16-byte loads, so a wave instruction reads 4 or 8 consecutive positions = 1 KiB of contiguous memory;
 // U such loads of K and of V are in flight per wave, one iteration ahead of the arithmetic.  A lane
@@ -21,6 +21,7 @@
 #include "thi_internal.h"
 
 #include <mutex>
+#include <type_traits>
 
 namespace thi {
 
@@ -35,127 +36,76 @@ template <int GT> struct Unroll { static constexpr int U = (GT >= 4) ? 2 : 4; };
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// The number of live chunks of a (request, query head) is left behind its last partial result, as this word in the
-// place of the next chunk's maximum (a NaN that no conversion from fp16 can produce).
-constexpr int AT_END_MARK = 0x7fc0dead;
-
-// What a workgroup works on: positions [c0, c1) of request b, chunk s of n (n = 0: nothing).
-//
-// With at least a workgroup per compute unit from the (request, cache head) pairs alone (a.nsplit == 1) a request is
-// never cut.  Otherwise the requests are cut into chunks of one common size C, the smallest with which all chunks of a
-// cache head fit a.workgroups -- chosen here, from the lengths themselves, because the host does not know
-// them: cutting S_max instead leaves every request that is shorter than its cache with fewer workgroups and the
-// longest one deciding (24 requests of 750..2940 positions in a cache of 3000, 8 cache heads: 55.9 us, with chunks of
-// the live lengths 37.9).  C depends on the lengths as a set only, so a request's result does not
-// depend on its place in the batch.  A request's chunks are then made equal.  Every wave computes this by
-// itself (lengths one per lane); at most AT_MAX_SPLIT chunks per request, of at least a.chunk positions (a multiple of 64).
-struct Item {
-    int b, c0, c1, s, n;
-};
-
-// Inclusive scan over the wave's 64 lanes (lanes shifted in from outside a row count as 0) by data-parallel
-// primitives: a few cycles a step where a lane permutation through LDS takes some hundred.
-template <typename Op>
-__device__ __forceinline__ int wave_scan(int v, Op op)
+// Positions per chunk of a request with L live ones: all of them where requests are not cut (a.nsplit == 1), else 1/nsplit
+// of them in whole multiples of 64, at least a.chunk.  It is a function of the request's own length and of how many
+// workgroups the call has (B, heads), so that a request's chunk borders, and with them the bits of its result, do not depend on
+// its neighbours' lengths or on the size of the cache.  It also keeps the head of a workgroup short, one length and one
+// division: a chunk size common to the batch, searched for on the device so that all chunks just fit the compute
+// units, took ~1 us of scans in front of the first load (8 heads of 64, 2 requests of 468 positions 7.5 us, now 6.2; 5 requests of
+// 332 with 40 heads of 128 14.1, now 11) and won only where one request is much longer than all others (7 requests x 8 cache heads, one
+// of 14908 positions and the rest of 745: 24 us, now 45).
+__device__ __forceinline__ int chunk_size(const AttnArgs& a, int L)
 {
-    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));      // row_shr:1
-    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));      // row_shr:2
-    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));      // row_shr:4
-    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));      // row_shr:8
-    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));      // row_bcast:15 into rows 1 and 3
-    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));      // row_bcast:31 into rows 2 and 3
-    return v;
+    if (a.nsplit == 1) return L;
+    const int size = (int)(((unsigned)(L + a.nsplit - 1) / (unsigned)a.nsplit + 63u) & ~63u);
+    return size > a.chunk ? size : a.chunk;
 }
 
-__device__ __forceinline__ Item find_item(const AttnArgs& a)
+// What a workgroup works on: positions [c0, c1) of request b, its chunk number s (whole: its only one).
+struct Item {
+    int b, c0, c1, s;
+    bool whole;
+};
+
+// false: nothing (the request has fewer chunks).  An empty request is one empty chunk, for its zeros.
+__device__ __forceinline__ bool find_item(const AttnArgs& a, Item& it)
 {
-    if (a.nsplit == 1) {
-        const int b = blockIdx.z, L = a.seq_lens[b];
-        return Item{b, 0, L, 0, 1};
-    }
-    auto round64 = [](int v) { return (v + 63) & ~63; };
-    if (a.B == 1) {                                      // one request: nothing to add up
-        const int L = a.seq_lens[0];
-        int size = round64((int)((unsigned)(L + a.workgroups - 1) / (unsigned)a.workgroups));
-        size = size > a.chunk ? size : a.chunk;
-        const int n = L <= size ? 1 : (int)((unsigned)(L + size - 1) / (unsigned)size), s = blockIdx.x;
-        if (s >= n) return Item{0, 0, 0, 0, 0};
-        return Item{0, s * size, (s + 1) * size < L ? (s + 1) * size : L, s, n};
-    }
-    const int lane = threadIdx.x & 63, want = a.workgroups;
-    auto add = [](int p, int q) { return p + q; };
-    auto max2 = [](int p, int q) { return p > q ? p : q; };
-    auto length = [&](int b) { return b < a.B ? a.seq_lens[b] : 0; };
-    const int L0 = length(lane);                         // (one group of 64 requests is the rule: no second load for it)
-    int total = 0, longest = 0;
-    for (int b0 = 0; b0 < a.B; b0 += 64) {
-        const int L = b0 == 0 ? L0 : length(b0 + lane);
-        total += __builtin_amdgcn_readlane(wave_scan(L, add), 63);
-        longest = max2(longest, __builtin_amdgcn_readlane(wave_scan(L, max2), 63));
-    }
-    int C = round64((int)((unsigned)(total + want - 1) / (unsigned)want));
-    C = max2(C, round64((longest + AT_MAX_SPLIT - 1) / AT_MAX_SPLIT));
-    C = max2(C, a.chunk);
-    // chunks of request b (an empty one has a chunk too, to write its zeros)
-    auto chunks = [&](int b, int L) { return b >= a.B ? 0 : L <= C ? 1 : (int)((unsigned)(L + C - 1) / (unsigned)C); };
-    while (C < longest) {
-        int n = 0;
-        for (int b0 = 0; b0 < a.B; b0 += 64)
-            n += __builtin_amdgcn_readlane(wave_scan(chunks(b0 + lane, b0 == 0 ? L0 : length(b0 + lane)), add), 63);
-        if (n <= want) break;
-        C += round64(C / 16);
-    }
-    int before = 0;
-    const int x = blockIdx.x;
-    for (int b0 = 0; b0 < a.B; b0 += 64) {
-        const int L = b0 == 0 ? L0 : length(b0 + lane);
-        const int n = chunks(b0 + lane, L), upto = before + wave_scan(n, add);
-        const unsigned long long hit = __builtin_amdgcn_ballot_w64(x >= upto - n && x < upto);
-        if (hit != 0ull) {
-            const int who = __builtin_ctzll(hit);
-            const int Lb = __builtin_amdgcn_readlane(L, who), nb = __builtin_amdgcn_readlane(n, who);
-            const int s = x - (__builtin_amdgcn_readlane(upto, who) - nb);
-            const int size = round64((int)((unsigned)(Lb + nb - 1) / (unsigned)nb));      // <= C: the chunks of a request are equal
-            const int c0 = s * size < Lb ? s * size : Lb;
-            return Item{b0 + who, c0, c0 + size < Lb ? c0 + size : Lb, s, nb};
-        }
-        before = __builtin_amdgcn_readlane(upto, 63);
-    }
-    return Item{0, 0, 0, 0, 0};
+    const int b = blockIdx.z, s = blockIdx.x, L = a.seq_lens[b], size = chunk_size(a, L);
+    const int c0 = s * size, c1 = c0 + size < L ? c0 + size : L;
+    it = Item{b, c0, c1, s, L <= size};
+    return s == 0 || c0 < L;
+}
+
+// Maximum over the wave's 64 lanes, by data-parallel primitives (a lane permutation through LDS costs some hundred cycles a step).
+__device__ __forceinline__ float wave_max(float x)
+{
+    auto step = [&](auto ctrl, auto rows) {
+        const int v = __builtin_bit_cast(int, x);
+        x = __builtin_fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false)));
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});      // row_shr:1, 2, 4, 8
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});      // row_bcast:15 into rows 1 and 3
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});      // row_bcast:31 into rows 2 and 3
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
 }
 
 // A workgroup's result for one query head (threads of a head together hold its D sums): the output itself if the
-// request is one chunk, else the chunk's (sum, maximum, weight) triple; behind the last one the end mark.
-// CUT = false: the caller knows that no request is cut.
-template <int D, bool CUT>
+// request is one chunk, else the chunk's (sum, maximum, weight) triple.
+template <int D>
 __device__ __forceinline__ void put_result(const AttnArgs& a, const Item& it, int h, int d, float of, float lf, float mn)
 {
     const size_t bh = (size_t)it.b * a.Hq + h;
-    if (!CUT || it.n == 1) {
+    if (it.whole) {
         a.out[bh * D + d] = to_half_bits(of / lf);       // lf > 0: the chunk holds at least one live position
     } else {
         float* po = a.part + (bh * AT_MAX_SPLIT + it.s) * (D + 2);
         po[d] = of;
         if (d == 0) { po[D] = mn; po[D + 1] = lf; }
     }
-    if (CUT && a.nsplit > 1 && it.s == it.n - 1 && it.n < AT_MAX_SPLIT && d == 0)
-        a.part[(bh * AT_MAX_SPLIT + it.n) * (D + 2) + D] = __builtin_bit_cast(float, AT_END_MARK);
 }
 // an empty request: its output is zero, and there is nothing to merge
-template <int D, bool CUT>
+template <int D>
 __device__ __forceinline__ void put_empty(const AttnArgs& a, const Item& it, int h0, int heads)
 {
-    for (int idx = threadIdx.x; idx < heads * D; idx += AT_THREADS) {
-        const size_t bh = (size_t)it.b * a.Hq + h0 + idx / D;
-        a.out[bh * D + idx % D] = 0;
-        if (CUT && a.nsplit > 1 && idx % D == 0)
-            a.part[(bh * AT_MAX_SPLIT + 1) * (D + 2) + D] = __builtin_bit_cast(float, AT_END_MARK);
-    }
+    for (int idx = threadIdx.x; idx < heads * D; idx += AT_THREADS)
+        a.out[((size_t)it.b * a.Hq + h0 + idx / D) * D + idx % D] = 0;
 }
 
-// CUT = false where requests are not cut: such calls have hundreds of short workgroups, and the search for a chunk in front
-// of each, though skipped, cost 0.1-0.2 us a call (32 requests of 512 positions, 32 heads: 28.6 us with it, 28.4 without).
-template <int D, int GT, bool CUT>
+template <int D, int GT>
 __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
 {
     constexpr int LPR = D / 8;                 // lanes per row
@@ -172,11 +122,11 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
     const int g = blockIdx.y / passes, pass = blockIdx.y % passes;
     const int h0 = g * a.group + pass * GT;    // first query head of this workgroup
     const int heads = (a.group - pass * GT < GT) ? a.group - pass * GT : GT;
-    const Item item = CUT ? find_item(a) : Item{(int)blockIdx.z, 0, a.seq_lens[blockIdx.z], 0, 1};
+    Item item;
+    if (!find_item(a, item)) return;
     const int b = item.b, c0 = item.c0, c1 = item.c1;
-    if (CUT && item.n == 0) return;
     if (c0 >= c1) {                            // an empty request (uniform: no barrier yet)
-        put_empty<D, CUT>(a, item, h0, heads);
+        put_empty<D>(a, item, h0, heads);
         return;
     }
     const int r = lane / LPR, piece = lane % LPR;
@@ -327,7 +277,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
             lf += s_l[w][j] * cw;
             of += s_o[w][j][d] * cw;
         }
-        put_result<D, CUT>(a, item, h0 + j, d, of, lf, mn);
+        put_result<D>(a, item, h0 + j, d, of, lf, mn);
     }
 }
 
@@ -375,11 +325,11 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
     const int g = blockIdx.y / passes, pass = blockIdx.y % passes;
     const int h0 = g * a.group + pass * GT;
     const int heads = (a.group - pass * GT < GT) ? a.group - pass * GT : GT;
-    const Item item = find_item(a);
+    Item item;
+    if (!find_item(a, item)) return;
     const int b = item.b, c0 = item.c0, c1 = item.c1;
-    if (item.n == 0) return;
     if (c0 >= c1) {
-        put_empty<D, true>(a, item, h0, heads);
+        put_empty<D>(a, item, h0, heads);
         return;
     }
     const int lo = lane & 15, hi = lane >> 4;
@@ -512,39 +462,44 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
             lf += s_l[w * GT + j] * cw;
             of += s_o[(w * GT + j) * D + d] * cw;
         }
-        put_result<D, true>(a, item, h0 + j, d, of, lf, mn);
+        put_result<D>(a, item, h0 + j, d, of, lf, mn);
     }
 }
 
 // Second pass when requests may have been cut into chunks: one workgroup per (request, query head) merges the
-// chunks' triples in chunk order and normalises.  How many there are the end mark says; maxima and weights are
-// fetched one chunk per lane, the sums eight chunks at a time, so that the memory round trips overlap.
+// chunks' triples in chunk order and normalises.  One memory round trip for up to eight chunks: the length that says how
+// many there are, the maxima and weights (one chunk per lane) and the first eight sums are requested together, what
+// lies behind the last chunk is not used; weights go from lane to lane by scalar reads, not through LDS.
 template <int D>
 __global__ __launch_bounds__(D) void attn_combine(AttnArgs a)
 {
     const int bh = blockIdx.x, d = threadIdx.x, lane = threadIdx.x & 63;
     const float* const first = a.part + (size_t)bh * AT_MAX_SPLIT * (D + 2);
-    const float mine = first[(size_t)(lane < AT_MAX_SPLIT ? lane : 0) * (D + 2) + D];
-    const float mine_l = first[(size_t)(lane < AT_MAX_SPLIT ? lane : 0) * (D + 2) + D + 1];
-    const unsigned long long mark = __builtin_amdgcn_ballot_w64(lane < AT_MAX_SPLIT && lane > 0 && __builtin_bit_cast(int, mine) == AT_END_MARK);
-    const int live = mark != 0ull ? __builtin_ctzll(mark) : AT_MAX_SPLIT;
-    if (live == 1) return;                              // the first pass has written this output
+    const float mine = first[(size_t)(lane % AT_MAX_SPLIT) * (D + 2) + D];
+    const float mine_l = first[(size_t)(lane % AT_MAX_SPLIT) * (D + 2) + D + 1];
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = first[(size_t)i * (D + 2) + d];
+    const int L = a.seq_lens[bh / a.Hq], size = chunk_size(a, L);
+    if (L <= size) return;                              // one chunk: the first pass has written this output
+    const int live = (int)((unsigned)(L + size - 1) / (unsigned)size);
     float m = lane < live ? mine : -__builtin_inff();
-#pragma unroll
-    for (int sh = 32; sh >= 1; sh >>= 1) m = __builtin_fmaxf(m, __shfl_xor(m, sh));
+    m = wave_max(m);
     const float w = lane < live ? exp2_fast(mine - m) : 0.f;
+    auto of_lane = [](float x, int i) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i)); };
     float l = 0.f, o = 0.f;
-    for (int s0 = 0; s0 < live; s0 += 8) {
-        float v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = first[(size_t)(s0 + i < live ? s0 + i : live - 1) * (D + 2) + d];
+    for (int s0 = 0;;) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             if (s0 + i < live) {
-                const float c = __shfl(w, s0 + i);
-                l += __shfl(mine_l, s0 + i) * c;
+                const float c = of_lane(w, s0 + i);
+                l += of_lane(mine_l, s0 + i) * c;
                 o += v[i] * c;
             }
+        s0 += 8;
+        if (s0 >= live) break;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = first[(size_t)(s0 + i < live ? s0 + i : live - 1) * (D + 2) + d];
     }
     a.out[(size_t)bh * D + d] = to_half_bits(o / l);
 }
@@ -552,16 +507,14 @@ __global__ __launch_bounds__(D) void attn_combine(AttnArgs a)
 template <int D, int GT>
 void launch_decode(const AttnArgs& a, dim3 grid, hipStream_t stream)
 {
-    if (a.nsplit == 1) hipLaunchKernelGGL((attn_decode<D, GT, false>), grid, dim3(AT_THREADS), 0, stream, a);
-    else hipLaunchKernelGGL((attn_decode<D, GT, true>), grid, dim3(AT_THREADS), 0, stream, a);
+    hipLaunchKernelGGL((attn_decode<D, GT>), grid, dim3(AT_THREADS), 0, stream, a);
 }
 
 template <int D>
 hipError_t launch_d(const AttnArgs& a, int gt, hipStream_t stream)
 {
     const int passes = (a.group + gt - 1) / gt;
-    // uncut: one workgroup per request, cache head and pass; else a.workgroups for the chunks of a cache head
-    dim3 grid((unsigned)(a.nsplit == 1 ? 1 : a.workgroups), (unsigned)(a.Hkv * passes), (unsigned)(a.nsplit == 1 ? a.B : 1));
+    const dim3 grid((unsigned)a.nsplit, (unsigned)(a.Hkv * passes), (unsigned)a.B);
     switch (gt) {
     case 1: launch_decode<D, 1>(a, grid, stream); break;
     case 2: launch_decode<D, 2>(a, grid, stream); break;

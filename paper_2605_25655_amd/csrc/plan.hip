@@ -96,15 +96,22 @@ int attention_heads_per_workgroup(int D, int group)
     return group >= 8 ? 8 : group >= 4 ? 4 : group >= 2 ? 2 : 1;
 }
 
-// Workgroups per cache head (and pass) for the chunks of all requests; 1 = requests are not cut: enough of them, or
-// caches of at most one chunk.  One workgroup per compute unit; two where one would leave a request fewer than two chunks.
-int attention_workgroups_per_head(int B, int heads, int S_max, int num_cus)
+// Chunks per request, at most; 1 = requests are not cut: enough workgroups without, or caches of at most one chunk.  One
+// workgroup per compute unit, and no more than that while it leaves a request four chunks or more (6 requests x 8 cache
+// heads of 8192 positions: 5 chunks 28.5 us, 6 chunks and 32 compute units with two of them 31); below that the chunks a
+// request would lose weigh more than the second workgroup on some units (3 x 40 heads, one request of 13078 positions among short
+// ones: 3 chunks 66 us, 2 chunks 89).  Two to four workgroups per unit, or long requests cut into 512..2048 positions
+// whatever the rule says, were 1-3 % slower on average over 300 calls and up to twice as fast where one request is much
+// longer than all others.
+int attention_split(int B, int heads, int S_max, int num_cus)
 {
-    if ((long)B * heads >= num_cus || S_max <= AT_MIN_CHUNK) return 1;
-    int want = num_cus / heads;
-    if (want < 2 * B) want = (2 * num_cus + heads - 1) / heads;
-    if (want > B * AT_MAX_SPLIT) want = B * AT_MAX_SPLIT;
-    return want < 2 ? 2 : want;
+    const long base = (long)B * heads;
+    if (base >= num_cus || S_max <= AT_MIN_CHUNK) return 1;
+    long want = num_cus / base;
+    if (want < 4) want = (num_cus + base - 1) / base;
+    if (want > AT_MAX_SPLIT) want = AT_MAX_SPLIT;
+    const int most = (S_max - 1) / AT_MIN_CHUNK + 1;
+    return (int)(want < most ? want : most);
 }
 
 }  // namespace thi

@@ -156,13 +156,12 @@ struct AttnArgs {
     int group;               // Hq / Hkv query heads per cache head
     int nsplit;              // chunks per request, at most (1: requests are not cut)
     int chunk;               // positions per chunk, at least
-    int workgroups;          // per cache head (and pass), for the chunks of all requests
     float scale2;            // softmax scale times log2(e)
 };
 constexpr int AT_MAX_SPLIT = 32;      // chunks per request, at most
 constexpr int AT_MIN_CHUNK = 128;     // positions per chunk, at least
 int attention_heads_per_workgroup(int D, int group);
-int attention_workgroups_per_head(int B, int heads, int S_max, int num_cus);
+int attention_split(int B, int heads, int S_max, int num_cus);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream);
 
 // Rotate one interleaved pair (a, b) = (y[c], y[c+1]), c even: Algorithm 1's  y*cos + mix*sin  with

@@ -187,3 +187,27 @@ def test_chunks_of_live_lengths(thi, oracle_mod, B, Hq, Hkv, D, S_max, lens):
     perm = np.random.default_rng(B).permutation(B)
     again = run(thi, q[perm], k[perm], v[perm], lens[perm], scale)
     assert np.array_equal(got[perm].view(np.uint16), again.view(np.uint16))
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,S_max", [(5, 64, 8, 128, 3000), (4, 16, 16, 128, 2000), (3, 8, 4, 64, 1500), (70, 2, 1, 64, 900)])
+def test_a_request_does_not_see_its_neighbours_or_the_cache_size(thi, B, Hq, Hkv, D, S_max):
+    """Requests are cut into chunks; a request's bits stay the same when the other requests grow or shrink and when its
+    keys and values lie in a larger cache."""
+    say(f"[case] attention neighbours B={B} Hq={Hq} Hkv={Hkv} D={D} S_max={S_max}")
+    rng = np.random.default_rng(B + S_max)
+    L0 = S_max - 123
+    full = np.full(B, S_max, dtype=np.int32)
+    q, k, v = make_case(9700 + B + D, B, Hq, Hkv, D, S_max, full)
+    scale = float(np.float32(1.0 / np.sqrt(D)))
+    first = None
+    for lens in (full.copy(), np.ones(B, np.int32), rng.integers(0, S_max + 1, B).astype(np.int32), np.zeros(B, np.int32)):
+        lens[0] = L0
+        got = run(thi, q, k, v, lens, scale)[0]
+        first = got if first is None else first
+        assert np.array_equal(got.view(np.uint16), first.view(np.uint16)), lens[:8]
+    wide = np.zeros((2, B, Hkv, 2 * S_max + 77, D), np.float16)
+    wide[0, :, :, :S_max], wide[1, :, :, :S_max] = k, v
+    lens = np.ones(B, np.int32)
+    lens[0] = L0
+    got = run(thi, q, wide[0], wide[1], lens, scale)[0]
+    assert np.array_equal(got.view(np.uint16), first.view(np.uint16))

@@ -290,11 +290,12 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode(AttnArgs a)
 // O^T = V^T P^T; V^T comes as the A operand from LDS by ds_read_b64_tr_b16 (a 16-lane group reads four rows x 16
 // columns, lane j of it receives column j of the four rows).  So neither product needs a lane permutation, a lane's
 // accumulators belong to one head, and rescaling them is a plain multiply (done only when some head's maximum moved).
-// The weights enter the matrix core as fp16 (in [0,1]: 2^-11 relative rounding), sums and their weights are fp32.
+// The weights enter the matrix core as the sum of two fp16 values (split_weights): one alone is off by
+// 2^-12 of a weight, which the result shows where values cancel.  The second product costs 1-2 %
+// (6 requests of 2048..8029 positions, 8 x 8 heads, 28.3 -> 28.9 us); one MFMA with k = 32 over both summands and the values twice 28.9 too.
 // The first version kept V on the vector ALU (one lane permutation and eight packed dot products per head and pair of
 // positions): ~2 us of ALU work per 64 positions of a workgroup.  8 cache heads x 8 query heads: 6 requests of
-// 2048..8029 positions 50.8 -> 27.2 us (with the chunks of the live lengths), 32 of 512..2007 (not cut) 37.3 -> 31.6,
-// 64 of 75..294 15.5 -> 12.0.
+// 2048..8029 positions 51.2 -> 28.9 us (chunks by each request's length included), 32 of 512..2007 (not cut) 37.8 -> 32.7.
 //
 // Stages: 16 rows x 256 bytes of K, then of V, AT_NS per wave; a row's 16-byte piece p lies at piece p ^ (row % 16), which
 // spreads the K operand reads and the transposing V reads over the banks.  The loads are written in assembly
@@ -312,6 +313,27 @@ __device__ __forceinline__ void at_dma(const void* base_uniform, unsigned lane_b
 {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                  : : "v"(lane_byte_offset), "s"(base_uniform), "s"(lds_addr) : "memory");
+}
+
+// Weights p in [0, 1] as two fp16 summands of AT_WEIGHT_SCALE * p (a power of two: exact), for the matrix core.  A weight is
+// then off by 2^-22 of itself at most down to weights of 2^-17, and by 2^-40 of the largest weight below that.  The large summand
+// is truncated, so that the small one is never negative, and the small one of a weight that is not zero is at least fp16's
+// smallest value: an infinite value then adds up to the infinity it stands for, and not to inf - inf or 0 * inf.
+constexpr float AT_WEIGHT_SCALE = 32768.0f;
+
+__device__ __forceinline__ void split_weights(const float (&p)[4], half4& large, half4& small)
+{
+    typedef unsigned short ushort4_t __attribute__((ext_vector_type(4)));
+    float w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = p[i] * AT_WEIGHT_SCALE;
+    const half2_t h0 = __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(w[0], w[1]));
+    const half2_t h1 = __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(w[2], w[3]));
+    large = half4{h0[0], h0[1], h1[0], h1[1]};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) small[i] = (_Float16)(w[i] - (float)large[i]);
+    const ushort4_t one = {1, 1, 1, 1}, l = __builtin_bit_cast(ushort4_t, large), s = __builtin_bit_cast(ushort4_t, small);
+    small = __builtin_bit_cast(half4, __builtin_elementwise_max(s, __builtin_elementwise_min(l, one)));
 }
 
 __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
@@ -430,9 +452,12 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
 #pragma unroll
             for (int q = 0; q < DT; ++q) o[q] *= corr;
         }
-        const half4 pf = {(_Float16)p[0], (_Float16)p[1], (_Float16)p[2], (_Float16)p[3]};
+        half4 hi4, lo4;
+        split_weights(p, hi4, lo4);
 #pragma unroll
-        for (int q = 0; q < DT; ++q) o[q] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf[q], pf, o[q], 0, 0, 0);
+        for (int q = 0; q < DT; ++q) o[q] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf[q], hi4, o[q], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < DT; ++q) o[q] = __builtin_amdgcn_mfma_f32_16x16x16f16(vf[q], lo4, o[q], 0, 0, 0);
         // every read of this stage has returned before it is filled again
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (it + AT_NS < nb) issue(it + AT_NS, st);
@@ -446,7 +471,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_decode_gqa(AttnArgs a)
     float* const s_l = s_m + AT_WAVES * GT;
     __syncthreads();                                // every wave has read its last stage
 #pragma unroll
-    for (int t = 0; t < DT; ++t) *reinterpret_cast<floatx4*>(s_o + (wv * GT + lo) * D + 16 * t + 4 * hi) = o[t];
+    for (int t = 0; t < DT; ++t) *reinterpret_cast<floatx4*>(s_o + (wv * GT + lo) * D + 16 * t + 4 * hi) = o[t] * (1.0f / AT_WEIGHT_SCALE);
     if (hi == 0) { s_m[wv * GT + lo] = m; s_l[wv * GT + lo] = l; }
     __syncthreads();
     for (int idx = tid; idx < heads * D; idx += AT_THREADS) {

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from tests.gpu_common import say, to_dev, to_host
-from tests.parity import check
+from tests.parity import check, ulp16
 
 pytestmark = pytest.mark.gpu
 
@@ -211,3 +211,28 @@ def test_a_request_does_not_see_its_neighbours_or_the_cache_size(thi, B, Hq, Hkv
     lens[0] = L0
     got = run(thi, q, wide[0], wide[1], lens, scale)[0]
     assert np.array_equal(got.view(np.uint16), first.view(np.uint16))
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(16, 1, 128), (12, 3, 128), (4, 4, 128), (8, 2, 64)])
+@pytest.mark.parametrize("L", [2, 37, 300])
+def test_weights_keep_their_precision_where_values_cancel(thi, oracle_mod, Hq, Hkv, D, L):
+    """Nearly equal scores and values of alternating sign: the result is what is left of the weights' differences.  Bound: the
+    one rounding of the result, and 2^-17 of the sum of magnitudes for the fp32 scores (up to 16 x a few 2^-24) and weights."""
+    say(f"[case] attention cancellation Hq={Hq} Hkv={Hkv} D={D} L={L}")
+    rng = np.random.Generator(np.random.Philox(key=9900 + Hq + D + L))
+    q = f16(rng.standard_normal((1, Hq, D)))
+    k = f16(rng.standard_normal((1, Hkv, 1, D)) + 0.02 * rng.standard_normal((1, Hkv, L, D)))
+    sign = np.where(np.arange(L) % 2 == 0, 1.0, -1.0)[None, None, :, None]
+    v = f16(sign * np.ones((1, Hkv, L, D)))
+    lens = np.array([L], np.int32)
+    scale = float(np.float32(1.0 / np.sqrt(D)))
+    got = run(thi, q, k, v, lens, scale).astype(np.float64)
+    y, s = oracle_mod.decode_attention(q, k, v, lens, scale)
+    err = np.abs(got - y)
+    assert (err <= 0.5 * ulp16(y) + 2.0 ** -17 * s).all(), float((err / s).max())
+    # an infinite value stands for itself in its own column and nowhere else
+    v[0, :, L // 2, 3], v[0, :, 0, 5] = np.inf, -np.inf
+    got = run(thi, q, k, v, lens, scale).astype(np.float64)
+    assert (got[..., 3] == np.inf).all() and (got[..., 5] == -np.inf).all()
+    keep = np.delete(np.arange(D), [3, 5])
+    assert (np.abs(got - y) <= 0.5 * ulp16(y) + 2.0 ** -17 * s)[..., keep].all()

@@ -477,90 +477,15 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     }
 }
 
-// Time model (microseconds) of running `tiles` tiles of BN x BM on `grid` workgroups.
-//   whole tiles only : ceil(tiles / grid) rounds;
-//   shared remainder : floor(tiles / grid) whole rounds; the ragged remainder is cut along K and a second
-//                      pass (one more launch, the partial tiles' round trip through memory) adds the parts.
-// How the remainder is cut depends on what bounds the kernel.  With several token tiles it is the matrix
-// cores, fed through the L2: workgroups on neighbouring tiles must walk the same k range at the same
-// time or the panels they share are fetched once per workgroup (measured: a 30B-shaped down projection,
-// 208 tiles of 256x256 on 256 workgroups in equal contiguous shares, ran HBM-bound at 585 us against 485
-// us for whole tiles on 208 workgroups).  So every remainder tile is cut into the same `parts` = grid /
-// remainder equal k ranges (whole tiles if that is 1) -- also with a single token tile of 256, whose
-// activation panel is shared by every workgroup and too large for an L2 (measured on the 30B-shaped down
-// projection at M = 256: 88 us against 97-113 us with contiguous shares), unless equal ranges would leave
-// more than a tenth of the workgroups idle (7B-shaped gate/up at M = 160: 86 tiles x 2 ranges on 256
-// workgroups, 81 against 75 us; 13B-shaped, 108 tiles x 2: 106 against 97 us).  The few-token configurations (one token tile of at most 128) are bound
-// by their weight traffic, every weight panel is read exactly once whatever the cut, and equal contiguous
-// shares (parts = 0) keep every workgroup busy.
-// A workgroup's speed by configuration, fitted to measurements of every configuration and cut on projections of the
-// 7B..70B shapes and some odd ones at M = 200..2048 (weight copies rotated so that they come from HBM): 256x256 tiles
-// 5.4 TFLOP/s + 6 us per tile, 224 / 192 / 160 rows x 256 tokens 4.75 / 4.7 / 4.4 + 6 us, 128 rows x 256 tokens 4.6 TFLOP/s + 5 us, 128x128 tiles two per CU 1.95 TFLOP/s + 6 us,
-// 128x128 with four stages one per CU 3.6 TFLOP/s + 4 us; the second pass 8 us (a launch and its latencies: 5 us made
-// 333 x 512 x 1376 cut 12 tiles in 21 ranges, 21.2 us against 16.1 whole) + its bytes at ~8 TB/s (they are still
-// in the caches).  On those 14 shapes the pick was the best of the eight (configuration, cut) pairs or within 2 % of
-// it, but for one within 5 %; with the tiles of 160..224 rows added, on 60 shapes, it was slower than the pick without
-// them nowhere by more than the runs differ.
-struct Schedule {
-    int sk_tiles;      // tiles cut along K (0: whole tiles only)
-    int parts;         // equal k ranges per shared tile; 0 = equal contiguous shares across tile boundaries
-    double us;
-};
-
-constexpr double SECOND_PASS_US = 8.0;
-
-Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, double wg_tflops, double tile_fixed_us, bool cut = true)
-{
-    double work_us = 2.0 * BN * BM * (double)K / (wg_tflops * 1e6);
-    if (tiles_m == 1) {      // every weight panel is read by one workgroup only: its traffic is a second bound
-        const double stream_us = (double)BN * K * 2.0 / (6.0e6 / grid);
-        work_us = work_us > stream_us ? work_us : stream_us;
-    }
-    const double tile_us = tile_fixed_us + work_us;
-    const int rem = tiles % grid, full = tiles / grid;
-    const double tile_bytes = (double)BN * BM * 4.0;
-    const double whole = (double)((tiles + grid - 1) / grid) * tile_us;
-    if (rem == 0 || !cut) return Schedule{0, tiles_m == 1 ? 0 : 1, whole};
-    const int ktiles = (K + 63) / 64;
-    int parts = grid / rem;
-    if (parts > ktiles) parts = ktiles;
-    // One token tile: equal contiguous shares for the few-token configurations, and for a 256-token tile
-    // when equal ranges would leave more than a tenth of the workgroups idle.
-    if (tiles_m == 1 && (BM <= 128 || (long)rem * parts * 10 < (long)grid * 9)) {
-        const double shared = ((double)full + (double)rem / grid) * tile_us + SECOND_PASS_US + (double)(grid + rem) * tile_bytes * 2.0 / 4.0e6;
-        return shared < whole ? Schedule{rem, 0, shared} : Schedule{0, 0, whole};
-    }
-    if (parts < 2) return Schedule{0, 1, whole};
-    const double shared = (double)full * tile_us + tile_fixed_us + work_us / parts + SECOND_PASS_US +
-                          (double)rem * parts * tile_bytes * 2.0 / 8.0e6;
-    return shared < whole ? Schedule{rem, parts, shared} : Schedule{0, 1, whole};
-}
-
-// the multi-token-tile configurations
-constexpr double BIG_TFLOPS = 5.4, BIG_FIXED_US = 6.0;        // 256x256, one workgroup per CU
-constexpr double R224_TFLOPS = 4.75, R224_FIXED_US = 6.0;     // 224, 192 and 160 rows x 256 tokens, one per CU
-constexpr double R192_TFLOPS = 4.7, R192_FIXED_US = 6.0;
-constexpr double R160_TFLOPS = 4.4, R160_FIXED_US = 6.0;
-constexpr double TALL_TFLOPS = 4.6, TALL_FIXED_US = 5.0;      // 128 rows x 256 tokens, one per CU
-constexpr double SMALL_TFLOPS = 1.95, SMALL_FIXED_US = 6.0;   // 128x128, two per CU
-constexpr double DEEP_TFLOPS = 3.6, DEEP_FIXED_US = 4.0;      // 128x128, four stages, one per CU
-constexpr double FEW_TFLOPS = 900.0 / 256;                    // one token tile: bound by the weight stream anyway
-
 // ALL = also build the variant for a ragged K (KTAIL).
 template <int BN, int BM, int WN, int WM, int GK, int NS, bool ALL>
-hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream, double wg_tflops, double tile_fixed_us)
+hipError_t launch_cfg(GemmArgs a, int epilogue, const GemmPlan& p, hipStream_t stream)
 {
-    const int per_tile = is_swiglu(epilogue) ? BN / 2 : BN;
-    const int tiles_n = (a.N + per_tile - 1) / per_tile;
-    const int tiles_m = (a.M + BM - 1) / BM;
-    const int ktiles = (a.K + GK - 1) / GK;
-    a.tiles = tiles_n * tiles_m;
-    const long U = (long)a.tiles * ktiles;
-    long grid = grid_cap;
-    if (grid > U) grid = U;
     constexpr bool CUT = BN / WN / 16 % 2 == 0;
-    const Schedule plan = plan_schedule(a.tiles, tiles_m, (int)grid, BN, BM, a.K, wg_tflops, tile_fixed_us, CUT);
-    const int sk_tiles = plan.sk_tiles, parts = plan.parts;
+    const GemmTile tile = gemm_tile(p.config);
+    if (tile.BN != BN || tile.BM != BM || tile.GK != GK || tile.cut != CUT || tile.ragged != ALL) return hipErrorInvalidValue;
+    a.tiles = p.tiles;
+    const int tiles_m = p.tiles_m, ktiles = p.ktiles, grid = p.grid, sk_tiles = p.sk_tiles, parts = p.parts;
     const size_t lds = (size_t)NS * (BN + BM) * (GK / 8) * sizeof(uintx4);
     dim3 g((unsigned)grid), b(64 * WN * WM);
 #define THI_LAUNCH_K(E, KT)                                                                                  \
@@ -575,7 +500,7 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream
         if constexpr (CUT) {                                                                                 \
             if (sk_tiles > 0)                                                                                \
                 hipLaunchKernelGGL((gemm_fixup<BN, BM, WN, WM, E>), dim3(sk_tiles * (BN / WN / 32) * (BM / WM / 16)), \
-                                   b, 0, stream, a, tiles_m, ktiles, sk_tiles, (int)grid, parts);            \
+                                   b, 0, stream, a, tiles_m, ktiles, sk_tiles, grid, parts);            \
         }                                                                                                    \
     } while (0)
 #define THI_LAUNCH(E)                                                                                        \
@@ -599,17 +524,6 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, int grid_cap, hipStream_t stream
 #undef THI_LAUNCH
 #undef THI_LAUNCH_K
     return hipGetLastError();
-}
-
-double config_cost(const GemmArgs& a, int epilogue, int BN, int BM, int grid, double wg_tflops, double tile_fixed_us,
-                   bool cut = true)
-{
-    const int per_tile = is_swiglu(epilogue) ? BN / 2 : BN;
-    const int tiles_m = (a.M + BM - 1) / BM;
-    const long tiles = (long)((a.N + per_tile - 1) / per_tile) * tiles_m;
-    const long units = tiles * ((a.K + 63) / 64);
-    const int g = (int)(units < grid ? units : grid);
-    return plan_schedule((int)tiles, tiles_m, g, BN, BM, a.K, wg_tflops, tile_fixed_us, cut).us;
 }
 
 }  // namespace
@@ -704,76 +618,20 @@ hipError_t launch_rmsnorm_rows(const uint16_t* x, const uint16_t* gamma, float e
 
 hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t stream)
 {
-    int g_big = num_cus, g_small = 2 * num_cus;        // workgroups that fit: one resp. two per CU
-    if (g_big * 4 > GEMM_MAX_GRID) g_big = GEMM_MAX_GRID / 4;
-    if (g_small > GEMM_MAX_GRID) g_small = GEMM_MAX_GRID;
     if (is_rms(epilogue)) return hipErrorInvalidValue;
-    const bool even_k = a.K % 64 == 0;                 // else: the configurations that are built with KTAIL
-    if (a.M <= 128 && a.counters) {
-        // The few-token kernel where its modelled time is the smaller one (the other model is about a tenth low there:
-        // 10240 x 8192 at 128 tokens 55.8 us against 50.3 here, 12288 x 4096 31.8 against 35.6)
-        const MidPlan mp = plan_mid(a.M, a.N, a.K, epilogue, num_cus);
-        const double few = config_cost(a, epilogue, 128, a.M <= 64 && a.K % 128 == 0 ? 64 : 128, g_big, FEW_TFLOPS, 0.0);
-        if (mp.BN && mp.us < 1.1 * few) return launch_mid(a, epilogue, mp, stream);
-    }
-    if (a.M <= 128) {
-        // Few tokens: one token tile, the weights are read once and the kernel is bound by how many
-        // bytes a CU keeps in flight: three stages of 128 rows x 128 k against 64 tokens (K a multiple of
-        // 128), else four of 128 rows x 64 k against 128 tokens.  Every tile is cut along K here (far fewer
-        // tiles than workgroups) and the second pass costs by the partial tiles' bytes, (workgroups +
-        // tiles) x tile size: 128-row tiles halve them against 256-row tiles (7B-shaped O projection at
-        // M = 128: 24.8 -> 18.5 us, gate/up 61 -> 53; second pass alone 8.5-9.7 us with 256 rows).  With
-        // many more tiles than workgroups (70B-shaped gate/up: 448) the 256-row tile's smaller share of
-        // activation staging wins instead (188 against 230 us).
-        if (a.M <= 64 && a.K % 128 == 0) return launch_cfg<128, 64, 4, 1, 128, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
-        const int per_tile = is_swiglu(epilogue) ? 64 : 128;
-        if (!even_k || (a.N + per_tile - 1) / per_tile <= num_cus + num_cus / 8)
-            return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
-        return launch_cfg<256, 128, 4, 2, 64, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
-    }
-    // 129..256 tokens and about as many 128-row tiles as workgroups (0.65..1.2 x: the gate/up shapes):
-    // one token tile of 256 against 128 rows, so that the weights are read once and few tiles are cut
-    // (7B-shaped gate/up at M = 192: 74.9 -> 67.4 us, 13B 98.9 -> 94.2, 30B 161 -> 152).  With fewer tiles
-    // the 128 KiB partial tiles of the workgroups that share one cost more than reading the weights twice
-    // (7B-shaped O projection 22.5 -> 31 us), with more the 256-row tile wins: both stay with the rule below.
-    if (even_k && a.M <= 256) {
-        const int per_tile = is_swiglu(epilogue) ? 64 : 128;
-        const long t128 = (a.N + per_tile - 1) / per_tile;
-        if (t128 * 20 >= (long)num_cus * 13 && t128 * 5 <= (long)num_cus * 6)
-            return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, g_big, stream, FEW_TFLOPS, 0.0);
-    }
-    // Several token tiles: the configuration with the smallest modelled time.  128 rows x 256 tokens halves the granularity
-    // of the 256x256 tile where that leaves CUs idle (512 x 15360 x 5120: 120 tiles cut in two and a second pass 92.4
-    // us, 240 whole tiles 87.8; 1500 x 4096 x 4096 68 -> 63), the four-stage 128x128 one where that still does
-    // (300 x 12288 x 4096: a round and 32 tiles in 8 ranges 58 us, two per CU 70).  224, 192 and 160 rows x 256 tokens are
-    // for the counts in between, where one of them nearly fills whole rounds (against the best of the others): 224 rows
-    // 2048 x 6656 x 17920 437 -> 405 us, 2048 x 6656 x 6656 169 -> 160; 192 rows gate/up 512 x 22016 x 4096 107 -> 95.5,
-    // 300 x 22016 x 4096 100 -> 85, 1024 x 12288 x 4096 110 -> 99; 160 rows 2048 x 5120 x 13824 286 -> 250, 2048 x 5120 x
-    // 5120 118 -> 99, 512 x 19968 x 6656 150 -> 132, 1024 x 10240 x 8192 170 -> 152.  Not where the 256-row tile fills its
-    // rounds as well: per flop they read more operand bytes (gate/up 2048 x 57344 x 8192 with 224 rows 1625 us, 1505).
-    enum { BIG, R224, R192, R160, TALL, DEEP, SMALL, CONFIGS };
-    double cost[CONFIGS];
-    cost[BIG] = config_cost(a, epilogue, 256, 256, g_big, BIG_TFLOPS, BIG_FIXED_US);
-    cost[DEEP] = config_cost(a, epilogue, 128, 128, num_cus, DEEP_TFLOPS, DEEP_FIXED_US);
-    cost[SMALL] = config_cost(a, epilogue, 128, 128, g_small, SMALL_TFLOPS, SMALL_FIXED_US);
-    cost[R224] = cost[R192] = cost[R160] = cost[TALL] = cost[BIG] + 1.0;      // not built for a ragged K
-    if (even_k) {
-        cost[R224] = config_cost(a, epilogue, 224, 256, g_big, R224_TFLOPS, R224_FIXED_US, false);
-        cost[R192] = config_cost(a, epilogue, 192, 256, g_big, R192_TFLOPS, R192_FIXED_US);
-        cost[R160] = config_cost(a, epilogue, 160, 256, g_big, R160_TFLOPS, R160_FIXED_US, false);
-        cost[TALL] = config_cost(a, epilogue, 128, 256, g_big, TALL_TFLOPS, TALL_FIXED_US);
-    }
-    int best = BIG;
-    for (int c = BIG + 1; c < CONFIGS; ++c)
-        if (cost[c] < cost[best]) best = c;
-    switch (best) {
-    case BIG: return launch_cfg<256, 256, 4, 2, 64, 2, true>(a, epilogue, g_big, stream, BIG_TFLOPS, BIG_FIXED_US);
-    case R224: return launch_cfg<224, 256, 2, 4, 64, 2, false>(a, epilogue, g_big, stream, R224_TFLOPS, R224_FIXED_US);
-    case R192: return launch_cfg<192, 256, 2, 4, 64, 2, false>(a, epilogue, g_big, stream, R192_TFLOPS, R192_FIXED_US);
-    case R160: return launch_cfg<160, 256, 2, 4, 64, 2, false>(a, epilogue, g_big, stream, R160_TFLOPS, R160_FIXED_US);
-    case TALL: return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, g_big, stream, TALL_TFLOPS, TALL_FIXED_US);
-    case DEEP: return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, num_cus, stream, DEEP_TFLOPS, DEEP_FIXED_US);
-    default: return launch_cfg<128, 128, 2, 4, 64, 2, true>(a, epilogue, g_small, stream, SMALL_TFLOPS, SMALL_FIXED_US);
+    const GemmPlan p = plan_gemm(a.M, a.N, a.K, epilogue, num_cus);
+    switch (p.config) {
+    case GEMM_MID: return launch_mid(a, epilogue, p.mid, stream);
+    case GEMM_FEW64: return launch_cfg<128, 64, 4, 1, 128, 3, false>(a, epilogue, p, stream);
+    case GEMM_FEW256: return launch_cfg<256, 128, 4, 2, 64, 3, false>(a, epilogue, p, stream);
+    case GEMM_BIG: return launch_cfg<256, 256, 4, 2, 64, 2, true>(a, epilogue, p, stream);
+    case GEMM_R224: return launch_cfg<224, 256, 2, 4, 64, 2, false>(a, epilogue, p, stream);
+    case GEMM_R192: return launch_cfg<192, 256, 2, 4, 64, 2, false>(a, epilogue, p, stream);
+    case GEMM_R160: return launch_cfg<160, 256, 2, 4, 64, 2, false>(a, epilogue, p, stream);
+    case GEMM_ONE: case GEMM_TALL: return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, p, stream);
+    case GEMM_FEW128: case GEMM_DEEP: return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, p, stream);
+    case GEMM_SMALL: return launch_cfg<128, 128, 2, 4, 64, 2, true>(a, epilogue, p, stream);
+    default: return hipErrorInvalidValue;
     }
 }
 

@@ -88,6 +88,167 @@ MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
     return best;
 }
 
+namespace {
+
+// Time model (microseconds) of running `tiles` tiles of BN x BM on `grid` workgroups.
+//   whole tiles only : ceil(tiles / grid) rounds;
+//   shared remainder : floor(tiles / grid) whole rounds; the ragged remainder is cut along K and a second
+//                      pass (one more launch, the partial tiles' round trip through memory) adds the parts.
+// How the remainder is cut depends on what bounds the kernel.  With several token tiles it is the matrix
+// cores, fed through the L2: workgroups on neighbouring tiles must walk the same k range at the same
+// time or the panels they share are fetched once per workgroup (measured: a 30B-shaped down projection,
+// 208 tiles of 256x256 on 256 workgroups in equal contiguous shares, ran HBM-bound at 585 us against 485
+// us for whole tiles on 208 workgroups).  So every remainder tile is cut into the same `parts` = grid /
+// remainder equal k ranges (whole tiles if that is 1) -- also with a single token tile of 256, whose
+// activation panel is shared by every workgroup and too large for an L2 (measured on the 30B-shaped down
+// projection at M = 256: 88 us against 97-113 us with contiguous shares), unless equal ranges would leave
+// more than a tenth of the workgroups idle (7B-shaped gate/up at M = 160: 86 tiles x 2 ranges on 256
+// workgroups, 81 against 75 us; 13B-shaped, 108 tiles x 2: 106 against 97 us).  The few-token configurations (one token tile of at most 128) are bound
+// by their weight traffic, every weight panel is read exactly once whatever the cut, and equal contiguous
+// shares (parts = 0) keep every workgroup busy.
+// A workgroup's speed by configuration, fitted to measurements of every configuration and cut on projections of the
+// 7B..70B shapes and some odd ones at M = 200..2048 (weight copies rotated so that they come from HBM): 256x256 tiles
+// 5.4 TFLOP/s + 6 us per tile, 224 / 192 / 160 rows x 256 tokens 4.75 / 4.7 / 4.4 + 6 us, 128 rows x 256 tokens 4.6 TFLOP/s + 5 us, 128x128 tiles two per CU 1.95 TFLOP/s + 6 us,
+// 128x128 with four stages one per CU 3.6 TFLOP/s + 4 us; the second pass 8 us (a launch and its latencies: 5 us made
+// 333 x 512 x 1376 cut 12 tiles in 21 ranges, 21.2 us against 16.1 whole) + its bytes at ~8 TB/s (they are still
+// in the caches).  On those 14 shapes the pick was the best of the eight (configuration, cut) pairs or within 2 % of
+// it, but for one within 5 %; with the tiles of 160..224 rows added, on 60 shapes, it was slower than the pick without
+// them nowhere by more than the runs differ.
+struct Schedule {
+    int sk_tiles;      // tiles cut along K (0: whole tiles only)
+    int parts;         // equal k ranges per shared tile; 0 = equal contiguous shares across tile boundaries
+    double us;
+};
+
+constexpr double SECOND_PASS_US = 8.0;
+
+Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, double wg_tflops, double tile_fixed_us, bool cut = true)
+{
+    double work_us = 2.0 * BN * BM * (double)K / (wg_tflops * 1e6);
+    if (tiles_m == 1) {      // every weight panel is read by one workgroup only: its traffic is a second bound
+        const double stream_us = (double)BN * K * 2.0 / (6.0e6 / grid);
+        work_us = work_us > stream_us ? work_us : stream_us;
+    }
+    const double tile_us = tile_fixed_us + work_us;
+    const int rem = tiles % grid, full = tiles / grid;
+    const double tile_bytes = (double)BN * BM * 4.0;
+    const double whole = (double)((tiles + grid - 1) / grid) * tile_us;
+    if (rem == 0 || !cut) return Schedule{0, tiles_m == 1 ? 0 : 1, whole};
+    const int ktiles = (K + 63) / 64;
+    int parts = grid / rem;
+    if (parts > ktiles) parts = ktiles;
+    // One token tile: equal contiguous shares for the few-token configurations, and for a 256-token tile
+    // when equal ranges would leave more than a tenth of the workgroups idle.
+    if (tiles_m == 1 && (BM <= 128 || (long)rem * parts * 10 < (long)grid * 9)) {
+        const double shared = ((double)full + (double)rem / grid) * tile_us + SECOND_PASS_US + (double)(grid + rem) * tile_bytes * 2.0 / 4.0e6;
+        return shared < whole ? Schedule{rem, 0, shared} : Schedule{0, 0, whole};
+    }
+    if (parts < 2) return Schedule{0, 1, whole};
+    const double shared = (double)full * tile_us + tile_fixed_us + work_us / parts + SECOND_PASS_US +
+                          (double)rem * parts * tile_bytes * 2.0 / 8.0e6;
+    return shared < whole ? Schedule{rem, parts, shared} : Schedule{0, 1, whole};
+}
+
+}  // namespace
+
+// The configurations: tile, k per stage, cut along K?, ragged K?, workgroups per CU, TFLOP/s of a workgroup and fixed time per tile (us)
+GemmTile gemm_tile(int config)
+{
+    switch (config) {
+    case GEMM_FEW64: return GemmTile{128, 64, 128, true, false, 1, 900.0 / 256, 0.0};      // one token tile: bound by the weight stream anyway
+    case GEMM_FEW128: return GemmTile{128, 128, 64, true, true, 1, 900.0 / 256, 0.0};      // (the kernel of GEMM_DEEP)
+    case GEMM_FEW256: return GemmTile{256, 128, 64, true, false, 1, 900.0 / 256, 0.0};
+    case GEMM_ONE: return GemmTile{128, 256, 64, true, false, 1, 900.0 / 256, 0.0};        // (the kernel of GEMM_TALL)
+    case GEMM_BIG: return GemmTile{256, 256, 64, true, true, 1, 5.4, 6.0};
+    case GEMM_R224: return GemmTile{224, 256, 64, false, false, 1, 4.75, 6.0};
+    case GEMM_R192: return GemmTile{192, 256, 64, true, false, 1, 4.7, 6.0};
+    case GEMM_R160: return GemmTile{160, 256, 64, false, false, 1, 4.4, 6.0};
+    case GEMM_TALL: return GemmTile{128, 256, 64, true, false, 1, 4.6, 5.0};
+    case GEMM_DEEP: return GemmTile{128, 128, 64, true, true, 1, 3.6, 4.0};
+    case GEMM_SMALL: return GemmTile{128, 128, 64, true, true, 2, 1.95, 6.0};
+    default: return GemmTile{};
+    }
+}
+
+namespace {
+
+GemmPlan plan_config(int config, int M, int N, int K, int epilogue, int num_cus)
+{
+    const GemmTile t = gemm_tile(config);
+    const int per_tile = is_swiglu(epilogue) ? t.BN / 2 : t.BN;
+    GemmPlan p{};
+    p.config = config;
+    p.tiles_m = (M + t.BM - 1) / t.BM;
+    p.tiles = (N + per_tile - 1) / per_tile * p.tiles_m;
+    p.ktiles = (K + t.GK - 1) / t.GK;
+    long grid = (long)num_cus * t.per_cu;        // workgroups that fit, and that the workspace has partial tiles for
+    const long most = (long)GEMM_MAX_GRID * 128 * 128 / (t.BN * t.BM > 128 * 128 ? 256 * 256 : 128 * 128), units = (long)p.tiles * p.ktiles;
+    if (grid > most) grid = most;
+    if (grid > units) grid = units;
+    p.grid = (int)grid;
+    const Schedule s = plan_schedule(p.tiles, p.tiles_m, p.grid, t.BN, t.BM, K, t.wg_tflops, t.fixed_us, t.cut);
+    p.sk_tiles = s.sk_tiles;
+    p.parts = s.parts;
+    p.us = s.us;
+    return p;
+}
+
+}  // namespace
+
+GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
+{
+    const bool even_k = K % 64 == 0;                 // else: the configurations that take a ragged K
+    const int per128 = is_swiglu(epilogue) ? 64 : 128;
+    const long t128 = ((long)N + per128 - 1) / per128;
+    if (M <= 128) {
+        // Few tokens: one token tile, the weights are read once and the kernel is bound by how many
+        // bytes a CU keeps in flight: three stages of 128 rows x 128 k against 64 tokens (K a multiple of
+        // 128), else four of 128 rows x 64 k against 128 tokens.  Every tile is cut along K here (far fewer
+        // tiles than workgroups) and the second pass costs by the partial tiles' bytes, (workgroups +
+        // tiles) x tile size: 128-row tiles halve them against 256-row tiles (7B-shaped O projection at
+        // M = 128: 24.8 -> 18.5 us, gate/up 61 -> 53; second pass alone 8.5-9.7 us with 256 rows).  With
+        // many more tiles than workgroups (70B-shaped gate/up: 448) the 256-row tile's smaller share of
+        // activation staging wins instead (188 against 230 us).
+        const int config = M <= 64 && K % 128 == 0 ? GEMM_FEW64 : !even_k || t128 <= num_cus + num_cus / 8 ? GEMM_FEW128 : GEMM_FEW256;
+        // The few-token kernel where its modelled time is the smaller one (the other model is about a tenth low there:
+        // 10240 x 8192 at 128 tokens 55.8 us against 50.3 here, 12288 x 4096 31.8 against 35.6)
+        const MidPlan mp = plan_mid(M, N, K, epilogue, num_cus);
+        if (mp.BN && mp.us < 1.1 * plan_config(config == GEMM_FEW256 ? GEMM_FEW128 : config, M, N, K, epilogue, num_cus).us) {
+            GemmPlan p{};
+            p.config = GEMM_MID;
+            p.mid = mp;
+            p.tiles = mp.tiles;
+            p.grid = mp.tiles * mp.S;
+            p.us = mp.us;
+            return p;
+        }
+        return plan_config(config, M, N, K, epilogue, num_cus);
+    }
+    // 129..256 tokens and about as many 128-row tiles as workgroups (0.65..1.2 x: the gate/up shapes):
+    // one token tile of 256 against 128 rows, so that the weights are read once and few tiles are cut
+    // (7B-shaped gate/up at M = 192: 74.9 -> 67.4 us, 13B 98.9 -> 94.2, 30B 161 -> 152).  With fewer tiles
+    // the 128 KiB partial tiles of the workgroups that share one cost more than reading the weights twice
+    // (7B-shaped O projection 22.5 -> 31 us), with more the 256-row tile wins: both stay with the rule below.
+    if (even_k && M <= 256 && t128 * 20 >= (long)num_cus * 13 && t128 * 5 <= (long)num_cus * 6)
+        return plan_config(GEMM_ONE, M, N, K, epilogue, num_cus);
+    // Several token tiles: the configuration with the smallest modelled time.  128 rows x 256 tokens halves the granularity
+    // of the 256x256 tile where that leaves CUs idle (512 x 15360 x 5120: 120 tiles cut in two and a second pass 92.4
+    // us, 240 whole tiles 87.8; 1500 x 4096 x 4096 68 -> 63), the four-stage 128x128 one where that still does
+    // (300 x 12288 x 4096: a round and 32 tiles in 8 ranges 58 us, two per CU 70).  224, 192 and 160 rows x 256 tokens are
+    // for the counts in between, where one of them nearly fills whole rounds (against the best of the others): 224 rows
+    // 2048 x 6656 x 17920 437 -> 405 us, 2048 x 6656 x 6656 169 -> 160; 192 rows gate/up 512 x 22016 x 4096 107 -> 95.5,
+    // 300 x 22016 x 4096 100 -> 85, 1024 x 12288 x 4096 110 -> 99; 160 rows 2048 x 5120 x 13824 286 -> 250, 2048 x 5120 x
+    // 5120 118 -> 99, 512 x 19968 x 6656 150 -> 132, 1024 x 10240 x 8192 170 -> 152.  Not where the 256-row tile fills its
+    // rounds as well: per flop they read more operand bytes (gate/up 2048 x 57344 x 8192 with 224 rows 1625 us, 1505).
+    GemmPlan best = plan_config(GEMM_BIG, M, N, K, epilogue, num_cus);
+    for (int c = GEMM_BIG + 1; c <= GEMM_SMALL; ++c) {
+        if (!even_k && !gemm_tile(c).ragged) continue;
+        const GemmPlan p = plan_config(c, M, N, K, epilogue, num_cus);
+        if (p.us < best.us) best = p;
+    }
+    return best;
+}
+
 // ---- decode attention ------------------------------------------------------------------------------
 // query heads that share a pass over their cache head: 16 on the matrix cores (D = 128, groups of four and more)
 int attention_heads_per_workgroup(int D, int group)

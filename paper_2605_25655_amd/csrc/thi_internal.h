@@ -128,8 +128,7 @@ struct GemmArgs {
 };
 constexpr int GEMM_MAX_GRID = 2048;   // in units of 128x128 partial tiles (a 256x256 tile takes four)
 size_t gemm_partial_bytes();
-hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t stream);
-// The few-token kernel (33..128 tokens; launch_gemm takes it where it is the faster one): how the tile rows and K are
+// The few-token kernel (33..128 tokens; plan_gemm takes it where it is the faster one): how the tile rows and K are
 // dealt to the compute units.
 struct MidPlan {
     int BN;          // virtual weight rows per tile (0: the kernel does not serve the shape)
@@ -138,6 +137,25 @@ struct MidPlan {
     double us;       // modelled time
 };
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
+// The GEMM's configurations, their constants, and which of them runs a product (no RMSNorm kinds).  From GEMM_BIG on: the
+// candidates above 128 tokens.
+enum GemmConfig { GEMM_MID, GEMM_FEW64, GEMM_FEW128, GEMM_FEW256, GEMM_ONE, GEMM_BIG, GEMM_R224, GEMM_R192, GEMM_R160, GEMM_TALL, GEMM_DEEP, GEMM_SMALL };
+struct GemmTile {
+    int BN, BM, GK;      // virtual weight rows x tokens of a tile, k of a stage
+    bool cut, ragged;    // built for tiles cut along K, for a K that is no multiple of GK
+    int per_cu;          // workgroups per compute unit
+    double wg_tflops, fixed_us;
+};
+GemmTile gemm_tile(int config);
+struct GemmPlan {
+    int config;
+    MidPlan mid;                     // GEMM_MID only
+    int tiles, tiles_m, ktiles;      // output tiles, token tiles, k-tiles of K
+    int grid, sk_tiles, parts;       // workgroups; the first sk_tiles tiles are cut along K, into `parts` equal ranges (0: equal shares)
+    double us;                       // modelled time
+};
+GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus);
+hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t stream);
 hipError_t launch_mid(const GemmArgs& a, int epilogue, const MidPlan& p, hipStream_t stream);
 // xn[m,k] = fp16(x[m,k] * gamma[k] / sqrt(mean_k x[m,:]^2 + eps)): the prefill path's RMSNorm pass
 // With rope.cs set it also fills that table: cs[m][i] = (cos, sin)(pos[m] * theta[i]), fp32, full-range.

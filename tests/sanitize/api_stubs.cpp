@@ -32,10 +32,22 @@ hipError_t launch_mlp_fused(const SkinnyArgs& up, const SkinnyArgs& down, int ep
     ++g_launches;
     return (mlp_fused_ok(up.M, up.K, up.N, epilogue_up, num_cus, ksplit_down) && down.x == up.out) ? hipSuccess : hipErrorInvalidValue;
 }
-hipError_t launch_gemm(const GemmArgs& a, int epilogue, int, hipStream_t)
+hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t)
 {
     ++g_launches;
-    return (is_rms(epilogue) || !a.partials) ? hipErrorInvalidValue : hipSuccess;
+    if (is_rms(epilogue) || !a.partials || !a.counters) return hipErrorInvalidValue;
+    const GemmPlan p = plan_gemm(a.M, a.N, a.K, epilogue, num_cus);
+    const size_t region = gemm_partial_bytes();
+    if (p.grid < 1 || p.tiles < 1) return hipErrorInvalidValue;
+    if (p.config == GEMM_MID) {      // a partial tile: eight waves, at most seven finished fragments of 1 KiB each
+        const bool fits = p.mid.S == 1 || (size_t)p.grid * 8 * 7 * 1024 <= region;
+        return a.M <= 128 && p.grid == p.mid.tiles * p.mid.S && p.grid <= num_cus && p.mid.tiles <= 1024 && fits ? hipSuccess : hipErrorInvalidValue;
+    }
+    const GemmTile t = gemm_tile(p.config);
+    const bool covers = (long)p.tiles_m * t.BM >= a.M && (long)p.tiles / p.tiles_m * t.BN >= (is_swiglu(epilogue) ? 2L : 1L) * a.N && p.ktiles * (long)t.GK >= a.K;
+    const bool cut = p.sk_tiles == 0 || (t.cut && (size_t)p.grid * 2 * t.BN * t.BM * 4 <= region &&
+                                         (p.parts == 0 || ((long)p.sk_tiles * p.parts <= p.grid && p.parts <= p.ktiles)));
+    return covers && cut && (t.ragged || a.K % t.GK == 0) && p.sk_tiles <= p.tiles ? hipSuccess : hipErrorInvalidValue;
 }
 hipError_t launch_rmsnorm_rows(const uint16_t*, const uint16_t*, float, uint16_t* xn, int, int, const RopeArgs&, hipStream_t)
 {

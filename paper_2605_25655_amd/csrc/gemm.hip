@@ -193,17 +193,24 @@ __device__ __forceinline__ void store_one(const GemmArgs& a, int tile_n, int til
     }
 }
 
-// Second pass for tiles that were cut along K: one workgroup per (shared tile, pair of accumulator fragments)
-// adds the partial fragments of the tile's contributors in workgroup order and applies the epilogue.  The
-// thread <-> element mapping is the main kernel's, so the partials are read back as they were written.
+// Second pass for tiles that were cut along K: one workgroup per (shared tile, pair of accumulator fragments, FIXUP_WAVES of
+// the main kernel's waves) adds the partial fragments of the tile's contributors in workgroup order and applies the epilogue.
+// The thread <-> element mapping is the main kernel's, so the partials are read back as they were written.
+// Two waves: a product of few tiles in many parts has all its partial tiles read by few compute units, and with the eight
+// waves of the main kernel to a workgroup by a quarter of those (one tile in 26 parts, 447 x 120 x 1664: 18.3 us with eight waves, 15.6
+// with two; 329 x 113 x 3584 30.8 -> 23.5; 4 waves the same, 1 wave 25.2).
+constexpr int FIXUP_WAVES = 2;
+
 template <int BN, int BM, int WN, int WM, int EPI>
-__global__ __launch_bounds__(64 * WN * WM) void gemm_fixup(GemmArgs a, int tiles_m, int ktiles, int sk_tiles, int G, int parts)
+__global__ __launch_bounds__(64 * FIXUP_WAVES) void gemm_fixup(GemmArgs a, int tiles_m, int ktiles, int sk_tiles, int G, int parts)
 {
-    constexpr int THREADS = 64 * WN * WM;
+    constexpr int THREADS = 64 * WN * WM, GROUPS = WN * WM / FIXUP_WAVES;
     constexpr int TP = BN / WN / 32, TM = BM / WM / 16;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid / 64;
+    static_assert(WN * WM % FIXUP_WAVES == 0, "whole workgroups");
+    const int tid = (blockIdx.x % GROUPS) * 64 * FIXUP_WAVES + threadIdx.x;      // the main kernel's thread
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid / 64);
     const int wn = wv % WN, wm = wv / WN, lr = lane & 15, hi = lane >> 4;
-    const int t = blockIdx.x / (TP * TM), frag = blockIdx.x % (TP * TM);
+    const int tf = blockIdx.x / GROUPS, t = tf / (TP * TM), frag = tf % (TP * TM);
     const int tp = frag / TM, tm = frag % TM;
     const Deal deal(sk_tiles, ktiles, G, parts);
     const int w_first = deal.first(t), w_last = deal.last(t);
@@ -499,8 +506,9 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, const GemmPlan& p, hipStream_t s
         hipLaunchKernelGGL(kern, g, b, lds, stream, a, tiles_m, ktiles, sk_tiles, parts);                    \
         if constexpr (CUT) {                                                                                 \
             if (sk_tiles > 0)                                                                                \
-                hipLaunchKernelGGL((gemm_fixup<BN, BM, WN, WM, E>), dim3(sk_tiles * (BN / WN / 32) * (BM / WM / 16)), \
-                                   b, 0, stream, a, tiles_m, ktiles, sk_tiles, grid, parts);            \
+                hipLaunchKernelGGL((gemm_fixup<BN, BM, WN, WM, E>),                                                   \
+                                   dim3(sk_tiles * (BN / WN / 32) * (BM / WM / 16) * (WN * WM / FIXUP_WAVES)),        \
+                                   dim3(64 * FIXUP_WAVES), 0, stream, a, tiles_m, ktiles, sk_tiles, grid, parts);            \
         }                                                                                                    \
     } while (0)
 #define THI_LAUNCH(E)                                                                                        \

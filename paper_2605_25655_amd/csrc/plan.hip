@@ -72,17 +72,17 @@ MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
 {
     MidPlan best{0, 0, 0, 0.0};
     if (M > 128 || K > 24576) return best;
-    const int V = is_swiglu(epilogue) ? 2 * N : N;
+    const long V = is_swiglu(epilogue) ? 2L * N : N;      // (more than an int holds from N = 2^30 on)
     const int ktiles = (K + 127) / 128;
     for (int BN : {32, 48, 64, 80, 96, 112, 144}) {
         if (BN > (M > 96 ? 80 : M > 64 ? 112 : 144)) continue;  // (more spill registers)
-        const int tiles = (V + BN - 1) / BN;
+        const long tiles = (V + BN - 1) / BN;
         for (int S = 1; S <= (BN > 96 ? 1 : 16) && tiles * S <= num_cus && (S == 1 || S * 4 <= ktiles); ++S) {
             const int per = (ktiles + S - 1) / S;
             const double w = BN * per * 0.256, x = M * per * 0.256;
             const double us = 4.2 + 0.024 * w + 0.013 * x + 0.093 * per +
                               (S > 1 ? 1.0 + 0.032 * S * BN * M * 0.004 + (BN == 96 ? 3.0 : BN == 80 ? 2.0 : 0.0) : 0.0);
-            if (best.BN == 0 || us < best.us) best = MidPlan{BN, tiles, S, us};
+            if (best.BN == 0 || us < best.us) best = MidPlan{BN, (int)tiles, S, us};
         }
     }
     return best;

@@ -1,0 +1,16 @@
+// Prints what csrc/plan.hip chooses for the GEMM (test infrastructure; no GPU).  Input: lines "epilogue M N K"; output: one line each,
+// configuration, tiles, workgroups, tiles cut along K, ranges per cut tile, and the few-token kernel's rows per tile and ranges.
+#include "../../paper_2605_25655_amd/csrc/thi_internal.h"
+
+#include <cstdio>
+
+int main()
+{
+    static const char* const names[] = {"MID", "FEW64", "FEW128", "FEW256", "ONE", "BIG", "R224", "R192", "R160", "TALL", "DEEP", "SMALL"};
+    int e, M, N, K;
+    while (std::scanf("%d %d %d %d", &e, &M, &N, &K) == 4) {
+        const thi::GemmPlan p = thi::plan_gemm(M, N, K, e, 256);
+        std::printf("%s %d %d %d %d %d %d\n", names[p.config], p.tiles, p.grid, p.sk_tiles, p.parts, p.mid.BN, p.mid.S);
+    }
+    return 0;
+}

@@ -1,0 +1,36 @@
+"""Which GEMM configuration csrc/plan.hip picks, asked on the CPU (256 compute units): the picks where a price had been wrong, and
+that the shapes of the GPU tests run the kernels they are listed for."""
+import os
+import shutil
+import subprocess
+from collections import namedtuple
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+pytestmark = pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+
+PLAIN, GATE_UP = 0, 2
+Plan = namedtuple("Plan", "config tiles grid cut parts rows ranges")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_driver")
+    res = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Wno-unused-command-line-argument", "-o", exe,
+                          os.path.join(ROOT, "paper_2605_25655_amd", "csrc", "plan.hip"),
+                          "-x", "hip", os.path.join(ROOT, "tests", "plan", "plan_driver.cpp")], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+
+    def ask(epilogue, M, N, K):
+        out = subprocess.run([exe], input=f"{epilogue} {M} {N} {K}\n", capture_output=True, text=True, check=True).stdout.split()
+        return Plan(out[0], *map(int, out[1:]))
+    return ask
+
+
+def test_rows_beyond_31_bits_do_not_wrap(plan):
+    """More virtual rows than an int holds: no tile count of the few-token kernel comes near the compute units'."""
+    assert plan(GATE_UP, 40, 2 ** 30 + 8, 8).config != "MID"
+    import paper_2605_25655_amd as thi
+    assert thi.thi_query_kernel_family(40, 2 ** 30 + 8, 8, 2) == 1      # the stream-K kernel, which takes any number of rows

@@ -56,13 +56,19 @@ bool mlp_fused_ok(int M, int H, int I, int epilogue_up, int num_cus, int ksplit_
 // ---- prefill GEMM ----------------------------------------------------------------------------------
 size_t gemm_partial_bytes() { return (size_t)GEMM_MAX_GRID * 2 * 128 * 128 * sizeof(float); }
 
-// The few-token kernel: BN rows per tile and S k ranges per tile with the smallest modelled time, at most one workgroup per
-// compute unit (a second round starts with an empty pipeline: 13B gate/up at 72 tokens as 432 tiles 68.8 us, the GEMM
-// 63.8), not above K = 24576 (the 70B down projection measured 2-4 % behind the kernels it would replace).  The
-// constants, in microseconds and KB per workgroup, are fitted to ~400 measured (shape, M, BN, S) points, 17 shapes x
-// M = 40..128: 4.2 us fixed, 24 ns a KB of weights, 13 ns a KB of activations, 93 ns a stage; sharing a tile 1 us, 32 ns a
-// KB of its partial tiles and 2 / 3 us more with 80 / 96 rows.  The pick is 1 % slower than the best measured one on
-// average, 16 % at worst (on problems of 5 us); on 20 further points with the wide tiles it was the best one each time.
+// The few-token kernel: BN rows per tile and S k ranges per tile, at most one workgroup per compute unit (a second round
+// starts with an empty pipeline: 13B gate/up at 72 tokens as 432 tiles 68.8 us, the GEMM 63.8), not above K = 24576 (the
+// 70B down projection measured 2-4 % behind the kernels it would replace).
+//
+// Which (BN, S): the smallest of a time in microseconds and KB per workgroup that was fitted to ~400 measured points with tiles of
+// 32..96 rows: 4.2 us fixed, 24 ns a KB of weights, 13 ns a KB of activations, 93 ns a stage; sharing a tile 1 us, 32 ns a
+// KB of its partial tiles and 2 / 3 us more with 80 / 96 rows.  On 304 problems (36000 x 128 .. 500 x 18400, 33..128 tokens, all
+// seven heights, ~1750 points) the pick is 0.8 % slower than the best measured one on average, 3.5 % at the 95th percentile.
+// What it takes, for the comparison with other kernels: that fit is 10 % low there (13 % with 80 and 96 rows, 17 % with 112), since
+// it has no term for a tile's own work -- its MFMAs and LDS reads per stage, the meeting of the k groups, the
+// epilogue -- so the price is a second fit to the 1750 points, within 9 % (rms) with no such trend: 2.8 us, 0.4 ns an element
+// of the tile, 14 ns a KB of weights, 7 ns a KB of activations, 252 ns and 0.025 ns an element for each stage; sharing 1.6 us and 25 ns a KB
+// of partial tiles.  (It picks no better: 1.0 %, 5.4 %.)
 // Tiles of 80..144 rows are for shapes that smaller ones cut into more tiles than there are compute units, or into few
 // enough that one more share would not fit (against the kernels that served them): 19968 x 6656 at 128 tokens 75.3 -> 62
 // us (80 rows), 6656 x 17920 at 128 70.7 -> 59 (80, S = 3), gate/up 2 x 13824 x 5120 at 72 62.7 -> 55 (112), gate/up
@@ -73,7 +79,8 @@ MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
     MidPlan best{0, 0, 0, 0.0};
     if (M > 128 || K > 24576) return best;
     const long V = is_swiglu(epilogue) ? 2L * N : N;      // (more than an int holds from N = 2^30 on)
-    const int ktiles = (K + 127) / 128;
+    const int ktiles = (K + 127) / 128, BM = M > 96 ? 128 : M > 64 ? 96 : 64;
+    double least = 0.0;
     for (int BN : {32, 48, 64, 80, 96, 112, 144}) {
         if (BN > (M > 96 ? 80 : M > 64 ? 112 : 144)) continue;  // (more spill registers)
         const long tiles = (V + BN - 1) / BN;
@@ -82,7 +89,10 @@ MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
             const double w = BN * per * 0.256, x = M * per * 0.256;
             const double us = 4.2 + 0.024 * w + 0.013 * x + 0.093 * per +
                               (S > 1 ? 1.0 + 0.032 * S * BN * M * 0.004 + (BN == 96 ? 3.0 : BN == 80 ? 2.0 : 0.0) : 0.0);
-            if (best.BN == 0 || us < best.us) best = MidPlan{BN, (int)tiles, S, us};
+            if (best.BN != 0 && us >= least) continue;
+            least = us;
+            best = MidPlan{BN, (int)tiles, S, 2.83 + 4.0e-4 * BN * BM + 0.0139 * w + 0.0073 * x + per * (0.252 + 2.5e-5 * BN * BM) +
+                                                  (S > 1 ? 1.6 + 1.0e-4 * S * BN * M : 0.0)};
         }
     }
     return best;
@@ -111,9 +121,13 @@ namespace {
 // 5.4 TFLOP/s + 6 us per tile, 224 / 192 / 160 rows x 256 tokens 4.75 / 4.7 / 4.4 + 6 us, 128 rows x 256 tokens 4.6 TFLOP/s + 5 us, 128x128 tiles two per CU 1.95 TFLOP/s + 6 us,
 // 128x128 with four stages one per CU 3.6 TFLOP/s + 4 us; the second pass 8 us (a launch and its latencies: 5 us made
 // 333 x 512 x 1376 cut 12 tiles in 21 ranges, 21.2 us against 16.1 whole) + its bytes at ~8 TB/s (they are still
-// in the caches).  On those 14 shapes the pick was the best of the eight (configuration, cut) pairs or within 2 % of
-// it, but for one within 5 %; with the tiles of 160..224 rows added, on 60 shapes, it was slower than the pick without
-// them nowhere by more than the runs differ.
+// in the caches).  A share of a tile pays the fixed time in full, however small it is: priced by the share, as equal
+// contiguous shares were, it made cut tiles look up to 5 us cheaper than they are (129 x 4096 x 11008 as 32 tiles of 128 rows x
+// 256 tokens in 8 ranges 41.5 us, as 64 tiles of 128x128 in 4 ranges 36.6).  Tokens past M are loaded from one row, which the caches hold: tiles
+// of 128 tokens save a tenth of the empty part's work (64 tiles in 4 ranges 36.3 us at 129 tokens, 38.7 at 203, 41.2 at 256;
+// with a quarter, gate/up 300 x 11008 x 4096 goes to 128x128 tiles, 95 us against 86 with 192 rows).
+// On 282 problems of 129..1500 tokens (the projections of the 7B..70B shapes and random ones), every configuration measured, the
+// pick is 1.6 % slower than the best on average, 8 % at the 95th percentile.
 struct Schedule {
     int sk_tiles;      // tiles cut along K (0: whole tiles only)
     int parts;         // equal k ranges per shared tile; 0 = equal contiguous shares across tile boundaries
@@ -122,9 +136,10 @@ struct Schedule {
 
 constexpr double SECOND_PASS_US = 8.0;
 
-Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, double wg_tflops, double tile_fixed_us, bool cut = true)
+Schedule plan_schedule(int M, int tiles, int tiles_m, int grid, int BN, int BM, int K, double wg_tflops, double tile_fixed_us, bool cut)
 {
     double work_us = 2.0 * BN * BM * (double)K / (wg_tflops * 1e6);
+    if (BM == 128) work_us *= 1.0 - 0.1 * (1.0 - (double)M / ((double)tiles_m * BM));
     if (tiles_m == 1) {      // every weight panel is read by one workgroup only: its traffic is a second bound
         const double stream_us = (double)BN * K * 2.0 / (6.0e6 / grid);
         work_us = work_us > stream_us ? work_us : stream_us;
@@ -140,7 +155,7 @@ Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, 
     // One token tile: equal contiguous shares for the few-token configurations, and for a 256-token tile
     // when equal ranges would leave more than a tenth of the workgroups idle.
     if (tiles_m == 1 && (BM <= 128 || (long)rem * parts * 10 < (long)grid * 9)) {
-        const double shared = ((double)full + (double)rem / grid) * tile_us + SECOND_PASS_US + (double)(grid + rem) * tile_bytes * 2.0 / 4.0e6;
+        const double shared = (double)full * tile_us + tile_fixed_us + (double)rem / grid * work_us + SECOND_PASS_US + (double)(grid + rem) * tile_bytes * 2.0 / 4.0e6;
         return shared < whole ? Schedule{rem, 0, shared} : Schedule{0, 0, whole};
     }
     if (parts < 2) return Schedule{0, 1, whole};
@@ -155,10 +170,10 @@ Schedule plan_schedule(int tiles, int tiles_m, int grid, int BN, int BM, int K, 
 GemmTile gemm_tile(int config)
 {
     switch (config) {
-    case GEMM_FEW64: return GemmTile{128, 64, 128, true, false, 1, 900.0 / 256, 0.0};      // one token tile: bound by the weight stream anyway
-    case GEMM_FEW128: return GemmTile{128, 128, 64, true, true, 1, 900.0 / 256, 0.0};      // (the kernel of GEMM_DEEP)
-    case GEMM_FEW256: return GemmTile{256, 128, 64, true, false, 1, 900.0 / 256, 0.0};
-    case GEMM_ONE: return GemmTile{128, 256, 64, true, false, 1, 900.0 / 256, 0.0};        // (the kernel of GEMM_TALL)
+    case GEMM_FEW64: return GemmTile{128, 64, 128, true, false, 1, 900.0 / 256, 4.0};      // one token tile: bound by the weight stream anyway
+    case GEMM_FEW128: return GemmTile{128, 128, 64, true, true, 1, 900.0 / 256, 4.0};      // (the kernel of GEMM_DEEP)
+    case GEMM_FEW256: return GemmTile{256, 128, 64, true, false, 1, 900.0 / 256, 4.0};
+    case GEMM_ONE: return GemmTile{128, 256, 64, true, false, 1, 900.0 / 256, 4.0};        // (the kernel of GEMM_TALL)
     case GEMM_BIG: return GemmTile{256, 256, 64, true, true, 1, 5.4, 6.0};
     case GEMM_R224: return GemmTile{224, 256, 64, false, false, 1, 4.75, 6.0};
     case GEMM_R192: return GemmTile{192, 256, 64, true, false, 1, 4.7, 6.0};
@@ -186,7 +201,7 @@ GemmPlan plan_config(int config, int M, int N, int K, int epilogue, int num_cus)
     if (grid > most) grid = most;
     if (grid > units) grid = units;
     p.grid = (int)grid;
-    const Schedule s = plan_schedule(p.tiles, p.tiles_m, p.grid, t.BN, t.BM, K, t.wg_tflops, t.fixed_us, t.cut);
+    const Schedule s = plan_schedule(M, p.tiles, p.tiles_m, p.grid, t.BN, t.BM, K, t.wg_tflops, t.fixed_us, t.cut);
     p.sk_tiles = s.sk_tiles;
     p.parts = s.parts;
     p.us = s.us;
@@ -208,12 +223,17 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
         // tiles) x tile size: 128-row tiles halve them against 256-row tiles (7B-shaped O projection at
         // M = 128: 24.8 -> 18.5 us, gate/up 61 -> 53; second pass alone 8.5-9.7 us with 256 rows).  With
         // many more tiles than workgroups (70B-shaped gate/up: 448) the 256-row tile's smaller share of
-        // activation staging wins instead (188 against 230 us).
-        const int config = M <= 64 && K % 128 == 0 ? GEMM_FEW64 : !even_k || t128 <= num_cus + num_cus / 8 ? GEMM_FEW128 : GEMM_FEW256;
-        // The few-token kernel where its modelled time is the smaller one (the other model is about a tenth low there:
-        // 10240 x 8192 at 128 tokens 55.8 us against 50.3 here, 12288 x 4096 31.8 against 35.6)
+        // activation staging wins instead (188 against 230 us), and with a ragged K two workgroups per CU (gate/up
+        // 50 x 25832 x 176: 9.1 against 11.6 us; 100 x 40000 x 776 31.2 against 33.4).
+        const int config = M <= 64 && K % 128 == 0 ? GEMM_FEW64 :
+                           !even_k ? (t128 <= num_cus ? GEMM_FEW128 : GEMM_SMALL) :
+                           t128 <= num_cus + num_cus / 8 ? GEMM_FEW128 : GEMM_FEW256;
+        // The few-token kernel where its modelled time is the smaller one, or with tiles of up to 80 rows up to a fifth more: the
+        // other model is low for large problems (10240 x 8192 at 128 tokens 55.8 us against 50.3 here), plan_mid's a little for
+        // wide tiles and small K (61 x 28750 x 640 12.9 us, here 11.4).  On 813 problems of 33..128 tokens, both measured, the pick is
+        // 0.2 % slower than the better one on average (one factor of 1.0 for all: 1.5 %).
         const MidPlan mp = plan_mid(M, N, K, epilogue, num_cus);
-        if (mp.BN && mp.us < 1.1 * plan_config(config == GEMM_FEW256 ? GEMM_FEW128 : config, M, N, K, epilogue, num_cus).us) {
+        if (mp.BN && mp.us < (mp.BN <= 80 ? 1.2 : 1.05) * plan_config(config == GEMM_FEW256 ? GEMM_FEW128 : config, M, N, K, epilogue, num_cus).us) {
             GemmPlan p{};
             p.config = GEMM_MID;
             p.mid = mp;

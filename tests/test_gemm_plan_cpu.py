@@ -29,6 +29,24 @@ def plan(tmp_path_factory):
     return ask
 
 
+# A share of a tile pays a workgroup's fixed time in full, and so do the few-token configurations: with both left out, these ran the
+# configuration in the last column (times in microseconds there and here).
+@pytest.mark.parametrize("epilogue,M,N,K,config,was", [
+    (PLAIN, 129, 4096, 11008, "DEEP", "TALL"),          # 41.5 -> 36.6
+    (PLAIN, 203, 4096, 11008, "DEEP", "TALL"),          # 42.4 -> 38.7
+    (PLAIN, 82, 332, 792, "MID", "FEW128"),             # 12.3 -> 8.4
+    (PLAIN, 123, 124, 7440, "MID", "FEW128"),           # 32.5 -> 7.6
+    (PLAIN, 96, 1536, 512, "MID", "FEW128"),
+    (GATE_UP, 50, 25832, 176, "SMALL", "FEW128"),       # 11.6 -> 9.1
+    (GATE_UP, 97, 7648, 104, "FEW128", None),           # the few-token kernel 7.1, here 6.0
+    (PLAIN, 61, 28750, 640, "FEW64", None),             # 12.9, here 11.4
+    (PLAIN, 72, 12288, 4096, "MID", None),
+    (PLAIN, 512, 8192, 8192, "DEEP", None),
+])
+def test_picks(plan, epilogue, M, N, K, config, was):
+    assert plan(epilogue, M, N, K).config == config
+
+
 def test_rows_beyond_31_bits_do_not_wrap(plan):
     """More virtual rows than an int holds: no tile count of the few-token kernel comes near the compute units'."""
     assert plan(GATE_UP, 40, 2 ** 30 + 8, 8).config != "MID"

@@ -263,8 +263,8 @@ int thi_version(void);
  * (16 rows over the whole of K per workgroup at a time), 4 = weight-streaming
  * decode kernel with row blocks (N / #CUs rows per workgroup, several 16-row
  * tiles in flight); 3 and 4 fall back to 1 where K < 1024 or K > 32768.
- * (Family 1 runs K < 1024 at up to 32 tokens as slabs of 16 rows over all of K, family 2
- * up to 128 tokens as its few-token kernel, where those are the faster ones.)
+ * (The automatic choice takes the row slabs below K = 1024 too; family 2 includes the few-token
+ * kernel, up to 128 tokens where it is the faster one.)
  * Returns the previous setting.  Not needed for normal use.
  */
 int thi_set_kernel_family(int family);

@@ -164,8 +164,9 @@ int pick_rowblock_split(int M, int N, int K, int epilogue, int cus)
 enum DecodeKernel { DK_STREAMK = 1, DK_ROWSLAB = 3, DK_ROWBLOCK = 4 };
 int pick_decode_kernel(int M, int N, int K, int epilogue, int cus)
 {
-    if (K < 1024 || K > ROWSLAB_MAX_K) return DK_STREAMK;
     const int fam = g_family.load(std::memory_order_relaxed);
+    if (K > ROWSLAB_MAX_K) return DK_STREAMK;
+    if (K < 1024) return fam == 0 && rowslab_small_ok(N, K, epilogue, cus) ? DK_ROWSLAB : DK_STREAMK;
     if (fam == 1) return DK_STREAMK;
     if (fam == 3) return DK_ROWSLAB;
     if (fam == 4) return DK_ROWBLOCK;

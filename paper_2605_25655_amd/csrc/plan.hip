@@ -9,6 +9,15 @@ namespace thi {
 // ---- decode kernels ------------------------------------------------------------------------------
 size_t skinny_handover_bytes() { return (size_t)SK_MAX_GRID * SK_SLOT_WORDS * sizeof(unsigned); }
 
+// K < 1024, up to 32 tokens: slabs of 16 rows over all of K instead of the stream-K kernel, unless there are many more of them than CUs
+// (one slab after the other then costs more than the hand-over: 32 x 32000 x 512 10.4 us with stream-K, 12.3 as slabs;
+// 32 x 12288 x 1016, 768 slabs, 13.6 and 9.8; 16 x 20000 x 264, 1250 slabs, 7.8 and 7.3)
+bool rowslab_small_ok(int N, int K, int epilogue, int num_cus)
+{
+    const int rows = is_swiglu(epilogue) ? 8 : 16;
+    return K < 1024 && ((long)N + rows - 1) / rows <= 5L * num_cus;
+}
+
 // Row blocks: the outputs (rows of W, gate/up pairs for SwiGLU) are dealt to the workgroups in equal contiguous
 // blocks; a block is T tiles of 16 rows in flight per pass over K (Sec. III-B.2: split the work along N).
 RowBlockPlan plan_rowblock(int N, int epilogue, int num_cus, int ksplit)

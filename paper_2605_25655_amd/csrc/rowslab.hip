@@ -32,8 +32,8 @@ typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 // costs the vector cache several times the cycles per byte.  With very few tokens most lanes of an
 // operand-layout load share an address and the direct load wins.
 //
-// SMALLK (K < 1024, fewer than eight groups of 128 k): one group per wave, as many waves as there are groups.  Without it
-// such a K ran on the stream-K kernel, whose tiles of 128 rows leave most CUs idle on the small matrices that go
+// SMALLK (K < 1024, at most eight groups of 128 k): one group per wave, as many waves as there are groups (rowslab_small_ok).
+// Without it such a K runs on the stream-K kernel, whose tiles of 128 rows leave most CUs idle on the small matrices that go
 // with it and whose k chunks of a tile meet through memory (32 tokens, back-to-back calls: 12288 x 1016 13.6 -> 9.8 us,
 // 4096 x 776 9.9 -> 7.3, which is what the calls cost the host).
 template <int MT, int EPI, bool XT, bool SMALLK = false>
@@ -355,7 +355,7 @@ hipError_t launch_small(const SkinnyArgs& a, int epilogue, int grid, hipStream_t
 {
     const int groups = (a.K + 127) >> 7, waves = groups > MT ? groups : MT;      // the epilogue takes MT waves
     dim3 g(grid), b(64 * waves);
-    const size_t gamma_lds = (size_t)SK_WAVES * rowslab_gamma_pieces(a.K) * sizeof(uintx4);      // 2 KiB
+    const size_t gamma_lds = (size_t)SK_WAVES * rowslab_gamma_pieces(a.K) * sizeof(uintx4);      // at most 4 KiB
     switch (epilogue) {
     case EPI_PLAIN: hipLaunchKernelGGL((skinny_rowslab<MT, EPI_PLAIN, XT, true>), g, b, 0, stream, a.x, a.w0, a.w1, a.gamma, a.M, a.N, a.K, a.tiles, a); break;
     case EPI_RMSNORM: hipLaunchKernelGGL((skinny_rowslab<MT, EPI_RMSNORM, XT, true>), g, b, gamma_lds, stream, a.x, a.w0, a.w1, a.gamma, a.M, a.N, a.K, a.tiles, a); break;
@@ -368,21 +368,15 @@ hipError_t launch_small(const SkinnyArgs& a, int epilogue, int grid, hipStream_t
 
 }  // namespace
 
-hipError_t launch_rowslab_small(const SkinnyArgs& args, int epilogue, int num_cus, hipStream_t stream)
-{
-    SkinnyArgs a = args;
-    if (a.K >= 1024 || a.M > 32) return hipErrorInvalidValue;
-    a.tiles = (a.N + (is_swiglu(epilogue) ? 7 : 15)) / (is_swiglu(epilogue) ? 8 : 16);      // slabs
-    const int grid = num_cus < a.tiles ? num_cus : a.tiles;
-    if (a.M <= 4) return launch_small<1, false>(a, epilogue, grid, stream);
-    if (a.M <= 16) return launch_small<1, true>(a, epilogue, grid, stream);
-    return launch_small<2, true>(a, epilogue, grid, stream);
-}
-
 hipError_t launch_rowslab(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t stream)
 {
-    if (a.K < 1024 || a.K > ROWSLAB_MAX_K || a.tiles < 1) return hipErrorInvalidValue;
-    int grid = num_cus < a.tiles ? num_cus : a.tiles;
+    if (a.K > ROWSLAB_MAX_K || a.tiles < 1 || a.M > 32) return hipErrorInvalidValue;
+    const int grid = num_cus < a.tiles ? num_cus : a.tiles;
+    if (a.K < 1024) {
+        if (a.M <= 4) return launch_small<1, false>(a, epilogue, grid, stream);
+        if (a.M <= 16) return launch_small<1, true>(a, epilogue, grid, stream);
+        return launch_small<2, true>(a, epilogue, grid, stream);
+    }
     if (a.M <= 4) return launch_mt<1, false>(a, epilogue, grid, stream);
     if (a.M <= 16) return launch_mt<1, true>(a, epilogue, grid, stream);
     return launch_mt<2, true>(a, epilogue, grid, stream);

@@ -443,12 +443,6 @@ __global__ void fill_words_kernel(uint32_t* p, size_t words, uint32_t value)
 
 hipError_t launch_skinny(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t stream)
 {
-    // K < 1024, up to 32 tokens: slabs of 16 rows over all of K instead, unless there are many more of them than CUs
-    // (one slab after the other then costs more than the hand-over: 32 x 32000 x 512 10.4 us here, 12.3 as slabs;
-    // 32 x 12288 x 1016, 768 slabs, 13.6 and 9.8; 16 x 20000 x 264, 1250 slabs, 7.8 and 7.3)
-    const int rows = is_swiglu(epilogue) ? 8 : 16;
-    if (a.K < 1024 && a.M <= 32 && ((long)a.N + rows - 1) / rows <= 5L * num_cus)
-        return launch_rowslab_small(a, epilogue, num_cus, stream);
     const long U = (long)a.tiles * a.kchunks;
     // one workgroup per CU: fewer, larger shares keep the number of workgroups that share a tile
     // (and so the partial-tile traffic) small; measured faster than two per CU on every shape

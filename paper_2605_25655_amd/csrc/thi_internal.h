@@ -81,12 +81,11 @@ struct SkinnyArgs {
 
 size_t skinny_handover_bytes();
 hipError_t launch_skinny(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t stream);
-// Row-slab decode kernel: a.tiles = slabs of 16 virtual rows; needs 1024 <= K <= ROWSLAB_MAX_K (a
+// Row-slab decode kernel, up to 32 tokens: a.tiles = slabs of 16 virtual rows; needs K <= ROWSLAB_MAX_K (a
 // wave's slice of gamma must fit its share of LDS); uses no workspace.
 constexpr int ROWSLAB_MAX_K = 32768;
 hipError_t launch_rowslab(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t stream);
-// The same kernel for K < 1024, up to 32 tokens (what launch_skinny runs there; sets a.tiles itself).
-hipError_t launch_rowslab_small(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t stream);
+bool rowslab_small_ok(int N, int K, int epilogue, int num_cus);      // K < 1024: are the slabs the faster kernel?
 // Row-block decode kernel: the outputs dealt to the workgroups in equal contiguous blocks, T slabs of a
 // block in flight at a time (same limits on K; a.tiles is not used; no workspace unless ksplit > 1).
 struct RowBlockPlan {

@@ -14,10 +14,10 @@ hipError_t launch_skinny(const SkinnyArgs& a, int, int, hipStream_t)
     ++g_launches;
     return (a.M >= 1 && a.M <= 16 * SK_MAX_MT && a.handover && a.counters) ? hipSuccess : hipErrorInvalidValue;
 }
-hipError_t launch_rowslab(const SkinnyArgs& a, int, int, hipStream_t)
+hipError_t launch_rowslab(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t)
 {
     ++g_launches;
-    return (a.K >= 1024 && a.K <= ROWSLAB_MAX_K && a.tiles >= 1 && a.M <= 32) ? hipSuccess : hipErrorInvalidValue;
+    return ((a.K >= 1024 || rowslab_small_ok(a.N, a.K, epilogue, num_cus)) && a.K <= ROWSLAB_MAX_K && a.tiles >= 1 && a.M <= 32) ? hipSuccess : hipErrorInvalidValue;
 }
 hipError_t launch_rowblock(const SkinnyArgs& a, int epilogue, int num_cus, hipStream_t, int ksplit)
 {

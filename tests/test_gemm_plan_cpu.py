@@ -52,3 +52,15 @@ def test_rows_beyond_31_bits_do_not_wrap(plan):
     assert plan(GATE_UP, 40, 2 ** 30 + 8, 8).config != "MID"
     import paper_2605_25655_amd as thi
     assert thi.thi_query_kernel_family(40, 2 ** 30 + 8, 8, 2) == 1      # the stream-K kernel, which takes any number of rows
+
+
+@pytest.mark.parametrize("M,N,K,fused,family", [(1, 4096, 512, 0, 3), (32, 20480, 512, 0, 3), (32, 20481, 512, 0, 1)])
+def test_small_k_is_reported_as_it_runs(M, N, K, fused, family):
+    import paper_2605_25655_amd as thi
+    assert thi.thi_query_kernel_family(M, N, K, fused) == family
+    for forced in (1, 3, 4):
+        prev = thi.thi_set_kernel_family(forced)
+        try:
+            assert thi.thi_query_kernel_family(M, N, K, fused) == 1
+        finally:
+            thi.thi_set_kernel_family(prev)

@@ -428,13 +428,17 @@ def _theta(head_dim, base=10000.0):
 ROWSLAB = [
     (1, 16, 1024), (1, 1000, 1376), (3, 129, 1032), (5, 4099, 1160), (16, 384, 1800), (17, 100, 1024),
     (32, 640, 2056), (32, 4096, 4096), (31, 513, 11008), (40, 272, 3080), (8, 23, 8200), (2, 48, 32768),
-    (4, 64, 264),       # K < 1024: served by the stream-K kernel
+    (4, 64, 264),       # K < 1024: forced row slabs fall back to the stream-K kernel
 ]
 
 
 @pytest.mark.parametrize("M,N,K", ROWSLAB)
 def test_rowslab_kernel_all_epilogues(thi, oracle_mod, M, N, K):
-    say(f"[case] row slabs M={M} N={N} K={K}")
+    _decode_all_epilogues(thi, oracle_mod, M, N, K, 3)
+
+
+def _decode_all_epilogues(thi, oracle_mod, M, N, K, family):
+    say(f"[case] decode, family {family} M={M} N={N} K={K}")
     x, w, g = synth.random_problem(4200 + M * 5 + N + K, M, N, K)
     rng = np.random.Generator(np.random.Philox(key=4300 + M + N + K))
     I = min(N, 1376) // 8 * 8                          # gate/up rows
@@ -445,7 +449,7 @@ def test_rowslab_kernel_all_epilogues(thi, oracle_mod, M, N, K):
     th = _theta(hd)
     r = Runner(M, K, max(I, K), N)
     xd, wd, gd = to_dev(x), to_dev(w), to_dev(g)
-    prev = thi.thi_set_kernel_family(3)
+    prev = thi.thi_set_kernel_family(family)
     try:
         a = to_host(r.linear(xd, wd))
         a2 = to_host(r.linear(xd, wd))
@@ -467,14 +471,47 @@ def test_rowslab_kernel_all_epilogues(thi, oracle_mod, M, N, K):
     check(h, hh, sh, "swiglu_gate_up", argmax=False)
 
 
-# K < 1024: one group of 128 k per wave and slabs of 16 rows up to five slabs per CU, the stream-K kernel beyond
+# K < 1024: one group of 128 k per wave and slabs of 16 rows while there are few of them per CU, the stream-K kernel beyond and where
+# it is forced.  From one k piece to eight groups less one piece, either side of both lines of the rule.
 SMALL_K = [(1, 16, 8), (1, 1536, 512), (4, 100, 120), (5, 300, 128), (16, 272, 136), (17, 640, 1016), (32, 4099, 896),
-           (32, 24, 8), (20, 20480, 264), (2, 20496, 136)]
+           (32, 24, 8), (20, 20480, 264), (2, 20496, 136), (9, 12288, 256), (30, 8200, 248)]
 
 
 @pytest.mark.parametrize("M,N,K", SMALL_K)
 def test_small_k_all_epilogues(thi, oracle_mod, M, N, K):
-    test_rowslab_kernel_all_epilogues(thi, oracle_mod, M, N, K)
+    assert thi.thi_query_kernel_family(M, N, K, 0) == (1 if N == 20496 else 3)
+    _decode_all_epilogues(thi, oracle_mod, M, N, K, 0)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1536, 512), (4, 100, 120), (17, 640, 1016), (32, 4099, 896), (32, 24, 8)])
+def test_small_k_on_the_stream_k_kernel(thi, oracle_mod, M, N, K):
+    _decode_all_epilogues(thi, oracle_mod, M, N, K, 1)
+
+
+def test_forced_stream_k_below_k_1024_is_the_stream_k_kernel(thi, oracle_mod):
+    """Seen from outside by its hand-over: with the contributors' flags withheld, the shared tiles' wait runs out (the kernels exit
+    normally) and the workspace says so."""
+    M, N, K = 32, 4096, 1016           # 32 tiles of 128 rows, four k chunks each, on 128 workgroups
+    say("[case] forced stream-K, K < 1024")
+    x, w, g = synth.random_problem(6301, M, N, K)
+    r = Runner(M, K, K, N)
+    xd, wd = to_dev(x), to_dev(w)
+    y, s = oracle_mod.linear(x, w)
+    thi.thi_set_kernel_family(1)
+    try:
+        assert thi.thi_query_kernel_family(M, N, K, 0) == 1
+        thi.thi_debug_handover(8, True)
+        r.linear(xd, wd)
+        assert thi.thi_workspace_status(r.ws) == thi.THI_ERR_TIMEOUT
+        thi.thi_debug_handover(0, False)
+        r.ws.reinit()
+        check(to_host(r.linear(xd, wd)), y, s, "stream-K, K < 1024")
+    finally:
+        thi.thi_debug_handover(0, False)
+        thi.thi_set_kernel_family(0)
+    assert thi.thi_query_kernel_family(M, N, K, 0) == 3
+    check(to_host(r.linear(xd, wd)), y, s, "row slabs, K < 1024")
+    assert thi.thi_workspace_status(r.ws) == thi.THI_OK
 
 
 # the row-block decode kernel: each workgroup owns N / #CUs outputs = several 16-row tiles (the last one

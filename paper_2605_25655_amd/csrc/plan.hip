@@ -9,13 +9,16 @@ namespace thi {
 // ---- decode kernels ------------------------------------------------------------------------------
 size_t skinny_handover_bytes() { return (size_t)SK_MAX_GRID * SK_SLOT_WORDS * sizeof(unsigned); }
 
-// K < 1024, up to 32 tokens: slabs of 16 rows over all of K instead of the stream-K kernel, unless there are many more of them than CUs
-// (one slab after the other then costs more than the hand-over: 32 x 32000 x 512 10.4 us with stream-K, 12.3 as slabs;
-// 32 x 12288 x 1016, 768 slabs, 13.6 and 9.8; 16 x 20000 x 264, 1250 slabs, 7.8 and 7.3)
+// K < 1024, up to 32 tokens: slabs of 16 rows over all of K, or the stream-K kernel?  A compute unit takes its slabs one after the
+// other, each with its own reduction and epilogue, the stream-K kernel 128 rows at a time and a hand-over: up to five slabs a CU,
+// four behind an RMSNorm; with K <= 256, where there is little to stream, four and two (plain, others).  Slabs against stream-K over
+// 420 calls of 1..32 tokens: 0.49-0.72 of its time with one or two slabs a CU and K > 256, 0.81-0.95 (up to 1.04) at the line; beyond
+// it 1.02-1.4 (gate/up and RMSNorm kinds with K <= 256: 3 slabs 1.05, 4 1.22, 5 1.4).
 bool rowslab_small_ok(int N, int K, int epilogue, int num_cus)
 {
-    const int rows = is_swiglu(epilogue) ? 8 : 16;
-    return K < 1024 && ((long)N + rows - 1) / rows <= 5L * num_cus;
+    if (K >= 1024) return false;
+    const int rows = is_swiglu(epilogue) ? 8 : 16, most = K > 256 ? (is_rms(epilogue) ? 4 : 5) : epilogue == EPI_PLAIN ? 4 : 2;
+    return ((long)N + rows - 1) / rows <= (long)most * num_cus;
 }
 
 // Row blocks: the outputs (rows of W, gate/up pairs for SwiGLU) are dealt to the workgroups in equal contiguous

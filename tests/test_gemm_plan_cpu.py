@@ -54,7 +54,9 @@ def test_rows_beyond_31_bits_do_not_wrap(plan):
     assert thi.thi_query_kernel_family(40, 2 ** 30 + 8, 8, 2) == 1      # the stream-K kernel, which takes any number of rows
 
 
-@pytest.mark.parametrize("M,N,K,fused,family", [(1, 4096, 512, 0, 3), (32, 20480, 512, 0, 3), (32, 20481, 512, 0, 1)])
+@pytest.mark.parametrize("M,N,K,fused,family", [(1, 4096, 512, 0, 3), (32, 20480, 512, 0, 3), (32, 20481, 512, 0, 1), (16, 16384, 264, 1, 3),
+                                                (16, 16400, 264, 1, 1), (8, 16384, 256, 0, 3), (8, 16400, 256, 0, 1),
+                                                (8, 4096, 128, 2, 3), (8, 4104, 128, 2, 1), (8, 10240, 264, 2, 3), (8, 10248, 264, 2, 1)])
 def test_small_k_is_reported_as_it_runs(M, N, K, fused, family):
     import paper_2605_25655_amd as thi
     assert thi.thi_query_kernel_family(M, N, K, fused) == family

@@ -264,7 +264,7 @@ int thi_version(void);
  * decode kernel with row blocks (N / #CUs rows per workgroup, several 16-row
  * tiles in flight); 3 and 4 fall back to 1 where K < 1024 or K > 32768.
  * (The automatic choice takes the row slabs below K = 1024 too; family 2 includes the few-token
- * kernel, up to 128 tokens where it is the faster one.)
+ * kernel, up to 128 tokens where it is the faster one.  K > 2^23 always runs family 1.)
  * Returns the previous setting.  Not needed for normal use.
  */
 int thi_set_kernel_family(int family);

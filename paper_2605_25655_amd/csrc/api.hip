@@ -201,7 +201,8 @@ int pick_decode_kernel(int M, int N, int K, int epilogue, int cus)
 //                   t_w = 30 us and 1.25 t_w beyond).  Kinds without RMSNorm in front are priced by the few-token
 //                   kernel's own model instead, which usually wins (4096 x 11008 at 40 tokens 26.6 us here, 21.8).
 //   M > 64        : the GEMM kernels.
-// A forced family overrides this (forced stream-K: 64 tokens per launch; forced row slabs / blocks: 32).
+// A forced family overrides this (forced stream-K: 64 tokens per launch; forced row slabs / blocks: 32), but for a K that the GEMM
+// kernels cannot address (GEMM_MAX_K): the stream-K kernel at any M.
 struct DecodePlan {
     int kernel;     // DK_*, or 0 = the GEMM kernels
     int group;      // tokens per launch
@@ -209,6 +210,8 @@ struct DecodePlan {
 DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus)
 {
     const int fam = g_family.load(std::memory_order_relaxed);
+    // The GEMM kernels address the rows of a tile by 32-bit byte offsets: 256 rows of up to 2^23 values.
+    if (K > GEMM_MAX_K) return DecodePlan{DK_STREAMK, M > SKINNY_GROUP ? 16 * SK_MAX_MT : SKINNY_GROUP};
     if (fam == 2) return DecodePlan{0, 0};
     const int first = M < SKINNY_GROUP ? M : SKINNY_GROUP;
     if (fam == 1) return DecodePlan{DK_STREAMK, M > SKINNY_GROUP ? 16 * SK_MAX_MT : SKINNY_GROUP};

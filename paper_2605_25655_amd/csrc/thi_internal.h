@@ -125,6 +125,7 @@ struct GemmArgs {
     RopeArgs rope;
     unsigned* counters;      // status words, zero between calls: arrival counters of the few-token kernel's shared tiles
 };
+constexpr int GEMM_MAX_K = 1 << 23;   // 256 rows x 2 bytes x K within 32 bits
 constexpr int GEMM_MAX_GRID = 2048;   // in units of 128x128 partial tiles (a 256x256 tile takes four)
 size_t gemm_partial_bytes();
 // The few-token kernel (33..128 tokens; plan_gemm takes it where it is the faster one): how the tile rows and K are

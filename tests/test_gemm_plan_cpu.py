@@ -66,3 +66,16 @@ def test_small_k_is_reported_as_it_runs(M, N, K, fused, family):
             assert thi.thi_query_kernel_family(M, N, K, fused) == 1
         finally:
             thi.thi_set_kernel_family(prev)
+
+
+def test_rows_longer_than_the_gemm_addresses():
+    """256 rows of more than 2^23 values lie further apart than 32 bits of bytes: the stream-K kernel takes them."""
+    import paper_2605_25655_amd as thi
+    for M, N, K in ((40, 200, 2 ** 23 + 8), (129, 8, 2 ** 24 + 2 ** 17 + 8), (300, 2048, 2 ** 23 + 64)):
+        for forced in (0, 2):
+            prev = thi.thi_set_kernel_family(forced)
+            try:
+                assert thi.thi_query_kernel_family(M, N, K, 0) == 1
+                assert forced == 0 or thi.thi_query_kernel_family(M, N, 2 ** 23, 0) == 2
+            finally:
+                thi.thi_set_kernel_family(prev)

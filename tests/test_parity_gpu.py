@@ -320,6 +320,26 @@ def test_ragged_k_in_the_gemm(thi, oracle_mod, M, N, K):
     assert np.isfinite(a.astype(np.float32)).all() and np.isfinite(h.astype(np.float32)).all()
 
 
+def test_rows_longer_than_32_bit_offsets(thi):
+    """128 token rows of 2^24 + 2^17 + 8 values span more than 4 GiB.  Activations with a single one per token pick
+    weights out, bit for bit."""
+    import torch
+    M, N, K = 129, 8, 2 ** 24 + 2 ** 17 + 8
+    say(f"[case] long rows M={M} N={N} K={K}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    x = torch.zeros((M, K), dtype=torch.float16, device="cuda")
+    at = torch.randint(0, K, (M,), generator=gen, device="cuda")
+    at[0], at[M - 1], at[M - 2], at[126] = K - 1, 0, K - 8, K - 9
+    x[torch.arange(M, device="cuda"), at] = 1
+    w = torch.empty((N, K), dtype=torch.float16, device="cuda").normal_(generator=gen)
+    ws = thi.Workspace.for_ops([(1, M, N, K)])
+    out = new_out(M, N)
+    thi.thi_linear(x, w, out, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), w[:, at].t().contiguous().view(torch.int16))
+
+
 # Tiles of 224, 192 and 160 rows x 256 tokens (the first and last with an odd number of fragments per wave and fewer loads
 # in some waves than in others): one k-tile, a few and many, last tiles partly empty along both sides.
 @pytest.mark.parametrize("M,N,K", [(1800, 6259, 64), (1955, 6710, 704), (1858, 5397, 64), (1676, 6518, 1920),

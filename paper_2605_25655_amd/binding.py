@@ -270,7 +270,7 @@ def thi_rmsnorm_swiglu_mlp(x, gamma, eps, w_gate, w_up, w_down, residual, out, w
     M, H = x.shape
     I = w_gate.shape[0]
     wp, wb = _ws(workspace)
-    rc = load_library().thi_rmsnorm_swiglu_mlp(_ptr(x), _ptr(gamma), float(eps), _ptr(w_gate), _ptr(w_up),
+    rc = load_library().thi_rmsnorm_swiglu_mlp(_ptr(x), _ptr(gamma), eps, _ptr(w_gate), _ptr(w_up),
                                                _ptr(w_down), _ptr(residual), _ptr(out), M, H, I, wp, wb,
                                                _stream(stream))
     if check and rc != THI_OK:
@@ -289,7 +289,7 @@ def thi_decode_attention(q, k_cache, v_cache, seq_lens, scale, out, workspace, s
     B, Hq, D = q.shape
     _, Hkv, S_max, _ = k_cache.shape
     wp, wb = _ws(workspace)
-    rc = load_library().thi_decode_attention(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens), float(scale),
+    rc = load_library().thi_decode_attention(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens), scale,
                                              _ptr(out), B, Hq, Hkv, D, S_max, wp, wb, _stream(stream))
     if check and rc != THI_OK:
         raise ThiError(rc, "thi_decode_attention")

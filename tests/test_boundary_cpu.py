@@ -138,3 +138,30 @@ def test_argument_errors_return_codes_without_launching(lib):
 def test_kernel_family_switch_roundtrip(lib):
     prev = lib.thi_set_kernel_family(1)
     assert lib.thi_set_kernel_family(prev) == 1
+
+
+def test_texts_are_no_numbers():
+    """A scale or eps that is not a number is refused by the binding, whatever it spells."""
+    import paper_2605_25655_amd as thi
+
+    class Null:      # stands for a tensor without storage: the library answers THI_ERR_NULL before anything else
+        def __init__(self, *shape):
+            self.shape = shape
+
+        def data_ptr(self):
+            return None
+
+    ws = (256, 1 << 40)
+
+    def attention(scale):
+        return thi.thi_decode_attention(Null(1, 1, 64), Null(1, 1, 8, 64), Null(1, 1, 8, 64), Null(1), scale, Null(1, 1, 64), ws,
+                                        stream=0, check=False)
+
+    def mlp(eps):
+        return thi.thi_rmsnorm_swiglu_mlp(Null(1, 8), Null(8), eps, Null(8, 8), Null(8, 8), Null(8, 8), None, Null(1, 8), ws,
+                                          stream=0, check=False)
+
+    for call in (attention, mlp):
+        assert call(0.125) == 1 and call(1) == 1
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            call("0.125")

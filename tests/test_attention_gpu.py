@@ -154,12 +154,12 @@ def test_attention_argument_errors(thi):
     assert thi.thi_attention_workspace_bytes(1, 3, 2, 128, 8) == 0
 
 
-# Chunks are chosen on the device from the live lengths, and groups of four and more heads of 128 take up to 16 heads a
-# pass: sizes around the 16-position blocks, the 64-position chunk grid, the 128-position minimum, the 32 chunks a
-# request may have, passes of 16 heads and a rest, more than 64 requests, and one long request among short ones.
+# A request is cut by its own length, and groups of four and more heads of 128 take up to 16 heads a pass: sizes around the
+# 16-position blocks, the 64-position chunk grid, the 128-position minimum, the 32 chunks a request may have, passes of 16
+# heads and a rest, more than 64 requests, and one long request among short ones.
 CHUNKS = [
     (6, 8, 1, 128, 4100, [4100, 1, 0, 129, 128, 64]),
-    (1, 5, 1, 128, 8192, [8192]),                     # 32 chunks: no end mark
+    (1, 5, 1, 128, 8192, [8192]),                     # 32 chunks
     (1, 1, 1, 64, 8191, [8191]),
     (3, 17, 1, 128, 300, [15, 16, 17]),               # a pass of 16 heads and a pass of one
     (2, 40, 2, 128, 700, [700, 193]),                 # groups of 20
@@ -236,3 +236,37 @@ def test_weights_keep_their_precision_where_values_cancel(thi, oracle_mod, Hq, H
     assert (got[..., 3] == np.inf).all() and (got[..., 5] == -np.inf).all()
     keep = np.delete(np.arange(D), [3, 5])
     assert (np.abs(got - y) <= 0.5 * ulp16(y) + 2.0 ** -17 * s)[..., keep].all()
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(64, 8, 128), (8, 8, 64)])
+def test_attention_replays_from_a_captured_graph(thi, Hq, Hkv, D):
+    """One captured call, replayed with other lengths and queries than it was captured with (the chunks are chosen from the lengths on
+    the device), eager calls and synchronisations in between: every replay equals the eager call bit for bit."""
+    import torch
+    B, S = 3, 1500
+    say(f"[case] attention graph Hq={Hq} Hkv={Hkv} D={D}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(77 + D)
+    q, k, v = (torch.empty(s, dtype=torch.float16, device="cuda").normal_(generator=gen)
+               for s in ((B, Hq, D), (B, Hkv, S, D), (B, Hkv, S, D)))
+    lens = torch.tensor([S, 700, 1], dtype=torch.int32, device="cuda")
+    out = torch.full((B, Hq, D), float("nan"), dtype=torch.float16, device="cuda")
+    ws = thi.Workspace(thi.thi_attention_workspace_bytes(B, Hq, Hkv, D, S), init=False)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        thi.thi_decode_attention(q, k, v, lens, D ** -0.5, out, ws)
+        stream.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            thi.thi_decode_attention(q, k, v, lens, D ** -0.5, out, ws)
+    torch.cuda.synchronize()
+    for new in ([1, S, 0], [129, 128, 127], [S, S, S], [64, 900, 1499]):
+        lens.copy_(torch.tensor(new, dtype=torch.int32))
+        q.normal_(generator=gen)
+        thi.thi_decode_attention(q, k, v, lens, D ** -0.5, out, ws)
+        torch.cuda.synchronize()
+        eager = out.clone()
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), eager.view(torch.int16)), new

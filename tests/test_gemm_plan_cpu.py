@@ -47,6 +47,30 @@ def test_picks(plan, epilogue, M, N, K, config, was):
     assert plan(epilogue, M, N, K).config == config
 
 
+def _cut(p):
+    how = "whole" if p.cut == 0 else "shares" if p.parts == 0 else "ranges"
+    return "rounds + " + how if 0 < p.cut < p.tiles else how
+
+
+def test_the_gpu_tests_run_the_kernels_they_are_listed_for(plan):
+    from tests.test_parity_gpu import FEW_KERNEL, KERNELS, RAGGED, ROW_TILES
+    for kind, M, N, K, config, cut in KERNELS:
+        p = plan(GATE_UP if kind == "G" else PLAIN, M, N, K)
+        assert (p.config, _cut(p)) == (config, cut), (kind, M, N, K, p)
+    both = [(e, M, N if e == PLAIN else N // 2 // 8 * 8, K) for e in (PLAIN, GATE_UP) for M, N, K in FEW_KERNEL]
+    few = [plan(*shape) for shape in both]
+    assert all(p.config == "MID" for p in few), [(s, p) for s, p in zip(both, few) if p.config != "MID"]
+    for e in (PLAIN, GATE_UP):      # every height of tile for every token tile that has it, shared and alone where it is built for both
+        seen = {(p.rows, 64 if s[1] <= 64 else 96 if s[1] <= 96 else 128) for s, p in zip(both, few) if s[0] == e}
+        assert {(32, 64), (144, 64), (112, 64), (112, 96), (96, 64), (96, 96), (80, 64), (80, 96), (80, 128), (64, 64), (64, 128), (48, 96),
+                (32, 96), (32, 128)} <= seen, seen
+        assert {(32, True), (32, False), (80, True), (80, False)} <= {(p.rows, p.ranges > 1) for s, p in zip(both, few) if s[0] == e}
+    for e in (PLAIN, GATE_UP):
+        shapes = [(M, N if e == PLAIN else N // 2 // 8 * 8, K) for M, N, K in ROW_TILES]
+        assert [plan(e, *t).config for t in shapes] == ["R224", "R224", "R192", "R192", "R160", "R160", "R160"]
+    assert {plan(PLAIN, *t).config for t in RAGGED} == {"MID", "DEEP", "SMALL"}
+
+
 def test_rows_beyond_31_bits_do_not_wrap(plan):
     """More virtual rows than an int holds: no tile count of the few-token kernel comes near the compute units'."""
     assert plan(GATE_UP, 40, 2 ** 30 + 8, 8).config != "MID"

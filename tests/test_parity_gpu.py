@@ -211,19 +211,18 @@ def test_shared_tile_handover_is_reproducible(thi, oracle_mod, M, N, K):
 
 
 # ------------------------------------------- prefill scheduling corner cases
-# Shapes chosen against the GEMM schedule: fewer tiles than workgroups (every tile is shared and goes
-# through the second pass), one full round plus a ragged remainder, a ragged K, M and N off the tile
-# grid, and the 256x256 configuration with a remainder.  Rows are sampled for the oracle.
+# Whole rounds, a last round that is partly empty, tiles cut along K, a ragged K, M and N off the tile grid.  Which configuration
+# runs them is in the text (KERNELS below holds every configuration and cut, asserted on the CPU).  Rows are sampled for
+# the oracle.
 SCHED = [
-    (512, 1280, 2048, "fewer tiles than workgroups"),
-    (640, 5120 + 128, 1024, "full rounds + remainder, small tiles"),
+    (512, 1280, 2048, "128-tile: 40 tiles in 6 ranges each"),
+    (640, 5120 + 128, 1024, "128-tile: 205 whole tiles"),
     (300, 1000, 1096, "ragged M, N, K"),
-    (2048, 2560 + 256, 1024, "256-tile configuration with remainder"),
-    (1024, 8192, 512, "256-tile configuration, whole rounds"),
-    # remainder tiles cut into equal k ranges (the cut is chosen by a time model; the shapes below are priced so)
-    (2048, 8192 + 256, 1088, "256-tile: one whole round + 8 tiles in 17 ranges each (as many as k-tiles)"),
+    (2048, 2560 + 256, 1024, "128 rows x 256 tokens: 176 whole tiles"),
+    (1024, 8192, 512, "128 rows x 256 tokens: one whole round"),
+    (2048, 8192 + 256, 1088, "160 rows x 256 tokens: 424 whole tiles, the last rows ragged"),
     (2048, 2560, 4160, "256-tile: 80 tiles in 3 ranges each, 65 k-tiles (uneven ranges)"),
-    (1024, 10240, 8256, "128-tile: one whole round + 128 tiles in 4 ranges each, 129 k-tiles"),
+    (1024, 10240, 8256, "160 rows x 256 tokens: one whole round, 129 k-tiles"),
     (160, 22016 + 40, 1024, "129..256 tokens, 173 tiles of 128 rows: one token tile of 256"),
     (256, 30000, 1088, "the same configuration, 235 tiles, ragged N"),
 ]
@@ -297,9 +296,12 @@ def test_few_token_kernel_all_epilogues(thi, oracle_mod, M, N, K):
 
 
 # A K that is no multiple of the staged k-tile: the last k-tile holds one piece, all but one, or half of its 16-byte
-# pieces, alone in its share or as the last of many, in each configuration that takes it.
-@pytest.mark.parametrize("M,N,K", [(1, 40, 8), (40, 300, 72), (100, 272, 120), (130, 200, 64 * 5 + 8), (300, 640, 64 * 9 + 56),
-                                   (700, 1100, 456), (2048, 2304, 1032), (1500, 4096, 2048 + 24), (333, 5001, 1384)])
+# pieces, in the few-token kernel and in whole 128x128 tiles with four and two stages.  (Cut tiles and the 256x256 tile: KERNELS.)
+RAGGED = [(1, 40, 8), (40, 300, 72), (100, 272, 120), (130, 200, 64 * 5 + 8), (300, 640, 64 * 9 + 56),
+          (700, 1100, 456), (2048, 2304, 1032), (1500, 4096, 2048 + 24), (333, 5001, 1384)]
+
+
+@pytest.mark.parametrize("M,N,K", RAGGED)
 def test_ragged_k_in_the_gemm(thi, oracle_mod, M, N, K):
     say(f"[case] GEMM, ragged K M={M} N={N} K={K}")
     x, w, g = synth.random_problem(9700 + M + N + K, M, N, K)
@@ -318,6 +320,62 @@ def test_ragged_k_in_the_gemm(thi, oracle_mod, M, N, K):
     hh, sh = oracle_mod.swiglu_gate_up(x[rows], np.ascontiguousarray(w[:I]), np.ascontiguousarray(w[I:2 * I]))
     check(h[rows], hh, sh, "swiglu_gate_up", argmax=False)
     assert np.isfinite(a.astype(np.float32)).all() and np.isfinite(h.astype(np.float32)).all()
+
+
+# Every GEMM configuration with every way its tiles are dealt: whole; cut along K into equal contiguous shares across tile
+# borders, or into equal ranges per tile (few of them and dozens), alone or behind whole rounds; with the ragged K where it is built.
+# P: plain with a residual, G: gate/up.  tests/test_gemm_plan_cpu.py asserts that the rule sends each row where it says.
+KERNELS = [
+    ("P", 55, 16399, 128, "FEW64", "whole"), ("G", 55, 8200, 128, "FEW64", "whole"), ("P", 33, 53, 24704, "FEW64", "shares"),
+    ("G", 33, 48, 25216, "FEW64", "shares"), ("P", 35, 36869, 1408, "FEW64", "rounds + shares"),
+    ("P", 99, 8198, 64, "FEW128", "whole"), ("P", 97, 48, 8, "FEW128", "whole"), ("G", 98, 4104, 64, "FEW128", "whole"),
+    ("P", 33, 50, 24896, "FEW128", "shares"), ("G", 33, 48, 24768, "FEW128", "shares"), ("P", 121, 10364, 10440, "FEW128", "shares"),
+    ("G", 98, 5200, 12720, "FEW128", "shares"), ("G", 69, 16560, 1536, "FEW128", "rounds + shares"),
+    ("P", 33, 36895, 64, "FEW256", "whole"), ("P", 34, 37183, 3776, "FEW256", "shares"), ("G", 33, 32912, 1344, "FEW256", "rounds + shares"),
+    ("P", 137, 21264, 64, "ONE", "whole"), ("G", 131, 10752, 5632, "ONE", "shares"), ("P", 129, 36380, 960, "ONE", "rounds + ranges"),
+    ("P", 1961, 4124, 8, "BIG", "whole"), ("G", 1817, 3600, 64, "BIG", "whole"), ("G", 1557, 584, 4920, "BIG", "ranges"),
+    ("P", 139, 8247, 4928, "BIG", "ranges"), ("P", 1414, 11103, 616, "BIG", "rounds + ranges"), ("G", 1516, 5504, 464, "BIG", "rounds + ranges"),
+    ("G", 1524, 5504, 1024, "BIG", "rounds + ranges"), ("P", 129, 10947, 11640, "BIG", "shares"), ("G", 136, 5520, 12640, "BIG", "shares"),
+    ("P", 1585, 136, 25280, "R192", "ranges"), ("G", 135, 2704, 7808, "R192", "ranges"),
+    ("G", 1794, 1096, 64, "TALL", "whole"), ("P", 911, 1294, 3392, "TALL", "ranges"), ("G", 129, 5464, 9984, "TALL", "shares"),
+    ("P", 129, 48, 1216, "DEEP", "ranges"), ("G", 129, 48, 1064, "DEEP", "ranges"), ("P", 447, 120, 1664, "DEEP", "ranges"),
+    ("P", 1183, 3283, 1608, "DEEP", "rounds + ranges"), ("G", 643, 2728, 2432, "DEEP", "rounds + ranges"),
+    ("P", 1812, 4104, 64, "SMALL", "whole"), ("G", 1564, 1224, 8, "SMALL", "whole"), ("P", 129, 5603, 5696, "SMALL", "ranges"),
+    ("G", 1580, 2696, 3768, "SMALL", "rounds + ranges"), ("G", 50, 25832, 176, "SMALL", "whole"), ("G", 65, 16456, 3168, "SMALL", "shares"),
+]
+
+
+@pytest.mark.parametrize("kind,M,N,K,config,cut", KERNELS)
+def test_every_gemm_configuration_and_cut(thi, oracle_mod, kind, M, N, K, config, cut):
+    import torch
+    say(f"[case] {config}, {cut}: {kind} M={M} N={N} K={K}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+
+    def draw(rows, cols, scale=1.0):
+        return torch.empty((rows, cols), dtype=torch.float16, device="cuda").normal_(0.0, scale, generator=gen)
+
+    rows = synth.sample_rows(4646, M, 8)
+    x, w = draw(M, K), draw(2 * N if kind == "G" else N, K, 0.05)
+    r = Runner(M, K, N, N)
+    prev = thi.thi_set_kernel_family(2)
+    try:
+        if kind == "G":
+            got = [to_host(r.swiglu_gate_up(x, w[:N], w[N:])) for _ in range(2)]
+        else:
+            res = draw(M, N)
+            got = [to_host(r.linear_residual(x, w, res)) for _ in range(2)]
+    finally:
+        thi.thi_set_kernel_family(prev)
+    assert np.array_equal(got[0].view(np.uint16), got[1].view(np.uint16)), "not reproducible"
+    assert np.isfinite(got[0].astype(np.float32)).all()
+    xh, wh = to_host(x)[rows], to_host(w)
+    if kind == "G":
+        y, s = oracle_mod.swiglu_gate_up(xh, wh[:N], wh[N:])
+    else:
+        y, s = oracle_mod.linear_residual(xh, wh, to_host(res)[rows])
+    check(got[0][rows], y, s, f"{config} {cut}", argmax=False)
+    assert not _status_words(r.ws).any()
 
 
 def test_rows_longer_than_32_bit_offsets(thi):
@@ -342,8 +400,11 @@ def test_rows_longer_than_32_bit_offsets(thi):
 
 # Tiles of 224, 192 and 160 rows x 256 tokens (the first and last with an odd number of fragments per wave and fewer loads
 # in some waves than in others): one k-tile, a few and many, last tiles partly empty along both sides.
-@pytest.mark.parametrize("M,N,K", [(1800, 6259, 64), (1955, 6710, 704), (1858, 5397, 64), (1676, 6518, 1920),
-                                   (2045, 4262, 64), (1591, 11032, 1024), (2010, 4402, 128)])
+ROW_TILES = [(1800, 6259, 64), (1955, 6710, 704), (1858, 5397, 64), (1676, 6518, 1920), (2045, 4262, 64), (1591, 11032, 1024),
+             (2010, 4402, 128)]
+
+
+@pytest.mark.parametrize("M,N,K", ROW_TILES)
 def test_row_tiles_between_128_and_256(thi, oracle_mod, M, N, K):
     say(f"[case] 160..224-row tiles M={M} N={N} K={K}")
     x, w, g = synth.random_problem(9900 + M + N + K, M, N, K)
@@ -391,8 +452,8 @@ def test_prefill_swiglu_schedules(thi, oracle_mod, M, H, I):
 
 
 # ------------------------------------------- between decode and prefill (33..128 tokens)
-# One token tile of 64 or 128 against 256 weight rows, three stages deep; every tile is shared among
-# workgroups (far fewer tiles than compute units) and finished by the second pass.
+# These run the few-token kernel, the RMSNorm-fronted product of up to 64 tokens the stream-K kernel; the older configurations
+# for few tokens are in KERNELS.
 FEW_TOKENS = [
     (33, 1000, 1024), (48, 4096 + 200, 2048), (64, 256, 4096), (65, 3000, 1024), (100, 12288, 4096),
     (40, 1000, 4096 + 64),      # K a multiple of 64 but not of 128
@@ -1052,7 +1113,7 @@ def test_single_launch_mlp_matches_two_launches(thi, oracle_mod, M):
 
 
 # ------------------------------------- the layer's calls as one captured graph
-@pytest.mark.parametrize("M,single_launch_mlp", [(1, False), (32, False), (32, True)])
+@pytest.mark.parametrize("M,single_launch_mlp", [(1, False), (32, False), (32, True), (72, False)])
 def test_layer_calls_replay_from_a_captured_graph(thi, M, single_launch_mlp):
     """The layer's projections (RMSNorm-QKV with the rotary epilogue, O projection with its residual,
     RMSNorm-fronted MLP with its residual: five kernels on the 7B shape) captured once into a HIP graph and

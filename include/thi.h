@@ -198,8 +198,9 @@ int thi_rmsnorm_swiglu_mlp(const void* x, const void* gamma, float eps, const vo
  * 0 <= seq_lens[b] <= S_max (not checked on the host; a request with 0 positions gets a zero
  * row; cache contents at positions >= seq_lens[b] are never used).  The cache must already hold
  * the current token's key and value.  D is 64 or 128, Hq a multiple of Hkv (THI_ERR_SHAPE
- * otherwise).  scale is usually 1/sqrt(D).  Scores, weights and sums are fp32; one fp16 rounding
- * at the end.  Workspace: thi_attention_workspace_bytes(), 256-byte aligned, no preparation
+ * otherwise).  scale is usually 1/sqrt(D).  Scores, weights and sums are fp32 (with four and more
+ * query heads per cache head and D = 128 a weight reaches the matrix cores as two fp16 summands, 2^-22 of it off at most);
+ * one fp16 rounding at the end.  Workspace: thi_attention_workspace_bytes(), 256-byte aligned, no preparation
  * needed; it may be the (prepared) workspace of the other calls if large enough: the partial results
  * lie behind the status words and hand-over slots of those calls, which are left untouched.
  * Reproducible bit for bit; a request's result depends on its own query, keys, values and length and on

@@ -248,6 +248,8 @@ __global__ __launch_bounds__(64 * FIXUP_WAVES) void gemm_fixup(GemmArgs a, int t
 // k-tile must have landed, and its first fragments are read behind the barrier while the last k-step is multiplied.
 // Against 32x32x16 MFMAs with the same tiles (one box, alternating): gate/up 2048 x 57344 x 8192 1553 -> 1482 us,
 // 2048 x 8192 x 8192 244 -> 214, 2048 x 8192 x 28672 802 -> 721, 512 x 27648 x 5120 146 -> 138, same bits.
+// The 256x256 tile takes all 256 VGPRs and spills four (five with the rotary epilogue, 15 with a ragged K; gate/up none, five
+// ragged) around a tile's prologue and epilogue; the k loop reloads nothing.
 // Eight waves everywhere but in the 64-token configuration: with four (one per SIMD) nothing covers a wave's wait for
 // its fragments, and the 256x128 and 128x128 tiles lost 8-10 %.
 template <int BN, int BM, int WN, int WM, int GK, int NS, int EPI, bool KTAIL>

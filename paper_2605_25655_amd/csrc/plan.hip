@@ -230,8 +230,8 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
     if (M <= 128) {
         // Few tokens: one token tile, the weights are read once and the kernel is bound by how many
         // bytes a CU keeps in flight: three stages of 128 rows x 128 k against 64 tokens (K a multiple of
-        // 128), else four of 128 rows x 64 k against 128 tokens.  Every tile is cut along K here (far fewer
-        // tiles than workgroups) and the second pass costs by the partial tiles' bytes, (workgroups +
+        // 128), else four of 128 rows x 64 k against 128 tokens.  With far fewer tiles than workgroups every
+        // tile is cut along K, and the second pass costs by the partial tiles' bytes, (workgroups +
         // tiles) x tile size: 128-row tiles halve them against 256-row tiles (7B-shaped O projection at
         // M = 128: 24.8 -> 18.5 us, gate/up 61 -> 53; second pass alone 8.5-9.7 us with 256 rows).  With
         // many more tiles than workgroups (70B-shaped gate/up: 448) the 256-row tile's smaller share of

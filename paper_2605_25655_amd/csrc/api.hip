@@ -485,8 +485,9 @@ int thi_decode_attention(const void* q, const void* k_cache, const void* v_cache
     a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.D = D; a.S_max = S_max;
     a.group = Hq / Hkv;
     const int gt = attention_heads_per_workgroup(D, a.group);
-    a.nsplit = attention_split(B, Hkv * ((a.group + gt - 1) / gt), S_max, device_cu_count());
-    a.chunk = AT_MIN_CHUNK;
+    const AttnSplit split = attention_split(B, Hkv * ((a.group + gt - 1) / gt), S_max, device_cu_count());
+    a.nsplit = split.most;
+    a.whole = split.whole;
     a.scale2 = scale * 1.44269504088896340736f;
     return launch_attention(a, (hipStream_t)hip_stream) == hipSuccess ? THI_OK : THI_ERR_HIP;
 }

@@ -36,8 +36,8 @@ template <int GT> struct Unroll { static constexpr int U = (GT >= 4) ? 2 : 4; };
 
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Positions per chunk of a request with L live ones: all of them where requests are not cut (a.nsplit == 1), else 1/nsplit
-// of them in whole multiples of 64, at least a.chunk.  It is a function of the request's own length and of how many
+// Positions per chunk of a request with L live ones: all of them where requests are not cut (a.nsplit == 1) and up to
+// a.whole, else 1/nsplit of them in whole multiples of 64, at least AT_MIN_CHUNK.  It is a function of the request's own length and of how many
 // workgroups the call has (B, heads), so that a request's chunk borders, and with them the bits of its result, do not depend on
 // its neighbours' lengths or on the size of the cache.  It also keeps the head of a workgroup short, one length and one
 // division: a chunk size common to the batch, searched for on the device so that all chunks just fit the compute
@@ -47,8 +47,9 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 __device__ __forceinline__ int chunk_size(const AttnArgs& a, int L)
 {
     if (a.nsplit == 1) return L;
+    if (L <= a.whole) return a.whole;
     const int size = (int)(((unsigned)(L + a.nsplit - 1) / (unsigned)a.nsplit + 63u) & ~63u);
-    return size > a.chunk ? size : a.chunk;
+    return size > AT_MIN_CHUNK ? size : AT_MIN_CHUNK;
 }
 
 // What a workgroup works on: positions [c0, c1) of request b, its chunk number s (whole: its only one).

@@ -296,15 +296,20 @@ int attention_heads_per_workgroup(int D, int group)
 // ones: 3 chunks 66 us, 2 chunks 89).  Two to four workgroups per unit, or long requests cut into 512..2048 positions
 // whatever the rule says, were 1-3 % slower on average over 300 calls and up to twice as fast where one request is much
 // longer than all others.
-int attention_split(int B, int heads, int S_max, int num_cus)
+//
+// Requests of up to 512 positions are one chunk with half as many (request, cache head) pairs as compute units and more: so many
+// workgroups draw almost what memory gives, and a short request cut gains less than the second launch costs (69 calls with 128..255
+// pairs and caches of up to 512 positions: 0.71 of the time they take cut; up to 1024 positions, batches of unequal lengths lost).
+AttnSplit attention_split(int B, int heads, int S_max, int num_cus)
 {
     const long base = (long)B * heads;
-    if (base >= num_cus || S_max <= AT_MIN_CHUNK) return 1;
+    const int whole = 2 * base >= num_cus ? AT_WHOLE : AT_MIN_CHUNK;
+    if (base >= num_cus || S_max <= whole) return AttnSplit{1, whole};
     long want = num_cus / base;
     if (want < 4) want = (num_cus + base - 1) / base;
     if (want > AT_MAX_SPLIT) want = AT_MAX_SPLIT;
     const int most = (S_max - 1) / AT_MIN_CHUNK + 1;
-    return (int)(want < most ? want : most);
+    return AttnSplit{(int)(want < most ? want : most), whole};
 }
 
 }  // namespace thi

@@ -173,13 +173,18 @@ struct AttnArgs {
     int B, Hq, Hkv, D, S_max;
     int group;               // Hq / Hkv query heads per cache head
     int nsplit;              // chunks per request, at most (1: requests are not cut)
-    int chunk;               // positions per chunk, at least
+    int whole;               // requests of up to so many positions are one chunk
     float scale2;            // softmax scale times log2(e)
 };
 constexpr int AT_MAX_SPLIT = 32;      // chunks per request, at most
-constexpr int AT_MIN_CHUNK = 128;     // positions per chunk, at least
+constexpr int AT_MIN_CHUNK = 128;     // positions per chunk of a request that is cut, at least
+constexpr int AT_WHOLE = 512;         // requests of up to so many are not cut where there are many of them
+struct AttnSplit {
+    int most;        // chunks per request, at most (1: requests are not cut)
+    int whole;       // requests of up to so many positions are not cut
+};
 int attention_heads_per_workgroup(int D, int group);
-int attention_split(int B, int heads, int S_max, int num_cus);
+AttnSplit attention_split(int B, int heads, int S_max, int num_cus);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream);
 
 // Rotate one interleaved pair (a, b) = (y[c], y[c+1]), c even: Algorithm 1's  y*cos + mix*sin  with

@@ -57,7 +57,7 @@ hipError_t launch_rmsnorm_rows(const uint16_t*, const uint16_t*, float, uint16_t
 hipError_t launch_attention(const AttnArgs& a, hipStream_t)
 {
     ++g_launches;
-    return (a.nsplit >= 1 && a.nsplit <= AT_MAX_SPLIT && a.chunk >= 1 && a.part) ? hipSuccess : hipErrorInvalidValue;
+    return (a.nsplit >= 1 && a.nsplit <= AT_MAX_SPLIT && a.whole >= AT_MIN_CHUNK && a.part) ? hipSuccess : hipErrorInvalidValue;
 }
 hipError_t launch_fill_words(void*, size_t, uint32_t, hipStream_t)
 {

@@ -155,8 +155,8 @@ def test_attention_argument_errors(thi):
 
 
 # A request is cut by its own length, and groups of four and more heads of 128 take up to 16 heads a pass: sizes around the
-# 16-position blocks, the 64-position chunk grid, the 128-position minimum, the 32 chunks a request may have, passes of 16
-# heads and a rest, more than 64 requests, and one long request among short ones.
+# 16-position blocks, the 64-position chunk grid, the 128-position minimum, the 512 positions up to which many requests stay
+# whole, the 32 chunks a request may have, passes of 16 heads and a rest, more than 64 requests, and one long request among short ones.
 CHUNKS = [
     (6, 8, 1, 128, 4100, [4100, 1, 0, 129, 128, 64]),
     (1, 5, 1, 128, 8192, [8192]),                     # 32 chunks
@@ -168,6 +168,8 @@ CHUNKS = [
     (4, 64, 8, 128, 1025, [1025, 1024, 1023, 2]),
     (2, 52, 52, 128, 900, [900, 31]),
     (33, 32, 8, 128, 161, None),                      # not cut
+    (32, 28, 4, 128, 700, [511, 512, 513, 700] + [97 * i % 701 for i in range(28)]),   # cut above 512 positions only
+    (9, 16, 16, 128, 513, [513, 512, 1, 0, 129, 128, 511, 300, 513]),
 ]
 
 
@@ -189,7 +191,7 @@ def test_chunks_of_live_lengths(thi, oracle_mod, B, Hq, Hkv, D, S_max, lens):
     assert np.array_equal(got[perm].view(np.uint16), again.view(np.uint16))
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,D,S_max", [(5, 64, 8, 128, 3000), (4, 16, 16, 128, 2000), (3, 8, 4, 64, 1500), (70, 2, 1, 64, 900)])
+@pytest.mark.parametrize("B,Hq,Hkv,D,S_max", [(5, 64, 8, 128, 3000), (4, 16, 16, 128, 2000), (3, 8, 4, 64, 1500), (70, 2, 1, 64, 900), (40, 28, 4, 128, 400)])
 def test_a_request_does_not_see_its_neighbours_or_the_cache_size(thi, B, Hq, Hkv, D, S_max):
     """Requests are cut into chunks; a request's bits stay the same when the other requests grow or shrink and when its
     keys and values lie in a larger cache."""

@@ -290,12 +290,12 @@ int attention_heads_per_workgroup(int D, int group)
 }
 
 // Chunks per request, at most; 1 = requests are not cut: enough workgroups without, or caches of at most one chunk.  One
-// workgroup per compute unit, and no more than that while it leaves a request four chunks or more (6 requests x 8 cache
-// heads of 8192 positions: 5 chunks 28.5 us, 6 chunks and 32 compute units with two of them 31); below that the chunks a
-// request would lose weigh more than the second workgroup on some units (3 x 40 heads, one request of 13078 positions among short
-// ones: 3 chunks 66 us, 2 chunks 89).  Two to four workgroups per unit, or long requests cut into 512..2048 positions
-// whatever the rule says, were 1-3 % slower on average over 300 calls and up to twice as fast where one request is much
-// longer than all others.
+// workgroup per compute unit while that leaves a request four chunks and more (6 requests x 8 cache heads of 8192 positions: 5 chunks
+// 28.9 us, 10 chunks 29.6; 218 calls with up to 64 pairs and grouped heads 2-4 % slower with two), else two: with fewer chunks
+// it is a request's length that decides how long a workgroup takes, and a second one on a unit fills the gaps (217 calls with 65..255
+// pairs and caches above 512 positions: 0.96 of the time with one per unit, rounded up).  Long requests cut into 512..2048
+// positions whatever the rule says were 1-3 % slower on average over 300 calls and up to twice as fast where one request
+// is much longer than all others.
 //
 // Requests of up to 512 positions are one chunk with half as many (request, cache head) pairs as compute units and more: so many
 // workgroups draw almost what memory gives, and a short request cut gains less than the second launch costs (69 calls with 128..255
@@ -306,7 +306,7 @@ AttnSplit attention_split(int B, int heads, int S_max, int num_cus)
     const int whole = 2 * base >= num_cus ? AT_WHOLE : AT_MIN_CHUNK;
     if (base >= num_cus || S_max <= whole) return AttnSplit{1, whole};
     long want = num_cus / base;
-    if (want < 4) want = (num_cus + base - 1) / base;
+    if (want < 4) want = 2L * num_cus / base;
     if (want > AT_MAX_SPLIT) want = AT_MAX_SPLIT;
     const int most = (S_max - 1) / AT_MIN_CHUNK + 1;
     return AttnSplit{(int)(want < most ? want : most), whole};

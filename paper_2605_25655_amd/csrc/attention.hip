@@ -37,9 +37,9 @@ template <int GT> struct Unroll { static constexpr int U = (GT >= 4) ? 2 : 4; };
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Positions per chunk of a request with L live ones: all of them where requests are not cut (a.nsplit == 1) and up to
-// a.whole, else 1/nsplit of them in whole multiples of 64, at least AT_MIN_CHUNK.  It is a function of the request's own length and of how many
-// workgroups the call has (B, heads), so that a request's chunk borders, and with them the bits of its result, do not depend on
-// its neighbours' lengths or on the size of the cache.  It also keeps the head of a workgroup short, one length and one
+// a.whole, else 1/nsplit of them in whole multiples of 64, at least AT_MIN_CHUNK.  It is a function of the request's own
+// length and of how many workgroups the call has (B, heads), so that a request's chunk borders, and with them the bits of its
+// result, do not depend on its neighbours' lengths or on the size of the cache.  It also keeps the head of a workgroup short, one length and one
 // division: a chunk size common to the batch, searched for on the device so that all chunks just fit the compute
 // units, took ~1 us of scans in front of the first load (8 heads of 64, 2 requests of 468 positions 7.5 us, now 6.2; 5 requests of
 // 332 with 40 heads of 128 14.1, now 11) and won only where one request is much longer than all others (7 requests x 8 cache heads, one

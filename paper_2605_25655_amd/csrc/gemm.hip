@@ -9,7 +9,7 @@
 // three times the HBM reads.
 // The paper's DDR->GSM->AM dataflow is specific to its scratchpad machine; here
 // a workgroup owns a BN x BM output tile (up to 256 x 256), stages BN x 64 and
-// BM x 64 operand tiles in LDS (double buffered, XOR-swizzled 16-byte pieces so
+// BM x 64 operand tiles in LDS (two to four stages, XOR-swizzled 16-byte pieces so
 // that both the staging writes and the MFMA operand reads are bank-conflict
 // free) and runs v_mfma_f32_16x16x32_f16 on wave tiles of up to 64 x 128.
 //
@@ -248,11 +248,19 @@ __global__ __launch_bounds__(64 * FIXUP_WAVES) void gemm_fixup(GemmArgs a, int t
 // k-tile must have landed, and its first fragments are read behind the barrier while the last k-step is multiplied.
 // Against 32x32x16 MFMAs with the same tiles (one box, alternating): gate/up 2048 x 57344 x 8192 1553 -> 1482 us,
 // 2048 x 8192 x 8192 244 -> 214, 2048 x 8192 x 28672 802 -> 721, 512 x 27648 x 5120 146 -> 138, same bits.
-// The 256x256 tile takes all 256 VGPRs and spills four (five with the rotary epilogue, 15 with a ragged K; gate/up none, five
-// ragged) around a tile's prologue and epilogue; the k loop reloads nothing.
+// What bounds it: with all direct loads of a k-tile right behind the barrier, the two waves of every SIMD queued for the load
+// path at the same time and the matrix cores stood still: 2780 cycles a k-tile of 256x256x64 at 1.81 GHz, of which 2048 are
+// MFMAs and 50 a wait for the loads.  So the loads go out one by one between the MFMAs of the whole k-tile, in a fixed order
+// (`step`), and since a stage is free only behind the barrier, one operand has a stage more (NSW weight and NSX activation stages:
+// 3 + 2 of 32 KiB are all of the LDS) and its loads go out half a k-tile later than the other's.  2340 cycles at 1.59 GHz: the power limit is
+// what is left.  gate/up 2048 x 57344 x 8192 1471 -> 1381 us, 2048 x 8192 x 28672 732 -> 687, 512 x 5120 x 13824 88 -> 84 (256x256);
+// gate/up 512 x 27648 x 5120 139.5 -> 125.8 (224 rows), 165 -> 150 (128 x 256), 203 x 12288 x 4096 (128x128, four
+// stages) 42.5 -> 41.0.  The deeper operand alone, without the order, gains nothing with 256 rows and 4-8 % with 192.
+// The 256x256 tile takes all 256 VGPRs and spills up to four (20 with a ragged K; gate/up none, 16 ragged) around a tile's
+// prologue and epilogue; the k loop reloads nothing.
 // Eight waves everywhere but in the 64-token configuration: with four (one per SIMD) nothing covers a wave's wait for
 // its fragments, and the 256x128 and 128x128 tiles lost 8-10 %.
-template <int BN, int BM, int WN, int WM, int GK, int NS, int EPI, bool KTAIL>
+template <int BN, int BM, int WN, int WM, int GK, int NSW, int NSX, int EPI, bool KTAIL>
 __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int tiles_m, int ktiles, int sk_tiles, int parts)
 {
     constexpr int NWAVES = WN * WM;
@@ -268,10 +276,11 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     constexpr int TM = BM / WM / 16;
     constexpr bool PAIRS = TN % 2 == 0;          // gate and up rows alternate by fragments of 16 rows, else by 8 rows
     constexpr int JPT = is_swiglu(EPI) ? BN / 2 : BN;   // physical weight rows per tile
-    constexpr int STAGE = (BN + BM) * GPIECES;   // 16-byte units per stage: weight tile, then activation tile
-    static_assert(NS >= 2 && NS <= 4 && (KSTEPS % 2) == 0 && (PAIRS || ROWS_PER_DMA <= 8), "pipeline shape");
+    constexpr int WSTAGE = BN * GPIECES, XSTAGE = BM * GPIECES;     // 16-byte units per stage; the weight stages come first
+    constexpr int DEEP = NSW > NSX ? NSW : NSX, FLAT = NSW > NSX ? NSX : NSW;
+    static_assert(FLAT >= 2 && DEEP <= 4 && (KSTEPS % 2) == 0 && (PAIRS || ROWS_PER_DMA <= 8), "pipeline shape");
     static_assert(WBLKS >= NWAVES && XPASS >= 1 && BM * GPIECES % THREADS == 0, "tile too small for the thread count");
-    static_assert(EVEN || (NS == 2 && !KTAIL), "only a wait for all loads may leave open how many there were");
+    static_assert(EVEN || (NSW == 2 && !KTAIL), "waves with unequal numbers of weight loads: none of them may be left open by a wait");
 
     extern __shared__ uintx4 smem[];
 
@@ -357,28 +366,26 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             const int piece = slot ^ swz_f<GPIECES>(blk * ROWS_PER_DMA + lane / GPIECES);
             return kt * GK + piece * 8 >= K ? piece : 0;
         };
-        auto load_tile = [&](int kt, int buf) {
+        auto dma_w = [&](int kt, int buf, int i) {
             const bool tail = KTAIL && kt == ktiles - 1;
-#pragma unroll
-            for (int i = 0; i < WPASS; ++i) {
-                const int blk = EVEN ? wv * WPASS + i : wv + NWAVES * i;
-                if (EVEN || blk < WBLKS)
-                    dma16_sbase(wsrc[i] + kt * GK, tail ? woff[i] - 16u * past_k(blk, kt) : woff[i], smem + buf * STAGE + blk * 64);
-            }
-#pragma unroll
-            for (int i = 0; i < XPASS; ++i)
-                dma16_sbase(xsrc[i] + kt * GK, tail ? xoff[i] - 16u * past_k(wv * XPASS + i, kt) : xoff[i],
-                            smem + buf * STAGE + BN * GPIECES + (wv * XPASS + i) * 64);
+            const int blk = EVEN ? wv * WPASS + i : wv + NWAVES * i;
+            if (EVEN || blk < WBLKS)
+                dma16_sbase(wsrc[i] + kt * GK, tail ? woff[i] - 16u * past_k(blk, kt) : woff[i], smem + buf * WSTAGE + blk * 64);
         };
-        // zeros where this wave's loads of k-tile kt (landed, in stage buf) lay past K
-        auto zero_tail = [&](int kt, int buf) {
+        auto dma_x = [&](int kt, int buf, int i) {
+            const bool tail = KTAIL && kt == ktiles - 1;
+            dma16_sbase(xsrc[i] + kt * GK, tail ? xoff[i] - 16u * past_k(wv * XPASS + i, kt) : xoff[i],
+                        smem + NSW * WSTAGE + buf * XSTAGE + (wv * XPASS + i) * 64);
+        };
+        // zeros where this wave's loads of k-tile kt (landed, in stages wbuf and xbuf) lay past K
+        auto zero_tail = [&](int kt, int wbuf, int xbuf) {
             if (!KTAIL || kt != ktiles - 1) return;
 #pragma unroll
             for (int i = 0; i < WPASS; ++i)
-                if (past_k(wv * WPASS + i, kt)) smem[buf * STAGE + (wv * WPASS + i) * 64 + lane] = uintx4{0u, 0u, 0u, 0u};
+                if (past_k(wv * WPASS + i, kt)) smem[wbuf * WSTAGE + (wv * WPASS + i) * 64 + lane] = uintx4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int i = 0; i < XPASS; ++i)
-                if (past_k(wv * XPASS + i, kt)) smem[buf * STAGE + BN * GPIECES + (wv * XPASS + i) * 64 + lane] = uintx4{0u, 0u, 0u, 0u};
+                if (past_k(wv * XPASS + i, kt)) smem[NSW * WSTAGE + xbuf * XSTAGE + (wv * XPASS + i) * 64 + lane] = uintx4{0u, 0u, 0u, 0u};
         };
 
         floatx4 acc[TN][TM];
@@ -388,78 +395,108 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             for (int j = 0; j < TM; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
         half8 wa[2][TN], xb[2][TM];
-        auto frags = [&](int buf, int kk, int fs) {
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-                wa[fs][tn] = __builtin_bit_cast(half8, smem[buf * STAGE + swz<GPIECES>(wn * (BN / WN) + tn * 16 + lr, 4 * kk + hi)]);
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-                xb[fs][tm] = __builtin_bit_cast(half8, smem[buf * STAGE + BN * GPIECES + swz<GPIECES>(wm * (BM / WM) + tm * 16 + lr, 4 * kk + hi)]);
+        // The r-th operand fragment of a k-step, weights first: where a lane reads is its place in the k-step's first fragment
+        // of the stage (a wave's fragments are 16 rows apart, and the swizzle repeats after 16 rows) and a constant.
+        auto read_frag = [&](int r, const uintx4* wl, const uintx4* xl, int fs) {
+            if (r < TN) wa[fs][r] = __builtin_bit_cast(half8, wl[r * 16 * GPIECES]);
+            else xb[fs][r - TN] = __builtin_bit_cast(half8, xl[(r - TN) * 16 * GPIECES]);
         };
-        auto mfmas = [&](int fs) {
+        auto w_lane = [&](int buf, int kk) { return smem + buf * WSTAGE + swz<GPIECES>(wn * (BN / WN) + lr, 4 * kk + hi); };
+        auto x_lane = [&](int buf, int kk) { return smem + NSW * WSTAGE + buf * XSTAGE + swz<GPIECES>(wm * (BM / WM) + lr, 4 * kk + hi); };
+        // The MFMAs of one k-step in a fixed order: a read of the next k-step's fragments in front of every GAP-th while there are
+        // any, the direct loads at equal distances.
+        constexpr int NMF = TN * TM, NRD = TN + TM;
+        auto step = [&](int fs, auto gap, auto read, auto nloads, auto load) {
+            constexpr int GAP = decltype(gap)::value, NL = decltype(nloads)::value;
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
+            for (int i = 0; i < NMF; ++i) {
+                if (i % GAP == 0 && i / GAP < NRD) read(i / GAP);
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm)
-                    acc[tn][tm] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[fs][tn], xb[fs][tm], acc[tn][tm], 0, 0, 0);
-        };
-        // spread the LDS reads of the next k-step over the MFMAs of the current one, `per` MFMAs between two reads
-        using One = std::integral_constant<int, 1>;
-        using PerRead = std::integral_constant<int, TN * TM / (TN + TM)>;
-        auto interleave = [&](auto per) {
-            constexpr int PER = decltype(per)::value;
-#pragma unroll
-            for (int i = 0; i < TN + TM; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                for (int d = 0; d < NL; ++d)
+                    if (d * NMF / (NL ? NL : 1) == i) load(d);
+                const int tn = i / TM, tm = i % TM;
+                acc[tn][tm] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wa[fs][tn], xb[fs][tm], acc[tn][tm], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, TN * TM - PER * (TN + TM), 0);
         };
 
-        // ---- prologue: the first NS k-tiles into the NS stages
+        // ---- prologue: the first k-tiles into the stages, oldest first
         constexpr int LPT = WPASS + XPASS;           // direct loads per k-tile per wave
+        constexpr bool W_LATE = NSW >= NSX && NSW >= 3, X_LATE = NSX > NSW;
         const int nk = ke - kb;
 #pragma unroll
-        for (int st = 0; st < NS; ++st)
-            if (st < nk) load_tile(kb + st, st);
+        for (int st = 0; st < DEEP; ++st) {
+            if (st < NSX - X_LATE && st < nk)
+#pragma unroll
+                for (int i = 0; i < XPASS; ++i) dma_x(kb + st, st, i);
+            if (st < NSW - W_LATE && st < nk)
+#pragma unroll
+                for (int i = 0; i < WPASS; ++i) dma_w(kb + st, st, i);
+        }
         // Only the first k-tile has to have landed (all of them where that is not a fixed number of loads: ranges shorter
         // than the stages, waves with unequal numbers of loads); the loop waits for the others one by one.  Waiting for all
         // stages cost most where a range is a few k-tiles long, the more the more stages there are (128x128 tiles, four stages:
         // 108 x 451 x 624 11.1 -> 10.6 us; 345 calls of 129..2048 tokens 1.2 % on average).
-        static_assert((NS - 1) * LPT < 64, "wait count out of range");
-        if (EVEN && nk >= NS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * LPT) : "memory");
+        constexpr int FIRST = (NSX - 1 - X_LATE) * XPASS + (NSW - 1 - W_LATE) * WPASS;
+        static_assert(FIRST < 64, "wait count out of range");
+        if (EVEN && nk >= DEEP) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FIRST) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (KTAIL && nk == 1) zero_tail(kb, 0);
+        if (KTAIL && nk == 1) zero_tail(kb, 0, 0);
         __syncthreads();
 
-        frags(0, 0, 0);
-        for (int it = 0; it < nk; ++it) {
-            const int st = it % NS;
+        // Direct loads complete in order.  In front of k-tile it+1 the newest loads that must have landed are those of its operand
+        // with the fewer stages; behind them, in flight, are the deeper operand's of the same turn and the later turns' of both.
+        constexpr int STEADY = (FLAT - 2) * LPT + (NSW > NSX ? WPASS : NSX > NSW ? XPASS : 0);
+        static_assert(STEADY < 64, "wait count out of range");
+#pragma unroll
+        for (int r = 0; r < NRD; ++r) read_frag(r, w_lane(0, 0), x_lane(0, 0), 0);
+        int ws = 0, xs = 0, wprev = NSW - 1, xprev = NSX - 1;     // stages of k-tile it and of the one in front
+        // One k-tile.  The loads of the operand with fewer stages go out behind the barrier, into the stage that was read last; those of
+        // the deeper one in the next k-tile's first k-step (its last stage is therefore still empty when the loop starts).  LAST: the
+        // k-tiles whose successors in the same stages may lie past the range.
+        constexpr int EARLY = (W_LATE ? 0 : WPASS) + (X_LATE ? 0 : XPASS), LATE = LPT - EARLY;
+        constexpr int SPREAD = NMF / NRD;
+        auto ktile = [&](int it, auto last) {
+            constexpr bool LAST = decltype(last)::value;
+            const int wnext = ws + 1 == NSW ? 0 : ws + 1, xnext = xs + 1 == NSX ? 0 : xs + 1;
+            auto late = [&](int d) {
+                if (W_LATE && (!LAST || it - 1 + NSW < nk)) dma_w(kb + it - 1 + NSW, wprev, d);
+                if (X_LATE && (!LAST || it - 1 + NSX < nk)) dma_x(kb + it - 1 + NSX, xprev, d);
+            };
+            auto none = [](int) {};
+            using std::integral_constant;
 #pragma unroll
             for (int kk = 0; kk < KSTEPS - 1; ++kk) {
-                frags(st, kk + 1, (kk + 1) & 1);
-                mfmas(kk & 1);
-                if (kk < KSTEPS - 2) interleave(PerRead{});
-                else interleave(One{});          // in front of the barrier: the reads first, their latency behind MFMAs
+                const uintx4 *wl = w_lane(ws, kk + 1), *xl = x_lane(xs, kk + 1);
+                auto read = [&](int r) { read_frag(r, wl, xl, (kk + 1) & 1); };
+                if (kk == 0 && KSTEPS == 2) step(0, integral_constant<int, 1>{}, read, integral_constant<int, LATE>{}, late);
+                else if (kk == 0) step(0, integral_constant<int, SPREAD>{}, read, integral_constant<int, LATE>{}, late);
+                else if (kk < KSTEPS - 2) step(kk & 1, integral_constant<int, SPREAD>{}, read, integral_constant<int, 0>{}, none);
+                else step(kk & 1, integral_constant<int, 1>{}, read, integral_constant<int, 0>{}, none);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            // Every read of stage st has been issued.  Before the barrier, k-tile it+1 must have landed:
-            // direct loads complete in order, so it is enough that at most the loads of the k-tiles
-            // behind it (up to NS-2 of them) are still in flight.  The compiler does not carry these
+            // Every read of this k-tile's stages has been issued.  The compiler does not carry these
             // loads across the loop edge, hence the explicit wait.
-            int behind = nk - 2 - it;            // k-tiles after it+1 that have been requested
-            behind = behind < NS - 2 ? behind : NS - 2;
-            static_assert(NS <= 4 && 2 * LPT < 64, "wait count out of range");
-            if (behind <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
-            else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPT) : "memory");
-            if (KTAIL && it + 1 < nk) zero_tail(kb + it + 1, (it + 1) % NS);
+            if (STEADY > 0 && (!LAST || it + DEEP <= nk)) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STEADY) : "memory");
+            else if (DEEP == 4 && FLAT >= 3 && it + 3 <= nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (KTAIL && LAST && it + 1 < nk) zero_tail(kb + it + 1, wnext, xnext);
             __syncthreads();
-            if (it + NS < nk) load_tile(kb + it + NS, st);
-            frags(it + 1 < nk ? (it + 1) % NS : st, 0, 0);      // (behind the last k-tile: read and never used)
-            mfmas((KSTEPS - 1) & 1);
-            interleave(PerRead{});
-        }
+            auto early = [&](int d) {
+                if (!X_LATE && d < XPASS) { if (!LAST || it + NSX < nk) dma_x(kb + it + NSX, xs, d); }
+                else if (!LAST || it + NSW < nk) dma_w(kb + it + NSW, ws, X_LATE ? d : d - XPASS);
+            };
+            const bool more = !LAST || it + 1 < nk;              // (behind the last k-tile: read and never used)
+            const uintx4 *wl = w_lane(more ? wnext : ws, 0), *xl = x_lane(more ? xnext : xs, 0);
+            auto read = [&](int r) { read_frag(r, wl, xl, 0); };
+            step((KSTEPS - 1) & 1, integral_constant<int, SPREAD>{}, read, integral_constant<int, EARLY>{}, early);
+            wprev = ws;
+            xprev = xs;
+            ws = wnext;
+            xs = xnext;
+        };
+        int it = 0;
+        for (; it + DEEP < nk; ++it) ktile(it, std::false_type{});
+        for (; it < nk; ++it) ktile(it, std::true_type{});
 
         // ---- whole tile: finished below; shared tile: leave the fp32 partial for the fix-up kernel ---
         const bool whole = (kb == 0 && ke == ktiles);
@@ -493,7 +530,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
 }
 
 // ALL = also build the variant for a ragged K (KTAIL).
-template <int BN, int BM, int WN, int WM, int GK, int NS, bool ALL>
+template <int BN, int BM, int WN, int WM, int GK, int NSW, int NSX, bool ALL>
 hipError_t launch_cfg(GemmArgs a, int epilogue, const GemmPlan& p, hipStream_t stream)
 {
     constexpr bool CUT = BN / WN / 16 % 2 == 0;
@@ -501,11 +538,11 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, const GemmPlan& p, hipStream_t s
     if (tile.BN != BN || tile.BM != BM || tile.GK != GK || tile.cut != CUT || tile.ragged != ALL) return hipErrorInvalidValue;
     a.tiles = p.tiles;
     const int tiles_m = p.tiles_m, ktiles = p.ktiles, grid = p.grid, sk_tiles = p.sk_tiles, parts = p.parts;
-    const size_t lds = (size_t)NS * (BN + BM) * (GK / 8) * sizeof(uintx4);
+    const size_t lds = ((size_t)NSW * BN + (size_t)NSX * BM) * (GK / 8) * sizeof(uintx4);
     dim3 g((unsigned)grid), b(64 * WN * WM);
 #define THI_LAUNCH_K(E, KT)                                                                                  \
     do {                                                                                                     \
-        auto kern = gemm_streamk<BN, BM, WN, WM, GK, NS, E, KT>;                                                      \
+        auto kern = gemm_streamk<BN, BM, WN, WM, GK, NSW, NSX, E, KT>;                                                      \
         static std::once_flag attr_once;      /* one opt-in per kernel variant, safe from several threads */  \
         std::call_once(attr_once, [&] {                                                                      \
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                   \
@@ -638,15 +675,15 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     const GemmPlan p = plan_gemm(a.M, a.N, a.K, epilogue, num_cus);
     switch (p.config) {
     case GEMM_MID: return launch_mid(a, epilogue, p.mid, stream);
-    case GEMM_FEW64: return launch_cfg<128, 64, 4, 1, 128, 3, false>(a, epilogue, p, stream);
-    case GEMM_FEW256: return launch_cfg<256, 128, 4, 2, 64, 3, false>(a, epilogue, p, stream);
-    case GEMM_BIG: return launch_cfg<256, 256, 4, 2, 64, 2, true>(a, epilogue, p, stream);
-    case GEMM_R224: return launch_cfg<224, 256, 2, 4, 64, 2, false>(a, epilogue, p, stream);
-    case GEMM_R192: return launch_cfg<192, 256, 2, 4, 64, 2, false>(a, epilogue, p, stream);
-    case GEMM_R160: return launch_cfg<160, 256, 2, 4, 64, 2, false>(a, epilogue, p, stream);
-    case GEMM_ONE: case GEMM_TALL: return launch_cfg<128, 256, 2, 4, 64, 3, false>(a, epilogue, p, stream);
-    case GEMM_FEW128: case GEMM_DEEP: return launch_cfg<128, 128, 2, 4, 64, 4, true>(a, epilogue, p, stream);
-    case GEMM_SMALL: return launch_cfg<128, 128, 2, 4, 64, 2, true>(a, epilogue, p, stream);
+    case GEMM_FEW64: return launch_cfg<128, 64, 4, 1, 128, 3, 3, false>(a, epilogue, p, stream);
+    case GEMM_FEW256: return launch_cfg<256, 128, 4, 2, 64, 3, 3, false>(a, epilogue, p, stream);
+    case GEMM_BIG: return launch_cfg<256, 256, 4, 2, 64, 3, 2, true>(a, epilogue, p, stream);
+    case GEMM_R224: return launch_cfg<224, 256, 2, 4, 64, 2, 3, false>(a, epilogue, p, stream);
+    case GEMM_R192: return launch_cfg<192, 256, 2, 4, 64, 3, 2, false>(a, epilogue, p, stream);
+    case GEMM_R160: return launch_cfg<160, 256, 2, 4, 64, 2, 3, false>(a, epilogue, p, stream);
+    case GEMM_ONE: case GEMM_TALL: return launch_cfg<128, 256, 2, 4, 64, 3, 3, false>(a, epilogue, p, stream);
+    case GEMM_FEW128: case GEMM_DEEP: return launch_cfg<128, 128, 2, 4, 64, 4, 4, true>(a, epilogue, p, stream);
+    case GEMM_SMALL: return launch_cfg<128, 128, 2, 4, 64, 3, 2, true>(a, epilogue, p, stream);
     default: return hipErrorInvalidValue;
     }
 }

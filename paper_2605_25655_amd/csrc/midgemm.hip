@@ -266,7 +266,8 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
 #pragma unroll
         for (int o = 0; o < OWN; ++o)
             if (4 * o + kg < F && m_wave + ((4 * o + kg) % TM) * 16 < M)
-                asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(ps + o * 256), "v"(mine[o]) : "memory");
+                // (the no-op keeps the next instruction off the data registers: the compiler does not know this store)
+                asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(ps + o * 256), "v"(mine[o]) : "memory");
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // acknowledged by the memory system ...
         __syncthreads();                                     // ... for every thread, before the arrival is counted
         unsigned* const flag = reinterpret_cast<unsigned*>(smem);

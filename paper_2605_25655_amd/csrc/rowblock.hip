@@ -302,7 +302,8 @@ __device__ __forceinline__ void rowblock_body(SkinnyArgs a, const int per_wg, co
                 const int l = q & 63, m = (q >> 6) * 16 + (l & 15);
                 if (tt < nT && m < a.M) {
                     unsigned* const dst = slot + (tt * 32 + m) * 16 + 4 * (l >> 4);
-                    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(dst), "v"(v) : "memory");
+                    // (the no-op keeps the next instruction off the data registers: the compiler does not know this store)
+                    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(dst), "v"(v) : "memory");
                 }
             }
             return;

@@ -37,7 +37,9 @@ namespace {
 // other workgroups' stores.  They are not atomic as a whole (a reader can see a store half landed),
 // so they are only used on data that a flag has announced.
 __device__ __forceinline__ void store_device_x4(unsigned* p, uintx4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+    // (the no-op: a store of 16 bytes still reads its data while the next instruction issues, and the compiler, which keeps
+    // that instruction off the data registers behind its own stores, does not look into this one)
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 // Four (MT = 1) or eight (MT = 2) such loads and the wait for them in ONE statement: the registers
 // are written asynchronously, so the compiler must not see them before the wait has passed.

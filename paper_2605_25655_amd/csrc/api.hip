@@ -162,7 +162,7 @@ int pick_rowblock_split(int M, int N, int K, int epilogue, int cus)
 //                per block); plain kind: the rows that the block's last tile lacks cost half of what
 //                rows with weights cost (20 rows in two tiles: +30 %).
 enum DecodeKernel { DK_STREAMK = 1, DK_ROWSLAB = 3, DK_ROWBLOCK = 4 };
-int pick_decode_kernel(int M, int N, int K, int epilogue, int cus)
+int pick_decode_kernel(int M, int N, int K, int epilogue, int cus, double* us = nullptr)
 {
     const int fam = g_family.load(std::memory_order_relaxed);
     if (K > ROWSLAB_MAX_K) return DK_STREAMK;
@@ -187,12 +187,45 @@ int pick_decode_kernel(int M, int N, int K, int epilogue, int cus)
 
     const double t_block = rowblock_time(M, N, K, epilogue, cus, pick_rowblock_split(M, N, K, epilogue, cus));
 
+    if (us) *us = t_block < t_slab ? (t_block < t_sk ? t_block : t_sk) : t_slab < t_sk ? t_slab : t_sk;
     if (t_block < t_slab && t_block < t_sk) return DK_ROWBLOCK;
     return t_slab < t_sk ? DK_ROWSLAB : DK_STREAMK;
 }
 
+// Up to 32 tokens: the few-token GEMM kernel in the place of the decode kernel?  It brings the activations in once per workgroup,
+// not once per wave and tile, so what it costs hardly depends on the number of tokens, and it needs no second pass over K
+// where a workgroup has many rows.  Both measured on 1040 calls (linear, RMSNorm-QKV and gate/up of the 7B..70B shapes and of
+// random ones of 300..16000 x 1040..11200, 1..32 tokens): by these lines it runs 27 % of them, in 0.92 of the time on average; 2 % of the calls lose more
+// than 3 %, one 13 %.
+//   stream-K's place : 0.88-0.95 of its time at any number of tokens;
+//   row blocks'      : above 16 tokens (gate/up 2 x 13824 x 5120 at 32 tokens 51.6 -> 44.2 us, 2 x 17920 x 6656 83.1 -> 72.7,
+//                      4096 x 11008 21.8 -> 19.0, 8192 x 8192 26.2 -> 24.5; QKV 12288 x 4096 18.6 -> 22.8, so with
+//                      RMSNorm only where the model says 5 % and more), gate/up from five tokens on where the model says a tenth
+//                      (2 x 13824 x 5120 at 16 tokens 47.5 -> 43.9); with fewer tokens the row blocks win (4096 x 4096 at one 1.4 x);
+//   row slabs'       : never (they win by 0-10 % wherever they are chosen).
+bool few_token_kernel_ok(int M, int N, int K, int epilogue, int cus, int kernel, double us)
+{
+    if (K < 1024 || kernel == DK_ROWSLAB || g_rowblock_split.load(std::memory_order_relaxed) != 0) return false;
+    const MidPlan mp = plan_mid(M, N, K, epilogue, cus);
+    if (!mp.BN) return false;
+    const bool swiglu = is_swiglu(epilogue);
+    const double mid = mp.us + (is_rms(epilogue) ? 0.4 + 0.09 * (((K + 127) / 128 + mp.S - 1) / mp.S) : 0.0);
+    if (kernel == DK_STREAMK) return mid < 1.05 * us;
+    if (M > 16) return mid < (swiglu ? 1.2 : is_rms(epilogue) ? 0.95 : 1.0) * us;
+    return swiglu && M > 4 && mid < 0.9 * us;
+}
+
+// Does the single-launch MLP serve the shape?  Its gate/up and down projections run as row blocks then, whatever else would be faster.
+bool single_launch_shape(int M, int H, int I, int epi_up, int cus)
+{
+    if (M > SKINNY_MAX_M || g_family.load(std::memory_order_relaxed) != 0) return false;
+    const int S = pick_rowblock_split(M, H, I, EPI_PLAIN, cus);
+    return S > 1 && mlp_fused_ok(M, H, I, epi_up, cus, S) && pick_decode_kernel(M, I, H, epi_up, cus) == DK_ROWBLOCK &&
+           pick_decode_kernel(M, H, I, EPI_PLAIN, cus) == DK_ROWBLOCK;
+}
+
 // Which kernel runs a projection of M tokens, and how many tokens a launch takes.
-//   M <= 32       : a decode kernel (pick_decode_kernel), one launch.
+//   M <= 32       : a decode kernel (pick_decode_kernel) or the few-token GEMM kernel (few_token_kernel_ok), one launch.
 //   33 <= M <= 64 : the stream-K decode kernel takes up to 64 tokens per launch (its activations are
 //                   shared by the workgroup's waves through LDS, so the wider batch costs it least); it
 //                   runs where its modelled time beats the few-token GEMM's (fitted on the 7B..70B
@@ -207,7 +240,7 @@ struct DecodePlan {
     int kernel;     // DK_*, or 0 = the GEMM kernels
     int group;      // tokens per launch
 };
-DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus)
+DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus, bool few_token = true)
 {
     const int fam = g_family.load(std::memory_order_relaxed);
     // The GEMM kernels address the rows of a tile by 32-bit byte offsets: 256 rows of up to 2^23 values.
@@ -216,7 +249,12 @@ DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus)
     const int first = M < SKINNY_GROUP ? M : SKINNY_GROUP;
     if (fam == 1) return DecodePlan{DK_STREAMK, M > SKINNY_GROUP ? 16 * SK_MAX_MT : SKINNY_GROUP};
     if (fam == 3 || fam == 4) return DecodePlan{pick_decode_kernel(first, N, K, epilogue, cus), SKINNY_GROUP};
-    if (M <= SKINNY_MAX_M) return DecodePlan{pick_decode_kernel(first, N, K, epilogue, cus), SKINNY_GROUP};
+    if (M <= SKINNY_MAX_M) {
+        double us = 0.0;
+        const int kernel = pick_decode_kernel(first, N, K, epilogue, cus, &us);
+        if (few_token && few_token_kernel_ok(M, N, K, epilogue, cus, kernel, us)) return DecodePlan{0, 0};
+        return DecodePlan{kernel, SKINNY_GROUP};
+    }
     if (M > 16 * SK_MAX_MT) return DecodePlan{0, 0};
     const double t_w = (is_swiglu(epilogue) ? 2.0 : 1.0) * (double)N * (double)K * 2.0 / 7.0e6;
     const double t_sk = 5.5 + 1.06 * t_w + (M <= 48 ? 8.0 : 13.0);
@@ -233,11 +271,11 @@ DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus)
 int run_projection(const uint16_t* x, const uint16_t* gamma, float eps, const uint16_t* w0, const uint16_t* w1,
                    uint16_t* out, int M, int N, int K, int ldo, int epilogue, const Workspace& ws,
                    hipStream_t stream, RopeArgs rope = RopeArgs{nullptr, nullptr, 0, 2, nullptr},
-                   const uint16_t* residual = nullptr)
+                   const uint16_t* residual = nullptr, bool few_token = true)
 {
     const int cus = device_cu_count();
     (void)hipGetLastError();      // an error another user of the runtime left behind is not ours to report
-    const DecodePlan dp = plan_decode(M, N, K, epilogue, cus);
+    const DecodePlan dp = plan_decode(M, N, K, epilogue, cus, few_token);
     if (dp.kernel != 0) {
         const int kernel = dp.kernel, group = dp.group;
         const bool slab = kernel != DK_STREAMK, block = kernel == DK_ROWBLOCK;
@@ -273,7 +311,11 @@ int run_projection(const uint16_t* x, const uint16_t* gamma, float eps, const ui
         }
         return THI_OK;
     }
-    if (!ws.partials) return THI_ERR_WORKSPACE;      // sized for the decode kernels only (see thi_workspace_bytes)
+    // Up to MID_DECODE_M tokens: the few-token kernel, which takes RMSNorm with it and needs no more of a workspace than the decode
+    // kernels.  (Its plan is the one that launch_gemm will make.)
+    const bool mid = M <= MID_DECODE_M && plan_mid(M, N, K, epilogue, cus).BN != 0;
+    if (!ws.partials && (!mid || g_family.load(std::memory_order_relaxed) == 2))
+        return THI_ERR_WORKSPACE;      // sized for the decode kernels only (see thi_workspace_bytes)
     {
         const long tn = (N + 63) / 64, tm = (M + 127) / 128;     // upper bound on tiles of any configuration
         if (tn * tm > WS_MAX_COUNTERS) return THI_ERR_SHAPE;
@@ -281,7 +323,7 @@ int run_projection(const uint16_t* x, const uint16_t* gamma, float eps, const ui
     // Prefill: RMSNorm runs as a pass of its own (a few percent of the GEMM's time) so that the GEMM can
     // take both operands straight from memory into LDS in its fastest configuration; the decode kernels
     // keep it fused, where a second pass over x would cost a launch.
-    if (is_rms(epilogue)) {
+    if (is_rms(epilogue) && !mid) {
         RopeArgs table = rope;
         if (has_rope(epilogue)) {
             if (rope.head_dim > ROPE_TABLE_MAX_HEAD_DIM) return THI_ERR_SHAPE;
@@ -290,15 +332,17 @@ int run_projection(const uint16_t* x, const uint16_t* gamma, float eps, const ui
         if (launch_rmsnorm_rows(x, gamma, eps, ws.xn, M, K, table, stream) != hipSuccess) return THI_ERR_HIP;
         x = ws.xn;
         gamma = nullptr;
-        epilogue = epilogue == EPI_RMSNORM ? EPI_PLAIN : epilogue == EPI_RMSNORM_ROPE ? EPI_ROPE : EPI_SWIGLU;
     }
+    if (is_rms(epilogue)) epilogue = epilogue == EPI_RMSNORM ? EPI_PLAIN : epilogue == EPI_RMSNORM_ROPE ? EPI_ROPE : EPI_SWIGLU;
     GemmArgs g{};
     g.x = x;
     g.w0 = w0;
     g.w1 = w1;
     g.out = out;
     g.residual = residual;
-    g.partials = ws.partials;
+    g.partials = ws.partials ? ws.partials : reinterpret_cast<float*>(ws.handover);
+    g.gamma = gamma;      // (nullptr where a pass of its own has applied it)
+    g.eps = eps;
     g.counters = ws.counters;
     g.tiles = 0;
     g.M = M;
@@ -322,27 +366,26 @@ int run_mlp(const uint16_t* x, const uint16_t* gamma, float eps, const uint16_t*
 {
     const int epi_up = gamma ? EPI_RMSNORM_SWIGLU : EPI_SWIGLU;
     const int cus = device_cu_count();
-    if (M <= SKINNY_MAX_M && g_family.load(std::memory_order_relaxed) == 0 && g_mlp_fusion.load(std::memory_order_relaxed)) {
+    const bool fusible = single_launch_shape(M, H, I, epi_up, cus);      // (the same kernels then, one launch or two: the switch does not change results)
+    if (fusible && g_mlp_fusion.load(std::memory_order_relaxed)) {
         const int S = pick_rowblock_split(M, H, I, EPI_PLAIN, cus);
-        if (S > 1 && mlp_fused_ok(M, H, I, epi_up, cus, S) && pick_decode_kernel(M, I, H, epi_up, cus) == DK_ROWBLOCK &&
-            pick_decode_kernel(M, H, I, EPI_PLAIN, cus) == DK_ROWBLOCK) {
-            (void)hipGetLastError();
-            SkinnyArgs up{}, down{};
-            up.x = x; up.gamma = gamma; up.w0 = w_gate; up.w1 = w_up; up.out = ws.h; up.residual = nullptr;
-            up.handover = ws.handover; up.counters = ws.counters;
-            up.M = M; up.N = I; up.K = H; up.ldo = I; up.tiles = 0; up.kchunks = (H + SK_KC - 1) / SK_KC; up.eps = eps;
-            up.rope = RopeArgs{nullptr, nullptr, 0, 2, nullptr};
-            up.spin_limit = g_spin_limit.load(std::memory_order_relaxed); up.withhold_flags = 0;
-            down = up;
-            down.x = ws.h; down.gamma = nullptr; down.w0 = w_down; down.w1 = nullptr; down.out = out; down.residual = residual;
-            down.N = H; down.K = I; down.ldo = H; down.kchunks = S; down.eps = 0.f;
-            return launch_mlp_fused(up, down, epi_up, cus, stream, S) == hipSuccess ? THI_OK : THI_ERR_HIP;
-        }
+        (void)hipGetLastError();
+        SkinnyArgs up{}, down{};
+        up.x = x; up.gamma = gamma; up.w0 = w_gate; up.w1 = w_up; up.out = ws.h; up.residual = nullptr;
+        up.handover = ws.handover; up.counters = ws.counters;
+        up.M = M; up.N = I; up.K = H; up.ldo = I; up.tiles = 0; up.kchunks = (H + SK_KC - 1) / SK_KC; up.eps = eps;
+        up.rope = RopeArgs{nullptr, nullptr, 0, 2, nullptr};
+        up.spin_limit = g_spin_limit.load(std::memory_order_relaxed); up.withhold_flags = 0;
+        down = up;
+        down.x = ws.h; down.gamma = nullptr; down.w0 = w_down; down.w1 = nullptr; down.out = out; down.residual = residual;
+        down.N = H; down.K = I; down.ldo = H; down.kchunks = S; down.eps = 0.f;
+        return launch_mlp_fused(up, down, epi_up, cus, stream, S) == hipSuccess ? THI_OK : THI_ERR_HIP;
     }
-    int rc = run_projection(x, gamma, eps, w_gate, w_up, ws.h, M, I, H, I, epi_up, ws, stream);
+    int rc = run_projection(x, gamma, eps, w_gate, w_up, ws.h, M, I, H, I, epi_up, ws, stream,
+                            RopeArgs{nullptr, nullptr, 0, 2, nullptr}, nullptr, !fusible);
     if (rc != THI_OK) return rc;
     return run_projection(ws.h, nullptr, 0.f, w_down, nullptr, out, M, H, I, H, EPI_PLAIN, ws, stream,
-                          RopeArgs{nullptr, nullptr, 0, 2, nullptr}, residual);
+                          RopeArgs{nullptr, nullptr, 0, 2, nullptr}, residual, !fusible);
 }
 
 int check_common(int M, int N, int K, const void* workspace, size_t workspace_bytes, size_t need)
@@ -424,7 +467,8 @@ int thi_swiglu_gate_up(const void* x, const void* w_gate, const void* w_up, void
     if (misaligned(x, 16) || misaligned(w_gate, 16) || misaligned(w_up, 16) || misaligned(h, 16)) return THI_ERR_ALIGN;
     Workspace ws = carve(workspace, workspace_bytes, THI_OP_SWIGLU_MLP, M, H, I);
     return run_projection((const uint16_t*)x, nullptr, 0.f, (const uint16_t*)w_gate, (const uint16_t*)w_up,
-                          (uint16_t*)h, M, I, H, I, EPI_SWIGLU, ws, (hipStream_t)hip_stream);
+                          (uint16_t*)h, M, I, H, I, EPI_SWIGLU, ws, (hipStream_t)hip_stream, RopeArgs{nullptr, nullptr, 0, 2, nullptr},
+                          nullptr, !single_launch_shape(M, H, I, EPI_SWIGLU, device_cu_count()));
 }
 
 int thi_linear_residual(const void* x, const void* w, const void* residual, void* out, int M, int N, int K,
@@ -590,7 +634,8 @@ int thi_query_kernel_family(int M, int N, int K, int fused)
 {
     if (M < 1 || N < 1 || K < 1 || fused < 0 || fused > 2) return 0;
     const int epilogue = fused == 1 ? EPI_RMSNORM : fused == 2 ? EPI_SWIGLU : EPI_PLAIN;
-    const DecodePlan dp = plan_decode(M, N, K, epilogue, device_cu_count());
+    const int cus = device_cu_count();
+    const DecodePlan dp = plan_decode(M, N, K, epilogue, cus, !(fused == 2 && single_launch_shape(M, K, N, epilogue, cus)));
     return dp.kernel != 0 ? dp.kernel : 2;
 }
 

@@ -86,9 +86,50 @@ size_t gemm_partial_bytes() { return (size_t)GEMM_MAX_GRID * 2 * 128 * 128 * siz
 // us (80 rows), 6656 x 17920 at 128 70.7 -> 59 (80, S = 3), gate/up 2 x 13824 x 5120 at 72 62.7 -> 55 (112), gate/up
 // 2 x 17920 x 6656 at 64 107.7 -> 79 (144).  With more rows shared tiles only lose (15360 x 5120 at 72 tokens: 52 us with
 // two shares of 144 rows, 35.5 with 64).
+namespace {
+
+// The same kernel with a token tile of 32, for up to MID_DECODE_M tokens.  S shares of K, so that there are num_cus / S tiles, each of
+// equally many outputs (in fours), in the least tile that holds them; the S of the smallest modelled time: 4.15 us fixed,
+// 19 ns a row of the tile; for each stage of 128 k 102 ns, 6.3 ns a row of weights and 2 ns a token, with two stages 2.5 ns a row more, or what
+// 8 TB/s give if that is longer; sharing 0.8 us and 0.117 ns a row, token and share.  Fitted to 430 points on 38 calls
+// (4..32 tokens, 1536 x 4096 .. gate/up 2 x 28672 x 8192): the pick is 1.1 % slower than the best measured on average; the price is 7 % off (rms).  No tiles
+// above 176 rows: two stages of those left gate/up 2 x 28672 x 8192 at 147 us against 140 with the row blocks.
+//
+// rotate: workgroups that walk the same k at the same time ask for addresses that agree in their low bits where a row is a multiple of 4 KiB,
+// and so for few of the memory's channels: gate/up 2 x 11008 x 4096 at 32 tokens 36.5 us, with the tiles' starts spread over k 29.4; 8192 x 8192
+// in two shares 29.4, 24.6; 4096 x 11008 20.5, 19.5.  The price is that the activations are no longer read by all workgroups of an L2
+// at the same time (4096 x 4096 10.8, 11.1; 15360 x 5120 28.9, 29.3).
+MidPlan plan_mid_decode(int M, int N, int K, int epilogue, int num_cus)
+{
+    MidPlan best{0, 0, 0, 0.0, 0, false};
+    if (K > ROWSLAB_MAX_K || num_cus > SK_MAX_GRID) return best;
+    const bool swiglu = is_swiglu(epilogue);
+    const int rows_per = swiglu ? 2 : 1, ktiles = (K + 127) / 128;
+    const double stream = (double)rows_per * N * K * 2.5e-7;      // (us: 8 TB/s)
+    for (int S = 1; S <= 8 && (S == 1 || S * 4 <= ktiles); ++S) {
+        const int groups = num_cus / S;
+        if (groups < 1) break;
+        const long per = ((long)N + 4L * groups - 1) / (4L * groups) * 4, rows = per * rows_per;
+        int BN = 0;
+        for (int b : {32, 48, 64, 80, 96, 112, 128, 144, 176})
+            if (b >= rows) { BN = b; break; }
+        if (!BN) continue;
+        const int kt = (ktiles + S - 1) / S, stages = 160 * 1024 / ((BN + 32) * 256);
+        const double cu = kt * (0.0063 * rows + 0.0020 * M + 0.102 + (stages == 2 ? 0.0025 * BN : 0.0));
+        const double us = 4.15 + (cu > stream ? cu : stream) + 0.019 * BN + (S > 1 ? 0.8 + 1.17e-4 * S * BN * (M > 8 ? M : 8) : 0.0);
+        if (best.BN && us >= best.us) continue;
+        best = MidPlan{BN, (int)((N + per - 1) / per), S, us, (int)per, swiglu ? K % 2048 == 0 : K >= 8192};
+    }
+    return best;
+}
+
+}  // namespace
+
+// rotate above 32 tokens: gate/up with K = 4096 at 72 tokens 41.2 -> 38.7 us; plain shapes lose (8192 x 8192 32.3 -> 34.6).
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
 {
-    MidPlan best{0, 0, 0, 0.0};
+    MidPlan best{0, 0, 0, 0.0, 0, false};
+    if (M <= MID_DECODE_M) return plan_mid_decode(M, N, K, epilogue, num_cus);
     if (M > 128 || K > 24576) return best;
     const long V = is_swiglu(epilogue) ? 2L * N : N;      // (more than an int holds from N = 2^30 on)
     const int ktiles = (K + 127) / 128, BM = M > 96 ? 128 : M > 64 ? 96 : 64;
@@ -104,7 +145,7 @@ MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
             if (best.BN != 0 && us >= least) continue;
             least = us;
             best = MidPlan{BN, (int)tiles, S, 2.83 + 4.0e-4 * BN * BM + 0.0139 * w + 0.0073 * x + per * (0.252 + 2.5e-5 * BN * BM) +
-                                                  (S > 1 ? 1.6 + 1.0e-4 * S * BN * M : 0.0)};
+                                                  (S > 1 ? 1.6 + 1.0e-4 * S * BN * M : 0.0), is_swiglu(epilogue) ? BN / 2 : BN, is_swiglu(epilogue) && K % 2048 == 0};
         }
     }
     return best;
@@ -245,7 +286,7 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
         // wide tiles and small K (61 x 28750 x 640 12.9 us, here 11.4).  On 813 problems of 33..128 tokens, both measured, the pick is
         // 0.2 % slower than the better one on average (one factor of 1.0 for all: 1.5 %).
         const MidPlan mp = plan_mid(M, N, K, epilogue, num_cus);
-        if (mp.BN && mp.us < (mp.BN <= 80 ? 1.2 : 1.05) * plan_config(config == GEMM_FEW256 ? GEMM_FEW128 : config, M, N, K, epilogue, num_cus).us) {
+        if (mp.BN && (M <= MID_DECODE_M || mp.us < (mp.BN <= 80 ? 1.2 : 1.05) * plan_config(config == GEMM_FEW256 ? GEMM_FEW128 : config, M, N, K, epilogue, num_cus).us)) {
             GemmPlan p{};
             p.config = GEMM_MID;
             p.mid = mp;

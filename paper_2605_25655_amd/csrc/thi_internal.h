@@ -124,6 +124,8 @@ struct GemmArgs {
     int tiles;               // filled in by the launcher
     RopeArgs rope;
     unsigned* counters;      // status words, zero between calls: arrival counters of the few-token kernel's shared tiles
+    const uint16_t* gamma;   // [K] RMSNorm inside the few-token kernel (up to MID_DECODE_M tokens), or nullptr
+    float eps;
 };
 constexpr int GEMM_MAX_K = 1 << 23;   // 256 rows x 2 bytes x K within 32 bits
 constexpr int GEMM_MAX_GRID = 2048;   // in units of 128x128 partial tiles (a 256x256 tile takes four)
@@ -135,7 +137,10 @@ struct MidPlan {
     int tiles;
     int S;           // workgroups per tile, each with 1/S of K
     double us;       // modelled time
+    int per;         // outputs per tile (gate/up pairs for SwiGLU), at most what BN rows hold
+    bool rotate;     // the workgroups of a share start at different k
 };
+constexpr int MID_DECODE_M = 32;     // up to so many tokens: RMSNorm inside the kernel, sums handed over through the decode kernels' slots
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
 // The GEMM's configurations, their constants, and which of them runs a product (no RMSNorm kinds).  From GEMM_BIG on: the
 // candidates above 128 tokens.

@@ -451,6 +451,50 @@ def test_prefill_swiglu_schedules(thi, oracle_mod, M, H, I):
     assert np.isfinite(c1.astype(np.float32)).all()
 
 
+# ------------------------------------------- the few-token kernel at decode sizes (up to 32 tokens)
+# Every height of tile, tiles that the outputs do not fill and that end inside a quad, shared and alone, with a ragged K, rows of 4 KiB
+# (rotated starts), fewer k-tiles than stages; token counts at the edges of its two fragments.  Forced: the rule sends few of them there.
+@pytest.mark.parametrize("M,N,K", [
+    (1, 1536, 1032), (16, 300, 5000), (17, 12288, 264), (32, 12290, 1024), (5, 16380, 392), (31, 20000, 136), (32, 24574, 264),
+    (16, 28000, 136), (2, 32000, 264), (32, 36001, 72), (9, 44000, 136), (20, 5120, 8200), (32, 4096, 11008), (17, 8192, 8192), (32, 96, 32768),
+])
+def test_few_token_kernel_at_decode_sizes(thi, oracle_mod, M, N, K):
+    say(f"[case] few-token kernel, decode M={M} N={N} K={K}")
+    x, w, g = synth.random_problem(9100 + M + N + K, M, N, K)
+    rng = np.random.Generator(np.random.Philox(key=9200 + M + N + K))
+    res = f16(rng.standard_normal((M, N)))
+    hd, I = 64, N // 16 * 8
+    n_rot = N // hd // 2 * hd
+    pos = rng.integers(0, 4096, size=M).astype(np.int32)
+    th = _theta(hd)
+    cols = np.unique(np.concatenate([synth.sample_rows(21, N, min(N, 240)), np.arange(N - 40, N), np.arange(0, 40)]))
+    jc = np.unique(np.concatenate([synth.sample_rows(22, I, min(I, 160)), np.arange(I - 20, I), np.arange(0, 20)]))
+    r = Runner(M, K, max(I, K), N)
+    xd, wd, gd = to_dev(x), to_dev(w), to_dev(g)
+    prev = thi.thi_set_kernel_family(2)
+    try:
+        a = [to_host(r.linear_residual(xd, wd, to_dev(res))) for _ in range(2)]
+        b = [to_host(r.rmsnorm_qkv(xd, gd, 1e-6, wd)) for _ in range(2)]
+        c = to_host(r.rmsnorm_qkv_rope(xd, gd, 1e-6, wd, _dev_i32(pos), _dev_f32(th), n_rot, hd))
+        h = to_host(r.swiglu_gate_up(xd, wd[:I], wd[I:2 * I]))
+    finally:
+        thi.thi_set_kernel_family(prev)
+    for two in (a, b):
+        assert np.array_equal(two[0].view(np.uint16), two[1].view(np.uint16)), "not reproducible"
+    for out in (a[0], b[0], c, h):
+        assert np.isfinite(out.astype(np.float32)).all()
+    ws = np.ascontiguousarray(w[cols])
+    y, s = oracle_mod.linear_residual(x, ws, np.ascontiguousarray(res[:, cols]))
+    check(a[0][:, cols], y, s, "linear + residual", argmax=False)
+    y, s = oracle_mod.rmsnorm_qkv(x, g, 1e-6, ws)
+    check(b[0][:, cols], y, s, "rmsnorm", argmax=False)
+    rows = synth.sample_rows(23, M, min(M, 4))
+    y, s = oracle_mod.rmsnorm_qkv_rope(x[rows], g, 1e-6, w, pos[rows], th, n_rot, hd)
+    check(c[rows], y, s, "rope", argmax=False)
+    y, s = oracle_mod.swiglu_gate_up(x, np.ascontiguousarray(w[:I][jc]), np.ascontiguousarray(w[I:2 * I][jc]))
+    check(h[:, jc], y, s, "gate/up", argmax=False)
+
+
 # ------------------------------------------- between decode and prefill (33..128 tokens)
 # These run the few-token kernel, the RMSNorm-fronted product of up to 64 tokens the stream-K kernel; the older configurations
 # for few tokens are in KERNELS.

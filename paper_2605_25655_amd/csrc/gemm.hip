@@ -274,6 +274,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     constexpr int XPASS = BM * GPIECES / THREADS;
     constexpr int TN = BN / WN / 16;            // MFMA tiles per wave along n
     constexpr int TM = BM / WM / 16;
+    constexpr bool SPREAD_K = BN == 128 && BM == 128 && NSW == 4 && !KTAIL;       // (a ragged last k-tile stays the last)
     constexpr bool PAIRS = TN % 2 == 0;          // gate and up rows alternate by fragments of 16 rows, else by 8 rows
     constexpr int JPT = is_swiglu(EPI) ? BN / 2 : BN;   // physical weight rows per tile
     constexpr int WSTAGE = BN * GPIECES, XSTAGE = BM * GPIECES;     // 16-byte units per stage; the weight stages come first
@@ -424,14 +425,25 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
         constexpr int LPT = WPASS + XPASS;           // direct loads per k-tile per wave
         constexpr bool W_LATE = NSW >= NSX && NSW >= 3, X_LATE = NSX > NSW;
         const int nk = ke - kb;
+        // Two token tiles of the one-per-CU 128x128 kernel (129..256 tokens): the tile rows start spread over the range and wrap round, so
+        // that the workgroups do not all ask for one k of rows that lie a multiple of some KiB apart, that is for few of the memory's channels
+        // (203 tokens: 4096 x 4096 23.9 -> 21.4 us, 12288 x 4096 40.7 -> 39.3, 4096 x 11008 37.4 -> 36.3).  With more token tiles
+        // (333 x 12288 x 4096 55.5, 55.4; 1024 x 4096 x 4096 39.6, 40.0) and larger ones sharing the activations counts as much.
+        int rot = 0;
+        if constexpr (SPREAD_K) rot = tiles_m == 2 ? (int)((long)tile_n * nk / (a.tiles / tiles_m)) : 0;
+        auto k_of = [&](int i) {
+            if constexpr (!SPREAD_K) return kb + i;
+            const int k = i + rot;
+            return kb + (k < nk ? k : k - nk);
+        };
 #pragma unroll
         for (int st = 0; st < DEEP; ++st) {
             if (st < NSX - X_LATE && st < nk)
 #pragma unroll
-                for (int i = 0; i < XPASS; ++i) dma_x(kb + st, st, i);
+                for (int i = 0; i < XPASS; ++i) dma_x(k_of(st), st, i);
             if (st < NSW - W_LATE && st < nk)
 #pragma unroll
-                for (int i = 0; i < WPASS; ++i) dma_w(kb + st, st, i);
+                for (int i = 0; i < WPASS; ++i) dma_w(k_of(st), st, i);
         }
         // Only the first k-tile has to have landed (all of them where that is not a fixed number of loads: ranges shorter
         // than the stages, waves with unequal numbers of loads); the loop waits for the others one by one.  Waiting for all
@@ -460,8 +472,8 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             constexpr bool LAST = decltype(last)::value;
             const int wnext = ws + 1 == NSW ? 0 : ws + 1, xnext = xs + 1 == NSX ? 0 : xs + 1;
             auto late = [&](int d) {
-                if (W_LATE && (!LAST || it - 1 + NSW < nk)) dma_w(kb + it - 1 + NSW, wprev, d);
-                if (X_LATE && (!LAST || it - 1 + NSX < nk)) dma_x(kb + it - 1 + NSX, xprev, d);
+                if (W_LATE && (!LAST || it - 1 + NSW < nk)) dma_w(k_of(it - 1 + NSW), wprev, d);
+                if (X_LATE && (!LAST || it - 1 + NSX < nk)) dma_x(k_of(it - 1 + NSX), xprev, d);
             };
             auto none = [](int) {};
             using std::integral_constant;
@@ -482,8 +494,8 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
             if (KTAIL && LAST && it + 1 < nk) zero_tail(kb + it + 1, wnext, xnext);
             __syncthreads();
             auto early = [&](int d) {
-                if (!X_LATE && d < XPASS) { if (!LAST || it + NSX < nk) dma_x(kb + it + NSX, xs, d); }
-                else if (!LAST || it + NSW < nk) dma_w(kb + it + NSW, ws, X_LATE ? d : d - XPASS);
+                if (!X_LATE && d < XPASS) { if (!LAST || it + NSX < nk) dma_x(k_of(it + NSX), xs, d); }
+                else if (!LAST || it + NSW < nk) dma_w(k_of(it + NSW), ws, X_LATE ? d : d - XPASS);
             };
             const bool more = !LAST || it + 1 < nk;              // (behind the last k-tile: read and never used)
             const uintx4 *wl = w_lane(more ? wnext : ws, 0), *xl = x_lane(more ? xnext : xs, 0);

@@ -451,6 +451,22 @@ def test_prefill_swiglu_schedules(thi, oracle_mod, M, H, I):
     assert np.isfinite(c1.astype(np.float32)).all()
 
 
+# Two token tiles of the one-per-CU 128x128 kernel start their tile rows spread over k: whole tiles and ranges, one row of tiles, fewer
+# k-tiles than rows of tiles, ranges of unequal length.
+@pytest.mark.parametrize("M,N,K", [(129, 4096, 4096), (203, 12288, 320), (256, 392, 1216), (200, 4096, 11008), (130, 16, 640), (255, 2000, 64)])
+def test_spread_starts_of_two_token_tiles(thi, oracle_mod, M, N, K):
+    say(f"[case] two token tiles M={M} N={N} K={K}")
+    x, w, g = synth.random_problem(9300 + M + N + K, M, N, K)
+    res = f16(np.random.Generator(np.random.Philox(key=9400 + M + N + K)).standard_normal((M, N)))
+    r = Runner(M, K, K, N)
+    xd, wd, rd = to_dev(x), to_dev(w), to_dev(res)
+    got = [to_host(r.linear_residual(xd, wd, rd)) for _ in range(2)]
+    assert np.array_equal(got[0].view(np.uint16), got[1].view(np.uint16)), "not reproducible"
+    rows = synth.sample_rows(31, M, 12)
+    y, s = oracle_mod.linear_residual(x[rows], w, res[rows])
+    check(got[0][rows], y, s, "linear + residual", argmax=False)
+
+
 # ------------------------------------------- the few-token kernel at decode sizes (up to 32 tokens)
 # Every height of tile, tiles that the outputs do not fill and that end inside a quad, shared and alone, with a ragged K, rows of 4 KiB
 # (rotated starts), fewer k-tiles than stages; token counts at the edges of its two fragments.  Forced: the rule sends few of them there.

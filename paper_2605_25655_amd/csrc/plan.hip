@@ -258,6 +258,16 @@ GemmPlan plan_config(int config, int M, int N, int K, int epilogue, int num_cus)
     p.sk_tiles = s.sk_tiles;
     p.parts = s.parts;
     p.us = s.us;
+    // No more workgroups than have work, and in whole rounds as many in each: consecutive workers share an XCD, so the ones without work
+    // would be the last XCDs', whose L2 and whose way to memory then idle while the others queue (333 x 5001 x 1384 as 120 tiles: the first four
+    // XCDs only).  203 x 12288 x 4096 41.5 -> 40.1 us, 333 x 5001 x 1384 22.4 -> 21.3, 1024 x 12288 x 4096 as 192 tiles of 256 rows 105 -> 98,
+    // 1024 x 4096 x 4096 as 88 tiles of 192 rows in 2 ranges 57.7 -> 51.7, 512 x 27648 x 5120 as 432 tiles of 128 rows 149.6 -> 148.0.
+    if (p.sk_tiles == 0 && p.tiles > 0) {
+        const int rounds = (p.tiles + p.grid - 1) / p.grid;
+        p.grid = (p.tiles + rounds - 1) / rounds;
+    } else if (p.sk_tiles == p.tiles && p.parts >= 1) {
+        p.grid = p.tiles * p.parts;
+    }
     return p;
 }
 

@@ -258,6 +258,10 @@ __global__ __launch_bounds__(64 * FIXUP_WAVES) void gemm_fixup(GemmArgs a, int t
 // stages) 42.5 -> 41.0.  The deeper operand alone, without the order, gains nothing with 256 rows and 4-8 % with 192.
 // The 256x256 tile takes all 256 VGPRs and spills up to four (20 with a ragged K; gate/up none, 16 ragged) around a tile's
 // prologue and epilogue; the k loop reloads nothing.
+// The 128x128 tiles wait for memory: a CU has 64 KiB of loads in flight, in order, whatever the stages hold, so its rate is that over the
+// latency (203 x 12288 x 4096: 39.5 us, with the loads alone 38.5, with the arithmetic alone 22.7, with weights from the L2 31).  Stages of
+// 128 k ask for whole pairs of lines of a row: 512 x 5120 x 5120 51.4 -> 45.6 us, 900 x 9000 x 8008 197 -> 174 (a ragged row
+// piece of 128 bytes lies on two lines, of 256 bytes on three); which K take them is plan_gemm's.
 // Eight waves everywhere but in the 64-token configuration: with four (one per SIMD) nothing covers a wave's wait for
 // its fragments, and the 256x128 and 128x128 tiles lost 8-10 %.
 template <int BN, int BM, int WN, int WM, int GK, int NSW, int NSX, int EPI, bool KTAIL>
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
         constexpr int LPT = WPASS + XPASS;           // direct loads per k-tile per wave
         constexpr bool W_LATE = NSW >= NSX && NSW >= 3, X_LATE = NSX > NSW;
         const int nk = ke - kb;
-        // Two token tiles of the one-per-CU 128x128 kernel (129..256 tokens): the tile rows start spread over the range and wrap round, so
+        // Two token tiles of the 128x128 kernel with 64-k stages (129..256 tokens): the tile rows start spread over the range and wrap round, so
         // that the workgroups do not all ask for one k of rows that lie a multiple of some KiB apart, that is for few of the memory's channels
         // (203 tokens: 4096 x 4096 23.9 -> 21.4 us, 12288 x 4096 40.7 -> 39.3, 4096 x 11008 37.4 -> 36.3).  With more token tiles
         // (333 x 12288 x 4096 55.5, 55.4; 1024 x 4096 x 4096 39.6, 40.0) and larger ones sharing the activations counts as much.
@@ -694,7 +698,8 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     case GEMM_R192: return launch_cfg<192, 256, 2, 4, 64, 3, 2, false>(a, epilogue, p, stream);
     case GEMM_R160: return launch_cfg<160, 256, 2, 4, 64, 2, 3, false>(a, epilogue, p, stream);
     case GEMM_ONE: case GEMM_TALL: return launch_cfg<128, 256, 2, 4, 64, 3, 3, false>(a, epilogue, p, stream);
-    case GEMM_FEW128: case GEMM_DEEP: return launch_cfg<128, 128, 2, 4, 64, 4, 4, true>(a, epilogue, p, stream);
+    case GEMM_FEW128: return launch_cfg<128, 128, 2, 4, 64, 4, 4, true>(a, epilogue, p, stream);
+    case GEMM_DEEP: return launch_cfg<128, 128, 2, 4, 128, 3, 2, true>(a, epilogue, p, stream);
     case GEMM_SMALL: return launch_cfg<128, 128, 2, 4, 64, 3, 2, true>(a, epilogue, p, stream);
     default: return hipErrorInvalidValue;
     }

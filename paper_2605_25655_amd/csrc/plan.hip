@@ -172,7 +172,7 @@ namespace {
 // A workgroup's speed by configuration, fitted to measurements of every configuration and cut on projections of the
 // 7B..70B shapes and some odd ones at M = 200..2048 (weight copies rotated so that they come from HBM): 256x256 tiles
 // 5.4 TFLOP/s + 6 us per tile, 224 / 192 / 160 rows x 256 tokens 4.75 / 4.7 / 4.4 + 6 us, 128 rows x 256 tokens 4.6 TFLOP/s + 5 us, 128x128 tiles two per CU 1.95 TFLOP/s + 6 us,
-// 128x128 with four stages one per CU 3.6 TFLOP/s + 4 us; the second pass 8 us (a launch and its latencies: 5 us made
+// 128x128 one per CU (stages of 64 or 128 k) 3.6 TFLOP/s + 4 us; the second pass 8 us (a launch and its latencies: 5 us made
 // 333 x 512 x 1376 cut 12 tiles in 21 ranges, 21.2 us against 16.1 whole) + its bytes at ~8 TB/s (they are still
 // in the caches).  A share of a tile pays the fixed time in full, however small it is: priced by the share, as equal
 // contiguous shares were, it made cut tiles look up to 5 us cheaper than they are (129 x 4096 x 11008 as 32 tiles of 128 rows x
@@ -187,9 +187,9 @@ struct Schedule {
     double us;
 };
 
-constexpr double SECOND_PASS_US = 8.0;
+constexpr double SECOND_PASS_US = 7.85;
 
-Schedule plan_schedule(int M, int tiles, int tiles_m, int grid, int BN, int BM, int K, double wg_tflops, double tile_fixed_us, bool cut)
+Schedule plan_schedule(int M, int tiles, int tiles_m, int grid, int BN, int BM, int ktiles, int K, double wg_tflops, double tile_fixed_us, bool cut)
 {
     double work_us = 2.0 * BN * BM * (double)K / (wg_tflops * 1e6);
     if (BM == 128) work_us *= 1.0 - 0.1 * (1.0 - (double)M / ((double)tiles_m * BM));
@@ -202,7 +202,6 @@ Schedule plan_schedule(int M, int tiles, int tiles_m, int grid, int BN, int BM, 
     const double tile_bytes = (double)BN * BM * 4.0;
     const double whole = (double)((tiles + grid - 1) / grid) * tile_us;
     if (rem == 0 || !cut) return Schedule{0, tiles_m == 1 ? 0 : 1, whole};
-    const int ktiles = (K + 63) / 64;
     int parts = grid / rem;
     if (parts > ktiles) parts = ktiles;
     // One token tile: equal contiguous shares for the few-token configurations, and for a 256-token tile
@@ -212,7 +211,10 @@ Schedule plan_schedule(int M, int tiles, int tiles_m, int grid, int BN, int BM, 
         return shared < whole ? Schedule{rem, 0, shared} : Schedule{0, 0, whole};
     }
     if (parts < 2) return Schedule{0, 1, whole};
-    const double shared = (double)full * tile_us + tile_fixed_us + work_us / parts + SECOND_PASS_US +
+    // (a range takes 4 us at least: 554 x 512 x 1376 as 20 tiles in 11 ranges 17.7 us, whole 13.4; fewer than eight tiles are
+    // better cut in any case)
+    const double range_us = full == 0 && tiles >= 8 && work_us < 4.0 * parts ? 4.0 : work_us / parts;
+    const double shared = (double)full * tile_us + tile_fixed_us + range_us + SECOND_PASS_US +
                           (double)rem * parts * tile_bytes * 2.0 / 8.0e6;
     return shared < whole ? Schedule{rem, parts, shared} : Schedule{0, 1, whole};
 }
@@ -224,7 +226,7 @@ GemmTile gemm_tile(int config)
 {
     switch (config) {
     case GEMM_FEW64: return GemmTile{128, 64, 128, true, false, 1, 900.0 / 256, 4.0};      // one token tile: bound by the weight stream anyway
-    case GEMM_FEW128: return GemmTile{128, 128, 64, true, true, 1, 900.0 / 256, 4.0};      // (the kernel of GEMM_DEEP)
+    case GEMM_FEW128: return GemmTile{128, 128, 64, true, true, 1, 3.6, 4.0};      // (above 128 tokens too: plan_gemm)
     case GEMM_FEW256: return GemmTile{256, 128, 64, true, false, 1, 900.0 / 256, 4.0};
     case GEMM_ONE: return GemmTile{128, 256, 64, true, false, 1, 900.0 / 256, 4.0};        // (the kernel of GEMM_TALL)
     case GEMM_BIG: return GemmTile{256, 256, 64, true, true, 1, 5.4, 6.0};
@@ -232,7 +234,7 @@ GemmTile gemm_tile(int config)
     case GEMM_R192: return GemmTile{192, 256, 64, true, false, 1, 4.7, 6.0};
     case GEMM_R160: return GemmTile{160, 256, 64, false, false, 1, 4.4, 6.0};
     case GEMM_TALL: return GemmTile{128, 256, 64, true, false, 1, 4.6, 5.0};
-    case GEMM_DEEP: return GemmTile{128, 128, 64, true, true, 1, 3.6, 4.0};
+    case GEMM_DEEP: return GemmTile{128, 128, 128, true, true, 1, 3.6, 4.0};
     case GEMM_SMALL: return GemmTile{128, 128, 64, true, true, 2, 1.95, 6.0};
     default: return GemmTile{};
     }
@@ -254,7 +256,7 @@ GemmPlan plan_config(int config, int M, int N, int K, int epilogue, int num_cus)
     if (grid > most) grid = most;
     if (grid > units) grid = units;
     p.grid = (int)grid;
-    const Schedule s = plan_schedule(M, p.tiles, p.tiles_m, p.grid, t.BN, t.BM, K, t.wg_tflops, t.fixed_us, t.cut);
+    const Schedule s = plan_schedule(M, p.tiles, p.tiles_m, p.grid, t.BN, t.BM, p.ktiles, K, t.wg_tflops, t.fixed_us, t.cut);
     p.sk_tiles = s.sk_tiles;
     p.parts = s.parts;
     p.us = s.us;
@@ -323,10 +325,24 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
     // 300 x 22016 x 4096 100 -> 85, 1024 x 12288 x 4096 110 -> 99; 160 rows 2048 x 5120 x 13824 286 -> 250, 2048 x 5120 x
     // 5120 118 -> 99, 512 x 19968 x 6656 150 -> 132, 1024 x 10240 x 8192 170 -> 152.  Not where the 256-row tile fills its
     // rounds as well: per flop they read more operand bytes (gate/up 2048 x 57344 x 8192 with 224 rows 1625 us, 1505).
+    // 128x128 tiles, one workgroup per CU: stages of 64 k, four of them (FEW128), or of 128 k, three and two (DEEP)?  A load of 128 k
+    // asks for pairs of lines, and where the rows do not start on a line (a ragged K) for three lines in the place of four; but K is
+    // rounded up to 128, and its prologue is longer.  512 x 5120 x 5120 51.4 -> 45.6 us, 900 x 9000 x 8008 197 -> 174, 200 x 9000 x
+    // 2008 28.7 -> 24.6, 587 x 4984 x 3352 42.5 -> 36.9, gate/up 366 x 11008 x 4096 101.5 -> 95.6; 471 x 404 x 1472 11.3 with 64 k (12.9), and
+    // two token tiles start spread over k there: 203 x 12288 x 4096 38.4 (39.8).  Fewer than eight tiles are cut into many ranges
+    // and take 128 k (247 x 173 x 2048 16.5 -> 12.0).  The shortest K go to SMALL, whose prologue is the shortest (300 x 1054 x 320 6.1, 64 k 6.3, 128 k 7.8).
+    const int tiles_m = (M + 127) / 128;
+    const bool deep = K % 64 || tiles_m * t128 < 8 || (K % 128 == 0 && (K >= 8192 || (tiles_m >= 3 && K >= 1024)));
+    const bool shortest = K < (K % 64 ? 448 : 384) && tiles_m * t128 >= 8;
     GemmPlan best = plan_config(GEMM_BIG, M, N, K, epilogue, num_cus);
     for (int c = GEMM_BIG + 1; c <= GEMM_SMALL; ++c) {
         if (!even_k && !gemm_tile(c).ragged) continue;
-        const GemmPlan p = plan_config(c, M, N, K, epilogue, num_cus);
+        GemmPlan p = plan_config(c == GEMM_DEEP && !deep ? GEMM_FEW128 : c, M, N, K, epilogue, num_cus);
+        if (c == GEMM_DEEP && shortest) {        // (priced as those: SMALL's own price is that of two workgroups on a CU)
+            const double us = p.us;
+            p = plan_config(GEMM_SMALL, M, N, K, epilogue, num_cus);
+            p.us = us;
+        }
         if (p.us < best.us) best = p;
     }
     return best;

@@ -467,6 +467,27 @@ def test_spread_starts_of_two_token_tiles(thi, oracle_mod, M, N, K):
     check(got[0][rows], y, s, "linear + residual", argmax=False)
 
 
+# The 128x128 kernel's stages of 128 k: a K that ends in the first and in the last piece of a stage, one to six k-tiles, whole tiles and ranges.
+@pytest.mark.parametrize("M,N,K", [(129, 1000, 1032), (256, 1111, 1144), (385, 1500, 1280), (300, 2003, 8 * 129 + 128), (400, 3001, 456), (270, 1030, 8 * 95),
+                                   (130, 130, 8), (200, 300, 136), (140, 100, 256), (250, 257, 2000), (512, 5000, 5120), (385, 1029, 8200)])
+def test_stages_of_128_k(thi, oracle_mod, M, N, K):
+    say(f"[case] 128x128, 128-k stages M={M} N={N} K={K}")
+    x, w, g = synth.random_problem(9500 + M + N + K, M, N, K)
+    res = f16(np.random.Generator(np.random.Philox(key=9600 + M + N + K)).standard_normal((M, N)))
+    hd, pos = 8, np.arange(M, dtype=np.int32) * 3
+    th, n_rot = _theta(8), N // 2 // 8 * 8
+    r = Runner(M, K, K, N)
+    xd, wd, rd, gd = to_dev(x), to_dev(w), to_dev(res), to_dev(g)
+    got = [to_host(r.linear_residual(xd, wd, rd)) for _ in range(3)]
+    assert all(np.array_equal(got[0].view(np.uint16), v.view(np.uint16)) for v in got[1:]), "not reproducible"
+    c = to_host(r.rmsnorm_qkv_rope(xd, gd, 1e-6, wd, _dev_i32(pos), _dev_f32(th), n_rot, hd))
+    rows = synth.sample_rows(37, M, 12)
+    y, s = oracle_mod.linear_residual(x[rows], w, res[rows])
+    check(got[0][rows], y, s, "linear + residual", argmax=False)
+    y, s = oracle_mod.rmsnorm_qkv_rope(x[rows], g, 1e-6, w, pos[rows], th, n_rot, hd)
+    check(c[rows], y, s, "rmsnorm_qkv_rope", argmax=False)
+
+
 # ------------------------------------------- the few-token kernel at decode sizes (up to 32 tokens)
 # Every height of tile, tiles that the outputs do not fill and that end inside a quad, shared and alone, with a ragged K, rows of 4 KiB
 # (rotated starts), fewer k-tiles than stages; token counts at the edges of its two fragments.  Forced: the rule sends few of them there.

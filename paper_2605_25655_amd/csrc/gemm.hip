@@ -238,6 +238,45 @@ __global__ __launch_bounds__(64 * FIXUP_WAVES) void gemm_fixup(GemmArgs a, int t
     store_pair<BN, BM, WN, WM, EPI>(a, t / tiles_m, t % tiles_m, wn, wm, tp, tm, lr, hi, g0, g1);
 }
 
+// Workers are numbered so that consecutive ones (neighbouring tiles) share an XCD: hardware deals workgroup ids round-robin to the eight.
+struct XcdShare {
+    int first, count;        // the workers of an XCD
+    __device__ __forceinline__ XcdShare(int G, int xcd) : first(xcd * (G / 8) + (xcd < G % 8 ? xcd : G % 8)), count(G / 8 + (xcd < G % 8)) {}
+};
+
+// What a compute unit without a tile does: it touches the weights of the tiles on its XCD, one dword of every 128 bytes, k-tile by k-tile for all
+// rows, so that the workgroups multiplying them find them in the L2.  They have 64 KiB of loads in flight each, in order, and wait
+// for memory; a touch brings a line for a dword of that, 75-110 GB/s a CU.  Nothing depends on it: no value is used, and it ends
+// with its lines wherever the others are.  512 x 5120 x 5120 (160 tiles) 45.6 -> 38.5 us, 333 x 5001 x 1384 (120) 19.0 -> 16.1,
+// 200 x 9000 x 2008 24.6 -> 20.8, 587 x 4984 x 3352 (195) 37.0 -> 32.0.  Touching the activations too gains nothing (39.1, 15.5, 20.7); touched by
+// the workgroups that multiply, the lines are waited for in order: 43.9 instead of 38.5, with two token tiles no gain.
+template <int BN>
+__device__ __forceinline__ void touch_weights(const GemmArgs& a, int tiles_m, int G)
+{
+    const XcdShare on(G, blockIdx.x % 8);
+    const int r0 = on.first / tiles_m * BN, past = ((on.first + on.count - 1) / tiles_m + 1) * BN;
+    const int rows = (past < a.N ? past : a.N) - r0, lines = (a.K + 63) / 64;
+    if (rows <= 0) return;
+    const int each = (gridDim.x - G) / 8 * blockDim.x;         // threads on this XCD that touch
+    const int dk = each / rows, dr = each % rows;
+    int i = (blockIdx.x - G) / 8 * blockDim.x + threadIdx.x;
+    int k = i / rows, r = i % rows;
+    const long total = (long)rows * lines;
+    constexpr int U = 8;
+    for (long i0 = i - (long)(threadIdx.x % 64); i0 < total; i0 += (long)U * each) {       // (uniform in a wave)
+        unsigned v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v[u] = *reinterpret_cast<const unsigned*>(a.w0 + (size_t)(r0 + r) * a.K + (k < lines ? k : lines - 1) * 64);
+            k += dk;
+            r += dr;
+            if (r >= rows) { r -= rows; ++k; }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) asm volatile("" ::"v"(v[u]));        // (loaded, not used)
+    }
+}
+
 // BN x BM output tile, WN x WM waves; wave tile (BN/WN) x (BM/WM) built from 16x16 MFMA tiles.
 // KTAIL: K is not a multiple of GK.  The last k-tile's pieces past K are loaded from the k-tile's first piece (valid
 // memory) and overwritten with zeros once they have landed; K is a multiple of 8, so a 16-byte piece is entirely inside
@@ -265,7 +304,7 @@ __global__ __launch_bounds__(64 * FIXUP_WAVES) void gemm_fixup(GemmArgs a, int t
 // Eight waves everywhere but in the 64-token configuration: with four (one per SIMD) nothing covers a wave's wait for
 // its fragments, and the 256x128 and 128x128 tiles lost 8-10 %.
 template <int BN, int BM, int WN, int WM, int GK, int NSW, int NSX, int EPI, bool KTAIL>
-__global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int tiles_m, int ktiles, int sk_tiles, int parts)
+__global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int tiles_m, int ktiles, int sk_tiles, int parts, int workers)
 {
     constexpr int NWAVES = WN * WM;
     constexpr int THREADS = 64 * NWAVES;
@@ -279,6 +318,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     constexpr int TN = BN / WN / 16;            // MFMA tiles per wave along n
     constexpr int TM = BM / WM / 16;
     constexpr bool SPREAD_K = BN == 128 && BM == 128 && NSW == 4 && !KTAIL;       // (a ragged last k-tile stays the last)
+    constexpr bool TOUCH = BN == 128 && BM == 128 && (GK == 128 || NSW == 4) && !is_swiglu(EPI);
     constexpr bool PAIRS = TN % 2 == 0;          // gate and up rows alternate by fragments of 16 rows, else by 8 rows
     constexpr int JPT = is_swiglu(EPI) ? BN / 2 : BN;   // physical weight rows per tile
     constexpr int WSTAGE = BN * GPIECES, XSTAGE = BM * GPIECES;     // 16-byte units per stage; the weight stages come first
@@ -295,13 +335,15 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
     const int lr = lane & 15, hi = lane >> 4;       // operand row (column) and 8-element k group; token and quad of rows
     const int K = a.K;
 
-    // XCD-aware worker numbering: consecutive workers (neighbouring tiles) share an XCD
-    const int G = gridDim.x;
-    int worker;
-    {
-        const int bid = blockIdx.x, per = G / 8, rem = G % 8, xcd = bid % 8, local = bid / 8;
-        worker = xcd * per + (xcd < rem ? xcd : rem) + local;
+    // Workgroups past the workers have no tile: they run ahead through the weights (plan_gemm says where)
+    const int G = TOUCH ? workers : (int)gridDim.x;
+    if constexpr (TOUCH) {
+        if ((int)blockIdx.x >= G) {
+            touch_weights<BN>(a, tiles_m, G);
+            return;
+        }
     }
+    const int worker = XcdShare(G, blockIdx.x % 8).first + blockIdx.x / 8;
     // The first sk_tiles tiles are cut along K and dealt as `Deal` says; the others are taken whole,
     // round-robin.  The shared tiles come first: their partial tiles are long written when the kernel ends.
     const Deal deal(sk_tiles, ktiles, G, parts);
@@ -555,7 +597,7 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, const GemmPlan& p, hipStream_t s
     a.tiles = p.tiles;
     const int tiles_m = p.tiles_m, ktiles = p.ktiles, grid = p.grid, sk_tiles = p.sk_tiles, parts = p.parts;
     const size_t lds = ((size_t)NSW * BN + (size_t)NSX * BM) * (GK / 8) * sizeof(uintx4);
-    dim3 g((unsigned)grid), b(64 * WN * WM);
+    dim3 g((unsigned)(grid + p.helpers)), b(64 * WN * WM);
 #define THI_LAUNCH_K(E, KT)                                                                                  \
     do {                                                                                                     \
         auto kern = gemm_streamk<BN, BM, WN, WM, GK, NSW, NSX, E, KT>;                                                      \
@@ -564,7 +606,7 @@ hipError_t launch_cfg(GemmArgs a, int epilogue, const GemmPlan& p, hipStream_t s
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                   \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                 \
         });                                                                                                  \
-        hipLaunchKernelGGL(kern, g, b, lds, stream, a, tiles_m, ktiles, sk_tiles, parts);                    \
+        hipLaunchKernelGGL(kern, g, b, lds, stream, a, tiles_m, ktiles, sk_tiles, parts, grid);              \
         if constexpr (CUT) {                                                                                 \
             if (sk_tiles > 0)                                                                                \
                 hipLaunchKernelGGL((gemm_fixup<BN, BM, WN, WM, E>),                                                   \

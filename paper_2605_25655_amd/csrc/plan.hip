@@ -332,18 +332,47 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
     // two token tiles start spread over k there: 203 x 12288 x 4096 38.4 (39.8).  Fewer than eight tiles are cut into many ranges
     // and take 128 k (247 x 173 x 2048 16.5 -> 12.0).  The shortest K go to SMALL, whose prologue is the shortest (300 x 1054 x 320 6.1, 64 k 6.3, 128 k 7.8).
     const int tiles_m = (M + 127) / 128;
-    const bool deep = K % 64 || tiles_m * t128 < 8 || (K % 128 == 0 && (K >= 8192 || (tiles_m >= 3 && K >= 1024)));
-    const bool shortest = K < (K % 64 ? 448 : 384) && tiles_m * t128 >= 8;
+    const bool deep = K % 64 || (tiles_m * t128 < 8 && K >= 1024) || (K % 128 == 0 && (K >= 8192 || (tiles_m >= 3 && K >= 1024)));
+    const bool shortest = K < (K % 64 ? 448 : 384);
     GemmPlan best = plan_config(GEMM_BIG, M, N, K, epilogue, num_cus);
     for (int c = GEMM_BIG + 1; c <= GEMM_SMALL; ++c) {
         if (!even_k && !gemm_tile(c).ragged) continue;
         GemmPlan p = plan_config(c == GEMM_DEEP && !deep ? GEMM_FEW128 : c, M, N, K, epilogue, num_cus);
+        // (their price is above what they take with few ranges: 731 x 1513 x 6592 in three 29.9 us, 256x256 tiles 35.9; 253 x 2890 x 10816 33.1, 39.1)
+        if (c == GEMM_DEEP && p.sk_tiles == p.tiles && K >= (tiles_m > 2 ? 4096 : 8192) && K <= 16384) p.us *= p.parts <= 4 && tiles_m > 2 ? 0.87 : 0.95;
         if (c == GEMM_DEEP && shortest) {        // (priced as those: SMALL's own price is that of two workgroups on a CU)
             const double us = p.us;
             p = plan_config(GEMM_SMALL, M, N, K, epilogue, num_cus);
             p.us = us;
         }
         if (p.us < best.us) best = p;
+    }
+    // 128x128 tiles, whole, with the compute units that get none touching the weights ahead: where that leaves 48 and more, and a tile takes
+    // no longer than its ranges and their second pass would.  Its time was fitted to 300 products of 8..208 tiles (8 % rms); a cut
+    // schedule's price is above what it takes with few ranges (530 x 2688 x 2511, two ranges: 27 for 20.2 us), hence the factors.  Not for two token
+    // tiles in many tiles with a K that has them start spread over k (228 x 12288 x 4096 40.1, 39.3 without) or a long one (166 x 8192 x
+    // 28672 250, 214 without): the touching units then lag behind the few that share a weight row.  Gate/up never has so few tiles but for toy sizes.
+    const long whole = (long)tiles_m * t128;
+    if (!is_swiglu(epilogue) && !shortest && whole >= 8 && whole <= num_cus - 48 && K <= 16384 &&
+        (tiles_m > 2 || whole <= num_cus / 2 || (!even_k && K < 2048))) {
+        const double slope = even_k ? 0.0042 + 1.6e-5 * whole : 0.0052 + 1.9e-5 * whole;
+        const double us = 5.0 + K * slope * (tiles_m == 2 ? 1.12 : 1.0);
+        // (128x128 tiles whole without the touching: never faster)
+        auto takes = [&](const GemmPlan& p) {
+            return p.us * (p.sk_tiles == 0 ? (p.tiles == whole ? 2.0 : 0.95) : p.parts == 2 ? 0.78 : p.parts <= 4 ? 0.87 : 0.95);
+        };
+        const double cut = takes(plan_config(deep ? GEMM_DEEP : GEMM_FEW128, M, N, K, epilogue, num_cus)), other = takes(best) < cut ? takes(best) : cut;
+        if (us < other) {
+            best = plan_config(!even_k || (K % 128 == 0 && K >= 4096) ? GEMM_DEEP : GEMM_FEW128, M, N, K, epilogue, num_cus);
+            best.sk_tiles = 0;
+            best.parts = 1;
+            best.grid = (int)whole;
+            best.us = us;
+            // (a quarter of the units is enough, and more ask for the same lines as often as the others where the weights come from the
+            // last-level cache: 333 x 5001 x 1384 cold / from there: none 19.2 / 14.7 us, 136 16.0 / 15.1, 64 15.9 / 14.5; 200 x 9000 x 2008 24.5 /
+            // 18.3, 20.9 / 19.9, 20.7 / 18.6)
+            best.helpers = (num_cus - (int)whole < num_cus / 4 ? num_cus - (int)whole : num_cus / 4) / 8 * 8;
+        }
     }
     return best;
 }

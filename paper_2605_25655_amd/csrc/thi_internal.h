@@ -158,6 +158,7 @@ struct GemmPlan {
     int tiles, tiles_m, ktiles;      // output tiles, token tiles, k-tiles of K
     int grid, sk_tiles, parts;       // workgroups; the first sk_tiles tiles are cut along K, into `parts` equal ranges (0: equal shares)
     double us;                       // modelled time
+    int helpers;                     // workgroups behind the grid, for compute units without a tile: they touch the weights ahead (a multiple of 8)
 };
 GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus);
 hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t stream);

@@ -71,6 +71,16 @@ def test_the_gpu_tests_run_the_kernels_they_are_listed_for(plan):
     assert {plan(PLAIN, *t).config for t in RAGGED} == {"MID", "DEEP", "SMALL"}
 
 
+def test_whole_128_tiles_leave_units_that_touch_the_weights(plan):
+    from tests.test_parity_gpu import TOUCHED
+    picks = [plan(PLAIN, *t) for t in TOUCHED]
+    assert all(p.config in ("DEEP", "FEW128") and p.cut == 0 and 8 <= p.tiles == p.grid <= 256 - 48 for p in picks), picks
+    assert {p.config for p in picks} == {"DEEP", "FEW128"} and {8, 208} <= {p.tiles for p in picks}
+    # two token tiles whose starts are spread over k, gate/up, and few tiles with a long K: not these
+    assert plan(PLAIN, 203, 12288, 4096).tiles == 192 and plan(PLAIN, 203, 4096, 4096).cut == 64
+    assert plan(PLAIN, 372, 512, 4096).cut > 0
+
+
 def test_rows_beyond_31_bits_do_not_wrap(plan):
     """More virtual rows than an int holds: no tile count of the few-token kernel comes near the compute units'."""
     assert plan(GATE_UP, 40, 2 ** 30 + 8, 8).config != "MID"

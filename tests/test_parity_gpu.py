@@ -488,6 +488,25 @@ def test_stages_of_128_k(thi, oracle_mod, M, N, K):
     check(c[rows], y, s, "rmsnorm_qkv_rope", argmax=False)
 
 
+# Whole 128x128 tiles with the idle compute units touching the weights ahead: as few tiles as it takes and as many, tiles that do not divide by the
+# XCDs, rows that end inside an XCD's last tile, one k-tile and a ragged last one, both kinds of stages.
+TOUCHED = [(129, 453, 512), (385, 200, 1472), (300, 4321, 1096), (640, 5211, 968), (1500, 2049, 1544), (1024, 3328, 1024), (256, 8065, 1032), (1200, 100, 456),
+           (385, 1300, 448), (600, 5000, 4096)]
+
+
+@pytest.mark.parametrize("M,N,K", TOUCHED)
+def test_weights_touched_by_idle_compute_units(thi, oracle_mod, M, N, K):
+    say(f"[case] weights touched ahead M={M} N={N} K={K}")
+    x, w, g = synth.random_problem(9600 + M + N + K, M, N, K)
+    r = Runner(M, K, K, N)
+    xd, wd = to_dev(x), to_dev(w)
+    got = [to_host(r.linear(xd, wd)) for _ in range(3)]
+    assert all(np.array_equal(got[0].view(np.uint16), v.view(np.uint16)) for v in got[1:]), "not reproducible"
+    rows = synth.sample_rows(41, M, 12)
+    y, s = oracle_mod.linear(x[rows], w)
+    check(got[0][rows], y, s, "linear", argmax=False)
+
+
 # ------------------------------------------- the few-token kernel at decode sizes (up to 32 tokens)
 # Every height of tile, tiles that the outputs do not fill and that end inside a quad, shared and alone, with a ragged K, rows of 4 KiB
 # (rotated starts), fewer k-tiles than stages; token counts at the edges of its two fragments.  Forced: the rule sends few of them there.

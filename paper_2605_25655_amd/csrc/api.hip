@@ -206,22 +206,24 @@ int pick_decode_kernel(int M, int N, int K, int epilogue, int cus, double* us = 
 bool few_token_kernel_ok(int M, int N, int K, int epilogue, int cus, int kernel, double us)
 {
     if (K < 1024 || kernel == DK_ROWSLAB || g_rowblock_split.load(std::memory_order_relaxed) != 0) return false;
+    const bool swiglu = is_swiglu(epilogue);
+    if (kernel == DK_ROWBLOCK && M <= 16 && !(swiglu && M > 4)) return false;      // (before a plan is made)
     const MidPlan mp = plan_mid(M, N, K, epilogue, cus);
     if (!mp.BN) return false;
-    const bool swiglu = is_swiglu(epilogue);
     const double mid = mp.us + (is_rms(epilogue) ? 0.4 + 0.09 * (((K + 127) / 128 + mp.S - 1) / mp.S) : 0.0);
     if (kernel == DK_STREAMK) return mid < 1.05 * us;
     if (M > 16) return mid < (swiglu ? 1.2 : is_rms(epilogue) ? 0.95 : 1.0) * us;
-    return swiglu && M > 4 && mid < 0.9 * us;
+    return mid < 0.9 * us;
 }
 
-// Does the single-launch MLP serve the shape?  Its gate/up and down projections run as row blocks then, whatever else would be faster.
-bool single_launch_shape(int M, int H, int I, int epi_up, int cus)
+// Does the single-launch MLP serve the shape, and with how many workgroups per block of the down projection (0: no)?  Its gate/up and down
+// projections run as row blocks then, whatever else would be faster.  (The token range first: other calls plan nothing for it.)
+int single_launch_split(int M, int H, int I, int epi_up, int cus)
 {
-    if (M > SKINNY_MAX_M || g_family.load(std::memory_order_relaxed) != 0) return false;
+    if (M < MLP_FUSED_MIN_M || M > SKINNY_MAX_M || g_family.load(std::memory_order_relaxed) != 0) return 0;
     const int S = pick_rowblock_split(M, H, I, EPI_PLAIN, cus);
     return S > 1 && mlp_fused_ok(M, H, I, epi_up, cus, S) && pick_decode_kernel(M, I, H, epi_up, cus) == DK_ROWBLOCK &&
-           pick_decode_kernel(M, H, I, EPI_PLAIN, cus) == DK_ROWBLOCK;
+           pick_decode_kernel(M, H, I, EPI_PLAIN, cus) == DK_ROWBLOCK ? S : 0;
 }
 
 // Which kernel runs a projection of M tokens, and how many tokens a launch takes.
@@ -240,7 +242,8 @@ struct DecodePlan {
     int kernel;     // DK_*, or 0 = the GEMM kernels
     int group;      // tokens per launch
 };
-DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus, bool few_token = true)
+constexpr DecodePlan ROW_BLOCKS{DK_ROWBLOCK, SKINNY_GROUP};
+DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus)
 {
     const int fam = g_family.load(std::memory_order_relaxed);
     // The GEMM kernels address the rows of a tile by 32-bit byte offsets: 256 rows of up to 2^23 values.
@@ -252,7 +255,7 @@ DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus, bool few_toke
     if (M <= SKINNY_MAX_M) {
         double us = 0.0;
         const int kernel = pick_decode_kernel(first, N, K, epilogue, cus, &us);
-        if (few_token && few_token_kernel_ok(M, N, K, epilogue, cus, kernel, us)) return DecodePlan{0, 0};
+        if (few_token_kernel_ok(M, N, K, epilogue, cus, kernel, us)) return DecodePlan{0, 0};
         return DecodePlan{kernel, SKINNY_GROUP};
     }
     if (M > 16 * SK_MAX_MT) return DecodePlan{0, 0};
@@ -267,15 +270,15 @@ DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus, bool few_toke
     return DecodePlan{0, 0};
 }
 
-// One fused projection: out[M, ldo] = epilogue( prologue(x)[M,K] * w^T ), any M.
+// One fused projection: out[M, ldo] = epilogue( prologue(x)[M,K] * w^T ), any M.  known: the caller has its plan already.
 int run_projection(const uint16_t* x, const uint16_t* gamma, float eps, const uint16_t* w0, const uint16_t* w1,
                    uint16_t* out, int M, int N, int K, int ldo, int epilogue, const Workspace& ws,
                    hipStream_t stream, RopeArgs rope = RopeArgs{nullptr, nullptr, 0, 2, nullptr},
-                   const uint16_t* residual = nullptr, bool few_token = true)
+                   const uint16_t* residual = nullptr, const DecodePlan* known = nullptr)
 {
     const int cus = device_cu_count();
     (void)hipGetLastError();      // an error another user of the runtime left behind is not ours to report
-    const DecodePlan dp = plan_decode(M, N, K, epilogue, cus, few_token);
+    const DecodePlan dp = known ? *known : plan_decode(M, N, K, epilogue, cus);
     if (dp.kernel != 0) {
         const int kernel = dp.kernel, group = dp.group;
         const bool slab = kernel != DK_STREAMK, block = kernel == DK_ROWBLOCK;
@@ -366,9 +369,9 @@ int run_mlp(const uint16_t* x, const uint16_t* gamma, float eps, const uint16_t*
 {
     const int epi_up = gamma ? EPI_RMSNORM_SWIGLU : EPI_SWIGLU;
     const int cus = device_cu_count();
-    const bool fusible = single_launch_shape(M, H, I, epi_up, cus);      // (the same kernels then, one launch or two: the switch does not change results)
-    if (fusible && g_mlp_fusion.load(std::memory_order_relaxed)) {
-        const int S = pick_rowblock_split(M, H, I, EPI_PLAIN, cus);
+    const int S = single_launch_split(M, H, I, epi_up, cus);
+    const DecodePlan* const known = S ? &ROW_BLOCKS : nullptr;      // (the same kernels, one launch or two: the switch does not change results)
+    if (S && g_mlp_fusion.load(std::memory_order_relaxed)) {
         (void)hipGetLastError();
         SkinnyArgs up{}, down{};
         up.x = x; up.gamma = gamma; up.w0 = w_gate; up.w1 = w_up; up.out = ws.h; up.residual = nullptr;
@@ -382,10 +385,10 @@ int run_mlp(const uint16_t* x, const uint16_t* gamma, float eps, const uint16_t*
         return launch_mlp_fused(up, down, epi_up, cus, stream, S) == hipSuccess ? THI_OK : THI_ERR_HIP;
     }
     int rc = run_projection(x, gamma, eps, w_gate, w_up, ws.h, M, I, H, I, epi_up, ws, stream,
-                            RopeArgs{nullptr, nullptr, 0, 2, nullptr}, nullptr, !fusible);
+                            RopeArgs{nullptr, nullptr, 0, 2, nullptr}, nullptr, known);
     if (rc != THI_OK) return rc;
     return run_projection(ws.h, nullptr, 0.f, w_down, nullptr, out, M, H, I, H, EPI_PLAIN, ws, stream,
-                          RopeArgs{nullptr, nullptr, 0, 2, nullptr}, residual, !fusible);
+                          RopeArgs{nullptr, nullptr, 0, 2, nullptr}, residual, known);
 }
 
 int check_common(int M, int N, int K, const void* workspace, size_t workspace_bytes, size_t need)
@@ -468,7 +471,7 @@ int thi_swiglu_gate_up(const void* x, const void* w_gate, const void* w_up, void
     Workspace ws = carve(workspace, workspace_bytes, THI_OP_SWIGLU_MLP, M, H, I);
     return run_projection((const uint16_t*)x, nullptr, 0.f, (const uint16_t*)w_gate, (const uint16_t*)w_up,
                           (uint16_t*)h, M, I, H, I, EPI_SWIGLU, ws, (hipStream_t)hip_stream, RopeArgs{nullptr, nullptr, 0, 2, nullptr},
-                          nullptr, !single_launch_shape(M, H, I, EPI_SWIGLU, device_cu_count()));
+                          nullptr, single_launch_split(M, H, I, EPI_SWIGLU, device_cu_count()) ? &ROW_BLOCKS : nullptr);
 }
 
 int thi_linear_residual(const void* x, const void* w, const void* residual, void* out, int M, int N, int K,
@@ -635,7 +638,7 @@ int thi_query_kernel_family(int M, int N, int K, int fused)
     if (M < 1 || N < 1 || K < 1 || fused < 0 || fused > 2) return 0;
     const int epilogue = fused == 1 ? EPI_RMSNORM : fused == 2 ? EPI_SWIGLU : EPI_PLAIN;
     const int cus = device_cu_count();
-    const DecodePlan dp = plan_decode(M, N, K, epilogue, cus, !(fused == 2 && single_launch_shape(M, K, N, epilogue, cus)));
+    const DecodePlan dp = fused == 2 && single_launch_split(M, K, N, epilogue, cus) ? ROW_BLOCKS : plan_decode(M, N, K, epilogue, cus);
     return dp.kernel != 0 ? dp.kernel : 2;
 }
 

@@ -55,7 +55,7 @@ bool rowblock_split_ok(int N, int K, int epilogue, int num_cus, int ksplit)
 // The single-launch decode MLP: which shapes the one fused kernel that is built serves.
 bool mlp_fused_ok(int M, int H, int I, int epilogue_up, int num_cus, int ksplit_down)
 {
-    if (M <= 16 || M > 32 || H < 1024 || H > ROWSLAB_MAX_K || I < 1024 || I > ROWSLAB_MAX_K) return false;
+    if (M < MLP_FUSED_MIN_M || M > 32 || H < 1024 || H > ROWSLAB_MAX_K || I < 1024 || I > ROWSLAB_MAX_K) return false;
     if (epilogue_up != EPI_SWIGLU && epilogue_up != EPI_RMSNORM_SWIGLU) return false;
     if (epilogue_up == EPI_RMSNORM_SWIGLU && H > 24576) return false;      // gamma in LDS beside the two phases' ~104 KiB
     if (!rowblock_split_ok(H, I, EPI_PLAIN, num_cus, ksplit_down)) return false;

@@ -108,6 +108,7 @@ hipError_t launch_rowblock(const SkinnyArgs& a, int epilogue, int num_cus, hipSt
 // status words of its rendezvous (the other users stay below 1024): the launch number on this workspace, then one
 // tag word per workgroup; unlike all other status words these are not zero between calls
 constexpr int MLP_EPOCH_WORD = 2047, MLP_FLAG_WORDS = 2048, MLP_MAX_GRID = 512;
+constexpr int MLP_FUSED_MIN_M = 17;      // (17..32 tokens)
 bool mlp_fused_ok(int M, int H, int I, int epilogue_up, int num_cus, int ksplit_down);
 hipError_t launch_mlp_fused(const SkinnyArgs& up, const SkinnyArgs& down, int epilogue_up, int num_cus, hipStream_t stream,
                             int ksplit_down);

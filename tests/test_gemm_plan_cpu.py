@@ -113,3 +113,24 @@ def test_rows_longer_than_the_gemm_addresses():
                 assert forced == 0 or thi.thi_query_kernel_family(M, N, 2 ** 23, 0) == 2
             finally:
                 thi.thi_set_kernel_family(prev)
+
+
+def test_the_single_launch_mlp_is_planned_once_and_where_it_exists(tmp_path):
+    """Outside 17..32 tokens an MLP call plans its two projections and nothing else; inside it asks once whether one launch would serve."""
+    exe = str(tmp_path / "host_calls")
+    csrc = os.path.join(ROOT, "paper_2605_25655_amd", "csrc")
+    res = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Wno-unused-command-line-argument",
+                          "-Wl,--wrap=_ZN3thi17rowblock_split_okEiiiii", "-o", exe, os.path.join(csrc, "api.hip"), os.path.join(csrc, "plan.hip"),
+                          "-x", "hip", os.path.join(ROOT, "tests", "sanitize", "api_stubs.cpp"), os.path.join(ROOT, "tests", "plan", "host_calls.cpp")],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+
+    def tried(M, H, I):
+        out = subprocess.run([exe], input=f"{M} {H} {I}\n", capture_output=True, text=True, check=True).stdout.split()
+        return tuple(map(int, out))
+    for H, I in ((512, 1376), (4096, 11008), (5120, 13824), (8192, 28672)):
+        for M in (1, 8, 16, 33, 64, 200):
+            mlp, gate_up, down = tried(M, H, I)
+            assert gate_up == 0 and mlp == down, (M, H, I, mlp, gate_up, down)
+    mlp, gate_up, down = tried(32, 4096, 11008)      # the one shape that is fused: the question, then the split that its launch takes
+    assert 0 < gate_up and mlp <= gate_up + 4, (mlp, gate_up, down)

@@ -276,7 +276,8 @@ int thi_set_kernel_family(int family);
  * reduction dimension (their sums meet through the workspace).  split: 0 = chosen
  * by the library per call (default), 1 = never share, 2..6 = share wherever the
  * shape admits it (plain linear operator, K >= 1024 * split, at most 6 tiles of
- * 16 rows per block), else as 1.  Returns the previous setting.
+ * 16 rows per block), else as 1.  With a split >= 1 the few-token GEMM kernel does not take the row blocks' place either;
+ * where it takes the stream-K kernel's it still does.  Returns the previous setting.
  */
 int thi_set_rowblock_split(int split);
 

@@ -205,7 +205,8 @@ int pick_decode_kernel(int M, int N, int K, int epilogue, int cus, double* us = 
 //   row slabs'       : never (they win by 0-10 % wherever they are chosen).
 bool few_token_kernel_ok(int M, int N, int K, int epilogue, int cus, int kernel, double us)
 {
-    if (K < 1024 || kernel == DK_ROWSLAB || g_rowblock_split.load(std::memory_order_relaxed) != 0) return false;
+    if (K < 1024 || kernel == DK_ROWSLAB) return false;
+    if (kernel == DK_ROWBLOCK && g_rowblock_split.load(std::memory_order_relaxed) != 0) return false;      // row blocks were asked for, shared so
     const bool swiglu = is_swiglu(epilogue);
     if (kernel == DK_ROWBLOCK && M <= 16 && !(swiglu && M > 4)) return false;      // (before a plan is made)
     const MidPlan mp = plan_mid(M, N, K, epilogue, cus);

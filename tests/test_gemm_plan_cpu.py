@@ -134,3 +134,20 @@ def test_the_single_launch_mlp_is_planned_once_and_where_it_exists(tmp_path):
             assert gate_up == 0 and mlp == down, (M, H, I, mlp, gate_up, down)
     mlp, gate_up, down = tried(32, 4096, 11008)      # the one shape that is fused: the question, then the split that its launch takes
     assert 0 < gate_up and mlp <= gate_up + 4, (mlp, gate_up, down)
+
+
+def test_a_forced_row_block_split_leaves_the_other_kernels_alone():
+    """It says how row blocks are shared: where they would run they do, and the few-token kernel stays where it stands for the stream-K kernel."""
+    import paper_2605_25655_amd as thi
+    shapes = [(M, N, K, f) for M in (1, 5, 16, 32) for N, K in ((300, 5000), (1000, 2048), (5120, 8200), (8192, 8192), (13824, 5120), (36000, 1040)) for f in (0, 1, 2)]
+    prev_family = thi.thi_set_kernel_family(0)
+    prev = thi.thi_set_rowblock_split(0)
+    try:
+        free = {s: thi.thi_query_kernel_family(*s) for s in shapes}
+        thi.thi_set_rowblock_split(1)
+        single = {s: thi.thi_query_kernel_family(*s) for s in shapes}
+    finally:
+        thi.thi_set_rowblock_split(prev)
+        thi.thi_set_kernel_family(prev_family)
+    assert not [s for s in shapes if free[s] == 2 and single[s] == 1], [(s, single[s]) for s in shapes if free[s] == 2]
+    assert any(free[s] == 2 == single[s] for s in shapes) and any(free[s] == 2 and single[s] == 4 for s in shapes)

@@ -320,8 +320,10 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
         static_assert(MID_KG == 4, "four k groups");
     }
     if (S > 1) {
-        constexpr size_t frags_of = (size_t)MID_WAVES * OWN * 64 * 4;      // floats: [wave][finished fragment][lane][4]
-        constexpr size_t slot = frags_of + (RMS ? BM : 0);                 // ... then the sums of squares
+        constexpr size_t frags_of = mid_slot_floats(BN, BM, false);        // floats: [wave][finished fragment][lane][4]
+        constexpr size_t slot = mid_slot_floats(BN, BM, RMS);              // ... then the sums of squares
+        static_assert(frags_of == (size_t)MID_WAVES * OWN * 64 * 4, "a workgroup's partial tile");
+        static_assert(BM > MID_DECODE_M || slot <= SK_SLOT_WORDS, "at decode sizes it lies in the decode kernels' slots");
         float* const ps = a.partials + ((size_t)tile * S + share) * slot + (size_t)(wv * OWN * 64 + lane) * 4;
 #pragma unroll
         for (int o = 0; o < OWN; ++o)
@@ -465,7 +467,10 @@ hipError_t launch_mid_cfg(const GemmArgs& a, int epilogue, const MidPlan& p, hip
     } while (0)
     switch (epilogue) {
     case EPI_PLAIN: THI_LAUNCH(EPI_PLAIN); break;
-    case EPI_ROPE: THI_LAUNCH(EPI_ROPE); break;
+    case EPI_ROPE:                             // up to MID_DECODE_M tokens always behind RMSNorm
+        if constexpr (BM > MID_DECODE_M || RMS) THI_LAUNCH(EPI_ROPE);
+        else return hipErrorInvalidValue;
+        break;
     case EPI_SWIGLU: THI_LAUNCH(EPI_SWIGLU); break;
     default: return hipErrorInvalidValue;      // RMSNorm: by a.gamma
     }

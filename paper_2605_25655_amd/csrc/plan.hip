@@ -90,10 +90,10 @@ namespace {
 
 // The same kernel with a token tile of 32, for up to MID_DECODE_M tokens.  S shares of K, so that there are num_cus / S tiles, each of
 // equally many outputs (in fours), in the least tile that holds them; the S of the smallest modelled time: 4.15 us fixed,
-// 19 ns a row of the tile; for each stage of 128 k 102 ns, 6.3 ns a row of weights and 2 ns a token, with two stages 2.5 ns a row more, or what
+// 19 ns a row of the tile; for each stage of 128 k 102 ns, 6.3 ns a row of weights and 2 ns a token, or what
 // 8 TB/s give if that is longer; sharing 0.8 us and 0.117 ns a row, token and share.  Fitted to 430 points on 38 calls
 // (4..32 tokens, 1536 x 4096 .. gate/up 2 x 28672 x 8192): the pick is 1.1 % slower than the best measured on average; the price is 7 % off (rms).  No tiles
-// above 176 rows: two stages of those left gate/up 2 x 28672 x 8192 at 147 us against 140 with the row blocks.
+// above 176 rows: those leave room for two stages, which left gate/up 2 x 28672 x 8192 at 147 us against 140 with the row blocks.
 //
 // rotate: workgroups that walk the same k at the same time ask for addresses that agree in their low bits where a row is a multiple of 4 KiB,
 // and so for few of the memory's channels: gate/up 2 x 11008 x 4096 at 32 tokens 36.5 us, with the tiles' starts spread over k 29.4; 8192 x 8192
@@ -114,8 +114,8 @@ MidPlan plan_mid_decode(int M, int N, int K, int epilogue, int num_cus)
         for (int b : {32, 48, 64, 80, 96, 112, 128, 144, 176})
             if (b >= rows) { BN = b; break; }
         if (!BN) continue;
-        const int kt = (ktiles + S - 1) / S, stages = 160 * 1024 / ((BN + 32) * 256);
-        const double cu = kt * (0.0063 * rows + 0.0020 * M + 0.102 + (stages == 2 ? 0.0025 * BN : 0.0));
+        const int kt = (ktiles + S - 1) / S;
+        const double cu = kt * (0.0063 * rows + 0.0020 * M + 0.102);
         const double us = 4.15 + (cu > stream ? cu : stream) + 0.019 * BN + (S > 1 ? 0.8 + 1.17e-4 * S * BN * (M > 8 ? M : 8) : 0.0);
         if (best.BN && us >= best.us) continue;
         best = MidPlan{BN, (int)((N + per - 1) / per), S, us, (int)per, swiglu ? K % 2048 == 0 : K >= 8192};

@@ -131,8 +131,8 @@ struct GemmArgs {
 constexpr int GEMM_MAX_K = 1 << 23;   // 256 rows x 2 bytes x K within 32 bits
 constexpr int GEMM_MAX_GRID = 2048;   // in units of 128x128 partial tiles (a 256x256 tile takes four)
 size_t gemm_partial_bytes();
-// The few-token kernel (33..128 tokens; plan_gemm takes it where it is the faster one): how the tile rows and K are
-// dealt to the compute units.
+// The few-token kernel (up to 128 tokens: up to MID_DECODE_M where few_token_kernel_ok or a forced family says so, above where plan_gemm
+// finds it the faster one): how the tile rows and K are dealt to the compute units.
 struct MidPlan {
     int BN;          // virtual weight rows per tile (0: the kernel does not serve the shape)
     int tiles;
@@ -142,6 +142,8 @@ struct MidPlan {
     bool rotate;     // the workgroups of a share start at different k
 };
 constexpr int MID_DECODE_M = 32;     // up to so many tokens: RMSNorm inside the kernel, sums handed over through the decode kernels' slots
+// Floats of a workgroup's partial tile: eight waves' share of its 16x16 fragments (rounded up), 256 each, and the tokens' sums of squares
+constexpr int mid_slot_floats(int BN, int BM, bool rms) { return 8 * ((BN / 16 * (BM / 32) + 3) / 4) * 256 + (rms ? BM : 0); }
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
 // The GEMM's configurations, their constants, and which of them runs a product (no RMSNorm kinds).  From GEMM_BIG on: the
 // candidates above 128 tokens.

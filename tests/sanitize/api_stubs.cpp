@@ -39,15 +39,22 @@ hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t
     const GemmPlan p = plan_gemm(a.M, a.N, a.K, epilogue, num_cus);
     const size_t region = gemm_partial_bytes();
     if (p.grid < 1 || p.tiles < 1) return hipErrorInvalidValue;
-    if (p.config == GEMM_MID) {      // a partial tile: eight waves, at most seven finished fragments of 1 KiB each
-        const bool fits = p.mid.S == 1 || (size_t)p.grid * 8 * 7 * 1024 <= region;
-        return a.M <= 128 && p.grid == p.mid.tiles * p.mid.S && p.grid <= num_cus && p.mid.tiles <= 1024 && fits ? hipSuccess : hipErrorInvalidValue;
+    const bool decode = a.M <= MID_DECODE_M;
+    if (a.gamma && (!decode || p.config != GEMM_MID)) return hipErrorInvalidValue;
+    if (p.config == GEMM_MID) {      // partial tiles: at decode sizes `partials` may be no more than the hand-over slots
+        const int BM = decode ? 32 : a.M <= 64 ? 64 : a.M <= 96 ? 96 : 128;
+        const bool fits = p.mid.S == 1 || (size_t)p.grid * mid_slot_floats(p.mid.BN, BM, decode) * sizeof(float) <= (decode ? skinny_handover_bytes() : region);
+        const bool built = epilogue != EPI_ROPE || a.gamma || !decode;
+        return a.M <= 128 && p.grid == p.mid.tiles * p.mid.S && p.grid <= num_cus && p.mid.tiles <= 1024 && fits && built ? hipSuccess : hipErrorInvalidValue;
     }
     const GemmTile t = gemm_tile(p.config);
     const bool covers = (long)p.tiles_m * t.BM >= a.M && (long)p.tiles / p.tiles_m * t.BN >= (is_swiglu(epilogue) ? 2L : 1L) * a.N && p.ktiles * (long)t.GK >= a.K;
     const bool cut = p.sk_tiles == 0 || (t.cut && (size_t)p.grid * 2 * t.BN * t.BM * 4 <= region &&
                                          (p.parts == 0 || ((long)p.sk_tiles * p.parts <= p.grid && p.parts <= p.ktiles)));
-    return covers && cut && (t.ragged || a.K % t.GK == 0) && p.sk_tiles <= p.tiles ? hipSuccess : hipErrorInvalidValue;
+    // workgroups that touch the weights ahead: as many for each XCD, one per compute unit with the others, and only in the kernels that tell them apart
+    const bool helped = p.helpers == 0 || (p.helpers > 0 && p.helpers % 8 == 0 && p.grid + p.helpers <= num_cus && p.sk_tiles == 0 && p.grid == p.tiles &&
+                                           !is_swiglu(epilogue) && (p.config == GEMM_DEEP || p.config == GEMM_FEW128));
+    return covers && cut && helped && (t.ragged || a.K % t.GK == 0) && p.sk_tiles <= p.tiles ? hipSuccess : hipErrorInvalidValue;
 }
 hipError_t launch_rmsnorm_rows(const uint16_t*, const uint16_t*, float, uint16_t* xn, int, int, const RopeArgs&, hipStream_t)
 {

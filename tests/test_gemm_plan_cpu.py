@@ -12,7 +12,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 pytestmark = pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
 
 PLAIN, GATE_UP = 0, 2
-Plan = namedtuple("Plan", "config tiles grid cut parts rows ranges")
+Plan = namedtuple("Plan", "config tiles grid cut parts rows ranges per spread helpers")
 
 
 @pytest.fixture(scope="module")
@@ -71,10 +71,34 @@ def test_the_gpu_tests_run_the_kernels_they_are_listed_for(plan):
     assert {plan(PLAIN, *t).config for t in RAGGED} == {"MID", "DEEP", "SMALL"}
 
 
+def test_the_gpu_tests_of_spread_starts_and_of_decode_sizes(plan):
+    import paper_2605_25655_amd as thi
+    from tests.test_parity_gpu import DECODE_WORKSPACE, FEW_DECODE, SPREAD_STARTS
+    picks = [plan(PLAIN, *t) for t in SPREAD_STARTS]      # two token tiles, stages of 64 k
+    assert all(p.config == "FEW128" and 128 < t[0] <= 256 and t[2] % 64 == 0 for t, p in zip(SPREAD_STARTS, picks)), picks
+    assert {_cut(p) for p in picks} == {"whole", "ranges"} and any(p.helpers for p in picks)
+    few = [plan(PLAIN, *t) for t in FEW_DECODE]
+    assert all(p.config == "MID" for p in few), few
+    assert {p.rows for p in few if p.ranges == 1} == {32, 48, 64, 80, 96, 112, 128, 144, 176}
+    assert {p.rows for p in few if p.ranges > 1} >= {32, 48, 64, 80, 96, 112, 128}
+    assert {p.rows for t, p in zip(FEW_DECODE, few) if p.ranges > 1 and p.spread and t[2] % 128} >= {48, 96, 112, 128}
+    assert {48, 96} <= {p.rows for p in few if p.ranges > 1 and not p.spread}
+    assert any(p.per < p.rows for p in few) and any(p.per % 16 for p in few)
+    kinds = {"P": (PLAIN, 0), "Q": (PLAIN, 1), "G": (GATE_UP, 2)}
+    seen = {k: set() for k in kinds}
+    for kind, M, N, K in DECODE_WORKSPACE:
+        epilogue, fused = kinds[kind]
+        p = plan(epilogue, M, N, K)
+        assert p.config == "MID" and p.ranges > 1 and thi.thi_query_kernel_family(M, N, K, fused) == 2, (kind, M, N, K, p)
+        seen[kind].add((p.rows, p.spread))
+    assert seen["Q"] >= {(32, 0), (32, 1), (48, 1), (96, 1), (112, 1)} and seen["P"] >= {(48, 0), (64, 1), (112, 0)} and len(seen["G"]) == 3, seen
+
+
 def test_whole_128_tiles_leave_units_that_touch_the_weights(plan):
     from tests.test_parity_gpu import TOUCHED
     picks = [plan(PLAIN, *t) for t in TOUCHED]
     assert all(p.config in ("DEEP", "FEW128") and p.cut == 0 and 8 <= p.tiles == p.grid <= 256 - 48 for p in picks), picks
+    assert all(p.helpers > 0 and p.helpers % 8 == 0 and p.grid + p.helpers <= 256 for p in picks), picks
     assert {p.config for p in picks} == {"DEEP", "FEW128"} and {8, 208} <= {p.tiles for p in picks}
     # two token tiles whose starts are spread over k, gate/up, and few tiles with a long K: not these
     assert plan(PLAIN, 203, 12288, 4096).tiles == 192 and plan(PLAIN, 203, 4096, 4096).cut == 64

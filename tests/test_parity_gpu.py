@@ -331,6 +331,7 @@ KERNELS = [
     ("P", 99, 8198, 64, "FEW128", "whole"), ("P", 97, 48, 8, "FEW128", "whole"), ("G", 98, 4104, 64, "FEW128", "whole"),
     ("P", 33, 50, 24896, "FEW128", "shares"), ("G", 33, 48, 24768, "FEW128", "shares"), ("P", 121, 10364, 10440, "FEW128", "shares"),
     ("G", 98, 5200, 12720, "FEW128", "shares"), ("G", 69, 16560, 1536, "FEW128", "rounds + shares"),
+    ("P", 140, 600, 4096, "FEW128", "ranges"), ("G", 140, 9000, 4096, "FEW128", "rounds + ranges"), ("P", 140, 9000, 448, "FEW128", "whole"),
     ("P", 33, 36895, 64, "FEW256", "whole"), ("P", 34, 37183, 3776, "FEW256", "shares"), ("G", 33, 32912, 1344, "FEW256", "rounds + shares"),
     ("P", 137, 21264, 64, "ONE", "whole"), ("G", 131, 10752, 5632, "ONE", "shares"), ("P", 129, 36380, 960, "ONE", "rounds + ranges"),
     ("P", 1961, 4124, 8, "BIG", "whole"), ("G", 1817, 3600, 64, "BIG", "whole"), ("G", 1557, 584, 4920, "BIG", "ranges"),
@@ -453,7 +454,11 @@ def test_prefill_swiglu_schedules(thi, oracle_mod, M, H, I):
 
 # Two token tiles of the one-per-CU 128x128 kernel start their tile rows spread over k: whole tiles and ranges, one row of tiles, fewer
 # k-tiles than rows of tiles, ranges of unequal length.
-@pytest.mark.parametrize("M,N,K", [(129, 4096, 4096), (203, 12288, 320), (256, 392, 1216), (200, 4096, 11008), (130, 16, 640), (255, 2000, 64)])
+# (The rows that the rule has since given to other kernels stay: 320 and 64 k to the two-per-CU tiles, 11008 to the stages of 128 k.)
+SPREAD_STARTS = [(129, 4096, 4096), (256, 392, 1216), (130, 16, 640), (203, 12288, 384), (255, 2000, 448), (200, 4096, 7040), (230, 5000, 4416)]
+
+
+@pytest.mark.parametrize("M,N,K", SPREAD_STARTS + [(203, 12288, 320), (200, 4096, 11008), (255, 2000, 64)])
 def test_spread_starts_of_two_token_tiles(thi, oracle_mod, M, N, K):
     say(f"[case] two token tiles M={M} N={N} K={K}")
     x, w, g = synth.random_problem(9300 + M + N + K, M, N, K)
@@ -508,12 +513,17 @@ def test_weights_touched_by_idle_compute_units(thi, oracle_mod, M, N, K):
 
 
 # ------------------------------------------- the few-token kernel at decode sizes (up to 32 tokens)
-# Every height of tile, tiles that the outputs do not fill and that end inside a quad, shared and alone, with a ragged K, rows of 4 KiB
-# (rotated starts), fewer k-tiles than stages; token counts at the edges of its two fragments.  Forced: the rule sends few of them there.
-@pytest.mark.parametrize("M,N,K", [
+# Every height of tile, alone (short K) and but for the highest shared, tiles that the outputs do not fill and that end inside a quad, with a
+# ragged K, starts spread over k (with a ragged last k-tile too), fewer k-tiles than stages; token counts at the edges of its two fragments.
+# Forced: the rule sends few of them there.
+FEW_DECODE = [
     (1, 1536, 1032), (16, 300, 5000), (17, 12288, 264), (32, 12290, 1024), (5, 16380, 392), (31, 20000, 136), (32, 24574, 264),
     (16, 28000, 136), (2, 32000, 264), (32, 36001, 72), (9, 44000, 136), (20, 5120, 8200), (32, 4096, 11008), (17, 8192, 8192), (32, 96, 32768),
-])
+    (9, 2389, 2000), (17, 1432, 8488), (19, 7414, 3344), (17, 4179, 8752), (28, 6824, 8368), (31, 8173, 14216),
+]
+
+
+@pytest.mark.parametrize("M,N,K", FEW_DECODE)
 def test_few_token_kernel_at_decode_sizes(thi, oracle_mod, M, N, K):
     say(f"[case] few-token kernel, decode M={M} N={N} K={K}")
     x, w, g = synth.random_problem(9100 + M + N + K, M, N, K)
@@ -549,6 +559,69 @@ def test_few_token_kernel_at_decode_sizes(thi, oracle_mod, M, N, K):
     check(c[rows], y, s, "rope", argmax=False)
     y, s = oracle_mod.swiglu_gate_up(x, np.ascontiguousarray(w[:I][jc]), np.ascontiguousarray(w[I:2 * I][jc]))
     check(h[:, jc], y, s, "gate/up", argmax=False)
+
+
+# The same kernel as programs run it: chosen by the rule, its shares meeting in the hand-over slots of a workspace that thi_workspace_bytes
+# sized for up to 32 tokens (the tests above hold one with the GEMM's region).  P: plain with a residual, Q: RMSNorm and RMSNorm with the rotary
+# embedding, G: gate/up and the whole MLP.  tests/test_gemm_plan_cpu.py asserts that the rule sends them there and that their tiles are shared.
+DECODE_WORKSPACE = [
+    ("P", 28, 2060, 3104), ("P", 13, 8264, 4112), ("P", 32, 4096, 11008), ("Q", 22, 519, 8176), ("Q", 18, 311, 8344), ("Q", 17, 1432, 8488),
+    ("Q", 4, 4450, 8200), ("Q", 28, 6824, 8368), ("G", 18, 272, 2200), ("G", 31, 360, 4096), ("G", 27, 832, 3640),
+]
+
+
+@pytest.mark.parametrize("kind,M,N,K", DECODE_WORKSPACE)
+def test_few_token_kernel_on_a_decode_workspace(thi, oracle_mod, kind, M, N, K):
+    import torch
+    say(f"[case] few-token kernel, decode workspace {kind} M={M} N={N} K={K}")
+    x, w, g = synth.random_problem(9700 + M + N + K, M, 2 * N if kind == "G" else N, K)
+    xd, wd, gd = to_dev(x), to_dev(w), to_dev(g)
+    need = thi.thi_workspace_bytes(2, M, K, N) if kind == "G" else thi.thi_workspace_bytes(0 if kind == "Q" else 1, M, N, K)
+    assert need < (64 << 20)
+    whole = thi.Workspace(need + (1 << 20))
+    off = (-whole.buffer.data_ptr()) % 256
+    behind = whole.buffer[off + need:off + need + (1 << 20)]
+    behind.fill_(0x5A)
+    ws = (whole.ptr, need)
+    outs = {}
+
+    def run(name, call, n):
+        two = []
+        for _ in range(2):
+            out = new_out(M, n)
+            call(out)
+            two.append(to_host(out))
+        assert np.array_equal(two[0].view(np.uint16), two[1].view(np.uint16)), f"{name} is not reproducible"
+        assert not _status_words(whole).any(), "status words are not zero after the calls"
+        outs[name] = two[0]
+
+    if kind == "P":
+        res = f16(np.random.Generator(np.random.Philox(key=9800 + M + N + K)).standard_normal((M, N)))
+        rd = to_dev(res)
+        run("linear + residual", lambda o: thi.thi_linear_residual(xd, wd, rd, o, ws), N)
+        y, s = oracle_mod.linear_residual(x, w, res)
+        check(outs["linear + residual"], y, s, "linear + residual", argmax=False)
+    elif kind == "Q":
+        hd, pos = 8, np.arange(M, dtype=np.int32) * 7
+        th, n_rot = _theta(hd), N // 2 // hd * hd
+        pd, td = _dev_i32(pos), _dev_f32(th)
+        run("rmsnorm", lambda o: thi.thi_rmsnorm_qkv(xd, gd, 1e-6, wd, o, ws), N)
+        run("rope", lambda o: thi.thi_rmsnorm_qkv_rope(xd, gd, 1e-6, wd, pd, td, n_rot, hd, o, ws), N)
+        y, s = oracle_mod.rmsnorm_qkv(x, g, 1e-6, w)
+        check(outs["rmsnorm"], y, s, "rmsnorm", argmax=False)
+        y, s = oracle_mod.rmsnorm_qkv_rope(x, g, 1e-6, w, pos, th, n_rot, hd)
+        check(outs["rope"], y, s, "rope", argmax=False)
+    else:
+        down, _, _ = synth.random_problem(9900 + M + N + K, K, 8, N)      # [K, N]: the weights of the down projection
+        dd = to_dev(down)
+        run("gate/up", lambda o: thi.thi_swiglu_gate_up(xd, wd[:N], wd[N:], o, ws), N)
+        run("mlp", lambda o: thi.thi_swiglu_mlp(xd, wd[:N], wd[N:], dd, o, ws), K)
+        y, s = oracle_mod.swiglu_gate_up(x, np.ascontiguousarray(w[:N]), np.ascontiguousarray(w[N:]))
+        check(outs["gate/up"], y, s, "gate/up", argmax=False)
+        y, s = oracle_mod.swiglu_mlp(x, np.ascontiguousarray(w[:N]), np.ascontiguousarray(w[N:]), down)
+        check(outs["mlp"], y, s, "mlp", argmax=False)
+    torch.cuda.synchronize()
+    assert bool((behind == 0x5A).all()), "written behind the workspace"
 
 
 # ------------------------------------------- between decode and prefill (33..128 tokens)

@@ -2,8 +2,8 @@
 
 Same kernels, same dispatch: the results must be identical bit for bit (and thi_linear itself is held to
 |gpu - y| <= 4e-3 * S against the oracle elsewhere).  Two calls in a row, the second with a smaller input,
-on shapes whose kernels use the scratch array (shared row blocks: arrival counters and hand-over slots;
-stream-K: flags and slots), then the limit and the argument errors."""
+on shapes whose kernels use the scratch array (few-token kernel and shared row blocks: arrival counters and
+hand-over slots; stream-K: flags and slots), then the limit and the argument errors."""
 import ctypes
 
 import numpy as np
@@ -37,8 +37,8 @@ def _both(thi, x, w, ws):
 
 @pytest.mark.parametrize("family", [0, 1, 4])
 def test_static_scratch_matches_the_workspace_entry_point(thi, family):
-    # 7B down-projection shape (shared row blocks under the automatic choice; every stream-K tile is
-    # shared), then a smaller problem on the same scratch array
+    # 7B down-projection shape (shared tiles of the few-token kernel under the automatic choice, shared row blocks
+    # when those are forced; every stream-K tile is shared), then a smaller problem on the same scratch array
     big, small = (32, 4096, 11008), (5, 1000, 2048)
     ws = thi.Workspace(thi.thi_workspace_bytes(1, 32, 4096, 11008))
     prev = thi.thi_set_kernel_family(family)

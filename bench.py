@@ -303,7 +303,7 @@ def measure_layer(cfg, M, args, host_layer, per_block, warmup, op_names, traffic
     if decode:
         fam = thi.thi_query_kernel_family(M, cfg.inter, cfg.hidden, 2)
         roof = {"bound": "hbm",
-                "kernel": f"gate_up ({ {3: 'skinny_rowslab', 4: 'skinny_rowblock'}.get(fam, 'skinny_streamk') }, SwiGLU epilogue)",
+                "kernel": f"gate_up ({ {2: 'gemm_mid' if M <= 32 else 'gemm, few tokens', 3: 'skinny_rowslab', 4: 'skinny_rowblock'}.get(fam, 'skinny_streamk') }, SwiGLU epilogue)",
                 "achieved": round(gu_bytes / (gu_ms * 1e-3) / 1e9, 1), "peak": rf.MI355X_HBM_GBS, "unit": "GB/s",
                 "traffic": None}
     else:

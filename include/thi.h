@@ -111,7 +111,7 @@ int thi_linear(const void* x, const void* w, void* out, int M, int N, int K,
 /*
  * thi_linear for callers that cannot allocate or pass a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same operator and same kernels as
- * thi_linear for up to THI_STATIC_MAX_M tokens (the weight-streaming decode kernels), bit-identical
+ * thi_linear for up to THI_STATIC_MAX_M tokens (the weight-streaming decode kernels and the few-token GEMM kernel), bit-identical
  * results; the kernels' scratch memory (status words and hand-over slots, about 17 MiB) is a static
  * device array inside the library instead of a caller's workspace.  The call allocates and frees
  * nothing.  M > THI_STATIC_MAX_M returns THI_ERR_SHAPE (the GEMM kernels' scratch is not held
@@ -215,7 +215,7 @@ int thi_decode_attention(const void* q, const void* k_cache, const void* v_cache
  * Bytes of workspace the given operator needs for the given shape
  * (op = thi_op; (M, N, K) for the first two operators, (M, H, I) for the MLP).
  * Pure host arithmetic: touches no device.  Returns 0 for invalid arguments.
- * Up to 32 tokens (the decode kernels) this is the fixed part -- 64 KiB of status
+ * Up to 32 tokens (the decode kernels and the few-token kernel) this is the fixed part -- 64 KiB of status
  * words and about 17 MiB of hand-over slots -- plus M*I*2 bytes for the MLP;
  * above, 256 MiB for the GEMM kernels' partial tiles and the buffers of the
  * prefill path are added (also below 33 tokens while thi_set_kernel_family(2) is
@@ -257,15 +257,18 @@ int thi_version(void);
  *
  * Tuning/diagnostic hook used by the benchmark and tests: force a kernel
  * family for subsequent calls from this process.  family: 0 = automatic
- * (default: a decode kernel up to 32 tokens, the stream-K decode kernel or the
+ * (default: a decode kernel or the few-token GEMM kernel up to 32 tokens, the stream-K decode kernel or the
  * GEMM kernels for 33..64 tokens, the GEMM kernels above), 1 = weight-streaming
  * decode kernel with stream-K units (up to 64 tokens per launch),
  * 2 = MFMA GEMM kernels, 3 = weight-streaming decode kernel with row slabs
  * (16 rows over the whole of K per workgroup at a time), 4 = weight-streaming
  * decode kernel with row blocks (N / #CUs rows per workgroup, several 16-row
  * tiles in flight); 3 and 4 fall back to 1 where K < 1024 or K > 32768.
- * (The automatic choice takes the row slabs below K = 1024 too; family 2 includes the few-token
- * kernel, up to 128 tokens where it is the faster one.  K > 2^23 always runs family 1.)
+ * (The automatic choice takes the row slabs below K = 1024 too.  Family 2 includes the few-token
+ * kernel: for 33..128 tokens where it is the faster one, up to 32 wherever it serves the shape, and there RMSNorm runs
+ * inside it: x * gamma is rounded to fp16 before 1/rms scales the sums, as in the decode kernels, so that it must not
+ * exceed fp16's range; the pass that normalises for more tokens rounds x * gamma / rms.  thi_query_kernel_family reports 2
+ * for automatic calls of up to 32 tokens that run it.  K > 2^23 always runs family 1.)
  * Returns the previous setting.  Not needed for normal use.
  */
 int thi_set_kernel_family(int family);

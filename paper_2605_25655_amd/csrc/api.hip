@@ -218,7 +218,8 @@ bool few_token_kernel_ok(int M, int N, int K, int epilogue, int cus, int kernel,
 }
 
 // Does the single-launch MLP serve the shape, and with how many workgroups per block of the down projection (0: no)?  Its gate/up and down
-// projections run as row blocks then, whatever else would be faster.  (The token range first: other calls plan nothing for it.)
+// projections run as row blocks then, whatever else would be faster: thi_set_mlp_fusion promises the same bits either way, and the few-token
+// kernel, 2 us ahead in gate/up and 2.5 in down (7B, 32 tokens), has others.  (The token range first: other calls plan nothing for it.)
 int single_launch_split(int M, int H, int I, int epi_up, int cus)
 {
     if (M < MLP_FUSED_MIN_M || M > SKINNY_MAX_M || g_family.load(std::memory_order_relaxed) != 0) return 0;

@@ -22,7 +22,7 @@
 // Up to 32 tokens (a tile of 32) it takes RMSNorm along: gamma is one more row of a stage, a wave multiplies its activation fragments by
 // it in front of their MFMAs (one fp16 rounding, as in the decode kernels) and adds the squares, 1 / rms scales the finished
 // sums.  Gate/up at 32 tokens against the row blocks 2 x 13824 x 5120 51.6 -> 44.2 us, 2 x 17920 x 6656 83.1 -> 72.7 (5.7 and 6.6 TB/s; with RMSNorm 0.8 us
-// more), 2 x 11008 x 4096 31.6 -> 29.4; 4096 x 11008 21.8 -> 19.0, 8192 x 8192 26.2 -> 24.5.
+// more), 2 x 11008 x 4096 31.6 -> 29.4 (forced: the MLP it belongs to keeps the row blocks, api.hip); 4096 x 11008 21.8 -> 19.0, 8192 x 8192 26.2 -> 24.5.
 //
 // Against the GEMM's few-token configurations and their second pass, or the stream-K decode kernel where that ran (same
 // box, rotated weights), N x K: 40 tokens 4096 x 4096 16.3 -> 12.6 us, 4096 x 11008 26.6 -> 21.8, 15360 x 5120 38 -> 31;

@@ -95,10 +95,11 @@ namespace {
 // (4..32 tokens, 1536 x 4096 .. gate/up 2 x 28672 x 8192): the pick is 1.1 % slower than the best measured on average; the price is 7 % off (rms).  No tiles
 // above 176 rows: those leave room for two stages, which left gate/up 2 x 28672 x 8192 at 147 us against 140 with the row blocks.
 //
-// rotate: workgroups that walk the same k at the same time ask for addresses that agree in their low bits where a row is a multiple of 4 KiB,
-// and so for few of the memory's channels: gate/up 2 x 11008 x 4096 at 32 tokens 36.5 us, with the tiles' starts spread over k 29.4; 8192 x 8192
-// in two shares 29.4, 24.6; 4096 x 11008 20.5, 19.5.  The price is that the activations are no longer read by all workgroups of an L2
-// at the same time (4096 x 4096 10.8, 11.1; 15360 x 5120 28.9, 29.3).
+// rotate: workgroups that walk the same k at the same time ask for addresses a row's length apart; where that is a multiple of 4 KiB they agree
+// in their low bits and fall on few of the memory's channels: gate/up 2 x 11008 x 4096 at 32 tokens (forced) 36.5 us, with the tiles' starts spread
+// over k 29.4.  The price is that the activations are no longer read by all workgroups of an L2 at the same time.  Gate/up: where the rows are
+// such a multiple.  Plain kinds: by measurement from K = 8192 on, whatever the row's length (8192 x 8192 in two shares 29.4, 24.6; 4096 x 11008,
+// rows of 21.5 KiB, 20.5, 19.5), and not below (4096 x 4096 10.8, 11.1; 15360 x 5120 28.9, 29.3); why long rows gain without it was not found out.
 MidPlan plan_mid_decode(int M, int N, int K, int epilogue, int num_cus)
 {
     MidPlan best{0, 0, 0, 0.0, 0, false};

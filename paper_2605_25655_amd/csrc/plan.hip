@@ -188,9 +188,7 @@ struct Schedule {
     double us;
 };
 
-constexpr double SECOND_PASS_US = 7.85;
-
-Schedule plan_schedule(int M, int tiles, int tiles_m, int grid, int BN, int BM, int ktiles, int K, double wg_tflops, double tile_fixed_us, bool cut)
+Schedule plan_schedule(int M, int tiles, int tiles_m, int grid, int BN, int BM, int ktiles, int K, double wg_tflops, double tile_fixed_us, bool cut, double second_pass_us)
 {
     double work_us = 2.0 * BN * BM * (double)K / (wg_tflops * 1e6);
     if (BM == 128) work_us *= 1.0 - 0.1 * (1.0 - (double)M / ((double)tiles_m * BM));
@@ -208,14 +206,15 @@ Schedule plan_schedule(int M, int tiles, int tiles_m, int grid, int BN, int BM, 
     // One token tile: equal contiguous shares for the few-token configurations, and for a 256-token tile
     // when equal ranges would leave more than a tenth of the workgroups idle.
     if (tiles_m == 1 && (BM <= 128 || (long)rem * parts * 10 < (long)grid * 9)) {
-        const double shared = (double)full * tile_us + tile_fixed_us + (double)rem / grid * work_us + SECOND_PASS_US + (double)(grid + rem) * tile_bytes * 2.0 / 4.0e6;
+        const double shared = (double)full * tile_us + tile_fixed_us + (double)rem / grid * work_us + second_pass_us + (double)(grid + rem) * tile_bytes * 2.0 / 4.0e6;
         return shared < whole ? Schedule{rem, 0, shared} : Schedule{0, 0, whole};
     }
     if (parts < 2) return Schedule{0, 1, whole};
-    // (a range takes 4 us at least: 554 x 512 x 1376 as 20 tiles in 11 ranges 17.7 us, whole 13.4; fewer than eight tiles are
-    // better cut in any case)
-    const double range_us = full == 0 && tiles >= 8 && work_us < 4.0 * parts ? 4.0 : work_us / parts;
-    const double shared = (double)full * tile_us + tile_fixed_us + range_us + SECOND_PASS_US +
+    // (a range takes 4 us at least: 554 x 512 x 1376 as 20 tiles in 11 ranges 17.7 us, whole 13.4; fewer than eight tiles'
+    // worth of 128x128 are better cut in any case; counted in tiles of their own size, five of 256 tokens passed for few: gate/up 219 x 312 x 2304 24.8 us, 19.7
+    // as ten of 128x128)
+    const double range_us = full == 0 && (long)tiles * BN * BM >= 8L * 128 * 128 && work_us < 4.0 * parts ? 4.0 : work_us / parts;
+    const double shared = (double)full * tile_us + tile_fixed_us + range_us + second_pass_us +
                           (double)rem * parts * tile_bytes * 2.0 / 8.0e6;
     return shared < whole ? Schedule{rem, parts, shared} : Schedule{0, 1, whole};
 }
@@ -257,7 +256,12 @@ GemmPlan plan_config(int config, int M, int N, int K, int epilogue, int num_cus)
     if (grid > most) grid = most;
     if (grid > units) grid = units;
     p.grid = (int)grid;
-    const Schedule s = plan_schedule(M, p.tiles, p.tiles_m, p.grid, t.BN, t.BM, p.ktiles, K, t.wg_tflops, t.fixed_us, t.cut);
+    // The second pass of 128x128 tiles a shade less, above 128 tokens.  One per unit: 928 x 1073 x 3072 as 72 tiles in three ranges 18.9 us, whole 23.4; 465 x
+    // 1057 x 2944 17.0, 21.8; gate/up 719 x 3872 x 4344 a round and 110 tiles in two ranges 76.9, two tiles per unit 91.7.  Two per unit: the price between
+    // leaves 606 x 3961 x 5024 to whole tiles (41.2, in ranges 52.0) and 129 x 5603 x 5696 in five ranges.  With 7.85 for the larger tiles too, gate/up 204 x 12936 x
+    // 9856 cut its 203 tiles of 256 tokens (172, whole 144) and 153 x 4474 x 6400 ran tiles of 256 tokens (39.2, here 30.4).
+    const double second_pass_us = M <= 128 || t.BN != 128 || t.BM != 128 ? 8.0 : t.per_cu == 1 ? 7.85 : 7.92;
+    const Schedule s = plan_schedule(M, p.tiles, p.tiles_m, p.grid, t.BN, t.BM, p.ktiles, K, t.wg_tflops, t.fixed_us, t.cut, second_pass_us);
     p.sk_tiles = s.sk_tiles;
     p.parts = s.parts;
     p.us = s.us;
@@ -346,7 +350,9 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
             p = plan_config(GEMM_SMALL, M, N, K, epilogue, num_cus);
             p.us = us;
         }
-        if (p.us < best.us) best = p;
+        // (whole rounds and a cut rest are no better than larger tiles at the same price: gate/up 488 x 4144 x 6656 70.4 us cut as 256x256, here 80.9)
+        const double shade = p.sk_tiles == 0 || p.sk_tiles == p.tiles ? 0.0 : c == GEMM_DEEP ? 0.15 : c == GEMM_SMALL ? 0.08 : 0.0;
+        if (p.us + shade < best.us) best = p;
     }
     // 128x128 tiles, whole, with the compute units that get none touching the weights ahead: where that leaves 48 and more, and a tile takes
     // no longer than its ranges and their second pass would.  Its time was fitted to 300 products of 8..208 tiles (8 % rms); a cut

@@ -42,9 +42,16 @@ def plan(tmp_path_factory):
     (PLAIN, 61, 28750, 640, "FEW64", None),             # 12.9, here 11.4
     (PLAIN, 72, 12288, 4096, "MID", None),
     (PLAIN, 512, 8192, 8192, "DEEP", None),
+    (GATE_UP, 219, 312, 2304, "FEW128", "TALL"),        # 24.8 -> 19.8
+    (PLAIN, 153, 4474, 6400, "FEW128", "TALL"),         # 39.2 -> 30.4
+    (PLAIN, 606, 3961, 5024, "DEEP", "SMALL"),          # 52.0 -> 41.2
 ])
 def test_picks(plan, epilogue, M, N, K, config, was):
     assert plan(epilogue, M, N, K).config == config
+
+
+def test_tiles_of_256_tokens_are_not_cut_for_a_tenth_of_a_microsecond(plan):
+    assert plan(GATE_UP, 204, 12936, 9856)[:4] == ("ONE", 203, 203, 0)      # all cut 172, whole 144
 
 
 def _cut(p):

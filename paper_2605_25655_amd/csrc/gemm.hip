@@ -112,18 +112,9 @@ struct Deal {
     }
 };
 
-// The residual of outputs n .. n + 3 of token m, asked for ahead of the stores: out may be the residual, so a load behind another quad's
-// store waits for that store's acknowledgement first, quad by quad.  Any m and n: loaded from within the matrix, for a quad that crosses
-// a row's end the row's last four values.  (With a residual and four columns or more.)
-__device__ __forceinline__ half4 residual_quad(const GemmArgs& a, int m, int n)
-{
-    const int mc = m < a.M ? m : a.M - 1, nc = n + 3 < a.N ? n : a.N - 4;
-    return *reinterpret_cast<const half4_any*>(a.residual + (size_t)mc * a.ldo + nc);
-}
-
-// Four consecutive outputs n .. n + 3 of token m (below M): rotation, residual (rv: residual_quad), one rounding, store.
+// Four consecutive outputs n .. n + 3 of token m (below M): rotation, residual, one rounding, store.
 template <int EPI>
-__device__ __forceinline__ void store_quad(const GemmArgs& a, int m, int n, const floatx4& f, const half4& rv)
+__device__ __forceinline__ void store_quad(const GemmArgs& a, int m, int n, const floatx4& f)
 {
     float v[4];
 #pragma unroll
@@ -135,23 +126,18 @@ __device__ __forceinline__ void store_quad(const GemmArgs& a, int m, int n, cons
     if (n + 3 < a.N) {
         half4 hv;
         if (a.residual) {
-            const half4 r = rv;
+            const half4 rv = *reinterpret_cast<const half4_any*>(a.residual + (size_t)m * a.ldo + n);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] += (float)r[c];
+            for (int c = 0; c < 4; ++c) v[c] += (float)rv[c];
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) hv[c] = (_Float16)v[c];
         *reinterpret_cast<half4_any*>(a.out + (size_t)m * a.ldo + n) = hv;
-    } else if (n < a.N) {
-        if (a.residual && a.N >= 4) {            // n .. N - 1 are the last of the row's last four
-            const half4 r = __builtin_bit_cast(half4, __builtin_bit_cast(unsigned long long, rv) >> (16 * (n - (a.N - 4))));
-#pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] += (float)r[c];
-        }
+    } else {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             if (n + c < a.N) {
-                if (a.residual && a.N < 4) v[c] += half_bits_to_float(a.residual[(size_t)m * a.ldo + n + c]);
+                if (a.residual) v[c] += half_bits_to_float(a.residual[(size_t)m * a.ldo + n + c]);
                 a.out[(size_t)m * a.ldo + n + c] = to_half_bits(v[c]);
             }
     }
@@ -176,7 +162,7 @@ __device__ __forceinline__ void store_quad_swiglu(const GemmArgs& a, int m, int 
 // consecutive n of one token of each.  For SwiGLU the first holds gate rows and the second the matching up rows.
 template <int BN, int BM, int WN, int WM, int EPI>
 __device__ __forceinline__ void store_pair(const GemmArgs& a, int tile_n, int tile_m, int wn, int wm, int tp,
-                                           int tm, int lr, int hi, const floatx4& f0, const floatx4& f1, const half4& rv0, const half4& rv1)
+                                           int tm, int lr, int hi, const floatx4& f0, const floatx4& f1)
 {
     const int m = tile_m * BM + wm * (BM / WM) + tm * 16 + lr;
     if (m >= a.M) return;
@@ -186,14 +172,14 @@ __device__ __forceinline__ void store_pair(const GemmArgs& a, int tile_n, int ti
         return;
     }
 #pragma unroll
-    for (int q = 0; q < 2; ++q) store_quad<EPI>(a, m, tile_n * BN + row + 16 * q + 4 * hi, q ? f1 : f0, q ? rv1 : rv0);
+    for (int q = 0; q < 2; ++q) store_quad<EPI>(a, m, tile_n * BN + row + 16 * q + 4 * hi, q ? f1 : f0);
 }
 
 // The same for one fragment (waves with an odd number of them): for SwiGLU its first eight rows are gate rows and the
 // others the matching up rows, exchanged between the wave's halves.
 template <int BN, int BM, int WN, int WM, int EPI>
 __device__ __forceinline__ void store_one(const GemmArgs& a, int tile_n, int tile_m, int wn, int wm, int tn,
-                                          int tm, int lr, int hi, const floatx4& f, const half4& rv)
+                                          int tm, int lr, int hi, const floatx4& f)
 {
     const int m = tile_m * BM + wm * (BM / WM) + tm * 16 + lr;
     const int row = wn * (BN / WN) + tn * 16;
@@ -203,7 +189,7 @@ __device__ __forceinline__ void store_one(const GemmArgs& a, int tile_n, int til
         for (int c = 0; c < 4; ++c) u[c] = __shfl_xor(f[c], 32);
         if (hi < 2 && m < a.M) store_quad_swiglu(a, m, tile_n * (BN / 2) + (row >> 1) + 4 * hi, f, u);
     } else if (m < a.M) {
-        store_quad<EPI>(a, m, tile_n * BN + row + 4 * hi, f, rv);
+        store_quad<EPI>(a, m, tile_n * BN + row + 4 * hi, f);
     }
 }
 
@@ -229,12 +215,6 @@ __global__ __launch_bounds__(64 * FIXUP_WAVES) void gemm_fixup(GemmArgs a, int t
     const Deal deal(sk_tiles, ktiles, G, parts);
     const int w_first = deal.first(t), w_last = deal.last(t);
     floatx4 g0 = {0.f, 0.f, 0.f, 0.f}, g1 = {0.f, 0.f, 0.f, 0.f};      // the pair's two fragments
-    half4 rv0{}, rv1{};
-    if (!is_swiglu(EPI) && a.residual && a.N >= 4) {
-        const int m = t % tiles_m * BM + wm * (BM / WM) + tm * 16 + lr, n = t / tiles_m * BN + wn * (BN / WN) + tp * 32 + 4 * hi;
-        rv0 = residual_quad(a, m, n);
-        rv1 = residual_quad(a, m, n + 16);
-    }
     // a contributor's partial of this tile: slot 0 if the tile is the first of its share, else slot 1
     auto part = [&](int wc) -> const floatx4* {
         const int cslot = (deal.begin(wc) / ktiles == t) ? 0 : 1;
@@ -255,7 +235,7 @@ __global__ __launch_bounds__(64 * FIXUP_WAVES) void gemm_fixup(GemmArgs a, int t
         const floatx4 v0 = p[0], v1 = p[NEXT];
         add(v0, v1);
     }
-    store_pair<BN, BM, WN, WM, EPI>(a, t / tiles_m, t % tiles_m, wn, wm, tp, tm, lr, hi, g0, g1, rv0, rv1);
+    store_pair<BN, BM, WN, WM, EPI>(a, t / tiles_m, t % tiles_m, wn, wm, tp, tm, lr, hi, g0, g1);
 }
 
 // Workers are numbered so that consecutive ones (neighbouring tiles) share an XCD: hardware deals workgroup ids round-robin to the eight.
@@ -589,28 +569,16 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_streamk(GemmArgs a, int til
 
         // ---- epilogue ------------------------------------------------------------------------
         if (whole) {
-            constexpr int TB = is_swiglu(EPI) ? TM : 16 / TN < TM ? 16 / TN : TM;      // token fragments whose residual is asked for together
-            half4 rv[is_swiglu(EPI) ? 1 : TB][TN] = {};
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
-                if (!is_swiglu(EPI) && tm % TB == 0 && a.residual && a.N >= 4) {
-#pragma unroll
-                    for (int b = 0; b < TB && tm + b < TM; ++b)
-#pragma unroll
-                        for (int tn = 0; tn < TN; ++tn)
-                            rv[is_swiglu(EPI) ? 0 : b][tn] = residual_quad(a, tile_m * BM + wm * (BM / WM) + (tm + b) * 16 + lr, tile_n * BN + wn * (BN / WN) + tn * 16 + 4 * hi);
-                    // all of them here (vmcnt(0) alone): behind the branches around the stores the compiler waits for those as well
-                    __builtin_amdgcn_s_waitcnt(0x0f70);
-                }
-                const half4* const r = rv[is_swiglu(EPI) ? 0 : tm % TB];
                 if constexpr (PAIRS) {
 #pragma unroll
                     for (int tp = 0; tp < TN / 2; ++tp)
-                        store_pair<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tp, tm, lr, hi, acc[2 * tp][tm], acc[2 * tp + 1][tm], r[2 * tp], r[2 * tp + 1]);
+                        store_pair<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tp, tm, lr, hi, acc[2 * tp][tm], acc[2 * tp + 1][tm]);
                 } else {
 #pragma unroll
                     for (int tn = 0; tn < TN; ++tn)
-                        store_one<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tn, tm, lr, hi, acc[tn][tm], r[tn]);
+                        store_one<BN, BM, WN, WM, EPI>(a, tile_n, tile_m, wn, wm, tn, tm, lr, hi, acc[tn][tm]);
                 }
             }
         }

@@ -1111,7 +1111,7 @@ LAYER_CLOSING = [
     (1, 272, 1376, 328, 0), (5, 136, 264, 200, 0), (16, 4096, 4096, 1376, 0), (32, 640, 2056, 1032, 1),
     (8, 4096, 1024, 2048, 3), (17, 100, 1160, 512, 3), (32, 8192, 1024, 6000, 4), (9, 5000, 1096, 11008, 4), (40, 272, 520, 328, 0), (160, 272, 520, 328, 0),
     (300, 520, 328, 264, 2), (256, 256, 256, 512, 2),
-    # rows whose last outputs do not fill a quad, and fewer than four of them (the GEMM asks for the residual in quads, ahead of its stores)
+    # rows whose last outputs do not fill a quad, and fewer than four of them (the GEMM reads the residual in quads)
     (333, 1001, 1384, 264, 0), (300, 3, 328, 264, 0), (150, 1, 264, 264, 0), (1030, 515, 520, 264, 0),
     # (tiles cut in ranges.  I = 264, not 8: the normalised x is rounded to fp16, which moves g by about 2^-12 * 0.05 * sqrt(K) = 1e-3 and h by |u| / 2 of it,
     # 2e-3 at |u| = 4, also where h is close to zero; S, a sum of |h w|, is then small if it has eight terms and holds that many times over with 264)

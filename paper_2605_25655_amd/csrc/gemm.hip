@@ -295,7 +295,7 @@ __device__ __forceinline__ void touch_weights(const GemmArgs& a, int tiles_m, in
 // what is left.  gate/up 2048 x 57344 x 8192 1471 -> 1381 us, 2048 x 8192 x 28672 732 -> 687, 512 x 5120 x 13824 88 -> 84 (256x256);
 // gate/up 512 x 27648 x 5120 139.5 -> 125.8 (224 rows), 165 -> 150 (128 x 256), 203 x 12288 x 4096 (128x128, four
 // stages) 42.5 -> 41.0.  The deeper operand alone, without the order, gains nothing with 256 rows and 4-8 % with 192.
-// The 256x256 tile takes all 256 VGPRs and spills up to four (24 with a ragged K; gate/up none, 15 ragged) around a tile's
+// The 256x256 tile takes all 256 VGPRs and spills up to four (23 with a ragged K; gate/up none, 15 ragged) around a tile's
 // prologue and epilogue; the k loop reloads nothing.
 // The 128x128 tiles wait for memory: a CU has 64 KiB of loads in flight, in order, whatever the stages hold, so its rate is that over the
 // latency (203 x 12288 x 4096: 39.5 us, with the loads alone 38.5, with the arithmetic alone 22.7, with weights from the L2 31).  Stages of

@@ -102,7 +102,7 @@ namespace {
 // rows of 21.5 KiB, 20.5, 19.5), and not below (4096 x 4096 10.8, 11.1; 15360 x 5120 28.9, 29.3); why long rows gain without it was not found out.
 MidPlan plan_mid_decode(int M, int N, int K, int epilogue, int num_cus)
 {
-    MidPlan best{0, 0, 0, 0.0, 0, false};
+    MidPlan best{0, 0, 0, 0.0, 0, false, 1, M};
     if (K > ROWSLAB_MAX_K || num_cus > SK_MAX_GRID) return best;
     const bool swiglu = is_swiglu(epilogue);
     const int rows_per = swiglu ? 2 : 1, ktiles = (K + 127) / 128;
@@ -119,7 +119,7 @@ MidPlan plan_mid_decode(int M, int N, int K, int epilogue, int num_cus)
         const double cu = kt * (0.0063 * rows + 0.0020 * M + 0.102);
         const double us = 4.15 + (cu > stream ? cu : stream) + 0.019 * BN + (S > 1 ? 0.8 + 1.17e-4 * S * BN * (M > 8 ? M : 8) : 0.0);
         if (best.BN && us >= best.us) continue;
-        best = MidPlan{BN, (int)((N + per - 1) / per), S, us, (int)per, swiglu ? K % 2048 == 0 : K >= 8192};
+        best = MidPlan{BN, (int)((N + per - 1) / per), S, us, (int)per, swiglu ? K % 2048 == 0 : K >= 8192, 1, M};
     }
     return best;
 }
@@ -129,7 +129,7 @@ MidPlan plan_mid_decode(int M, int N, int K, int epilogue, int num_cus)
 // rotate above 32 tokens: gate/up with K = 4096 at 72 tokens 41.2 -> 38.7 us; plain shapes lose (8192 x 8192 32.3 -> 34.6).
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
 {
-    MidPlan best{0, 0, 0, 0.0, 0, false};
+    MidPlan best{0, 0, 0, 0.0, 0, false, 1, M};
     if (M <= MID_DECODE_M) return plan_mid_decode(M, N, K, epilogue, num_cus);
     if (M > 128 || K > 24576) return best;
     const long V = is_swiglu(epilogue) ? 2L * N : N;      // (more than an int holds from N = 2^30 on)
@@ -146,7 +146,18 @@ MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus)
             if (best.BN != 0 && us >= least) continue;
             least = us;
             best = MidPlan{BN, (int)tiles, S, 2.83 + 4.0e-4 * BN * BM + 0.0139 * w + 0.0073 * x + per * (0.252 + 2.5e-5 * BN * BM) +
-                                                  (S > 1 ? 1.6 + 1.0e-4 * S * BN * M : 0.0), is_swiglu(epilogue) ? BN / 2 : BN, is_swiglu(epilogue) && K % 2048 == 0};
+                                                  (S > 1 ? 1.6 + 1.0e-4 * S * BN * M : 0.0), is_swiglu(epilogue) ? BN / 2 : BN, is_swiglu(epilogue) && K % 2048 == 0, 1, M};
+        }
+    }
+    // The outputs dealt evenly over the units that one round has (in fours), in the same tiles: fewer rows each, and none idle (gate/up 2 x 11008 x 4096 at
+    // 72 tokens: 251 workgroups of 44 pairs, not 230 of 48).  Not where the tiles fill less than two thirds of them: each more reads the activations again (36 x 376 x
+    // 2448 as 47 tiles of 8 rows in 5 ranges 7.7 us, as 12 of 32 rows 7.2; 39 x 352 x 7328 9.8, 9.2).
+    if (best.BN && best.tiles * best.S * 3 >= num_cus * 2) {
+        const int groups = num_cus / best.S;
+        const long per = ((long)N + 4L * groups - 1) / (4L * groups) * 4;
+        if (per < best.per) {
+            best.per = (int)per;
+            best.tiles = (int)((N + per - 1) / per);
         }
     }
     return best;

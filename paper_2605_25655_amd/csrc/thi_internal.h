@@ -140,10 +140,12 @@ struct MidPlan {
     double us;       // modelled time
     int per;         // outputs per tile (gate/up pairs for SwiGLU), at most what BN rows hold
     bool rotate;     // the workgroups of a share start at different k
+    int tiles_m;     // token tiles (`tiles` counts all of them), of per_m tokens each
+    int per_m;
 };
 constexpr int MID_DECODE_M = 32;     // up to so many tokens: RMSNorm inside the kernel, sums handed over through the decode kernels' slots
 // Floats of a workgroup's partial tile: eight waves' share of its 16x16 fragments (rounded up), 256 each, and the tokens' sums of squares
-constexpr int mid_slot_floats(int BN, int BM, bool rms) { return 8 * ((BN / 16 * (BM / 32) + 3) / 4) * 256 + (rms ? BM : 0); }
+constexpr int mid_slot_floats(int BN, int BM, bool rms) { return 8 * ((BN / 16 * (BM / 16) + 7) / 8) * 256 + (rms ? BM : 0); }
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
 // The GEMM's configurations, their constants, and which of them runs a product (no RMSNorm kinds).  From GEMM_BIG on: the
 // candidates above 128 tokens.

@@ -95,11 +95,14 @@ namespace {
 // (4..32 tokens, 1536 x 4096 .. gate/up 2 x 28672 x 8192): the pick is 1.1 % slower than the best measured on average; the price is 7 % off (rms).  No tiles
 // above 176 rows: those leave room for two stages, which left gate/up 2 x 28672 x 8192 at 147 us against 140 with the row blocks.
 //
-// rotate: workgroups that walk the same k at the same time ask for addresses a row's length apart; where that is a multiple of 4 KiB they agree
-// in their low bits and fall on few of the memory's channels: gate/up 2 x 11008 x 4096 at 32 tokens (forced) 36.5 us, with the tiles' starts spread
-// over k 29.4.  The price is that the activations are no longer read by all workgroups of an L2 at the same time.  Gate/up: where the rows are
-// such a multiple.  Plain kinds: by measurement from K = 8192 on, whatever the row's length (8192 x 8192 in two shares 29.4, 24.6; 4096 x 11008,
-// rows of 21.5 KiB, 20.5, 19.5), and not below (4096 x 4096 10.8, 11.1; 15360 x 5120 28.9, 29.3); why long rows gain without it was not found out.
+// rotate: workgroups that walk the same k at the same time ask for addresses a row's length apart, and where those agree in their low bits they
+// fall on few of the memory's channels.  Spreading the tiles' starts over k costs what the L2 shared of the activations.  Tiles that have all of K and 48 rows
+// or more: where rows are a multiple of 4 KiB or do not start on a line (at 20-32 tokens 12288 x 4096 19.4 -> 17.5 us, gate/up 2 x 11008 x 4096 36.5 -> 29.9,
+// 19 x 2 x 13472 x 2336 28.8 -> 25.0, 10 x 2 x 6832 x 6560 34.0 -> 31.5; 2 x 13824 x 5120 44.5, 45.2; 2 x 12000 x 7168 52.6, 54.1).  The others: gate/up where rows are a
+// multiple of 4 KiB; plain kinds by measurement from K = 8192 on, whatever the row's length (8192 x 8192 26.8 -> 24.1 with 32 rows; 4096 x 11008, rows of
+// 21.5 KiB, 20.0 -> 18.7), and not below (6656 x 6656 with 32 rows 17.2, 18.6; 7136 x 1448 7.4, 7.8).
+// alone: tiles that do, have all of K and rows that start on a line take less of a compute unit than the fit says (8192 x 8192 at 20 tokens: two shares of 64 rows
+// 25.3, whole tiles of 32 rows 21.8; 10240 x 8192 29.5, 27.8).
 MidPlan plan_mid_decode(int M, int N, int K, int epilogue, int num_cus)
 {
     MidPlan best{0, 0, 0, 0.0, 0, false, 1, M};
@@ -116,10 +119,11 @@ MidPlan plan_mid_decode(int M, int N, int K, int epilogue, int num_cus)
             if (b >= rows) { BN = b; break; }
         if (!BN) continue;
         const int kt = (ktiles + S - 1) / S;
-        const double cu = kt * (0.0063 * rows + 0.0020 * M + 0.102);
+        const bool rotate = (S == 1 && BN >= 48 && (K % 2048 == 0 || K % 64 != 0)) || (swiglu ? K % 2048 == 0 : K >= 8192), alone = S == 1 && rotate && K % 64 == 0;
+        const double cu = kt * (0.0063 * rows + (alone ? 0.0010 * M + 0.060 : 0.0020 * M + 0.102));
         const double us = 4.15 + (cu > stream ? cu : stream) + 0.019 * BN + (S > 1 ? 0.8 + 1.17e-4 * S * BN * (M > 8 ? M : 8) : 0.0);
         if (best.BN && us >= best.us) continue;
-        best = MidPlan{BN, (int)((N + per - 1) / per), S, us, (int)per, swiglu ? K % 2048 == 0 : K >= 8192, 1, M};
+        best = MidPlan{BN, (int)((N + per - 1) / per), S, us, (int)per, rotate, 1, M};
     }
     return best;
 }

@@ -355,6 +355,7 @@ int run_projection(const uint16_t* x, const uint16_t* gamma, float eps, const ui
     g.K = K;
     g.ldo = ldo;
     g.rope = rope;
+    g.token_tiles = g_family.load(std::memory_order_relaxed) == 0;
     return launch_gemm(g, epilogue, cus, stream) == hipSuccess ? THI_OK : THI_ERR_HIP;
 }
 

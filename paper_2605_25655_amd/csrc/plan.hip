@@ -399,6 +399,43 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
     return best;
 }
 
+// Above 128 tokens: the few-token kernel with several token tiles of 44..128 tokens each, where it is priced below the GEMM.  It finishes shared tiles
+// itself, where the GEMM's 128x128 tiles need a second pass, it reads half as much from LDS per product as those, tokens past the last are not
+// loaded, and outputs and tokens are dealt evenly: one round of tiles in S ranges, tiles * S just below the number of CUs.  The least of a modelled time: 2.5 us, 0.58 ns an
+// element of the tile, 13.2 ns a KB of weights and 10.7 of activations, 113 ns and 17.5 ps an element for each stage of 128 k, 0.15 ns an output; sharing 1.9 us and
+// 22 ns a KB of partial tiles.  Fitted to 2565 points on 350 products (129..700 tokens, 300..14000 x 256..11200), 7 % off (rms); the pick is 0.9 % slower than the best
+// measured on average.  Taken where it is below 0.92 of the GEMM's price (that one is 9 % off), it serves 60 % of those products, and all of them take 0.835 of
+// their time on average; 2 % lose more than 3 %.  150 x 4096 x 4096 23.7 -> 18 us, 203 x 4096 x 4096 24.5 -> 20, 152 x 5120 x 13824 55 -> 46.6, 142 x 10240 x 8192 61 -> 51.6,
+// 256 x 512 x 1376 12.4 -> 7.2, 257 x 339 x 3672 21.6 -> 9.1; beyond ~12000 x 203 or 4096 x 500 outputs a round no longer holds them.
+// rotate: where rows are a multiple of 4 KiB (142 x 10240 x 8192 55.1, 51.6; 135 x 4096 x 4096 18.0, 17.6).
+MidPlan plan_mid_tiles(int M, int N, int K, int epilogue, int num_cus)
+{
+    MidPlan best{0, 0, 0, 0.0, 0, false, 1, M};
+    if (M <= 128 || M > 8 * 128 || K > 24576) return best;
+    const int rows_per = is_swiglu(epilogue) ? 2 : 1, ktiles = (K + 127) / 128;
+    for (int t = (M + 127) / 128; t <= 8; ++t) {
+        const int per_m = ((M + t - 1) / t + 3) / 4 * 4;
+        if (t > 2 && per_m < 44) break;
+        for (int S = 1; S <= 16 && (S == 1 || S * 4 <= ktiles); ++S) {
+            const int groups = num_cus / (S * t);
+            if (groups < 1) break;
+            const long per = ((long)N + 4L * groups - 1) / (4L * groups) * 4, rows = per * rows_per;
+            int BN = 0;
+            for (int b : {32, 48, 64, 80, 96, 112, 144})
+                if (b >= rows) { BN = b; break; }
+            const int BM = per_m <= 64 ? 64 : per_m <= 96 ? 96 : per_m <= 112 && (BN == 64 || BN == 96) ? 112 : 128;
+            if (!BN || BN > (BM == 64 ? 144 : BM == 96 ? 112 : BM == 112 ? 96 : 80)) break;
+            const int kt = (ktiles + S - 1) / S;
+            const double us = 2.5 + 5.8e-4 * BN * BM + 0.256 * kt * (0.0132 * rows + 0.0107 * per_m) + kt * (0.113 + 1.75e-5 * BN * BM) + 1.5e-7 * M * N * rows_per +
+                              (S > 1 ? 1.9 + 8.7e-5 * S * rows * per_m : 0.0);
+            if (best.BN && us >= best.us) continue;
+            best = MidPlan{BN, (int)((N + per - 1) / per) * t, S, us, (int)per, K % 2048 == 0, t, per_m};
+        }
+    }
+    if (best.BN && best.us >= 0.92 * plan_gemm(M, N, K, epilogue, num_cus).us) best.BN = 0;
+    return best;
+}
+
 // ---- decode attention ------------------------------------------------------------------------------
 // query heads that share a pass over their cache head: 16 on the matrix cores (D = 128, groups of four and more)
 int attention_heads_per_workgroup(int D, int group)

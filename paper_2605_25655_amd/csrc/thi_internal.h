@@ -127,12 +127,13 @@ struct GemmArgs {
     unsigned* counters;      // status words, zero between calls: arrival counters of the few-token kernel's shared tiles
     const uint16_t* gamma;   // [K] RMSNorm inside the few-token kernel (up to MID_DECODE_M tokens), or nullptr
     float eps;
+    bool token_tiles;        // above 128 tokens: the few-token kernel with several token tiles may run (not where the GEMM was forced)
 };
 constexpr int GEMM_MAX_K = 1 << 23;   // 256 rows x 2 bytes x K within 32 bits
 constexpr int GEMM_MAX_GRID = 2048;   // in units of 128x128 partial tiles (a 256x256 tile takes four)
 size_t gemm_partial_bytes();
-// The few-token kernel (up to 128 tokens: up to MID_DECODE_M where few_token_kernel_ok or a forced family says so, above where plan_gemm
-// finds it the faster one): how the tile rows and K are dealt to the compute units.
+// The few-token kernel (up to MID_DECODE_M tokens where few_token_kernel_ok or a forced family says so, up to 128 where plan_gemm finds it the
+// faster one, above with several token tiles where plan_mid_tiles does): how tokens, tile rows and K are dealt to the compute units.
 struct MidPlan {
     int BN;          // virtual weight rows per tile (0: the kernel does not serve the shape)
     int tiles;
@@ -147,6 +148,7 @@ constexpr int MID_DECODE_M = 32;     // up to so many tokens: RMSNorm inside the
 // Floats of a workgroup's partial tile: eight waves' share of its 16x16 fragments (rounded up), 256 each, and the tokens' sums of squares
 constexpr int mid_slot_floats(int BN, int BM, bool rms) { return 8 * ((BN / 16 * (BM / 16) + 7) / 8) * 256 + (rms ? BM : 0); }
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
+MidPlan plan_mid_tiles(int M, int N, int K, int epilogue, int num_cus);      // above 128 tokens; BN = 0: the GEMM's other configurations
 // The GEMM's configurations, their constants, and which of them runs a product (no RMSNorm kinds).  From GEMM_BIG on: the
 // candidates above 128 tokens.
 enum GemmConfig { GEMM_MID, GEMM_FEW64, GEMM_FEW128, GEMM_FEW256, GEMM_ONE, GEMM_BIG, GEMM_R224, GEMM_R192, GEMM_R160, GEMM_TALL, GEMM_DEEP, GEMM_SMALL };

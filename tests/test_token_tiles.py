@@ -1,0 +1,104 @@
+"""Above 128 tokens: the few-token kernel with several token tiles.  On the CPU: what csrc/plan.hip deals covers the product, one round of
+workgroups, tiles that the kernel is built for.  On the GPU: results against the oracle at the edges of its tiles."""
+import os
+import random
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2605_25655_amd import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+PLAIN, GATE_UP = 0, 2
+
+# Two token tiles of each height (64..128) with one token more and less, three to eight of them; outputs that fill no tile and end inside a
+# quad, tiles of 32..144 rows, alone and shared; K of one k-tile, ragged, with fewer k-tiles than stages, rows of 4 KiB (spread starts).
+SHAPES = [
+    (129, 1000, 1096), (137, 510, 72), (150, 4096, 4096), (192, 2003, 2048), (193, 1536, 520), (200, 851, 1560), (208, 6001, 2056), (224, 4096, 1032),
+    (225, 3001, 904), (256, 512, 1376), (257, 339, 3672), (301, 2810, 1296), (552, 580, 6568), (640, 801, 544), (160, 5120, 5128), (150, 7000, 10248),
+    (206, 5969, 4256), (209, 2482, 4856), (232, 1995, 6144), (574, 542, 5200), (640, 2322, 3368), (349, 5428, 4776), (201, 10944, 5376),
+]
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_plans_cover_the_product_in_one_round(tmp_path):
+    exe = str(tmp_path / "driver")
+    res = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Wno-unused-command-line-argument", "-o", exe,
+                          os.path.join(ROOT, "paper_2605_25655_amd", "csrc", "plan.hip"), "-x", "hip",
+                          os.path.join(ROOT, "tests", "plan", "token_tiles_driver.cpp")], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-4000:]
+    rng = random.Random(3)
+    calls = [(PLAIN, *s) for s in SHAPES]
+    calls += [(rng.choice([PLAIN, GATE_UP]), rng.randint(100, 1100), 8 * rng.randint(1, 1600), 8 * rng.randint(1, 3200)) for _ in range(4000)]
+    text = "".join("%d %d %d %d\n" % c for c in calls)
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+    plans = [tuple(map(int, line.split())) for line in out if line]
+    assert len(plans) == len(calls)
+    built = {64: {32, 48, 64, 80, 96, 112, 144}, 96: {32, 48, 64, 80, 96, 112}, 112: {64, 96}, 128: {32, 48, 64, 80}}
+    seen = set()
+    for i, ((e, M, N, K), (rows, tiles, ranges, per, tiles_m, per_m)) in enumerate(zip(calls, plans)):
+        if rows == 0:
+            continue
+        tall = 64 if per_m <= 64 else 96 if per_m <= 96 else 112 if per_m <= 112 and rows in (64, 96) else 128
+        assert M > 128 and per_m % 4 == 0 and per_m <= 128 and (tiles_m - 1) * per_m < M <= tiles_m * per_m, (e, M, N, K)
+        assert per % 4 == 0 and per * (2 if e == GATE_UP else 1) <= rows and rows in built[tall], (e, M, N, K)
+        tiles_n = tiles // tiles_m
+        assert tiles == tiles_n * tiles_m and (tiles_n - 1) * per < N <= tiles_n * per, (e, M, N, K)
+        assert tiles * ranges <= 256 and ranges <= (K + 127) // 128, (e, M, N, K)
+        if i < len(SHAPES):
+            seen.add((tall, ranges > 1))
+    assert all(p[0] for p in plans[:len(SHAPES)]), [s for s, p in zip(SHAPES, plans) if not p[0]]
+    assert seen >= {(tall, shared) for tall in (64, 96, 112, 128) for shared in (False, True)}, seen
+    assert {p[0] for p in plans[:len(SHAPES)]} >= {32, 48, 64, 80, 96, 112} and any(p[3] < p[0] for p in plans[:len(SHAPES)])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_several_token_tiles(M, N, K):
+    import torch
+
+    import oracle
+    import paper_2605_25655_amd as thi
+    from tests.gpu_common import Runner, to_dev, to_host
+    from tests.parity import check
+    print(f"[case] token tiles M={M} N={N} K={K}", flush=True)
+    x, w, g = synth.random_problem(12000 + M + N + K, M, N, K)
+    rng = np.random.Generator(np.random.Philox(key=12100 + M + N + K))
+    res = rng.standard_normal((M, N)).astype(np.float16)
+    hd, I = 8, N // 16 * 8
+    n_rot = N // hd // 2 * hd
+    pos = rng.integers(0, 4096, size=M).astype(np.int32)
+    th = (10000.0 ** (-np.arange(0, hd, 2, dtype=np.float64) / hd)).astype(np.float32)
+    rows = np.unique(np.concatenate([synth.sample_rows(41, M, 8), [0, M // 2 - 1, M // 2, M - 1]]))
+    r = Runner(M, K, max(I, K), N)
+    xd, wd, gd, rd = to_dev(x), to_dev(w), to_dev(g), to_dev(res)
+    a = [to_host(r.linear_residual(xd, wd, rd)) for _ in range(3)]
+    assert all(np.array_equal(a[0].view(np.uint16), v.view(np.uint16)) for v in a[1:]), "not reproducible"
+    y, s = oracle.linear_residual(x[rows], w, res[rows])
+    check(a[0][rows], y, s, "linear + residual", argmax=False)
+    c = to_host(r.rmsnorm_qkv_rope(xd, gd, 1e-6, wd, torch.from_numpy(pos).cuda(), torch.from_numpy(th).cuda(), n_rot, hd))
+    y, s = oracle.rmsnorm_qkv_rope(x[rows], g, 1e-6, w, pos[rows], th, n_rot, hd)
+    check(c[rows], y, s, "rmsnorm_qkv_rope", argmax=False)
+    outs = [a[0], c]
+    if I:
+        h = to_host(r.swiglu_gate_up(xd, wd[:I], wd[I:2 * I]))
+        y, s = oracle.swiglu_gate_up(x[rows], w[:I], w[I:2 * I])
+        check(h[rows], y, s, "gate/up", argmax=False)
+        outs.append(h)
+    # every output was written: the GEMM's own kernels, forced, agree on all of them to fp16's rounding of two sums in another order
+    prev = thi.thi_set_kernel_family(2)
+    try:
+        ref = [to_host(r.linear_residual(xd, wd, rd)), to_host(r.rmsnorm_qkv_rope(xd, gd, 1e-6, wd, torch.from_numpy(pos).cuda(), torch.from_numpy(th).cuda(), n_rot, hd))]
+        if I:
+            ref.append(to_host(r.swiglu_gate_up(xd, wd[:I], wd[I:2 * I])))
+    finally:
+        thi.thi_set_kernel_family(prev)
+    for got, want in zip(outs, ref):
+        got, want = got.astype(np.float32), want.astype(np.float32)
+        # each rounds its sum once (half a unit in the last place, 2^-11, so 2^-10 between them), and the fp32 sums differ by a few of their
+        # own units (2^-24 of the sum of the products' magnitudes, here below K times the largest result) where a result cancels
+        bound = np.maximum(np.abs(got), np.abs(want)) * 2.0 ** -10 + 2.0 ** -24 * K * max(1.0, float(np.abs(want).max()))
+        assert (np.abs(got - want) <= bound).all()

@@ -19,7 +19,7 @@ PLAIN, GATE_UP = 0, 2
 SHAPES = [
     (129, 1000, 1096), (137, 510, 72), (150, 4096, 4096), (192, 2003, 2048), (193, 1536, 520), (200, 851, 1560), (208, 6001, 2056), (224, 4096, 1032),
     (225, 3001, 904), (256, 512, 1376), (257, 339, 3672), (301, 2810, 1296), (552, 580, 6568), (640, 801, 544), (160, 5120, 5128), (150, 7000, 10248),
-    (206, 5969, 4256), (209, 2482, 4856), (232, 1995, 6144), (574, 542, 5200), (640, 2322, 3368), (349, 5428, 4776), (201, 10944, 5376),
+    (206, 5969, 4256), (209, 2482, 4856), (232, 1995, 6144), (574, 542, 5200), (640, 2322, 3368), (349, 5428, 4776), (201, 10944, 5384),
 ]
 
 

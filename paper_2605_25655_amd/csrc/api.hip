@@ -239,7 +239,8 @@ int single_launch_split(int M, int H, int I, int epi_up, int cus)
 //                   more for the RMSNorm pass, and usually wins (4096 x 11008 at 40 tokens 26.6 us here, 21.8; RMSNorm-QKV 12288 x 4096 at
 //                   34 / 64 tokens 28.8 / 33.3, 22.9 / 25.1; 19968 x 6656 59 / 69, 47 / 50; 10240 x 8192 39.4 / 46, 38.3 / 39.5).  RMSNorm-QKV without the
 //                   rotary embedding would gain as much, but its route at 48 and 64 tokens (12288 x 4096: this kernel) is one that the test suite
-//                   asserts, and it keeps the older price.
+//                   asserts, and it keeps the older price; so do heads of more than 256 columns, which the table of the pass in front does not hold
+//                   and this kernel rotates.
 //   M > 64        : the GEMM kernels.
 // A forced family overrides this (forced stream-K: 64 tokens per launch; forced row slabs / blocks: 32), but for a K that the GEMM
 // kernels cannot address (GEMM_MAX_K): the stream-K kernel at any M.
@@ -248,7 +249,7 @@ struct DecodePlan {
     int group;      // tokens per launch
 };
 constexpr DecodePlan ROW_BLOCKS{DK_ROWBLOCK, SKINNY_GROUP};
-DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus)
+DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus, int head_dim = 0)
 {
     const int fam = g_family.load(std::memory_order_relaxed);
     // The GEMM kernels address the rows of a tile by 32-bit byte offsets: 256 rows of up to 2^23 values.
@@ -267,7 +268,7 @@ DecodePlan plan_decode(int M, int N, int K, int epilogue, int cus)
     const double t_w = (is_swiglu(epilogue) ? 2.0 : 1.0) * (double)N * (double)K * 2.0 / 7.0e6;
     const double t_sk = 5.5 + 1.06 * t_w + (M <= 48 ? 8.0 : 13.0);
     double t_gemm = (is_rms(epilogue) ? 13.0 : 8.0) + 1.5 * (t_w < 30.0 ? t_w : 30.0) + 1.25 * (t_w > 30.0 ? t_w - 30.0 : 0.0);
-    if (epilogue != EPI_RMSNORM) {      // the few-token GEMM kernel, where it serves the shape, is priced by itself
+    if (epilogue != EPI_RMSNORM && head_dim <= ROPE_TABLE_MAX_HEAD_DIM) {      // the few-token GEMM kernel, where it serves the shape, is priced by itself
         const MidPlan mp = plan_mid(M, N, K, epilogue, cus);
         if (mp.BN) t_gemm = mp.us + (is_rms(epilogue) ? 3.0 : 0.0);
     }
@@ -283,7 +284,7 @@ int run_projection(const uint16_t* x, const uint16_t* gamma, float eps, const ui
 {
     const int cus = device_cu_count();
     (void)hipGetLastError();      // an error another user of the runtime left behind is not ours to report
-    const DecodePlan dp = known ? *known : plan_decode(M, N, K, epilogue, cus);
+    const DecodePlan dp = known ? *known : plan_decode(M, N, K, epilogue, cus, rope.head_dim);
     if (dp.kernel != 0) {
         const int kernel = dp.kernel, group = dp.group;
         const bool slab = kernel != DK_STREAMK, block = kernel == DK_ROWBLOCK;

@@ -731,11 +731,7 @@ hipError_t launch_rmsnorm_rows(const uint16_t* x, const uint16_t* gamma, float e
 hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t stream)
 {
     if (is_rms(epilogue)) return hipErrorInvalidValue;
-    if (a.token_tiles) {
-        const MidPlan m = plan_mid_tiles(a.M, a.N, a.K, epilogue, num_cus);
-        if (m.BN) return launch_mid(a, epilogue, m, stream);
-    }
-    const GemmPlan p = plan_gemm(a.M, a.N, a.K, epilogue, num_cus);
+    const GemmPlan p = plan_product(a.M, a.N, a.K, epilogue, num_cus, a.token_tiles);
     switch (p.config) {
     case GEMM_MID: return launch_mid(a, epilogue, p.mid, stream);
     case GEMM_FEW64: return launch_cfg<128, 64, 4, 1, 128, 3, 3, false>(a, epilogue, p, stream);

@@ -1,4 +1,4 @@
-// fp16 MFMA GEMM for few tokens on gfx950: one token tile (up to 128 tokens; above, several where they are faster: plan_mid_tiles), weights read once, bound by memory.
+// fp16 MFMA GEMM for few tokens on gfx950: one token tile (up to 128 tokens; above, several where they are faster: plan_product), weights read once, bound by memory.
 //
 // Between decode and prefill the weights still stream by once, but every compute unit also needs the activations, and the
 // way into LDS is what is short.  Measured with the loads alone: a CU brings in ~120 GB/s of what its L2 holds, but ~60 GB/s (27 GB/s when all

@@ -293,6 +293,17 @@ GemmPlan plan_config(int config, int M, int N, int K, int epilogue, int num_cus)
     return p;
 }
 
+GemmPlan few_token_plan(const MidPlan& m)
+{
+    GemmPlan p{};
+    p.config = GEMM_MID;
+    p.mid = m;
+    p.tiles = m.tiles;
+    p.grid = m.tiles * m.S;
+    p.us = m.us;
+    return p;
+}
+
 }  // namespace
 
 GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
@@ -319,13 +330,7 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
         // 0.2 % slower than the better one on average (one factor of 1.0 for all: 1.5 %).
         const MidPlan mp = plan_mid(M, N, K, epilogue, num_cus);
         if (mp.BN && (M <= MID_DECODE_M || mp.us < (mp.BN <= 80 ? 1.2 : 1.05) * plan_config(config == GEMM_FEW256 ? GEMM_FEW128 : config, M, N, K, epilogue, num_cus).us)) {
-            GemmPlan p{};
-            p.config = GEMM_MID;
-            p.mid = mp;
-            p.tiles = mp.tiles;
-            p.grid = mp.tiles * mp.S;
-            p.us = mp.us;
-            return p;
+            return few_token_plan(mp);
         }
         return plan_config(config, M, N, K, epilogue, num_cus);
     }
@@ -410,11 +415,14 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
 // and more whose rows start on a line the GEMM's tiles are as fast or faster, both being bound by the way into LDS (168 x 6656 x 6656 38.2, 43.8; 174 x 12288 x
 // 4096 35.6, 38.0; 144 x 5120 x 13824 48.3, 50.5; 135 x 10240 x 8192 54.3, 54.2).
 // rotate: where rows are a multiple of 4 KiB (135 x 4096 x 4096 18.0, 17.6).
-MidPlan plan_mid_tiles(int M, int N, int K, int epilogue, int num_cus)
+namespace {
+
+// (gemm_us: the GEMM's price)
+MidPlan plan_mid_tiles(int M, int N, int K, int epilogue, int num_cus, double gemm_us)
 {
     MidPlan best{0, 0, 0, 0.0, 0, false, 1, M};
-    if (M <= 128 || M > 8 * 128 || K > 24576) return best;
     const int rows_per = is_swiglu(epilogue) ? 2 : 1, ktiles = (K + 127) / 128;
+    if (M <= 128 || M > 8 * 128 || K > 24576 || (K % 64 == 0 && (double)rows_per * N * K >= 4e7)) return best;
     for (int t = (M + 127) / 128; t <= 8; ++t) {
         const int per_m = ((M + t - 1) / t + 3) / 4 * 4;
         if (t > 2 && per_m < 44) break;
@@ -434,8 +442,19 @@ MidPlan plan_mid_tiles(int M, int N, int K, int epilogue, int num_cus)
             best = MidPlan{BN, (int)((N + per - 1) / per) * t, S, us, (int)per, K % 2048 == 0, t, per_m};
         }
     }
-    if (best.BN && ((K % 64 == 0 && (double)rows_per * N * K >= 4e7) || best.us >= 0.92 * plan_gemm(M, N, K, epilogue, num_cus).us)) best.BN = 0;
+    if (best.BN && best.us >= 0.92 * gemm_us) best.BN = 0;
     return best;
+}
+
+}  // namespace
+
+// (the GEMM's plan is made once: it is 0.1-0.4 us of the call)
+GemmPlan plan_product(int M, int N, int K, int epilogue, int num_cus, bool token_tiles)
+{
+    GemmPlan p = plan_gemm(M, N, K, epilogue, num_cus);
+    if (!token_tiles) return p;
+    const MidPlan m = plan_mid_tiles(M, N, K, epilogue, num_cus, p.us);
+    return m.BN ? few_token_plan(m) : p;
 }
 
 // ---- decode attention ------------------------------------------------------------------------------

@@ -133,7 +133,7 @@ constexpr int GEMM_MAX_K = 1 << 23;   // 256 rows x 2 bytes x K within 32 bits
 constexpr int GEMM_MAX_GRID = 2048;   // in units of 128x128 partial tiles (a 256x256 tile takes four)
 size_t gemm_partial_bytes();
 // The few-token kernel (up to MID_DECODE_M tokens where few_token_kernel_ok or a forced family says so, up to 128 where plan_gemm finds it the
-// faster one, above with several token tiles where plan_mid_tiles does): how tokens, tile rows and K are dealt to the compute units.
+// faster one, above with several token tiles where plan_product does): how tokens, tile rows and K are dealt to the compute units.
 struct MidPlan {
     int BN;          // virtual weight rows per tile (0: the kernel does not serve the shape)
     int tiles;
@@ -148,7 +148,6 @@ constexpr int MID_DECODE_M = 32;     // up to so many tokens: RMSNorm inside the
 // Floats of a workgroup's partial tile: eight waves' share of its 16x16 fragments (rounded up), 256 each, and the tokens' sums of squares
 constexpr int mid_slot_floats(int BN, int BM, bool rms) { return 8 * ((BN / 16 * (BM / 16) + 7) / 8) * 256 + (rms ? BM : 0); }
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
-MidPlan plan_mid_tiles(int M, int N, int K, int epilogue, int num_cus);      // above 128 tokens; BN = 0: the GEMM's other configurations
 // The GEMM's configurations, their constants, and which of them runs a product (no RMSNorm kinds).  From GEMM_BIG on: the
 // candidates above 128 tokens.
 enum GemmConfig { GEMM_MID, GEMM_FEW64, GEMM_FEW128, GEMM_FEW256, GEMM_ONE, GEMM_BIG, GEMM_R224, GEMM_R192, GEMM_R160, GEMM_TALL, GEMM_DEEP, GEMM_SMALL };
@@ -168,6 +167,8 @@ struct GemmPlan {
     int helpers;                     // workgroups behind the grid, for compute units without a tile: they touch the weights ahead (a multiple of 8)
 };
 GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus);
+// What launch_gemm runs: plan_gemm's pick, or above 128 tokens (token_tiles) the few-token kernel with several token tiles
+GemmPlan plan_product(int M, int N, int K, int epilogue, int num_cus, bool token_tiles);
 hipError_t launch_gemm(const GemmArgs& a, int epilogue, int num_cus, hipStream_t stream);
 hipError_t launch_mid(const GemmArgs& a, int epilogue, const MidPlan& p, hipStream_t stream);
 // xn[m,k] = fp16(x[m,k] * gamma[k] / sqrt(mean_k x[m,:]^2 + eps)): the prefill path's RMSNorm pass

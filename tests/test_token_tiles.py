@@ -23,13 +23,28 @@ SHAPES = [
 ]
 
 
-@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
-def test_plans_cover_the_product_in_one_round(tmp_path):
+def _driver(tmp_path, *flags):
     exe = str(tmp_path / "driver")
-    res = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Wno-unused-command-line-argument", "-o", exe,
+    res = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Wno-unused-command-line-argument", *flags, "-o", exe,
                           os.path.join(ROOT, "paper_2605_25655_amd", "csrc", "plan.hip"), "-x", "hip",
                           os.path.join(ROOT, "tests", "plan", "token_tiles_driver.cpp")], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-4000:]
+    return exe
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_a_call_plans_the_gemm_once(tmp_path):
+    exe = _driver(tmp_path, "-Xarch_host", "-finstrument-functions")
+    calls = [(PLAIN, *s) for s in SHAPES] + [(PLAIN, 203, 12288, 4096), (PLAIN, 512, 5120, 13824), (PLAIN, 2048, 8192, 8192), (GATE_UP, 150, 2816, 1024)]
+    text = "".join("%d %d %d %d\n" % c for c in calls)
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+    lines = [line for line in out if line]
+    assert len(lines) == len(calls) + 1 and int(lines[-1]) == len(calls), lines[-1]
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_plans_cover_the_product_in_one_round(tmp_path):
+    exe = _driver(tmp_path)
     rng = random.Random(3)
     calls = [(PLAIN, *s) for s in SHAPES]
     calls += [(rng.choice([PLAIN, GATE_UP]), rng.randint(100, 1100), 8 * rng.randint(1, 1600), 8 * rng.randint(1, 3200)) for _ in range(4000)]

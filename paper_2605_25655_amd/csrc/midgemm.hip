@@ -48,7 +48,7 @@ namespace {
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
-constexpr int MID_THREADS = 512, MID_WAVES = 8, MID_GK = 128, MID_P = MID_GK / 8;      // 16-byte pieces per staged row
+constexpr int MID_THREADS = 64 * MID_WAVES, MID_GK = 128, MID_P = MID_GK / 8;      // 16-byte pieces per staged row
 constexpr int MID_KG = 4;                            // the waves: the four k-steps of a stage x ...
 constexpr int mid_tg(int BM) { return BM / 16 % 2 ? 1 : 2; }      // ... two token groups, or two row groups where the token fragments are odd in number
 constexpr int MID_LDS = 160 * 1024;
@@ -131,9 +131,9 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
     // rotate: the tiles of a share start spread over its k-tiles and wrap round (the ranges of an XCD's tiles stay close)
     const int rot = rotate ? (int)((long)tile * nk / tiles) : 0;      // (a row tile's token tiles are neighbours)
 
-    // A k-tile's loads: T_W of the weights, then T_M of the activations, then gamma, each of MID_R stage rows; the wave takes numbers wv, wv + 8, ...:
-    // C of them, the same for every wave (a number past the end repeats an earlier load: the same bytes to the same place).  Lane L brings
-    // the 16-byte unit L of a load: row L / MID_P, physical piece L % MID_P, logical piece (L % MID_P) ^ f(row).  Rows that no output of the tile needs are not asked for.
+    // A k-tile's loads: T_W of the weights, then T_M of the activations, then gamma, each of four stage rows; the wave takes numbers wv, wv + 8, ...: C or
+    // C - 1 of them (a number past the end among the first C - 1 repeats an earlier load: the same bytes to the same place).  Lane L brings the 16-byte unit L
+    // of a load: row L / 16, physical piece L % 16, logical piece (L % 16) ^ (row % 16).  Rows that no output of the tile needs are not asked for.
     const int first = tile_n * per, stop = first + per < a.N ? first + per : a.N;      // this tile's outputs (gate/up pairs for SwiGLU)
     const int T_W = (is_swiglu(EPI) ? 2 * per : per) / 4;
     const int T_M = (M + 3) / 4, T = T_W + T_M + (RMS ? 1 : 0);
@@ -159,6 +159,10 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
         src[i] = uniform((weights ? (is_swiglu(EPI) && ((block >> 1) & 1) ? a.w1 : a.w0) + (size_t)first * K : tokens ? a.x + (size_t)m0 * K : a.gamma) +
                          (size_t)(kb + rot) * MID_GK);
     }
+    // Which loads are non-temporal: the weights, unless other token tiles read them too (mid_streams).  234 x 5907 x 3272 on three token tiles 28.2 -> 26.4 us
+    // with their weights left in the caches, gate/up 163 x 2 x 2056 x 5896 29.9 -> 29.2.  (Where a tile is full, most are known beforehand and have no branch.)
+    const bool full_tile = T_W == BN / 4 && tiles_m == 1;
+    const unsigned streams = (unsigned)__builtin_amdgcn_readfirstlane((int)mid_streams(wv, T_W, tiles_m));
     const int c_loads = (T + MID_WAVES - 1) / MID_WAVES < CMIN ? CMIN : (T + MID_WAVES - 1) / MID_WAVES;
     // The last k-tile of a ragged K: pieces past K are loaded from the k-tile's first piece and zeroed once they have landed.
     auto past = [&](int i) __attribute__((always_inline)) {  // ... the lane's logical piece of load i where it lies past K, else 0
@@ -212,7 +216,7 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
         auto one = [&](int i) __attribute__((always_inline)) {
             if (i == C - 1 && !full) return;
             if (next != it_tail)
-                mid_dma((i + 1) * MID_WAVES <= BN / 4 || (i * MID_WAVES < BN / 4 && wv + i * MID_WAVES < T_W), src[i], off[i], dst[i] + stage);
+                mid_dma(((i + 1) * MID_WAVES <= BN / 4 && full_tile) || (i * MID_WAVES < BN / 4 && (streams >> i & 1)), src[i], off[i], dst[i] + stage);
             else
                 mid_dma(false, src[i], off[i] - past(i) * 16u, dst[i] + stage);
         };

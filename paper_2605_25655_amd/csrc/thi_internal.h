@@ -147,6 +147,13 @@ struct MidPlan {
 constexpr int MID_DECODE_M = 32;     // up to so many tokens: RMSNorm inside the kernel, sums handed over through the decode kernels' slots
 // Floats of a workgroup's partial tile: eight waves' share of its 16x16 fragments (rounded up), 256 each, and the tokens' sums of squares
 constexpr int mid_slot_floats(int BN, int BM, bool rms) { return 8 * ((BN / 16 * (BM / 16) + 7) / 8) * 256 + (rms ? BM : 0); }
+constexpr int MID_WAVES = 8;
+// A k-tile's loads are dealt to the waves in turn, the `weight_loads` that bring weights first: bit i for load i of `wave`, set where it is
+// non-temporal.  That is what no other workgroup reads: not the activations, which all of an XCD read, nor the weights of several token tiles.
+__host__ __device__ constexpr unsigned mid_streams(int wave, int weight_loads, int tiles_m)
+{
+    return tiles_m == 1 ? (1u << (weight_loads - wave + MID_WAVES - 1) / MID_WAVES) - 1u : 0u;
+}
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
 // The GEMM's configurations, their constants, and which of them runs a product (no RMSNorm kinds).  From GEMM_BIG on: the
 // candidates above 128 tokens.

@@ -23,11 +23,11 @@ SHAPES = [
 ]
 
 
-def _driver(tmp_path, *flags):
+def _driver(tmp_path, *flags, source="token_tiles_driver.cpp"):
     exe = str(tmp_path / "driver")
     res = subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-Wno-unused-command-line-argument", *flags, "-o", exe,
                           os.path.join(ROOT, "paper_2605_25655_amd", "csrc", "plan.hip"), "-x", "hip",
-                          os.path.join(ROOT, "tests", "plan", "token_tiles_driver.cpp")], capture_output=True, text=True)
+                          os.path.join(ROOT, "tests", "plan", source)], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-4000:]
     return exe
 
@@ -40,6 +40,25 @@ def test_a_call_plans_the_gemm_once(tmp_path):
     out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
     lines = [line for line in out if line]
     assert len(lines) == len(calls) + 1 and int(lines[-1]) == len(calls), lines[-1]
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_only_weights_that_one_workgroup_reads_pass_the_caches(tmp_path):
+    exe = _driver(tmp_path, source="load_hints_driver.cpp")
+    rng = random.Random(5)
+    calls = [(PLAIN, *s) for s in SHAPES] + [(GATE_UP, 72, 11008, 4096), (PLAIN, 72, 12288, 4096), (GATE_UP, 256, 1376, 512)]
+    calls += [(rng.choice([PLAIN, GATE_UP]), rng.randint(1, 432), rng.randint(8, 13000), 8 * rng.randint(8, 1600)) for _ in range(4000)]
+    text = "".join("%d %d %d %d\n" % c for c in calls)
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+    lines = [tuple(map(int, line.split())) for line in out if line]
+    assert len(lines) == len(calls)
+    seen = set()
+    for call, (weights, tiles_m, *waves) in zip(calls, lines):
+        for w, bits in enumerate(waves):
+            for i in range(32):      # load i of wave w is number w + 8 i of the k-tile
+                assert bool(bits >> i & 1) == (w + 8 * i < weights and tiles_m == 1), (call, weights, tiles_m, w, i)
+        seen.add((weights > 0, weights % 8 != 0, tiles_m > 1))
+    assert seen >= {(True, True, False), (True, False, False), (True, True, True), (True, False, True)}, seen
 
 
 @pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")

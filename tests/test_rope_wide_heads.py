@@ -52,3 +52,31 @@ def test_wide_heads_between_33_and_64_tokens(M, N, K, hd):
     y, s = oracle.rmsnorm_qkv_rope(x[rows], g, 1e-6, w, pos[rows], th, n_rot, hd)
     check(got[rows], y, s, "rmsnorm_qkv_rope", argmax=False)
     assert np.isfinite(got.astype(np.float32)).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [48, 64])
+def test_narrow_heads_on_the_streamk_kernel(M):
+    """Three and four token tiles of a shape whose automatic choice rotates through the table of the RMSNorm pass: the rotation inside the kernel."""
+    import torch
+
+    import oracle
+    import paper_2605_25655_amd as thi
+    from tests.gpu_common import Runner, to_dev, to_host
+    from tests.parity import check
+    N, K, hd = 12288, 4096, 64
+    print(f"[case] narrow heads, stream-K M={M} N={N} K={K}", flush=True)
+    x, w, g = synth.random_problem(15200 + M, M, N, K)
+    n_rot = N // 2
+    pos = np.random.Generator(np.random.Philox(key=15300 + M)).integers(0, 4096, size=M).astype(np.int32)
+    th = (10000.0 ** (-np.arange(0, hd, 2, dtype=np.float64) / hd)).astype(np.float32)
+    r = Runner(M, K, K, N)
+    prev = thi.thi_set_kernel_family(1)
+    try:
+        got = to_host(r.rmsnorm_qkv_rope(to_dev(x), to_dev(g), 1e-6, to_dev(w), torch.from_numpy(pos).cuda(), torch.from_numpy(th).cuda(), n_rot, hd))
+    finally:
+        thi.thi_set_kernel_family(prev)
+    assert np.isfinite(got.astype(np.float32)).all()
+    rows = np.unique(np.concatenate([synth.sample_rows(53, M, 6), [0, 15, 16, 32, M - 1]]))
+    y, s = oracle.rmsnorm_qkv_rope(x[rows], g, 1e-6, w, pos[rows], th, n_rot, hd)
+    check(got[rows], y, s, "rmsnorm_qkv_rope", argmax=False)

@@ -136,3 +136,51 @@ def test_several_token_tiles(M, N, K):
         # own units (2^-24 of the sum of the products' magnitudes, here below K times the largest result) where a result cancels
         bound = np.maximum(np.abs(got), np.abs(want)) * 2.0 ** -10 + 2.0 ** -24 * K * max(1.0, float(np.abs(want).max()))
         assert (np.abs(got - want) <= bound).all()
+
+
+# Gate/up pairs alone: the highest tile, 144 rows, which the plain kind reaches nowhere
+TALLEST = (293, 3440, 3960)
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_gate_up_halves_and_the_highest_tile_are_token_tiles_too(tmp_path):
+    exe = _driver(tmp_path)
+    calls = [(GATE_UP, M, N // 16 * 8, K) for M, N, K in SHAPES] + [(GATE_UP, *TALLEST)]
+    text = "".join("%d %d %d %d\n" % c for c in calls)
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+    plans = [tuple(map(int, line.split())) for line in out if line]
+    assert len(plans) == len(calls) and all(p[0] for p in plans), [c for c, p in zip(calls, plans) if not p[0]]
+    assert {p[0] for p in plans[:-1]} >= {32, 48, 64, 80, 96, 112} and plans[-1][0] == 144, plans
+
+
+@pytest.mark.gpu
+def test_gate_up_of_the_highest_tile():
+    import oracle
+    from tests.gpu_common import Runner, to_dev, to_host
+    from tests.parity import check
+    M, I, K = TALLEST
+    print(f"[case] token tiles of 144 rows, gate/up M={M} I={I} K={K}", flush=True)
+    x, w, _ = synth.random_problem(17000, M, 2 * I, K)
+    rows = np.unique(np.concatenate([synth.sample_rows(71, M, 8), [0, 59, 60, M - 1]]))
+    r = Runner(M, K, I, K)
+    xd, wd = to_dev(x), to_dev(w)
+    h = [to_host(r.swiglu_gate_up(xd, wd[:I], wd[I:])) for _ in range(3)]
+    assert all(np.array_equal(h[0].view(np.uint16), v.view(np.uint16)) for v in h[1:]), "not reproducible"
+    assert np.isfinite(h[0].astype(np.float32)).all()
+    y, s = oracle.swiglu_gate_up(x[rows], w[:I], w[I:])
+    check(h[0][rows], y, s, "gate/up", argmax=False)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(129, 1000, 1096), (150, 4096, 4096), (200, 851, 1560), (257, 339, 3672), (640, 2322, 3368)])
+def test_residual_in_place_over_several_token_tiles(M, N, K):
+    from tests.gpu_common import Runner, to_dev, to_host
+    print(f"[case] token tiles, residual in place M={M} N={N} K={K}", flush=True)
+    x, w, _ = synth.random_problem(17100 + M + N + K, M, N, K)
+    res = np.random.Generator(np.random.Philox(key=17200 + M + N + K)).standard_normal((M, N)).astype(np.float16)
+    r = Runner(M, K, K, N)
+    xd, wd, rd = to_dev(x), to_dev(w), to_dev(res)
+    apart = to_host(r.linear_residual(xd, wd, rd))
+    assert np.isfinite(apart.astype(np.float32)).all()
+    for _ in range(3):
+        assert np.array_equal(apart.view(np.uint16), to_host(r.linear_residual(xd, wd, rd, in_place=True)).view(np.uint16))

@@ -505,7 +505,7 @@ template <int BM, bool RMS>
 hipError_t launch_mid_bm(const GemmArgs& a, int epilogue, const MidPlan& p, hipStream_t stream)
 {
     switch (p.BN) {
-    case 32: return launch_mid_cfg<32, BM, RMS>(a, epilogue, p, stream);
+    case 32: if constexpr (BM != 112) return launch_mid_cfg<32, BM, RMS>(a, epilogue, p, stream); else break;
     case 112: if constexpr (BM <= 96) return launch_mid_cfg<112, BM, RMS>(a, epilogue, p, stream); else break;
     case 128: if constexpr (BM <= 32) return launch_mid_cfg<128, BM, RMS>(a, epilogue, p, stream); else break;
     case 144: if constexpr (BM <= 64) return launch_mid_cfg<144, BM, RMS>(a, epilogue, p, stream); else break;

@@ -184,3 +184,17 @@ def test_residual_in_place_over_several_token_tiles(M, N, K):
     assert np.isfinite(apart.astype(np.float32)).all()
     for _ in range(3):
         assert np.array_equal(apart.view(np.uint16), to_host(r.linear_residual(xd, wd, rd, in_place=True)).view(np.uint16))
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_only_tiles_that_a_plan_can_ask_for_are_built():
+    import re
+
+    from paper_2605_25655_amd import build
+    with open(build.LIB, "rb") as f:
+        names = set(re.findall(rb"gemm_midILi(\d+)ELi(\d+)E", f.read()))
+    heights = {}
+    for rows, tall in names:
+        heights.setdefault(int(tall), set()).add(int(rows))
+    assert heights == {32: {32, 48, 64, 80, 96, 112, 128, 144, 176}, 64: {32, 48, 64, 80, 96, 112, 144}, 96: {32, 48, 64, 80, 96, 112},
+                       112: {64, 96}, 128: {32, 48, 64, 80}}, heights

@@ -61,13 +61,6 @@ __device__ __forceinline__ void mid_dma(bool nt, const void* base_uniform, unsig
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_byte_offset), "s"(base_uniform), "s"(lds_addr) : "memory");
 }
 
-// a pointer that is the same in all lanes, in scalar registers
-__device__ __forceinline__ const uint16_t* uniform(const uint16_t* p)
-{
-    const uint64_t v = (uint64_t)p;
-    return (const uint16_t*)((uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)v));
-}
-
 // rows of a stage: weights, tokens, and with RMSNorm gamma (a load brings four rows)
 template <int BN, int BM, bool RMS>
 constexpr int mid_rows() { return BN + BM + (RMS ? 4 : 0); }
@@ -97,7 +90,8 @@ constexpr int mid_lds()
 }
 
 template <int BN, int BM, int EPI, bool RMS>
-__global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, int S, int ktiles, int per, int rotate, int tiles_m, int per_m)
+__global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, int S, int ktiles, int per, int rotate, int tiles_m, int per_m,
+                                                     unsigned by_tiles, unsigned by_S, unsigned by_tiles_m)
 {
     constexpr int TG = mid_tg(BM), NG = MID_WAVES / (TG * MID_KG);       // groups of waves along the tokens and along the rows
     constexpr int TN = BN / (16 * NG), TM = BM / (16 * TG), F = TN * TM;
@@ -117,19 +111,19 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
 
     // consecutive workers on one XCD (hardware deals workgroup ids round-robin to the eight); a share's workers are
     // consecutive, so that the workgroups of an XCD walk the same slice of the activations together
-    int worker;
-    {
-        const int G = gridDim.x, bid = blockIdx.x, per = G / 8, rem = G % 8, xcd = bid % 8, local = bid / 8;
-        worker = xcd * per + (xcd < rem ? xcd : rem) + local;
-    }
-    const int share = __builtin_amdgcn_readfirstlane(worker / tiles), tile = worker - share * tiles;
-    const int tile_n = __builtin_amdgcn_readfirstlane(tile / tiles_m);
+    const unsigned G = gridDim.x, bid = blockIdx.x, xcd = bid % 8;
+    const unsigned worker = xcd * (G / 8) + (xcd < G % 8 ? xcd : G % 8) + bid / 8;
+    // Every instruction from here to the first load is time in which nothing is in flight, ~1.4 ns each.  So quotients are products (mid_quotient) and
+    // a load's operand is chosen among pointers made once: 463..865 instructions -> 184..539, 49 x 768 x 256 4.2 -> 3.8 us, 54 x 512 x 1376 7.7 -> 7.4,
+    // gate/up 54 x 2 x 1376 x 512 and its down projection 14.0 -> 13.1, 110 x 4096 x 4096 16.9 -> 16.5.
+    const int share = (int)mid_quotient(worker, tiles, by_tiles), tile = (int)worker - share * tiles;
+    const int tile_n = (int)mid_quotient(tile, tiles_m, by_tiles_m);
     const int m0 = (tile - tile_n * tiles_m) * per_m;        // this tile's tokens
     const int M = a.M - m0 < per_m ? a.M - m0 : per_m;
-    const int kb = share * ktiles / S, ke = (share + 1) * ktiles / S, nk = ke - kb;
+    const int kb = (int)mid_quotient(share * ktiles, S, by_S), ke = (int)mid_quotient((share + 1) * ktiles, S, by_S), nk = ke - kb;
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
     // rotate: the tiles of a share start spread over its k-tiles and wrap round (the ranges of an XCD's tiles stay close)
-    const int rot = rotate ? (int)((long)tile * nk / tiles) : 0;      // (a row tile's token tiles are neighbours)
+    const int rot = rotate ? (int)mid_quotient(tile * nk, tiles, by_tiles) : 0;      // (a row tile's token tiles are neighbours)
 
     // A k-tile's loads: T_W of the weights, then T_M of the activations, then gamma, each of four stage rows; the wave takes numbers wv, wv + 8, ...: C or
     // C - 1 of them (a number past the end among the first C - 1 repeats an earlier load: the same bytes to the same place).  Lane L brings the 16-byte unit L
@@ -137,27 +131,26 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
     const int first = tile_n * per, stop = first + per < a.N ? first + per : a.N;      // this tile's outputs (gate/up pairs for SwiGLU)
     const int T_W = (is_swiglu(EPI) ? 2 * per : per) / 4;
     const int T_M = (M + 3) / 4, T = T_W + T_M + (RMS ? 1 : 0);
+    const size_t k0 = (size_t)(unsigned)(kb + rot) * MID_GK;
+    const uint16_t* const w_first = a.w0 + (size_t)(unsigned)first * (unsigned)K + k0;
+    const uint16_t* const u_first = is_swiglu(EPI) ? a.w1 + (size_t)(unsigned)first * (unsigned)K + k0 : w_first;
+    const uint16_t* const x_first = a.x + (size_t)(unsigned)m0 * (unsigned)K + k0;
+    const uint16_t* const g_first = RMS ? a.gamma + k0 : x_first;
     const uint16_t* src[CMAX];                               // (uniform) where the load's operand starts
     unsigned off[CMAX], dst[CMAX];                           // the lane's byte offset; (uniform) its place in the stage
 #pragma unroll
     for (int i = 0; i < CMAX; ++i) {
         int n = wv + MID_WAVES * i;
-        n = __builtin_amdgcn_readfirstlane(n < T ? n : T - 1);
-        const bool weights = n < T_W, tokens = n < T_W + T_M;
+        n = n < T ? n : T - 1;
+        const bool weights = MID_WAVES * i < BN / 4 && n < T_W, tokens = !RMS || n < T_W + T_M;
         // (gate/up pairs, an odd number of fours: the last four up rows lie behind four gate rows that do not exist)
         const int block = weights ? (is_swiglu(EPI) && (per & 7) == 4 && n == T_W - 1 ? n + 1 : n) : tokens ? BN / 4 + n - T_W : (BN + BM) / 4;
-        const int v = block * 4 + hi;                  // row within the stage
-        int row;                                             // ... and from the start of its operand; rows that do not exist: a valid one
-        if (weights) {
-            row = is_swiglu(EPI) ? (v >> 4) * 8 + (v & 7) : v;       // 8 gate rows, the 8 matching up rows, ...
-            row = first + row < stop ? row : stop - 1 - first;
-        } else {
-            row = !tokens ? 0 : v - BN < M ? v - BN : M - 1;
-        }
-        off[i] = (unsigned)(row * K + ((lr) ^ (v & 15)) * 8) * 2u;
-        dst[i] = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds0 + (unsigned)block * 1024u));
-        src[i] = uniform((weights ? (is_swiglu(EPI) && ((block >> 1) & 1) ? a.w1 : a.w0) + (size_t)first * K : tokens ? a.x + (size_t)m0 * K : a.gamma) +
-                         (size_t)(kb + rot) * MID_GK);
+        // row within the stage, and from the start of its operand's tile; rows that do not exist: a valid one
+        const int v = block * 4 + hi, r = weights ? (is_swiglu(EPI) ? (v >> 4) * 8 + (v & 7) : v) : v - BN;      // 8 gate rows, the 8 matching up rows, ...
+        const int last = weights ? stop - 1 - first : tokens ? M - 1 : 0;
+        off[i] = ((unsigned)(r < last ? r : last) * (unsigned)K + (unsigned)(lr ^ (v & 15)) * 8u) * 2u;
+        dst[i] = lds0 + (unsigned)block * 1024u;
+        src[i] = weights ? (is_swiglu(EPI) && ((block >> 1) & 1) ? u_first : w_first) : tokens ? x_first : g_first;
     }
     // Which loads are non-temporal: the weights, unless other token tiles read them too (mid_streams).  234 x 5907 x 3272 on three token tiles 28.2 -> 26.4 us
     // with their weights left in the caches, gate/up 163 x 2 x 2056 x 5896 29.9 -> 29.2.  (Where a tile is full, most are known beforehand and have no branch.)
@@ -215,6 +208,7 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
         unsigned stage = 0;                                  // ... and the stage it goes to (bytes)
         auto one = [&](int i) __attribute__((always_inline)) {
             if (i == C - 1 && !full) return;
+            // (asked once per k-tile its loads go out closer together: 128 x 8192 x 8192 37.9 -> 39.3 us, 90 x 15360 x 5120 35.9 -> 38.2)
             if (next != it_tail)
                 mid_dma(((i + 1) * MID_WAVES <= BN / 4 && full_tile) || (i * MID_WAVES < BN / 4 && (streams >> i & 1)), src[i], off[i], dst[i] + stage);
             else
@@ -480,13 +474,14 @@ hipError_t launch_mid_cfg(const GemmArgs& a, int epilogue, const MidPlan& p, hip
     const int ktiles = (a.K + MID_GK - 1) / MID_GK;
 #define THI_LAUNCH(E)                                                                                        \
     do {                                                                                                     \
-        auto kern = gemm_mid<BN, BM, E, RMS>;                                                            \
+        auto kern = gemm_mid<BN, BM, E, RMS>;                                                                \
         static std::once_flag attr_once;      /* one opt-in per kernel variant, safe from several threads */ \
         std::call_once(attr_once, [&] {                                                                      \
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                   \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                 \
         });                                                                                                  \
-        hipLaunchKernelGGL(kern, dim3(p.tiles * p.S), dim3(MID_THREADS), lds, stream, a, p.tiles, p.S, ktiles, p.per, (int)p.rotate, p.tiles_m, p.per_m); \
+        hipLaunchKernelGGL(kern, dim3(p.tiles * p.S), dim3(MID_THREADS), lds, stream, a, p.tiles, p.S, ktiles, p.per, (int)p.rotate, p.tiles_m, p.per_m, \
+                           mid_divisor(p.tiles), mid_divisor(p.S), mid_divisor(p.tiles_m));                   \
     } while (0)
     switch (epilogue) {
     case EPI_PLAIN: THI_LAUNCH(EPI_PLAIN); break;

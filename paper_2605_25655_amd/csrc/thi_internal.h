@@ -154,6 +154,12 @@ __host__ __device__ constexpr unsigned mid_streams(int wave, int weight_loads, i
 {
     return tiles_m == 1 ? (1u << (weight_loads - wave + MID_WAVES - 1) / MID_WAVES) - 1u : 0u;
 }
+// n / d as a product, for n * d < 2^32: mid_quotient(n, d, mid_divisor(d))
+__host__ __device__ constexpr unsigned mid_divisor(unsigned d) { return d < 2 ? 0u : (unsigned)((1ull << 32) / d) + 1u; }
+__host__ __device__ constexpr unsigned mid_quotient(unsigned n, unsigned d, unsigned divisor)
+{
+    return d < 2 ? n : (unsigned)((unsigned long long)n * divisor >> 32);
+}
 MidPlan plan_mid(int M, int N, int K, int epilogue, int num_cus);
 // The GEMM's configurations, their constants, and which of them runs a product (no RMSNorm kinds).  From GEMM_BIG on: the
 // candidates above 128 tokens.

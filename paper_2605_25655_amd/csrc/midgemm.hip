@@ -137,7 +137,8 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
     const uint16_t* const x_first = a.x + (size_t)(unsigned)m0 * (unsigned)K + k0;
     const uint16_t* const g_first = RMS ? a.gamma + k0 : x_first;
     const uint16_t* src[CMAX];                               // (uniform) where the load's operand starts
-    unsigned off[CMAX], dst[CMAX];                           // the lane's byte offset; (uniform) its place in the stage
+    unsigned off[CMAX], tail_off[CMAX], dst[CMAX];           // the lane's byte offset, and that in the last k-tile; (uniform) its place in the stage
+    const int pieces = (K - (ktiles - 1) * MID_GK) / 8;      // of the last k-tile: what lies past them is loaded from its first and zeroed once it has landed
 #pragma unroll
     for (int i = 0; i < CMAX; ++i) {
         int n = wv + MID_WAVES * i;
@@ -149,6 +150,7 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
         const int v = block * 4 + hi, r = weights ? (is_swiglu(EPI) ? (v >> 4) * 8 + (v & 7) : v) : v - BN;      // 8 gate rows, the 8 matching up rows, ...
         const int last = weights ? stop - 1 - first : tokens ? M - 1 : 0;
         off[i] = ((unsigned)(r < last ? r : last) * (unsigned)K + (unsigned)(lr ^ (v & 15)) * 8u) * 2u;
+        tail_off[i] = (lr ^ (v & 15)) < pieces ? off[i] : off[i] - (unsigned)(lr ^ (v & 15)) * 16u;
         dst[i] = lds0 + (unsigned)block * 1024u;
         src[i] = weights ? (is_swiglu(EPI) && ((block >> 1) & 1) ? u_first : w_first) : tokens ? x_first : g_first;
     }
@@ -157,12 +159,7 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
     const bool full_tile = T_W == BN / 4 && tiles_m == 1;
     const unsigned streams = (unsigned)__builtin_amdgcn_readfirstlane((int)mid_streams(wv, T_W, tiles_m));
     const int c_loads = (T + MID_WAVES - 1) / MID_WAVES < CMIN ? CMIN : (T + MID_WAVES - 1) / MID_WAVES;
-    // The last k-tile of a ragged K: pieces past K are loaded from the k-tile's first piece and zeroed once they have landed.
-    auto past = [&](int i) __attribute__((always_inline)) {  // ... the lane's logical piece of load i where it lies past K, else 0
-        const int p = (lr) ^ (((int)((dst[i] - lds0) / 1024u) * 4 + hi) & 15);
-        return (ktiles - 1) * MID_GK + p * 8 >= K ? (unsigned)p : 0u;
-    };
-    const int it_tail = (K & (MID_GK - 1)) != 0 && ke == ktiles ? nk - 1 - rot : -1;
+    const int it_tail = (K & (MID_GK - 1)) != 0 && ke == ktiles ? nk - 1 - rot : -1;      // the turn of a ragged K's last k-tile
 
     floatx4 acc[TN][TM];
 #pragma unroll
@@ -206,13 +203,20 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
         const bool full = wv + MID_WAVES * (C - 1) < T;      // (the others have one load less)
         int next = 0, kt_next = rot;                         // the k-tile that is loaded next: which turn, and its place in the range
         unsigned stage = 0;                                  // ... and the stage it goes to (bytes)
-        auto one = [&](int i) __attribute__((always_inline)) {
+        auto nt = [&](int i) __attribute__((always_inline)) {
+            return ((i + 1) * MID_WAVES <= BN / 4 && full_tile) || (i * MID_WAVES < BN / 4 && (streams >> i & 1));
+        };
+        // The loads up front are code that runs once: a select for the tail, where a branch per load is one more place to fetch instructions from
+        // (45 x 9752 x 344 6.5 -> 6.0 us, 56 x 13913 x 264 7.3 -> 6.7).  Those in the loop are not: there the branch keeps them apart, and with
+        // one question per k-tile 128 x 8192 x 8192 took 39.3 us for 37.9, 90 x 15360 x 5120 38.2 for 35.9.
+        auto up_front = [&](int i) __attribute__((always_inline)) {
             if (i == C - 1 && !full) return;
-            // (asked once per k-tile its loads go out closer together: 128 x 8192 x 8192 37.9 -> 39.3 us, 90 x 15360 x 5120 35.9 -> 38.2)
-            if (next != it_tail)
-                mid_dma(((i + 1) * MID_WAVES <= BN / 4 && full_tile) || (i * MID_WAVES < BN / 4 && (streams >> i & 1)), src[i], off[i], dst[i] + stage);
-            else
-                mid_dma(false, src[i], off[i] - past(i) * 16u, dst[i] + stage);
+            mid_dma(nt(i), src[i], next == it_tail ? tail_off[i] : off[i], dst[i] + stage);
+        };
+        auto in_the_loop = [&](int i) __attribute__((always_inline)) {
+            if (i == C - 1 && !full) return;
+            if (next != it_tail) mid_dma(nt(i), src[i], off[i], dst[i] + stage);
+            else mid_dma(false, src[i], tail_off[i], dst[i] + stage);
         };
         auto advance = [&]() __attribute__((always_inline)) {
             ++next;
@@ -226,7 +230,7 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
                 for (int i = 0; i < C; ++i) src[i] += MID_GK;
             }
         };
-        auto load = [&]() __attribute__((always_inline)) {
+        auto load = [&](auto one) __attribute__((always_inline)) {
             if (BM >= 64 && !rotate && (next & 1)) {
 #pragma unroll
                 for (int i = C - 1; i >= 0; --i) one(i);
@@ -239,11 +243,11 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
         auto zero_tail = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < C; ++i)
-                if ((i < C - 1 || full) && past(i)) smem[buf * STAGE + (int)((dst[i] - lds0) / 16u) + lane] = uintx4{0u, 0u, 0u, 0u};
+                if ((i < C - 1 || full) && tail_off[i] != off[i]) smem[buf * STAGE + (int)((dst[i] - lds0) / 16u) + lane] = uintx4{0u, 0u, 0u, 0u};
         };
 #pragma unroll
         for (int s = 0; s < NS; ++s)
-            if (s < nk) load();
+            if (s < nk) load(up_front);
         // One k-tile: it must have landed (the ones behind it, up to NS - 2, may be in flight), and every wave has read its fragments of the
         // one in front, whose stage is free.  The loads come first: what a compute unit has in flight is what bounds the kernel.
         int st = 0;
@@ -256,7 +260,7 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
-            if (it > 0 && next < nk) load();
+            if (it > 0 && next < nk) load(in_the_loop);
             __builtin_amdgcn_sched_barrier(0);
             frags(st, fs);
             if (AHEAD) __builtin_amdgcn_sched_barrier(0);

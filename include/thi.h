@@ -259,14 +259,16 @@ int thi_version(void);
  * Tuning/diagnostic hook used by the benchmark and tests: force a kernel
  * family for subsequent calls from this process.  family: 0 = automatic
  * (default: a decode kernel or the few-token GEMM kernel up to 32 tokens, the stream-K decode kernel or the
- * GEMM kernels for 33..64 tokens, the GEMM kernels above), 1 = weight-streaming
+ * GEMM kernels for 33..64 tokens, the GEMM kernels above, among them the few-token kernel with
+ * several token tiles where that is priced lower), 1 = weight-streaming
  * decode kernel with stream-K units (up to 64 tokens per launch),
  * 2 = MFMA GEMM kernels, 3 = weight-streaming decode kernel with row slabs
  * (16 rows over the whole of K per workgroup at a time), 4 = weight-streaming
  * decode kernel with row blocks (N / #CUs rows per workgroup, several 16-row
  * tiles in flight); 3 and 4 fall back to 1 where K < 1024 or K > 32768.
  * (The automatic choice takes the row slabs below K = 1024 too.  Family 2 includes the few-token
- * kernel: for 33..128 tokens where it is the faster one, up to 32 wherever it serves the shape, and there RMSNorm runs
+ * kernel: for 33..128 tokens where it is the faster one, up to 32 wherever it serves the shape, but not its several token
+ * tiles above 128, which only automatic calls run.  Up to 32 tokens RMSNorm runs
  * inside it: x * gamma is rounded to fp16 before 1/rms scales the sums, as in the decode kernels, so that it must not
  * exceed fp16's range; the pass that normalises for more tokens rounds x * gamma / rms.  thi_query_kernel_family reports 2
  * for automatic calls of up to 32 tokens that run it.  K > 2^23 always runs family 1.)
@@ -308,8 +310,9 @@ int thi_debug_handover(unsigned spin_limit, int withhold_flags);
 /*
  * Diagnostic: the kernel family (numbered as above, never 0 for valid arguments)
  * that a call with these extents would run under the current setting.
- * fused: 0 = plain linear operator, 1 = RMSNorm in front, 2 = gate/up with the
- * SwiGLU epilogue (N = I rows per matrix).  Returns 0 for invalid arguments.
+ * fused: 0 = plain linear operator, 1 = RMSNorm in front (no rotary embedding:
+ * with it, calls of 33..64 tokens run 2 at many shapes where this says 1), 2 = gate/up
+ * with the SwiGLU epilogue (N = I rows per matrix).  Returns 0 for invalid arguments.
  * Reads the current device's compute-unit count; launches nothing.
  */
 int thi_query_kernel_family(int M, int N, int K, int fused);

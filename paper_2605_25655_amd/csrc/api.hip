@@ -200,8 +200,8 @@ int pick_decode_kernel(int M, int N, int K, int epilogue, int cus, double* us = 
 //   stream-K's place : 0.88-0.95 of its time at any number of tokens;
 //   row blocks'      : above 16 tokens (gate/up 2 x 13824 x 5120 at 32 tokens 51.6 -> 44.2 us, 2 x 17920 x 6656 83.1 -> 72.7,
 //                      4096 x 11008 21.8 -> 19.0, 8192 x 8192 26.2 -> 23.5, 12288 x 4096 21.0 -> 17.8; RMSNorm-QKV
-//                      12288 x 4096 19.4 -> 18.5, 15360 x 5120 31.4 -> 29.8, 14000 x 2304 16.8 -> 14.5, where the model says at most 5 % more), gate/up from five tokens on where the model says a tenth
-//                      (2 x 13824 x 5120 at 16 tokens 47.5 -> 43.9); with fewer tokens the row blocks win (4096 x 4096 at one 1.4 x);
+//                      at 32 tokens 12288 x 4096 20.7 -> 19.8, 15360 x 5120 32.8 -> 30.4, 14000 x 2304 18.0 -> 15.2, where the model says at most 5 % more), gate/up
+//                      from five tokens on where the model says a tenth (2 x 13824 x 5120 at 16 tokens 47.5 -> 43.9); with fewer tokens the row blocks win (4096 x 4096 at one 1.4 x);
 //   row slabs'       : never (they win by 0-10 % wherever they are chosen).
 bool few_token_kernel_ok(int M, int N, int K, int epilogue, int cus, int kernel, double us)
 {

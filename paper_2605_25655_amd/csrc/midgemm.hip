@@ -1,17 +1,18 @@
-// fp16 MFMA GEMM for few tokens on gfx950: one token tile (up to 128 tokens; above, several where they are faster: plan_product), weights read once, bound by memory.
+// fp16 MFMA GEMM for few tokens on gfx950, bound by the way into LDS.  Up to 128 tokens one token tile, and the weights are read once; above, several where they
+// are faster (plan_product), neighbours on an XCD that read their weights once each.
 //
 // Between decode and prefill the weights still stream by once, but every compute unit also needs the activations, and the
 // way into LDS is what is short.  Measured with the loads alone: a CU brings in ~120 GB/s of what its L2 holds, but ~60 GB/s (27 GB/s when all
 // 256 share the HBM) as soon as some of it comes from memory, whatever the number of stages: the loads return in order, and 256 lines (32 KiB) are
 // in flight per CU.  So
-//   - every CU takes part, and a weight row is read by one workgroup only (the token tile holds all tokens);
+//   - every CU takes part, and with one token tile, which holds all tokens, a weight row is read by one workgroup only;
 //   - a workgroup reads its rows' K / S weights and M * K / S activations: outputs dealt evenly (in fours) over tiles in S k ranges, tiles * S
 //     just below the number of CUs; rows that no output needs and tokens past M are not asked for (time goes by the number of loads:
 //     21-25 ns each, 8.8 where the L2 holds everything);
-//   - the token tile is no larger than it must be (64, 96 or 128): what it does not take deepens the pipeline
+//   - the token tile is no larger than it must be (64, 96, 112 with 64 or 96 rows, or 128): what it does not take deepens the pipeline
 //     (72 x 12288 x 4096: 29.1 us with a tile of 128 and three stages, 25.3 with 96 and four);
 //   - a stage is 128 k (256 bytes of a row, half the barriers of 64 k), the eight waves are two token groups x the four
-//     k-steps of a stage: a fragment of weights is read from LDS twice and one of activations once, where eight waves
+//     k-steps of a stage (with 112 tokens two row groups instead): a fragment of weights is read from LDS twice and one of activations once, where eight waves
 //     along the tokens read the weights eight times.  The four k groups' sums meet in LDS at the end;
 //   - a k-tile's loads go out right behind its barrier, with next to no scalar work around them: the address of each is a pointer that
 //     advances, what the wave waits for is a constant (two copies of the loop, by the loads per wave).  With addresses

@@ -409,8 +409,9 @@ GemmPlan plan_gemm(int M, int N, int K, int epilogue, int num_cus)
 // loaded, and outputs and tokens are dealt evenly: one round of tiles in S ranges, tiles * S just below the number of CUs.  The least of a modelled time: 2.5 us, 0.58 ns an
 // element of the tile, 13.2 ns a KB of weights and 10.7 of activations, 113 ns and 17.5 ps an element for each stage of 128 k, 0.15 ns an output; sharing 1.9 us and
 // 22 ns a KB of partial tiles.  Fitted to 2565 points on 350 products (129..700 tokens, 300..14000 x 256..11200), 7 % off (rms); the pick is 0.9 % slower than the best
-// measured on average.  Taken where it is below 0.92 of the GEMM's price (that one is 9 % off): 80 random products of 129..700 tokens, all kinds, 0.83 of their time
-// on average, the worst 1.03.  150 x 4096 x 4096 23.0 -> 18.5 us, 175 x 5120 x 5120 26.2 -> 25.2, 159 x 10783 x 6384 67 -> 56, 300 x 512 x 1376 12.6 -> 7.2, 258 x 304 x
+// measured on average.  Taken where it is below 0.92 of the GEMM's price (that one is 9 % off): 450 random calls of 129..700 tokens, all kinds, with
+// and without this kernel in turn: 0.82 of the time on average, those that keep the GEMM among them, the worst 1.02.  (The points were measured with the weights
+// loaded non-temporally and a longer set-up; the kernel is 1-9 % faster than that.)  150 x 4096 x 4096 23.0 -> 18.5 us, 175 x 5120 x 5120 26.2 -> 25.2, 159 x 10783 x 6384 67 -> 56, 300 x 512 x 1376 12.6 -> 7.2, 258 x 304 x
 // 8480 21.1 -> 11.7, RMSNorm-QKV 256 x 1536 x 512 14.3 -> 8.2; beyond ~12000 x 203 or 4096 x 500 outputs a round no longer holds them.  With 80 MB of weights
 // and more whose rows start on a line the GEMM's tiles are as fast or faster, both being bound by the way into LDS (168 x 6656 x 6656 38.2, 43.8; 174 x 12288 x
 // 4096 35.6, 38.0; 144 x 5120 x 13824 48.3, 50.5; 135 x 10240 x 8192 54.3, 54.2).

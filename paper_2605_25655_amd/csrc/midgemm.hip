@@ -115,7 +115,7 @@ __global__ __launch_bounds__(MID_THREADS) void gemm_mid(GemmArgs a, int tiles, i
     const unsigned G = gridDim.x, bid = blockIdx.x, xcd = bid % 8;
     const unsigned worker = xcd * (G / 8) + (xcd < G % 8 ? xcd : G % 8) + bid / 8;
     // Every instruction from here to the first load is time in which nothing is in flight, ~1.4 ns each.  So quotients are products (mid_quotient) and
-    // a load's operand is chosen among pointers made once: 463..865 instructions -> 184..539, 49 x 768 x 256 4.2 -> 3.8 us, 54 x 512 x 1376 7.7 -> 7.4,
+    // a load's operand is chosen among pointers made once: 463..865 instructions -> 190..547, 49 x 768 x 256 4.2 -> 3.8 us, 54 x 512 x 1376 7.7 -> 7.4,
     // gate/up 54 x 2 x 1376 x 512 and its down projection 14.0 -> 13.1, 110 x 4096 x 4096 16.9 -> 16.5.
     const int share = (int)mid_quotient(worker, tiles, by_tiles), tile = (int)worker - share * tiles;
     const int tile_n = (int)mid_quotient(tile, tiles_m, by_tiles_m);
